@@ -93,6 +93,7 @@ void make_plan(Plan& p, const sr_tensor* lr, const sr_tensor* coeff, const sr_te
         if (gamma) { p.status = SR_ERR_KEPT; return; }
         for (int i = 0; i < L; ++i) { a.kept[i] = i; a.gamma[i] = 1.0f; }
         a.n_fold = L;
+        a.identity = 1;
     }
     a.io_f16 = lr->dtype == SR_F16;
     a.coeff_dtype = coeff->dtype;

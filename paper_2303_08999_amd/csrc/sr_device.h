@@ -24,7 +24,16 @@ struct AssembleArgs {
     const float* dict;    // [L][k][k]
     void*        out;     // [N][C][H][W]
     int N, C, h, w, H, W, s, L;
-    int xlast;            // matrix-core kernel: first column of the last tile column (set at launch)
+    // Matrix-core kernel, set at launch (walk_of in sr_mfma_kernel.h): its tiles, how they are dealt to the workgroups and
+    // the step from one tile of a workgroup to its next, split so that the kernel divides by nothing.
+    int tiles_x, per_img, ntiles;
+    int xlast;            // first column of the last tile column
+    int group_shift;      // workgroups are dealt to 2^group_shift shares of the tiles (the XCDs, or one)
+    int share, stride;    // tiles of a share; workgroups that walk it
+    int step_n, step_y, step_x;
+    unsigned inv_img, inv_tx;    // floor(2^32 / per_img), floor(2^32 / tiles_x)
+    int tiles_y;
+    int identity;         // every atom is folded, in its own order and unscaled (no kept list)
     int n_fold;           // atoms folded: L (dense) or n_kept
     int io_f16;           // lr and out are fp16 (else fp32)
     int coeff_dtype;      // sr_dtype of the stored coefficients

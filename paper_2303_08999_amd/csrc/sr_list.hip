@@ -191,7 +191,7 @@ static int assemble_list(const sr_tensor* lr, const sr_tensor* index, const sr_t
         memset(&m, 0, sizeof(m));
         m.lr = lr->data; m.coeff = value->data; m.index = a.index; m.dict = a.dict; m.out = out->data;
         m.N = a.N; m.C = a.C; m.h = a.h; m.w = a.w; m.H = a.H; m.W = a.W; m.s = a.s; m.L = L; m.T = entries;
-        m.n_fold = L; m.io_f16 = lr->dtype == SR_F16; m.coeff_dtype = SR_F16;
+        m.n_fold = L; m.identity = 1; m.io_f16 = lr->dtype == SR_F16; m.coeff_dtype = SR_F16;
         for (int i = 0; i < L; ++i) { m.kept[i] = i; m.gamma[i] = 1.0f; }
         if (force_kernel != SR_KERNEL_GENERIC && mfma_list_supported(m, k, value->dtype == SR_F16)) {
             e = launch_mfma_list(m, st);

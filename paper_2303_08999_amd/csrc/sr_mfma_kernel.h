@@ -349,7 +349,7 @@ __device__ __forceinline__ void divmod_scale(int v, int s, int& q, int& r) {
 // (8-bit coefficients in the same order: 8 bytes per lane and piece, widened to the operand with four conversions.)
 template <int K, int C, int NP8, int PX, int WR, int NW, int NU, int WPE, int CT, int SMIN, bool BIG, int PSM = 0>
 __global__ __launch_bounds__(64 * NW, WPE)
-void k_assemble_mfma(const AssembleArgs a, const int tiles_x, const int tiles_y, const int ntiles) {
+void k_assemble_mfma(const AssembleArgs a) {
     constexpr int NSUB = PSM == 4 ? 2 : (PSM == 3 ? 3 : 1);   // units per tile row
     constexpr bool PMAJ = PSM == 8;                // coefficients stored pixel-major, [H][W][L]
     constexpr bool BLK = PSM == 9;                 // coefficients stored blocked: the loaded registers are the operands
@@ -392,11 +392,11 @@ void k_assemble_mfma(const AssembleArgs a, const int tiles_x, const int tiles_y,
     __shared__ u32x4 lscr[LIST ? NW * F::LSW / 4 : 1];   // list form: per wavefront, [NP8 groups of 8 atoms][32 pixels][8 atoms] fp16
 
     const int tid0 = threadIdx.x;
-    const int groups = (gridDim.x & 7) == 0 ? 8 : 1;
-    const int G = gridDim.x / groups;                              // stride inside a share
-    const int share = (ntiles + groups - 1) / groups;
-    const int t_first = (int)(blockIdx.x % groups) * share + (int)(blockIdx.x / groups);
-    const int t_end = min(ntiles, ((int)(blockIdx.x % groups) + 1) * share);
+    const int wave = __builtin_amdgcn_readfirstlane(tid0 >> 6);     // scalar, loop-invariant
+    const int tiles_x = a.tiles_x, tiles_y = a.tiles_y, G = a.stride;
+    const int grp = (int)blockIdx.x & ((1 << a.group_shift) - 1);
+    const int t_first = grp * a.share + ((int)blockIdx.x >> a.group_shift);
+    const int t_end = min(a.ntiles, (grp + 1) * a.share);
     if (t_first >= t_end) return;                                  // whole workgroup: no tile
     // First column of a tile.  When the image width is not a whole number of pixel
     // groups the last tile column is moved left to end at the image edge (a.xlast =
@@ -415,11 +415,6 @@ void k_assemble_mfma(const AssembleArgs a, const int tiles_x, const int tiles_y,
         if constexpr (BIG) return img + (size_t)off * (size_t)F::CB;
         else return img + off;
     };
-    if (tid0 < 2 * a.s) {
-        float wt[4];
-        keys_weights(tid0, a.s, wt);
-        wk[tid0] = make_float4(wt[0], wt[1], wt[2], wt[3]);
-    }
     if constexpr (LIST) {
         for (int e = tid0; e < NW * F::LSW / 4; e += NT) lscr[e] = u32x4{0u, 0u, 0u, 0u};
         // half h takes entries h * ceil(T / 2) ...; a slot past the list repeats an entry the pixel has (the
@@ -432,76 +427,116 @@ void k_assemble_mfma(const AssembleArgs a, const int tiles_x, const int tiles_y,
             ltab[e] = (unsigned)t * ((unsigned)a.H * (unsigned)a.W);               // in elements
         }
     }
-    for (int e = tid0; e < (LIST ? 0 : 2 * F::NLOAD); e += NT) {
-        const int h = e / F::NLOAD, i = e - h * F::NLOAD;
-        // load i of half h serves folded atom idx; padding atoms re-read the last plane
-        const int idx = F32 ? 2 * i + h
-                            : (i < 8 * N16 ? 16 * (i >> 3) + 8 * h + (i & 7) : 16 * N16 + 4 * h + (i - 8 * N16));
-        ptab[e] = (unsigned)a.kept[idx < a.n_fold ? idx : a.n_fold - 1] * plane_b;
-    }
-    auto dval = [&](int idx, int tap) -> float {    // gamma * D[kept], zero for padding
-        if (tap < 0 || idx >= a.n_fold) return 0.0f;
-        return a.gamma[idx] * a.dict[(size_t)a.kept[idx] * F::KK + tap];
+    // Folded atom that load i of lane half h serves; the table of plane offsets (padding atoms re-read the last plane)
+    auto load_atom = [&](int i, int h) -> int {
+        return F32 ? 2 * i + h : (i < 8 * N16 ? 16 * (i >> 3) + 8 * h + (i & 7) : 16 * N16 + 4 * h + (i - 8 * N16));
     };
-    if (F32) {
-        for (int e = tid0; e < F::N2 * NMB * 64; e += NT) {
-            const int l = e & 63, blk = e >> 6, mb = blk % NMB, st = blk / NMB;
-            A32[e] = dval(2 * st + (l >> 5), tap_of_row<K>(l & 31, mb));
+    // What bounds the start of a launch is latency: each step that waits for memory, and each scalar load of another line
+    // of the kernel arguments, costs up to 1 us, and a launch used to spend 3.4 to 5.7 us before its first coefficient was
+    // requested (list and scales, then the dictionary entry by entry behind a branch, six divisions).  Now the dictionary's
+    // entries are requested first, all of them, unconditionally (clamped addresses; what is padding becomes zero at
+    // its use), then the LR footprint and the first unit's coefficients, and only then is anything waited for.  The whole
+    // dictionary in its own order (a.identity) needs no look at the list; a kept list goes through LDS once.
+    __shared__ int ktab[LIST ? 1 : 8 * NP8];        // first dictionary element of a folded atom
+    __shared__ float gtab[LIST ? 1 : 8 * NP8];      // its scale
+    if (!LIST && !a.identity) {
+        for (int e = tid0; e < 8 * NP8; e += NT) {
+            const int i = e < a.n_fold ? e : a.n_fold - 1;
+            const int k = a.kept[i];
+            const float g = a.gamma[i];
+            ktab[e] = k * F::KK;
+            gtab[e] = g;
         }
+        __syncthreads();
     }
-    for (int e = tid0; e < N16 * NMB * 64; e += NT) {
-        const int l = e & 63, blk = e >> 6, mb = blk % NMB, c16 = blk / NMB;
-        const int tap = tap_of_row<K>(l & 31, mb);
-        const bool ones = LG && sum_row<K>(l & 31, mb);       // logits form: this row sums the exponentials
-        float dv[8];
+    for (int e = tid0; e < (LIST ? 0 : 2 * F::NLOAD); e += NT) {
+        const int h = e / F::NLOAD, at = load_atom(e - h * F::NLOAD, h);
+        ptab[e] = (unsigned)(a.identity ? (at < a.n_fold ? at : a.n_fold - 1) : ktab[at] / F::KK) * plane_b;
+    }
+    // A wavefront makes whole blocks of 64 lanes of the dictionary operands: block b of a kind is that of wavefront b % NW.
+    const int lane0 = tid0 & 63, half0 = lane0 >> 5;
+    const bool whole = LIST || a.identity;
+    auto dict_entry = [&](int at, int tap) -> float {
+        const int row = whole ? (at < a.n_fold ? at : a.n_fold - 1) * F::KK : ktab[at];
+        return a.dict[(unsigned)(row + (tap < 0 ? 0 : tap))];
+    };
+    auto dict_value = [&](int at, int tap, float d) -> float {              // gamma * D[kept], zero for padding
+        const float g = whole ? 1.0f : gtab[at];
+        return tap < 0 || at >= a.n_fold ? 0.0f : g * d;
+    };
+    constexpr int NB32 = F32 ? F::N2 * NMB : 0, NB16 = N16 * NMB, NB8 = N8 ? NMB : 0;     // blocks of each kind
+    constexpr int M32 = (NB32 + NW - 1) / NW, M16 = (NB16 + NW - 1) / NW, M8 = (NB8 + NW - 1) / NW;   // ... of a wavefront
+    float dv32[M32 ? M32 : 1];
+    float dv16[M16 ? M16 : 1][8], dv8[M8 ? M8 : 1][4];
 #pragma unroll
-        for (int jj = 0; jj < 8; ++jj) {
-            const int idx = 16 * c16 + 8 * (l >> 5) + jj;
-            dv[jj] = ones ? (idx < a.n_fold ? 1.0f : 0.0f) : dval(idx, tap);
+    for (int m = 0; m < M32; ++m) {
+        const int blk = wave + NW * m < NB32 ? wave + NW * m : NB32 - 1, mb = blk % NMB, st = blk / NMB;
+        dv32[m] = dict_entry(2 * st + half0, tap_of_row<K>(lane0 & 31, mb));
+    }
+#pragma unroll
+    for (int m = 0; m < M16; ++m) {
+        const int blk = wave + NW * m < NB16 ? wave + NW * m : NB16 - 1, mb = blk % NMB, c16 = blk / NMB;
+#pragma unroll
+        for (int jj = 0; jj < 8; ++jj)
+            dv16[m][jj] = dict_entry(16 * c16 + 8 * half0 + jj, tap_of_row<K>(lane0 & 31, mb));
+    }
+#pragma unroll
+    for (int m = 0; m < M8; ++m) {
+        const int mb = wave + NW * m < NB8 ? wave + NW * m : NB8 - 1;
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj)
+            dv8[m][jj] = dict_entry(16 * N16 + 4 * half0 + jj, tap_of_row<K>(lane0 & 31, mb));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // ... and into LDS once they are there (with the up-sampling weights, by phase)
+    auto store_operands = [&]() {
+        if (tid0 < 2 * a.s) {
+            float wt[4];
+            keys_weights(tid0, a.s, wt);
+            wk[tid0] = make_float4(wt[0], wt[1], wt[2], wt[3]);
         }
-        u32x4 hi, lo;
-        split_hi_lo<BF, 8>(dv, hi, lo);
-        A16[(blk * 2 + 0) * 64 + l] = hi;
-        A16[(blk * 2 + 1) * 64 + l] = lo;
-    }
-    if (N8) {
-        for (int e = tid0; e < NMB * 64; e += NT) {
-            const int l = e & 63, mb = e >> 6;
-            const int tap = tap_of_row<K>(l & 31, mb);
-            const bool ones = LG && sum_row<K>(l & 31, mb);
-            float dv[4];
 #pragma unroll
-            for (int jj = 0; jj < 4; ++jj) {
-                const int idx = 16 * N16 + 4 * (l >> 5) + jj;
-                dv[jj] = ones ? (idx < a.n_fold ? 1.0f : 0.0f) : dval(idx, tap);
+        for (int m = 0; m < M32; ++m) {
+            const int blk = wave + NW * m, mb = blk % NMB, st = blk / NMB;
+            if (blk < NB32) A32[blk * 64 + lane0] = dict_value(2 * st + half0, tap_of_row<K>(lane0 & 31, mb), dv32[m]);
+        }
+#pragma unroll
+        for (int m = 0; m < M16; ++m) {
+            const int blk = wave + NW * m, mb = blk % NMB, c16 = blk / NMB;
+            if (blk < NB16) {
+                const int tap = tap_of_row<K>(lane0 & 31, mb);
+                const bool ones = LG && sum_row<K>(lane0 & 31, mb);   // logits form: this row sums the exponentials
+                float dv[8];
+#pragma unroll
+                for (int jj = 0; jj < 8; ++jj) {
+                    const int at = 16 * c16 + 8 * half0 + jj;
+                    dv[jj] = ones ? (at < a.n_fold ? 1.0f : 0.0f) : dict_value(at, tap, dv16[m][jj]);
+                }
+                u32x4 hi, lo;
+                split_hi_lo<BF, 8>(dv, hi, lo);
+                A16[(blk * 2 + 0) * 64 + lane0] = hi;
+                A16[(blk * 2 + 1) * 64 + lane0] = lo;
             }
-            u32x2 hi, lo;
-            split_hi_lo<BF, 4>(dv, hi, lo);
-            A8[(mb * 2 + 0) * 64 + l] = hi;
-            A8[(mb * 2 + 1) * 64 + l] = lo;
         }
-    }
-    __syncthreads();
-
-    // list form with up to 72 atoms, and pixel-major coefficients: the dictionary operands stay in registers (the
-    // fold reads them once per pixel slot, four times as often as the dense form does)
-    constexpr bool AREG = (LIST && NP8 <= 9) || PSM == 8;
-    u32x4 areg[AREG ? 2 * N16 : 1];
-    u32x2 areg8[AREG && N8 ? 2 : 1];
-    if constexpr (AREG) {
 #pragma unroll
-        for (int i = 0; i < 2 * N16; ++i) {
-            areg[i] = A16[i * 64 + (tid0 & 63)];
-            asm volatile("" : "+v"(areg[i]));           // opaque: or the compiler reloads it from LDS at every use
-        }
-        if constexpr (N8 != 0) {
+        for (int m = 0; m < M8; ++m) {
+            const int mb = wave + NW * m;
+            if (mb < NB8) {
+                const int tap = tap_of_row<K>(lane0 & 31, mb);
+                const bool ones = LG && sum_row<K>(lane0 & 31, mb);
+                float dv[4];
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                areg8[i] = A8[i * 64 + (tid0 & 63)];
-                asm volatile("" : "+v"(areg8[i]));
+                for (int jj = 0; jj < 4; ++jj) {
+                    const int at = 16 * N16 + 4 * half0 + jj;
+                    dv[jj] = ones ? (at < a.n_fold ? 1.0f : 0.0f) : dict_value(at, tap, dv8[m][jj]);
+                }
+                u32x2 hi, lo;
+                split_hi_lo<BF, 4>(dv, hi, lo);
+                A8[(mb * 2 + 0) * 64 + lane0] = hi;
+                A8[(mb * 2 + 1) * 64 + lane0] = lo;
             }
         }
-    }
+    };
 
     // ---- tile walk.  Workgroups are dealt to the 8 XCDs round-robin by index, and
     //      each XCD has its own L2.  When the grid is a multiple of 8, XCD x (the
@@ -510,9 +545,7 @@ void k_assemble_mfma(const AssembleArgs a, const int tiles_x, const int tiles_y,
     //      footprints overlap, meet in the same L2 at about the same time.  The
     //      step is pre-split into (image, tile row, tile column) so that no
     //      division is left in the loop.  All of it is scalar.
-    const int per_img = tiles_x * tiles_y;
-    const int step_n = G / per_img, step_r = G - step_n * per_img;
-    const int step_y = step_r / tiles_x, step_x = step_r - step_y * tiles_x;
+    const int step_n = a.step_n, step_y = a.step_y, step_x = a.step_x;
     auto advance = [&](TilePos p) -> TilePos {
         p.tx += step_x;
         if (p.tx >= tiles_x) { p.tx -= tiles_x; p.ty += 1; }
@@ -523,14 +556,15 @@ void k_assemble_mfma(const AssembleArgs a, const int tiles_x, const int tiles_y,
     };
     TilePos cur;
     {
-        const int t0 = t_first;
-        cur.n = t0 / per_img;
-        const int r2 = t0 - cur.n * per_img;
-        cur.ty = r2 / tiles_x;
+        // quotients by the rounded-down reciprocals are at most one too small (0 <= t_first < 2^31)
+        cur.n = (int)(((unsigned long long)(unsigned)t_first * a.inv_img) >> 32);
+        int r2 = t_first - cur.n * a.per_img;
+        if (r2 >= a.per_img) { r2 -= a.per_img; cur.n += 1; }
+        cur.ty = (int)(((unsigned long long)(unsigned)r2 * a.inv_tx) >> 32);
         cur.tx = r2 - cur.ty * tiles_x;
+        if (cur.tx >= tiles_x) { cur.tx -= tiles_x; cur.ty += 1; }
     }
 
-    const int wave = __builtin_amdgcn_readfirstlane(tid0 >> 6);     // scalar, loop-invariant
     const char* lr_base = (const char*)a.lr;
     const unsigned lr_esz = a.io_f16 ? 2u : 4u;
 
@@ -728,6 +762,7 @@ void k_assemble_mfma(const AssembleArgs a, const int tiles_x, const int tiles_y,
         const int lane = tid0 & 63, hf = lane >> 5, j = lane & 31;
         load_lr(cur, lane, lrv, lrpar);
         if constexpr (LIST) {
+            __syncthreads();                            // ltab is written
             load_list(cur, 0, j, hf, lval[0], lidx[0]);
         } else if constexpr (PMAJ) {
             const char* img = pm_image(cur);
@@ -746,11 +781,48 @@ void k_assemble_mfma(const AssembleArgs a, const int tiles_x, const int tiles_y,
         } else {
             unsigned pix_off[NPIX];
             const char* cimg = phi_base(cur, 0, j / F::WC, j % F::WC, pix_off);
-            const unsigned* pt = ptab + hf * F::NLOAD;
+            if (a.identity && a.n_fold == 8 * NP8) {
+                // load i's planes are the half's first plane plus a whole number of planes: the scalar base walks
+                const char* pl = cimg;
+                const unsigned half_b = hf ? plane_b : 0u;
 #pragma unroll
-            for (int i = 0; i < F::NLOAD; ++i) raw[i] = load_raw(cimg, pix_off, pt[i]);
+                for (int i = 0; i < F::NLOAD; ++i) {
+                    const unsigned first = F32 ? half_b : (i < 8 * N16 ? 8u * half_b : 4u * half_b);
+                    raw[i] = load_raw(pl, pix_off, first);
+                    if (i + 1 < F::NLOAD) pl = caddr(pl, plane_b) + (size_t)(load_atom(i + 1, 0) - load_atom(i, 0) - 1) * plane_b * (BIG ? F::CB : 1);
+                }
+            } else {
+                __syncthreads();                        // the table of plane offsets is written
+                const unsigned* pt = ptab + hf * F::NLOAD;
+#pragma unroll
+                for (int i = 0; i < F::NLOAD; ++i) raw[i] = load_raw(cimg, pix_off, pt[i]);
+            }
         }
     }
+    __builtin_amdgcn_sched_barrier(0);
+    store_operands();
+    __syncthreads();
+
+    // list form with up to 72 atoms, and pixel-major coefficients: the dictionary operands stay in registers (the
+    // fold reads them once per pixel slot, four times as often as the dense form does)
+    constexpr bool AREG = (LIST && NP8 <= 9) || PSM == 8;
+    u32x4 areg[AREG ? 2 * N16 : 1];
+    u32x2 areg8[AREG && N8 ? 2 : 1];
+    if constexpr (AREG) {
+#pragma unroll
+        for (int i = 0; i < 2 * N16; ++i) {
+            areg[i] = A16[i * 64 + (tid0 & 63)];
+            asm volatile("" : "+v"(areg[i]));           // opaque: or the compiler reloads it from LDS at every use
+        }
+        if constexpr (N8 != 0) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                areg8[i] = A8[i * 64 + (tid0 & 63)];
+                asm volatile("" : "+v"(areg8[i]));
+            }
+        }
+    }
+
 
     // ---- stage 1 in three steps; a workgroup barrier separates each from the next.
     // (a) tap tables of a tile and its LR footprint, registers -> LDS
@@ -1458,6 +1530,23 @@ inline long long wall_clock_khz() {
     return known[dev];
 }
 
+// How `blocks` workgroups walk the tiles: each of 8 shares (the XCDs; one share if the grid is no multiple of 8) is a
+// contiguous run of tiles, walked by every workgroup of that XCD in steps of their number.
+inline void walk_of(AssembleArgs& a, int ntiles, int blocks) {
+    a.ntiles = ntiles;
+    a.per_img = a.tiles_x * a.tiles_y;
+    a.group_shift = blocks % 8 == 0 ? 3 : 0;
+    const int groups = 1 << a.group_shift;
+    a.share = (int)(((long long)ntiles + groups - 1) / groups);
+    a.stride = blocks / groups;
+    a.step_n = a.stride / a.per_img;
+    const int r = a.stride - a.step_n * a.per_img;
+    a.step_y = r / a.tiles_x;
+    a.step_x = r - a.step_y * a.tiles_x;
+    a.inv_img = (unsigned)((1ull << 32) / (unsigned)a.per_img - (a.per_img == 1 ? 1 : 0));
+    a.inv_tx = (unsigned)((1ull << 32) / (unsigned)a.tiles_x - (a.tiles_x == 1 ? 1 : 0));
+}
+
 template <int K, int C, int NP8, int PX, int WR, int NW, int NU, int WPE, int CT = CT_F16, int SMIN = 2, bool BIG = false,
           int PSM = 0>
 hipError_t launch_one(const AssembleArgs& a0, hipStream_t st) {
@@ -1484,20 +1573,21 @@ hipError_t launch_one(const AssembleArgs& a0, hipStream_t st) {
         a.wb_flushers = xcds < 1 ? 1 : (xcds > 8 ? 8 : xcds);
     }
 #endif
-    const int tiles_x = (a.W + F::TW - 1) / F::TW, tiles_y = (a.H + F::TH - 1) / F::TH;
-    a.xlast = (tiles_x - 1) * F::TW;
+    a.tiles_x = (a.W + F::TW - 1) / F::TW;
+    a.tiles_y = (a.H + F::TH - 1) / F::TH;
+    a.xlast = (a.tiles_x - 1) * F::TW;
     if (a.W % PX != 0) {                                // ragged rows: the last tile column ends at the image edge
         if (a.W < F::TW) return hipErrorInvalidValue;
         a.xlast = a.W - F::TW;
     }
-    const long long nt = (long long)tiles_x * tiles_y * a.N;
+    const long long nt = (long long)a.tiles_x * a.tiles_y * a.N;
     if (nt > 0x7fffffffLL) return hipErrorInvalidValue;
     // as many workgroups as stay resident (WPE wavefronts per SIMD)
     const int cus = compute_units();
     const int cap = cus * (4 * WPE / NW > 0 ? 4 * WPE / NW : 1);
     const int blocks = nt < cap ? (int)nt : cap;
-    hipLaunchKernelGGL((k_assemble_mfma<K, C, NP8, PX, WR, NW, NU, WPE, CT, SMIN, BIG, PSM>), dim3(blocks), dim3(F::NT), 0, st,
-                       a, tiles_x, tiles_y, (int)nt);
+    walk_of(a, (int)nt, blocks);
+    hipLaunchKernelGGL((k_assemble_mfma<K, C, NP8, PX, WR, NW, NU, WPE, CT, SMIN, BIG, PSM>), dim3(blocks), dim3(F::NT), 0, st, a);
     return hipGetLastError();
 }
 
