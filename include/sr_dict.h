@@ -225,7 +225,9 @@ int sr_dict_assemble_selective(const sr_tensor* lr, const sr_tensor* coeff, cons
  * per image; the generic kernel everything else.
  *
  * opts->tile (the launch-shape search of section III-B, Eq. 11-12, as a small set of compiled
- * tile shapes): index 0 is the library's default for the frame and is always accepted.  Other
+ * tile shapes): index 0 is the library's default for the frame and is always accepted.  (By
+ * default large frames may be walked in strips of 128 columns instead of tiles; index 0 then reports the
+ * tile shape it would take otherwise.)  Other
  * indices exist only where alternative shapes are built - k = 5, C = 3, 65 to 72 folded f16
  * atoms, byte offsets: 1 = 64x8, 2 = 128x4, 3 = 64x16, 4 = 128x8, 5 = 64x32, 6 = 128x16,
  * 7 = 128x24 (scale 4 only) HR pixels per workgroup, i.e. 1, 1, 2, 2, 4, 4, 6 row groups per

@@ -33,6 +33,7 @@ struct AssembleArgs {
     int step_n, step_y, step_x;
     unsigned inv_img, inv_tx;    // floor(2^32 / per_img), floor(2^32 / tiles_x)
     int tiles_y;
+    int seg_rows;         // strip form: rows of a segment (tiles_y then counts segments)
     int identity;         // every atom is folded, in its own order and unscaled (no kept list)
     int n_fold;           // atoms folded: L (dense) or n_kept
     int io_f16;           // lr and out are fp16 (else fp32)

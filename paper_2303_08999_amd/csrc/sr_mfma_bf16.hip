@@ -10,6 +10,19 @@ namespace srd {
 
 template <int C>
 static hipError_t launch_k5(const AssembleArgs& a, int np8, hipStream_t st) {
+    const bool small = np8 == 9 && (long long)a.N * a.H * a.W <= 400000;
+    if (np8 == 16 ? strip_form(a, 64, 64, a.s == 4 ? 24 : 16)
+        : np8 <= 2 ? strip_form(a, 128, 64, a.s == 4 ? 32 : 16, a.s == 4 ? 3 : 2)
+                   : strip_form(a, 128, 128, small ? 4 : a.s == 4 ? 24 : 16)) {
+        switch (np8) {
+        case 1: return launch_strip<5, C, 1, 4, 3, CT_BF16>(a, st);
+        case 2: if (C == 3) return launch_strip<5, 3, 2, 4, 3, CT_BF16>(a, st); break;
+        case 4: return launch_strip<5, C, 4, 4, 2, CT_BF16>(a, st);
+        case 6: return launch_strip<5, C, 6, 4, 2, CT_BF16>(a, st);
+        case 9: return launch_strip<5, C, 9, 4, 2, CT_BF16>(a, st);
+        case 16: return launch_strip<5, C, 16, 2, 2, CT_BF16>(a, st);
+        }
+    }
     switch (np8) {
     case 1:
         if (a.s == 4) return launch_one<5, C, 1, 4, 2, 4, 4, 3, CT_BF16, 4>(a, st);      //  64 x 32
@@ -26,7 +39,7 @@ static hipError_t launch_k5(const AssembleArgs& a, int np8, hipStream_t st) {
         return launch_one<5, C, 6, 4, 1, 4, 4, 2, CT_BF16>(a, st);
     case 9:
         // small frames: 128 x 4 tiles put more CUs to work (as with fp16 coefficients)
-        if ((long long)a.N * a.H * a.W <= 400000) return launch_one<5, C, 9, 4, 1, 4, 1, 2, CT_BF16>(a, st);
+        if (small) return launch_one<5, C, 9, 4, 1, 4, 1, 2, CT_BF16>(a, st);
         if (a.s == 4) return launch_one<5, C, 9, 4, 1, 4, 6, 2, CT_BF16, 4>(a, st);
         return launch_one<5, C, 9, 4, 1, 4, 4, 2, CT_BF16>(a, st);
     case 16:                                                             // 73 to 128 atoms: two pixels per lane, as 7x7
@@ -38,6 +51,13 @@ static hipError_t launch_k5(const AssembleArgs& a, int np8, hipStream_t st) {
 
 template <int C>
 static hipError_t launch_k7(const AssembleArgs& a, int np8, hipStream_t st) {
+    if (strip_form(a, 64, 64, a.s == 4 ? 24 : 16)) {
+        switch (np8) {
+        case 2:  return launch_strip<7, C, 2, 2, 2, CT_BF16>(a, st);
+        case 9:  return launch_strip<7, C, 9, 2, 2, CT_BF16>(a, st);
+        case 16: return launch_strip<7, C, 16, 2, 2, CT_BF16>(a, st);
+        }
+    }
     switch (np8) {
     case 2:
         if (a.s == 4) return launch_one<7, C, 2, 2, 1, 4, 6, 2, CT_BF16, 4>(a, st);

@@ -45,18 +45,23 @@ hipError_t launch_mfma_k5(const AssembleArgs& a, int np8, int shape, hipStream_t
         switch (np8) {
         case 1:
             // x4: 64 x 32 still fits three workgroups per CU (measured 11 % faster)
+            if (strip_form(a, 128, 64, a.s == 4 ? 32 : 16, a.s == 4 ? 3 : 2)) return launch_strip<5, 3, 1, 4, 3>(a, st);
             if (a.s == 4) return launch_one<5, 3, 1, 4, 2, 4, 4, 3, CT_F16, 4>(a, st);
             return launch_one<5, 3, 1, 4, 2, 4, 2, 3>(a, st);        //  64 x 16
         case 2:
+            if (strip_form(a, 128, 64, a.s == 4 ? 32 : 16, a.s == 4 ? 3 : 2)) return launch_strip<5, 3, 2, 4, 3>(a, st);
             if (a.s == 4) return launch_one<5, 3, 2, 4, 2, 4, 4, 3, CT_F16, 4>(a, st);
             return launch_one<5, 3, 2, 4, 2, 4, 2, 3>(a, st);
         case 4:
+            if (strip_form(a, 128, 128, a.s == 4 ? 24 : 16)) return launch_strip<5, 3, 4, 4, 2>(a, st);
             if (a.s == 4) return launch_one<5, 3, 4, 4, 1, 4, 6, 2, CT_F16, 4>(a, st);   // 128 x 24 (6-10 % faster)
             return launch_one<5, 3, 4, 4, 1, 4, 4, 2>(a, st);
         case 6:
+            if (strip_form(a, 128, 128, a.s == 4 ? 24 : 16)) return launch_strip<5, 3, 6, 4, 2>(a, st);
             if (a.s == 4) return launch_one<5, 3, 6, 4, 1, 4, 6, 2, CT_F16, 4>(a, st);
             return launch_one<5, 3, 6, 4, 1, 4, 4, 2>(a, st);
         case 9:
+            if (shape == 0 && strip_form(a, 128, kShapeW[resolve_shape_k5(a, 0)], kShapeH[resolve_shape_k5(a, 0)])) return launch_strip<5, 3, 9, 4, 2>(a, st);
             switch (resolve_shape_k5(a, shape)) {
             case 1:  return launch_one<5, 3, 9, 4, 2, 4, 1, 2>(a, st);    //  64 x 8
             case 2:  return launch_one<5, 3, 9, 4, 1, 4, 1, 2>(a, st);    // 128 x 4
@@ -69,7 +74,8 @@ hipError_t launch_mfma_k5(const AssembleArgs& a, int np8, int shape, hipStream_t
             case 9:  return launch_one<5, 3, 9, 4, 1, 2, 8, 1>(a, st);    // 128 x 16, two wavefronts, 8 units, one per SIMD
             default: return hipErrorInvalidValue;
             }
-        case 16:                                                         // 73 to 128 atoms: two pixels per lane, as 7x7
+        case 16:
+            if (strip_form(a, 64, 64, a.s == 4 ? 24 : 16)) return launch_strip<5, 3, 16, 2, 2>(a, st);   // 73 to 128 atoms: two pixels per lane, as 7x7
             if (a.s == 4) return launch_one<5, 3, 16, 2, 1, 4, 6, 2, CT_F16, 4>(a, st);
             return launch_one<5, 3, 16, 2, 1, 4, 4, 2>(a, st);
         default: return hipErrorInvalidValue;
@@ -89,6 +95,15 @@ hipError_t launch_mfma_k5(const AssembleArgs& a, int np8, int shape, hipStream_t
         case 4:  return launch_one<5, 4, 4, 4, 1, 4, 2, 2>(a, st);
         case 9:  return launch_one<5, 4, 9, 4, 1, 4, 2, 2>(a, st);
         default: return hipErrorInvalidValue;
+        }
+    }
+    if (np8 == 16 ? strip_form(a, 64, 64, a.s == 4 ? 24 : 16) : strip_form(a, 128, 128, a.s == 4 && np8 == 9 ? 24 : 16)) {
+        switch (np8) {
+        case 1:  return launch_strip<5, 1, 1, 4, 2>(a, st);
+        case 4:  return launch_strip<5, 1, 4, 4, 2>(a, st);
+        case 6:  return launch_strip<5, 1, 6, 4, 2>(a, st);
+        case 9:  return launch_strip<5, 1, 9, 4, 2>(a, st);
+        case 16: return launch_strip<5, 1, 16, 2, 2>(a, st);
         }
     }
     switch (np8) {

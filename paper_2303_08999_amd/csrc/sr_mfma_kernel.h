@@ -57,6 +57,18 @@
 // network holds them before its pixel-shuffle layer, pixel-major storage and the blocked
 // order that needs no re-packing at all (see the kernel's own comment).
 //
+// Two forms of the walk over the image.  TILES (the original one, and the only one for the layouts before the pixel-shuffle and the
+// blocked and pixel-major orders): a workgroup up-samples a tile and its halo into LDS in three barrier-separated steps, then its
+// wavefronts fold and filter it.  STRIPS (template argument STRIP = the scale): a wavefront walks down its own segment of
+// a strip of 32 PX columns; each row it up-samples one more row into a ring of K + 1 in its own LDS and folds, filters and stores one.  A row is
+// up-sampled once per segment (not by every tile above and below it), neighbouring columns share their LR columns, the
+// weights of the horizontal pass are compile-time constants, nothing waits at a barrier after the start, and the segments are cut to the
+// number of wavefronts (a frame of 5.3 rounds of tiles takes six).  What bounded the light cases was exactly that: 4K with
+// 8 of 72 atoms 79 -> 62 us (3.8 TB/s of a mix that is half writes), 4K lists of 8 141 -> 107, 4K fp8 154 -> 150, 720p fp8 33 -> 23, 4K fp16
+// 248 -> 244, 4K logits 264 -> 253, four 7x7 video frames 409 -> 396; which form a call takes: strip_form().  Tried on top and not kept: two rows of
+// coefficients in flight (registers spill, 62 -> 92 us), workgroups of 8 and 12 wavefronts that take half of each other's remaining
+// rows (all wavefronts then end within 2 % instead of 15 %, and the call takes as long: the memory and the issue slots were busy before).
+//
 // L2 write-back pacing.  The output leaves the CUs as ordinary stores and sits in the XCDs' L2s as dirty lines that
 // the L2 writes to memory when it sees fit, interleaved with the read stream; reads and writes that alternate at the
 // memory cost more than their bytes (the stores of the 4K frame, 7.6 % of the bytes, cost 22 % of the time).  One
@@ -74,9 +86,7 @@
 // same launch with a part switched off, to see what that part costs.  SR_ABLATE_STORES keeps
 // every instruction but never executes the output stores; SR_ABLATE_STAGE1 skips the two
 // up-sampling passes (their barriers stay); results are then wrong by construction.
-// SR_STORES_WRITE_THROUGH writes the fp32 output of the four-pixel instantiations through the L2
-// (agent scope) instead of leaving dirty lines in it; results are unchanged.  The library built
-// by default contains none of them.
+// The library built by default contains none of them.
 #pragma once
 #include <type_traits>
 
@@ -121,7 +131,7 @@ constexpr int LIST_MAX_ENTRIES = 16;
 // of a tile shrinks with the scale, so an instantiation for scale 4 only needs half
 // the LDS for the footprint and the vertical-pass buffer, and can afford a taller
 // tile (fewer halo rows up-sampled per output row).
-template <int K, int C, int NP8, int PX, int WR, int NW, int NU, int CT = CT_F16, int SMIN = 2, int NSUB = 1, int SWZ = 0>
+template <int K, int C, int NP8, int PX, int WR, int NW, int NU, int CT = CT_F16, int SMIN = 2, int NSUB = 1, int SWZ = 0, int STRIP = 0>
 struct Cfg {
     static constexpr bool F32 = CT == CT_F32, F8 = CT == CT_F8, BF = CT == CT_BF16, LIST = CT == CT_LIST8 || CT == CT_LIST16;
     static constexpr bool LG = CT == CT_LOGIT || CT == CT_LOGIT_BF16, LGB = CT == CT_LOGIT_BF16;
@@ -133,7 +143,7 @@ struct Cfg {
     static constexpr int NMB = (NSLOT + 15) / 16;      // 32-row MFMA blocks
     static constexpr int WC = 32 / WR;                 // lane columns per wavefront
     static constexpr int TW = WC * PX * NSUB;          // tile of HR pixels per workgroup: NU units per wavefront, each
-    static constexpr int TH = WR * NW * NU / NSUB;     // WR rows of WC * PX pixels; NSUB units share a row (see PSM = 4)
+    static constexpr int TH = STRIP ? 1 : WR * NW * NU / NSUB;     // (strip form: a wavefront's own row) WR rows of WC * PX pixels; NSUB units share a row (see PSM = 4)
     static_assert(NU % NSUB == 0, "whole rows per wavefront");
     static constexpr int NT = 64 * NW;
     static constexpr int UW = TW + K - 1;
@@ -144,11 +154,17 @@ struct Cfg {
     // the odd banks.
     // SWZ = 1 (pixel-major coefficients): no swizzle, lane j's slots are pixels j, 32 + j, ... of the row.
     static constexpr int SW = SWZ ? SWZ : (NSUB == 2 ? 8 : PX);
-    static constexpr int NG = ((UW + SW - 1) / SW) | (NSUB == 2 ? 1 : 0);   // stride between the classes
+    static constexpr int NG = STRIP ? (UW + 3) / 4 * 4 / SW : ((UW + SW - 1) / SW) | (NSUB == 2 ? 1 : 0);   // stride between the classes
     static constexpr int P0 = SW * NG;
     // rows of one wavefront must land on disjoint banks: pitch == WC (mod 32)
     static constexpr int P = WR == 1 ? P0 : P0 + ((WC - P0 % 32) + 32) % 32;
-    static constexpr int MAXLRY = (UH - 1) / SMIN + 5, MAXLRX = (UW - 1) / SMIN + 5;
+    static constexpr int MAXLRY = (UH - 1) / SMIN + 5, MAXLRX = STRIP ? (UW + 1) / (STRIP ? STRIP : 1) + 6 : (UW - 1) / SMIN + 5;
+    // Strip form: a wavefront's own LDS: a ring of SLOTS up-sampled rows, one row after the vertical pass, a ring of four LR rows
+    static constexpr int SLOTS = 2 * RH0;
+    static constexpr int LIT = (C * MAXLRX + 63) / 64, LROW = 64 * LIT;      // elements of an LR footprint row: per lane, and padded to whole wavefronts
+    static constexpr int GPX = STRIP == 3 ? 3 : 4, GSTEP = STRIP == 2 ? 2 : 1;   // HR columns a lane up-samples at a time, their LR columns
+    static constexpr int NGRP = STRIP == 3 ? (UW + 2 + 2) / 3 : (UW + 3) / 4, GIT = (C * NGRP + 63) / 64;
+    static constexpr int WAVE_F = SLOTS * C * P + 5 * LROW;
     // fp16 coefficients: 16-atom MFMA steps and an optional 8-atom step;
     // fp32 coefficients: 2-atom steps of v_mfma_f32_32x32x2_f32, one load each
     static constexpr int N16 = F32 ? 0 : NP8 / 2, N8 = F32 ? 0 : NP8 % 2;
@@ -274,6 +290,24 @@ __device__ __forceinline__ _Float16 __attribute__((ext_vector_type(2))) pk_max_f
     return r;
 }
 
+// Output stores through a raw buffer resource of the image (fourth word: 32-bit data format), whose bounds check drops a lane
+// at BEYOND: no image has that many bytes (see mfma_supported), and BEYOND + 15 does not wrap.
+constexpr int RAW_BUFFER = 0x00020000;
+constexpr unsigned BEYOND = 0xffffffc0u;
+__device__ __forceinline__ void store16(__amdgpu_buffer_rsrc_t r, unsigned at, float v) {
+    __builtin_amdgcn_raw_buffer_store_b16(__half_as_ushort(narrow_f16(v)), r, at, 0, 0);
+}
+__device__ __forceinline__ void store32(__amdgpu_buffer_rsrc_t r, unsigned at, unsigned v) { __builtin_amdgcn_raw_buffer_store_b32(v, r, at, 0, 0); }
+__device__ __forceinline__ void store64(__amdgpu_buffer_rsrc_t r, unsigned at, unsigned v0, unsigned v1) {
+    __builtin_amdgcn_raw_buffer_store_b64(u32x2{v0, v1}, r, at, 0, 0);
+}
+__device__ __forceinline__ void store128(__amdgpu_buffer_rsrc_t r, unsigned at, const float (&v)[4]) {
+    __builtin_amdgcn_raw_buffer_store_b128(u32x4{__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])}, r, at, 0, 0);
+}
+__device__ __forceinline__ unsigned pack_f16(float a, float b) {
+    return (unsigned)__half_as_ushort(narrow_f16(a)) | ((unsigned)__half_as_ushort(narrow_f16(b)) << 16);
+}
+
 // filter tap served by MFMA row i of block mb, or -1 (padding / dummy row)
 template <int K>
 __device__ __forceinline__ int tap_of_row(int i, int mb) {
@@ -347,18 +381,19 @@ __device__ __forceinline__ void divmod_scale(int v, int s, int& q, int& r) {
 // of contiguous memory per load) and holds the B operand of that 16-atom step and slot as it stands: no re-packing, no
 // staging, and the slots are the planar form's four adjacent pixels, so stage 4 and the store are the planar form's too.
 // (8-bit coefficients in the same order: 8 bytes per lane and piece, widened to the operand with four conversions.)
-template <int K, int C, int NP8, int PX, int WR, int NW, int NU, int WPE, int CT, int SMIN, bool BIG, int PSM = 0>
+template <int K, int C, int NP8, int PX, int WR, int NW, int NU, int WPE, int CT, int SMIN, bool BIG, int PSM = 0, int STRIP = 0>
 __global__ __launch_bounds__(64 * NW, WPE)
 void k_assemble_mfma(const AssembleArgs a) {
     constexpr int NSUB = PSM == 4 ? 2 : (PSM == 3 ? 3 : 1);   // units per tile row
     constexpr bool PMAJ = PSM == 8;                // coefficients stored pixel-major, [H][W][L]
     constexpr bool BLK = PSM == 9;                 // coefficients stored blocked: the loaded registers are the operands
-    using F = Cfg<K, C, NP8, PX, WR, NW, NU, CT, SMIN, NSUB, (PMAJ ? 1 : 0)>;
+    using F = Cfg<K, C, NP8, PX, WR, NW, NU, CT, SMIN, NSUB, (PMAJ ? 1 : 0), STRIP>;
+    static_assert(!STRIP || (WR == 1 && NU == 1 && PSM == 0 && !BIG), "strip form: one row of a wavefront's strip at a time");
     constexpr bool F32 = F::F32, F8 = F::F8, BF = F::BF, LIST = F::LIST, LG = F::LG;
     static_assert(!LG || (PX == 4 && (PSM == 0 || PSM == 2 || PSM == 3 || PSM == 4 || PSM == 9) && !BIG && F::NSLOT < 16 * F::NMB),
                   "logits form: fp16 planes (or the permuted-slot forms of the layout before the pixel-shuffle), four pixels per lane, a free MFMA row");
     constexpr int LH = F::LH;                      // list entries a lane half loads
-    static_assert(!LIST || (PX == 4 && WR == 1 && !BIG && PSM == 0 && NU % 2 == 0), "list form: four pixels per lane, one row per unit");
+    static_assert(!LIST || (PX == 4 && WR == 1 && !BIG && PSM == 0 && (STRIP != 0 || NU % 2 == 0)), "list form: four pixels per lane, one row per unit");
     constexpr bool PS = PSM == 1;                  // one 16-bit load per pixel
     constexpr bool PERM = PSM == 2 || PSM == 3 || PSM == 4;    // permuted pixel slots
     static_assert(PSM == 0 || ((CT == CT_F16 || (CT == CT_F8 && PSM == 9) ||
@@ -370,18 +405,18 @@ void k_assemble_mfma(const AssembleArgs a) {
                   "blocked coefficients: fp16 (values or logits), bfloat16 or 8-bit, one row of 128 pixels per unit");
     static_assert(!PERM || (WR == 1 && SMIN >= PSM), "permuted slots: one row per wavefront and unit");
     // row of the wavefront's unit within the tile, and which of the row's NSUB units it is
-    auto unit_row = [](int unit, int wave_) { return (unit / NSUB) * NW + wave_; };
+    auto unit_row = [](int unit, int wave_) { return STRIP ? 0 : (unit / NSUB) * NW + wave_; };
     constexpr int NPIX = PS ? PX : 1;              // pixel offsets a lane keeps per unit
     using Raw = typename RawT<PX * F::CB>::type;
     constexpr int NT = F::NT, P = F::P, NG = F::NG, UH = F::UH, UW = F::UW;
     constexpr int N16 = F::N16, N8 = F::N8, NMB = F::NMB;
     constexpr int MAXLRY = F::MAXLRY, MAXLRX = F::MAXLRX;
 
-    __shared__ float U[C * UH * P];                 // up-sampled tile, column-swizzled
-    __shared__ float V[C * UH * MAXLRX];            // after the vertical pass
-    __shared__ float lrT[C * MAXLRY * MAXLRX];      // LR footprint (clamped reads)
-    __shared__ float4 xw[UW], yw[UH];               // per-column / per-row tap weights
-    __shared__ int xb[UW], yb[UH];                  // ... and first source index
+    __shared__ float U[STRIP ? NW * F::WAVE_F : C * UH * P];   // up-sampled tile, column-swizzled (strip form: all of a wavefront's buffers)
+    __shared__ float V[STRIP ? 1 : C * UH * MAXLRX];           // after the vertical pass
+    __shared__ float lrT[STRIP ? 1 : C * MAXLRY * MAXLRX];     // LR footprint (clamped reads)
+    __shared__ float4 xw[STRIP ? 1 : UW], yw[STRIP ? 1 : UH];  // per-column / per-row tap weights
+    __shared__ int xb[STRIP ? 1 : UW], yb[STRIP ? 1 : UH];     // ... and first source index
     __shared__ float4 wk[8];                        // Keys weights by phase numerator m
     __shared__ u32x4 A16[(N16 ? N16 : 1) * NMB * 2 * 64];
     __shared__ u32x2 A8[(F32 ? 1 : NMB * 2) * 64];
@@ -395,9 +430,12 @@ void k_assemble_mfma(const AssembleArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(tid0 >> 6);     // scalar, loop-invariant
     const int tiles_x = a.tiles_x, tiles_y = a.tiles_y, G = a.stride;
     const int grp = (int)blockIdx.x & ((1 << a.group_shift) - 1);
-    const int t_first = grp * a.share + ((int)blockIdx.x >> a.group_shift);
     const int t_end = min(a.ntiles, (grp + 1) * a.share);
-    if (t_first >= t_end) return;                                  // whole workgroup: no tile
+    const int t_block = grp * a.share + ((int)blockIdx.x >> a.group_shift) * (STRIP ? NW : 1);
+    if (t_block >= t_end) return;                                  // whole workgroup: no tile
+    // (strip form: a "tile" is a segment of a strip and belongs to one wavefront; one past the end loads what the last one
+    //  loads and does nothing with it)
+    const int t_first = STRIP ? t_block + wave : t_block;
     // First column of a tile.  When the image width is not a whole number of pixel
     // groups the last tile column is moved left to end at the image edge (a.xlast =
     // W - TW): it recomputes some pixels of its neighbour (same values, written twice)
@@ -554,16 +592,18 @@ void k_assemble_mfma(const AssembleArgs a) {
         p.n += step_n;
         return p;
     };
-    TilePos cur;
-    {
-        // quotients by the rounded-down reciprocals are at most one too small (0 <= t_first < 2^31)
-        cur.n = (int)(((unsigned long long)(unsigned)t_first * a.inv_img) >> 32);
-        int r2 = t_first - cur.n * a.per_img;
-        if (r2 >= a.per_img) { r2 -= a.per_img; cur.n += 1; }
-        cur.ty = (int)(((unsigned long long)(unsigned)r2 * a.inv_tx) >> 32);
-        cur.tx = r2 - cur.ty * tiles_x;
-        if (cur.tx >= tiles_x) { cur.tx -= tiles_x; cur.ty += 1; }
-    }
+    // quotients by the rounded-down reciprocals are at most one too small (0 <= t < 2^31)
+    auto tile_of = [&](int t) -> TilePos {
+        TilePos p;
+        p.n = (int)(((unsigned long long)(unsigned)t * a.inv_img) >> 32);
+        int r = t - p.n * a.per_img;
+        if (r >= a.per_img) { r -= a.per_img; p.n += 1; }
+        p.ty = (int)(((unsigned long long)(unsigned)r * a.inv_tx) >> 32);
+        p.tx = r - p.ty * tiles_x;
+        if (p.tx >= tiles_x) { p.tx -= tiles_x; p.ty += 1; }
+        return p;
+    };
+    TilePos cur = tile_of(STRIP ? min(t_first, t_end - 1) : t_first);
 
     const char* lr_base = (const char*)a.lr;
     const unsigned lr_esz = a.io_f16 ? 2u : 4u;
@@ -689,11 +729,8 @@ void k_assemble_mfma(const AssembleArgs a) {
     // list form: the entries of a unit, two register sets (the next unit's are loaded while this one is folded)
     u32x2 lval[2][LIST ? LH : 1];                   // four fp16 values (the lane's four pixels) per entry
     unsigned lidx[2][LIST ? LH : 1];                // their four atom numbers, one byte each
-    auto load_list = [&](const TilePos tp, int unit, int jc, int hf, u32x2 (&val)[LIST ? LH : 1], unsigned (&idx)[LIST ? LH : 1]) {
-        const int y = tp.ty * F::TH + unit_row(unit, wave), x = tile_x0(tp.tx) + PX * jc;
-        const int yc = y < a.H ? y : a.H - 1, xc = x < a.W ? x : a.W - PX;
-        const unsigned pix = (unsigned)yc * (unsigned)a.W + (unsigned)xc;           // elements within a plane
-        const size_t img = (size_t)tp.n * a.T * ((size_t)a.H * a.W);
+    // (img: elements before the image's first; pix: the lane's pixels within a plane)
+    auto load_list_at = [&](size_t img, unsigned pix, int hf, u32x2 (&val)[LIST ? LH : 1], unsigned (&idx)[LIST ? LH : 1]) {
         const unsigned char* ibase = a.index + img;
         const char* vbase = (const char*)a.coeff + img * 2;
         const unsigned* lt = ltab + hf * LH;
@@ -703,6 +740,11 @@ void k_assemble_mfma(const AssembleArgs a) {
             idx[e] = __builtin_nontemporal_load((const unsigned*)(ibase + at));
             val[e] = __builtin_nontemporal_load((const u32x2*)(vbase + (size_t)at * 2));
         }
+    };
+    auto load_list = [&](const TilePos tp, int unit, int jc, int hf, u32x2 (&val)[LIST ? LH : 1], unsigned (&idx)[LIST ? LH : 1]) {
+        const int y = tp.ty * F::TH + unit_row(unit, wave), x = tile_x0(tp.tx) + PX * jc;
+        const int yc = y < a.H ? y : a.H - 1, xc = x < a.W ? x : a.W - PX;
+        load_list_at((size_t)tp.n * a.T * ((size_t)a.H * a.W), (unsigned)yc * (unsigned)a.W + (unsigned)xc, hf, val, idx);
     };
     // pixel-major: the unit's 18 432 bytes, 16 per lane and load; byte offset of the lane's first piece within the image
     constexpr int NPM = 18;
@@ -752,6 +794,134 @@ void k_assemble_mfma(const AssembleArgs a) {
         r[1] = __builtin_bit_cast(unsigned, (h2)__builtin_amdgcn_cvt_scalef32_pk_f16_fp8(v, 1.0f, true));
         return r;
     };
+    // ---- strip form (STRIP = the scale): a wavefront walks down a segment of a strip of TW columns, row by row.  Its
+    //      up-sampled rows live in an LDS ring of its own (K rows, and the one that the second lane half reads against zero
+    //      weights): every row is up-sampled once per segment instead of once per tile that touches it, there is no barrier after
+    //      the start, and a lane's four (scale 3: three) neighbouring columns share their LR columns and have compile-time weights.
+    constexpr int S_ = STRIP ? STRIP : 4;
+    if constexpr (STRIP != 0) cur.ty *= a.seg_rows;     // `cur`: image, image row, strip
+    constexpr int LIT = STRIP ? F::LIT : 1, LROW = F::LROW;
+    float* const ring = U + (STRIP ? wave * F::WAVE_F : 0);
+    float* const vrow = ring + F::SLOTS * C * P;        // a row after the vertical pass: [channel][LR column]
+    float* const lring = vrow + LROW;                   // four LR rows
+    unsigned soff[LIT], sinit[4][LIT], spre[LIT];       // byte offset of the lane's elements in an LR row; raw LR rows on their way
+    int sfloor = 0, sshift = 0;                         // LR row sfloor + 2 is the last in the ring, sfloor + 3 is in spre
+    unsigned sread[STRIP ? F::GIT : 1], swrite[STRIP ? F::GIT : 1];   // a lane's groups of columns: first LR column in vrow, place in a ring row
+    const char* simg = lr_base;
+    auto strip_fence = []() {                           // other lanes' LDS writes: ordered by the hardware, and here for the compiler
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    auto strip_load = [&](int ly, unsigned (&v)[LIT], const auto io_f16) {
+        const char* row = simg + (size_t)clampi(ly, 0, a.h - 1) * ((size_t)a.w * lr_esz);
+        if (io_f16) {
+#pragma unroll
+            for (int i = 0; i < LIT; ++i) v[i] = (unsigned)*(const unsigned short*)(row + soff[i]);
+        } else {
+#pragma unroll
+            for (int i = 0; i < LIT; ++i) v[i] = *(const unsigned*)(row + soff[i]);
+        }
+    };
+    auto strip_store = [&](int ly, const unsigned (&v)[LIT], int lane, const auto io_f16) {
+#pragma unroll
+        for (int i = 0; i < LIT; ++i)
+            lring[(ly & 3) * LROW + lane + 64 * i] = io_f16 ? __half2float(__ushort_as_half((unsigned short)v[i])) : __uint_as_float(v[i]);
+    };
+    // a segment's first five LR rows are requested ... (sg.ty: its first row)
+    auto strip_begin = [&](const TilePos sg, int lane, const auto io_f16) {
+        const int X0 = tile_x0(sg.tx), xr = X0 - F::R;
+        sshift = STRIP == 3 ? (xr + 3) % 3 : 0;         // scale 3: groups start at a column that is a multiple of 3
+        const int f0 = (2 * (xr - sshift) + 1 - S_ + 4 * S_) / (2 * S_) - 2;
+        simg = lr_base + (size_t)sg.n * C * ((size_t)a.h * a.w * lr_esz);
+#pragma unroll
+        for (int i = 0; i < LIT; ++i) {
+            const int e = lane + 64 * i < C * MAXLRX ? lane + 64 * i : C * MAXLRX - 1, c = e / MAXLRX, rx = e - c * MAXLRX;
+            soff[i] = ((unsigned)c * (unsigned)a.h * (unsigned)a.w + (unsigned)clampi(f0 - 1 + rx, 0, a.w - 1)) * lr_esz;
+        }
+#pragma unroll
+        for (int i = 0; i < F::GIT; ++i) {
+            const int e = lane + 64 * i < C * F::NGRP ? lane + 64 * i : C * F::NGRP - 1, c = e / F::NGRP, g = e - c * F::NGRP;
+            sread[i] = c * MAXLRX + g * F::GSTEP;
+            swrite[i] = c * P + (STRIP == 3 ? 0 : g * (4 / F::SW));
+        }
+        int m;
+        sfloor = src_floor_s<S_>(clampi(sg.ty - F::R, 0, a.H - 1), m);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) strip_load(sfloor - 1 + i, sinit[i], io_f16);
+        strip_load(sfloor + 3, spre, io_f16);
+    };
+    // Row Y + 1 of the up-sampled image is begun and row Y finished (rows outside the image: its first and last).  Both
+    // passes' LDS reads go out together: the horizontal pass of Y, from what the vertical one left in vrow, into ring slot
+    // `slot` (not if that is negative), and the vertical pass of Y + 1.
+    auto strip_rows = [&](int Y, int slot, const TilePos sg, int lane, const auto io_f16) {
+        int m;
+        const int f = src_floor_s<S_>(clampi(Y + 1, 0, a.H - 1), m);
+        strip_fence();
+        if (f != sfloor) {                              // by one: the next LR row
+            strip_store(sfloor + 3, spre, lane, io_f16);
+            sfloor = f;
+            strip_load(f + 3, spre, io_f16);
+            strip_fence();
+        }
+        constexpr int PH = STRIP == 3 ? 0 : (F::R / S_ + 1) * S_ - F::R;     // a column with the phase of a group's first
+        constexpr int NV = 4 + (F::GPX - 1 + S_ - 1) / S_;                   // (at most that many LR columns)
+        float v[F::GIT][NV], r[LIT][4];
+#pragma unroll
+        for (int i = 0; i < F::GIT; ++i)
+#pragma unroll
+            for (int j = 0; j < NV; ++j) v[i][j] = vrow[sread[i] + j];
+        const float4 w4 = wk[m];
+#pragma unroll
+        for (int i = 0; i < LIT; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) r[i][j] = lring[((f - 1 + j) & 3) * LROW + lane + 64 * i];
+        strip_fence();
+        if (slot >= 0) {
+            float* const dst = ring + slot * (C * P);
+            int mp;
+            const int fp = src_floor_s<S_>(PH, mp);
+#pragma unroll
+            for (int i = 0; i < F::GIT; ++i)
+#pragma unroll
+                for (int q = 0; q < F::GPX; ++q) {
+                    int mq;
+                    const int d = src_floor_s<S_>(PH + q, mq) - fp;
+                    float wq[4];
+                    keys_weights(mq, S_, wq);
+                    const float u = dot4(wq, v[i][d], v[i][d + 1], v[i][d + 2], v[i][d + 3]);
+                    if constexpr (STRIP == 3) {
+                        const int e = lane + 64 * i < C * F::NGRP ? lane + 64 * i : C * F::NGRP - 1;
+                        const int xx = 3 * (e % F::NGRP) + q - sshift;
+                        if (xx >= 0 && xx < UW) dst[swrite[i] + (xx % F::SW) * NG + xx / F::SW] = u;
+                    } else {
+                        dst[swrite[i] + (q % F::SW) * NG + q / F::SW] = u;
+                    }
+                }
+            // columns outside the image are copies of its first and last column
+            const int X0 = tile_x0(sg.tx);
+            if (X0 == 0 || X0 + F::TW + F::R > a.W) {
+                strip_fence();
+                int le = lane;                          // (these few addresses are not worth registers held over the rows)
+                asm volatile("" : "+v"(le));
+                const int side = le / (C * F::R), c = le / F::R % C, i = le % F::R;
+                const int from = side == 0 ? F::R : a.W - 1 - X0 + F::R, to = side == 0 ? i : a.W - X0 + F::R + i;
+                if (side == 0 ? X0 == 0 : side == 1 && to < UW)
+                    dst[c * P + (to % F::SW) * NG + to / F::SW] = dst[c * P + (from % F::SW) * NG + from / F::SW];
+            }
+        }
+        const float wv[4] = {w4.x, w4.y, w4.z, w4.w};
+#pragma unroll
+        for (int i = 0; i < LIT; ++i) vrow[lane + 64 * i] = dot4(wv, r[i][0], r[i][1], r[i][2], r[i][3]);
+    };
+    // the next row's coefficients (image, the lane's offset in it) and this row's output, from row to row
+    const char* snext = nullptr;
+    char* sout = nullptr;
+    unsigned spix = 0u, so0 = 0u;
+    size_t slist = 0;
+    // this form's loads of few planes take their offsets from registers
+    constexpr bool PTREG = STRIP != 0 && !LIST && F::NLOAD <= 4;
+    unsigned preg[PTREG ? F::NLOAD : 1];
     Raw raw[F::NLOAD];
     unsigned lrv[F::NLRP][F::NXC], lrpar = 0u;
 #pragma unroll
@@ -760,7 +930,8 @@ void k_assemble_mfma(const AssembleArgs a) {
         for (int xc = 0; xc < F::NXC; ++xc) lrv[u][xc] = 0u;
     {
         const int lane = tid0 & 63, hf = lane >> 5, j = lane & 31;
-        load_lr(cur, lane, lrv, lrpar);
+        if constexpr (STRIP != 0) strip_begin(cur, lane, a.io_f16);
+        else load_lr(cur, lane, lrv, lrpar);
         if constexpr (LIST) {
             __syncthreads();                            // ltab is written
             load_list(cur, 0, j, hf, lval[0], lidx[0]);
@@ -931,46 +1102,23 @@ void k_assemble_mfma(const AssembleArgs a) {
         }
     };
 
+    float park[C][NSUB > 1 ? NSUB - 1 : 1][2];         // permuted slots, scales 3 and 4: the results of a row's earlier units wait for the last
     unsigned long long wb_last = a.wb_ticks > 0 ? __builtin_amdgcn_s_memrealtime() : 0ull;
-    for (int t = t_first; t < t_end; t += G) {
-        // Per-iteration copy of the thread id the optimiser cannot see through:
-        // index arithmetic derived from it is recomputed each tile instead of
-        // being hoisted out of the loop into dozens of long-lived registers.
-        int tid = tid0;
-        asm volatile("" : "+v"(tid));
+    // A unit: stage 3, stage 4 and the store of WR rows of WC * PX pixels; `more_tiles`: the unit after the tile's last is unit 0 of `nxt`.
+    // (slot0: strip form, ring slot of the first filter row; more_tiles and io_f16: booleans, or the types of known ones)
+    auto do_unit = [&](const int unit, const TilePos cur, const TilePos nxt, const auto more_tiles, const int tid, const int slot0, const auto io_f16) __attribute__((always_inline)) {
         const int lane = tid & 63;
         const int hf = lane >> 5, j = lane & 31, jr = j / F::WC, jc = j % F::WC;
         const int Y0 = cur.ty * F::TH, X0 = tile_x0(cur.tx);
-        const bool more_tiles = t + G < t_end;
-        const TilePos nxt = more_tiles ? advance(cur) : cur;
-
-        // (1) stage 1 of this tile.  (Spreading steps (a) and (b) of the next tile
-        //     over the unit loop was measured slower: the extra mid-tile barrier and
-        //     LDS traffic cost more than the shorter gap between tiles gains.)
-        stage1_setup(cur, tid);
-        __syncthreads();
-#ifdef SR_ABLATE_STAGE1
-        if (a.N < 0)
-#endif
-        stage1_vertical(cur, tid);
-        __syncthreads();      // also: every wavefront is done with the previous tile's U
-#ifdef SR_ABLATE_STAGE1
-        if (a.N < 0)
-#endif
-        stage1_horizontal(tid);
-        __syncthreads();
         const unsigned* pt = ptab + hf * F::NLOAD;
-        float park[C][NSUB > 1 ? NSUB - 1 : 1][2];     // permuted slots, scales 3 and 4: the results of a row's earlier units wait for the last
-        // The wavefront's NU units of this tile, one after the other; while a unit
-        // is folded, the coefficients of the next one (same tile, or unit 0 of the
-        // next tile) are loaded into the registers that fall free.
-#pragma unroll
-        for (int unit = 0; unit < NU; ++unit) {
-        const bool last_unit = unit == NU - 1;
-        const bool more = last_unit ? more_tiles : true;
+        const bool last_unit = STRIP || unit == NU - 1;
+        const bool more = last_unit ? (bool)more_tiles : true;
         unsigned pix_next[NPIX];
         const char* cnext = nullptr;
-        if constexpr (!LIST && !PMAJ && !BLK) cnext = last_unit ? phi_base(nxt, 0, jr, jc, pix_next) : phi_base(cur, unit + 1, jr, jc, pix_next);
+        if constexpr (STRIP != 0 && !BLK) {
+            pix_next[0] = spix;
+            cnext = snext;
+        } else if constexpr (!LIST && !PMAJ && !BLK) cnext = last_unit ? phi_base(nxt, 0, jr, jc, pix_next) : phi_base(cur, unit + 1, jr, jc, pix_next);
         const char* bimg = nullptr;                    // blocked: the next unit's image and offset
         unsigned boff = 0u;
         if constexpr (BLK) {
@@ -989,7 +1137,8 @@ void k_assemble_mfma(const AssembleArgs a) {
         if constexpr (LIST) {
             // the next unit's entries go into the other register set while this one is folded
             if (more) {
-                if (last_unit) load_list(nxt, 0, jc, hf, lval[(unit + 1) & 1], lidx[(unit + 1) & 1]);
+                if constexpr (STRIP != 0) load_list_at(slist, spix, hf, lval[(unit + 1) & 1], lidx[(unit + 1) & 1]);
+                else if (last_unit) load_list(nxt, 0, jc, hf, lval[(unit + 1) & 1], lidx[(unit + 1) & 1]);
                 else load_list(cur, unit + 1, jc, hf, lval[(unit + 1) & 1], lidx[(unit + 1) & 1]);
             }
             const u32x2 (&val)[LH] = lval[unit & 1];
@@ -1111,7 +1260,7 @@ void k_assemble_mfma(const AssembleArgs a) {
                             av[mb], __uint_as_float(raw_word(raw[st], q)), acc[q][mb], 0, 0, 0);
                 if ((st & 3) == 3) __builtin_amdgcn_sched_barrier(0);
                 if (more)
-                    raw[st] = load_raw(cnext, pix_next, pt[st]);
+                    raw[st] = load_raw(cnext, pix_next, PTREG ? preg[PTREG ? st : 0] : pt[st]);
                 if ((st & 3) == 3) __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -1214,7 +1363,7 @@ void k_assemble_mfma(const AssembleArgs a) {
                 } else {
 #pragma unroll
                     for (int i = 0; i < 8; ++i)
-                        raw[8 * c16 + i] = load_raw(cnext, pix_next, pt[8 * c16 + i]);
+                        raw[8 * c16 + i] = load_raw(cnext, pix_next, PTREG ? preg[PTREG ? 8 * c16 + i : 0] : pt[8 * c16 + i]);
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -1263,7 +1412,7 @@ void k_assemble_mfma(const AssembleArgs a) {
                 } else {
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
-                        raw[8 * N16 + i] = load_raw(cnext, pix_next, pt[8 * N16 + i]);
+                        raw[8 * N16 + i] = load_raw(cnext, pix_next, PTREG ? preg[PTREG ? 8 * N16 + i : 0] : pt[8 * N16 + i]);
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -1292,6 +1441,14 @@ void k_assemble_mfma(const AssembleArgs a) {
                 // (scale 2 and scale 4 alike: the pair's columns start 8 or 16 apart, two groups of SW columns)
                 ubo[0] = (unsigned)(row0 + jx * NG + 2 * m);
                 ubo[1] = (unsigned)(row0 + (jx ? 1 : (F::SW - 1) * NG) + 2 * m);
+            }
+        }
+        const float* srow[F::RH0];                     // strip form: the lane half's filter rows in the ring
+        if constexpr (STRIP != 0) {
+#pragma unroll
+            for (int dyv = 0; dyv < F::RH0; ++dyv) {
+                const int s0 = slot0 + dyv, s1 = s0 + F::RH0;
+                srow[dyv] = ring + (hf ? (s1 < F::SLOTS ? s1 : s1 - F::SLOTS) : (s0 < F::SLOTS ? s0 : s0 - F::SLOTS)) * (C * P) + jc;
             }
         }
         float outp[C][PX];
@@ -1342,8 +1499,12 @@ void k_assemble_mfma(const AssembleArgs a) {
 #pragma unroll
                     for (int vv = 0; vv < F::NSLOT; ++vv) {
                         const int dyv = vv / K, dxv = vv % K;
-                        const int off = c * UH * P + dyv * P + ((q + dxv) % PX) * NG + (q + dxv) / PX;
-                        s = fmaf(acc[q][vv / 16][vv % 16], ub[off], s);
+                        if constexpr (STRIP != 0) {
+                            s = fmaf(acc[q][vv / 16][vv % 16], srow[dyv][c * P + ((q + dxv) % PX) * NG + (q + dxv) / PX], s);
+                        } else {
+                            const int off = c * UH * P + dyv * P + ((q + dxv) % PX) * NG + (q + dxv) / PX;
+                            s = fmaf(acc[q][vv / 16][vv % 16], ub[off], s);
+                        }
                     }
                     outp[c][q] = LG ? s * rinv[q] : s;
                 }
@@ -1367,8 +1528,17 @@ void k_assemble_mfma(const AssembleArgs a) {
         const unsigned o0 = PMAJ ? (unsigned)y * (unsigned)a.W + x + hf * 64
                           : PSM == 3 ? (unsigned)y * (unsigned)a.W + x + hf * 6
                           : PERM ? (unsigned)y * (unsigned)a.W + x + hf * (2 * PSM) + (PSM == 4 ? 4 : 2) * (jc % 2)
-                                 : (unsigned)y * (unsigned)a.W + x + hf * (PX / 2);   // within the image
-        char* const out_img = (char*)a.out + (size_t)cur.n * C * ((size_t)plane_px * (a.io_f16 ? 2 : 4));
+                          : STRIP ? so0 : (unsigned)y * (unsigned)a.W + x + hf * (PX / 2);   // within the image
+        char* const out_img = STRIP ? sout : (char*)a.out + (size_t)cur.n * C * ((size_t)plane_px * (a.io_f16 ? 2 : 4));
+        // Every lane stores, one outside the image beyond the end of the buffer, which drops it.  Behind a branch the compiler cannot
+        // count the stores, and the next unit's fold, which waits for loads issued before them, waits for them as well.
+        // 512 x 512 x4: 14.1 -> 13.3 us; no different where a unit is long.
+        const __amdgpu_buffer_rsrc_t out_rsrc = __builtin_amdgcn_make_buffer_rsrc(out_img, 0, (int)(C * plane_px * (a.io_f16 ? 2u : 4u)), RAW_BUFFER);
+#ifdef SR_ABLATE_STORES
+        auto out_at = [&](unsigned e, unsigned size) -> unsigned { return valid && a.N < 0 ? e * size : BEYOND; };   // (never true)
+#else
+        auto out_at = [&](unsigned e, unsigned size) -> unsigned { return valid ? e * size : BEYOND; };
+#endif
 #pragma unroll
         for (int c = 0; c < C; ++c) {
             float tot[PX / 2];
@@ -1420,67 +1590,32 @@ void k_assemble_mfma(const AssembleArgs a) {
                 tot[0] = __uint_as_float(hi_slot ? a1 : a0);
                 tot[1] = __uint_as_float(hi_slot ? b1 : b0);
             }
-#ifdef SR_ABLATE_STORES
-            if (valid && a.N < 0) {                       // never true: the stores stay in the code, unexecuted
-#else
-            if (valid) {
-#endif
-                const unsigned oe = o0 + c * plane_px;
-                if constexpr (PMAJ) {
+            const unsigned oe = o0 + c * plane_px;
+            if constexpr (PMAJ) {
 #pragma unroll
-                    for (int t = 0; t < 2; ++t) {
-                        if (a.io_f16) *(__half*)(out_img + (size_t)((oe + 32 * t) * 2u)) = narrow_f16(tot[t]);
-                        else *(float*)(out_img + (size_t)((oe + 32 * t) * 4u)) = tot[t];
-                    }
-                } else if constexpr (PSM == 4) {
-                    if (a.io_f16) {
-                        __half2 lo2, hi2;
-                        lo2.x = narrow_f16(tot4[0]); lo2.y = narrow_f16(tot4[1]);
-                        hi2.x = narrow_f16(tot4[2]); hi2.y = narrow_f16(tot4[3]);
-                        u32x2 w2;
-                        w2[0] = __builtin_bit_cast(unsigned, lo2);
-                        w2[1] = __builtin_bit_cast(unsigned, hi2);
-                        *(u32x2*)(out_img + (size_t)(oe * 2u)) = w2;
-                    } else {
-                        *(float4*)(out_img + (size_t)(oe * 4u)) = make_float4(tot4[0], tot4[1], tot4[2], tot4[3]);
-                    }
-                } else if constexpr (PSM == 3) {
-#pragma unroll
-                    for (int i = 0; i < 3; ++i) {
-                        if (a.io_f16) {
-                            __half2 h2;
-                            h2.x = narrow_f16(tot6[2 * i]);
-                            h2.y = narrow_f16(tot6[2 * i + 1]);
-                            *(__half2*)(out_img + (size_t)((oe + 2 * i) * 2u)) = h2;
-                        } else {
-                            *(float2*)(out_img + (size_t)((oe + 2 * i) * 4u)) = make_float2(tot6[2 * i], tot6[2 * i + 1]);
-                        }
-                    }
-                } else if (a.io_f16) {
-                    __half* op = (__half*)(out_img + (size_t)(oe * 2u));
-                    if constexpr (PX >= 4) {
-#pragma unroll
-                        for (int q = 0; q < PX / 2; q += 2) {
-                            __half2 h2;
-                            h2.x = narrow_f16(tot[q]);
-                            h2.y = narrow_f16(tot[q + 1]);
-                            *(__half2*)(op + q) = h2;
-                        }
-                    } else {
-                        op[0] = narrow_f16(tot[0]);
-                    }
-                } else {
-                    float* op = (float*)(out_img + (size_t)(oe * 4u));
-                    if constexpr (PX == 8) *(float4*)op = make_float4(tot[0], tot[1], tot[2], tot[3]);
-#ifdef SR_STORES_WRITE_THROUGH
-                    else if constexpr (PX == 4)
-                        __hip_atomic_store((unsigned long long*)op, __builtin_bit_cast(unsigned long long, make_float2(tot[0], tot[1])),
-                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#else
-                    else if constexpr (PX == 4) *(float2*)op = make_float2(tot[0], tot[1]);
-#endif
-                    else op[0] = tot[0];
+                for (int t = 0; t < 2; ++t) {
+                    if (a.io_f16) store16(out_rsrc, out_at(oe + 32 * t, 2u), tot[t]);
+                    else store32(out_rsrc, out_at(oe + 32 * t, 4u), __float_as_uint(tot[t]));
                 }
+            } else if constexpr (PSM == 4) {
+                if (a.io_f16) {
+                    store64(out_rsrc, out_at(oe, 2u), pack_f16(tot4[0], tot4[1]), pack_f16(tot4[2], tot4[3]));
+                } else {
+                    store128(out_rsrc, out_at(oe, 4u), tot4);
+                }
+            } else if constexpr (PSM == 3) {
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    if (a.io_f16) store32(out_rsrc, out_at(oe + 2 * i, 2u), pack_f16(tot6[2 * i], tot6[2 * i + 1]));
+                    else store64(out_rsrc, out_at(oe + 2 * i, 4u), __float_as_uint(tot6[2 * i]), __float_as_uint(tot6[2 * i + 1]));
+                }
+            } else if constexpr (PX == 4) {
+                if (a.io_f16) store32(out_rsrc, out_at(oe, 2u), pack_f16(tot[0], tot[1]));
+                else store64(out_rsrc, out_at(oe, 4u), __float_as_uint(tot[0]), __float_as_uint(tot[1]));
+            } else {
+                static_assert(PX == 2, "two or four pixels per lane");
+                if (a.io_f16) store16(out_rsrc, out_at(oe, 2u), tot[0]);
+                else store32(out_rsrc, out_at(oe, 4u), __float_as_uint(tot[0]));
             }
         }
         // (6) L2 write-back pacing, see the note at the top of this file: workgroups 0 .. 7 run on the eight XCDs (fewer on a partition)
@@ -1491,12 +1626,128 @@ void k_assemble_mfma(const AssembleArgs a) {
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
             }
         }
+    };
+    if constexpr (STRIP != 0) {
+        if constexpr (PTREG) {
+#pragma unroll
+            for (int i = 0; i < F::NLOAD; ++i) preg[i] = ptab[((tid0 >> 5) & 1) * F::NLOAD + i];
+        }
+        const unsigned esz = LIST ? 1u : OU;            // units of the coefficients' offsets: bytes (lists: elements)
+        const size_t image_px = (size_t)a.H * a.W;
+        auto lane_pix = [&](const TilePos p, int jc) -> unsigned {              // of a strip's row
+            const int x = tile_x0(p.tx) + PX * jc, xc = x < a.W ? x : a.W - PX;
+            return ((unsigned)p.ty * (unsigned)a.W + (unsigned)xc) * esz;
+        };
+        // the row whose coefficients are requested next: place of a segment's row
+        auto ld_place = [&](const TilePos p, int jc) {
+            spix = lane_pix(p, jc);
+            snext = (const char*)a.coeff + (size_t)p.n * a.L * (image_px * F::CB);
+            slist = (size_t)p.n * a.T * image_px;
+        };
+        ld_place(cur, tid0 & 31);
+        const bool io_f16 = a.io_f16 != 0;
+        for (int t = t_first; t < t_end; t += G) {
+            int tid = tid0;
+            asm volatile("" : "+v"(tid));
+            const int lane = tid & 63, hf = lane >> 5, jc = lane & 31;
+            TilePos sg = cur;                           // image, first row of the segment, strip
+            if (t != t_first) {
+                sg = tile_of(t);
+                sg.ty *= a.seg_rows;
+                strip_begin(sg, lane, io_f16);
+            }
+            const int y1 = min(a.H, sg.ty + a.seg_rows);
+            strip_fence();
+#pragma unroll
+            for (int i = 0; i < 4; ++i) strip_store(sfloor - 1 + i, sinit[i], lane, io_f16);
+            for (int i = -1; i < K; ++i) strip_rows(sg.ty - F::R + i, i, sg, lane, io_f16);
+#pragma unroll
+            for (int i = 0; i < LIT; ++i) asm volatile("" : "+v"(spre[i]));    // (there before the loop, or every round of it waits for everything)
+            int slot = 0;                               // of row y - R
+            so0 = (unsigned)sg.ty * (unsigned)a.W + (unsigned)(tile_x0(sg.tx) + PX * jc) + hf * (PX / 2);
+            sout = (char*)a.out + (size_t)sg.n * C * (image_px * (io_f16 ? 2 : 4));
+            auto step = [&](int parity, int y, const auto more) __attribute__((always_inline)) {
+                strip_rows(y + F::R + 1, slot == 0 ? F::SLOTS - 1 : slot - 1, sg, lane, io_f16);
+                strip_fence();
+                int tid_row = tid;                      // (as `tid`: what a unit derives from it is not kept in registers across rows)
+                asm volatile("" : "+v"(tid_row));
+                const TilePos at = {sg.n, y, sg.tx};
+                do_unit(parity, at, at, more, tid_row, slot, io_f16);
+                so0 += (unsigned)a.W;
+                slot = slot == F::SLOTS - 1 ? 0 : slot + 1;
+            };
+            auto inner = [&](int parity, int y) __attribute__((always_inline)) {     // a row with another after it in the segment
+                spix += (unsigned)a.W * esz;
+                step(parity, y, std::true_type{});
+            };
+            const bool more = t + G < t_end;
+            auto before_last = [&]() {                  // what is requested next is the next segment's first row
+                if (!more) return;
+                TilePos sn = tile_of(t + G);
+                sn.ty *= a.seg_rows;
+                ld_place(sn, jc);
+            };
+            int y = sg.ty;
+            if constexpr (LIST) {                       // two register sets
+                for (; y + 2 < y1; y += 2) {
+                    inner(0, y);
+                    inner(1, y + 1);
+                }
+                if (y + 1 < y1) {
+                    inner(0, y++);
+                    before_last();
+                    step(1, y, more);
+                } else {
+                    before_last();
+                    step(0, y, more);
+#pragma unroll
+                    for (int e = 0; e < LH; ++e) { lval[0][e] = lval[1][e]; lidx[0][e] = lidx[1][e]; }
+                }
+            } else {
+                for (; y + 1 < y1; ++y) inner(0, y);
+                before_last();
+                step(0, y, more);
+            }
+        }
+    } else {
+    for (int t = t_first; t < t_end; t += G) {
+        // Per-iteration copy of the thread id the optimiser cannot see through:
+        // index arithmetic derived from it is recomputed each tile instead of
+        // being hoisted out of the loop into dozens of long-lived registers.
+        int tid = tid0;
+        asm volatile("" : "+v"(tid));
+        const int lane = tid & 63;
+        const bool more_tiles = t + G < t_end;
+        const TilePos nxt = more_tiles ? advance(cur) : cur;
+
+        // (1) stage 1 of this tile.  (Spreading steps (a) and (b) of the next tile
+        //     over the unit loop was measured slower: the extra mid-tile barrier and
+        //     LDS traffic cost more than the shorter gap between tiles gains.)
+        stage1_setup(cur, tid);
+        __syncthreads();
+#ifdef SR_ABLATE_STAGE1
+        if (a.N < 0)
+#endif
+        stage1_vertical(cur, tid);
+        __syncthreads();      // also: every wavefront is done with the previous tile's U
+#ifdef SR_ABLATE_STAGE1
+        if (a.N < 0)
+#endif
+        stage1_horizontal(tid);
+        __syncthreads();
+        // The wavefront's NU units of this tile, one after the other; while a unit
+        // is folded, the coefficients of the next one (same tile, or unit 0 of the
+        // next tile) are loaded into the registers that fall free.
+#pragma unroll
+        for (int unit = 0; unit < NU; ++unit) {
+        do_unit(unit, cur, nxt, more_tiles, tid, 0, a.io_f16);
         // (2) prefetch the next tile's LR footprint from inside the unit loop, where
         //     the wavefront waits on memory anyway, and not in the barrier-to-barrier
         //     up-sampling phase that every wavefront of the workgroup has to sit out
         if (unit == (NU > 1 ? 1 : 0) && more_tiles) load_lr(nxt, lane, lrv, lrpar);
         }   // unit
         cur = nxt;
+    }
     }
 }
 
@@ -1532,13 +1783,13 @@ inline long long wall_clock_khz() {
 
 // How `blocks` workgroups walk the tiles: each of 8 shares (the XCDs; one share if the grid is no multiple of 8) is a
 // contiguous run of tiles, walked by every workgroup of that XCD in steps of their number.
-inline void walk_of(AssembleArgs& a, int ntiles, int blocks) {
+inline void walk_of(AssembleArgs& a, int ntiles, int blocks, int per_block) {
     a.ntiles = ntiles;
     a.per_img = a.tiles_x * a.tiles_y;
     a.group_shift = blocks % 8 == 0 ? 3 : 0;
     const int groups = 1 << a.group_shift;
     a.share = (int)(((long long)ntiles + groups - 1) / groups);
-    a.stride = blocks / groups;
+    a.stride = blocks / groups * per_block;
     a.step_n = a.stride / a.per_img;
     const int r = a.stride - a.step_n * a.per_img;
     a.step_y = r / a.tiles_x;
@@ -1548,9 +1799,10 @@ inline void walk_of(AssembleArgs& a, int ntiles, int blocks) {
 }
 
 template <int K, int C, int NP8, int PX, int WR, int NW, int NU, int WPE, int CT = CT_F16, int SMIN = 2, bool BIG = false,
-          int PSM = 0>
+          int PSM = 0, int STRIP = 0>
 hipError_t launch_one(const AssembleArgs& a0, hipStream_t st) {
-    using F = Cfg<K, C, NP8, PX, WR, NW, NU, CT, SMIN, (PSM == 4 ? 2 : (PSM == 3 ? 3 : 1)), (PSM == 8 ? 1 : 0)>;
+    using F = Cfg<K, C, NP8, PX, WR, NW, NU, CT, SMIN, (PSM == 4 ? 2 : (PSM == 3 ? 3 : 1)), (PSM == 8 ? 1 : 0), STRIP>;
+    if (STRIP && a0.s != STRIP) return hipErrorInvalidValue;
     if (a0.s < SMIN) return hipErrorInvalidValue;       // its LDS footprint buffers would be too small
     if ((a0.pre_shuffle != 0) != (PSM >= 1 && PSM <= 4) || (a0.pixel_major != 0) != (PSM == 8)) return hipErrorInvalidValue;
     // logits: a softmax over every atom, so every plane is folded
@@ -1580,15 +1832,52 @@ hipError_t launch_one(const AssembleArgs& a0, hipStream_t st) {
         if (a.W < F::TW) return hipErrorInvalidValue;
         a.xlast = a.W - F::TW;
     }
+    const int cap = compute_units() * (4 * WPE / NW > 0 ? 4 * WPE / NW : 1);
+    a.seg_rows = F::TH;
+    if (STRIP) {
+        // as many segments as there are wavefronts, or one per strip
+        const long long strips = (long long)a.tiles_x * a.N, waves = (long long)cap * NW;
+        const int per_strip = (int)(strips < waves ? waves / strips : 1);
+        a.seg_rows = (a.H + per_strip - 1) / per_strip;
+        a.tiles_y = (a.H + a.seg_rows - 1) / a.seg_rows;
+    }
     const long long nt = (long long)a.tiles_x * a.tiles_y * a.N;
     if (nt > 0x7fffffffLL) return hipErrorInvalidValue;
-    // as many workgroups as stay resident (WPE wavefronts per SIMD)
-    const int cus = compute_units();
-    const int cap = cus * (4 * WPE / NW > 0 ? 4 * WPE / NW : 1);
-    const int blocks = nt < cap ? (int)nt : cap;
-    walk_of(a, (int)nt, blocks);
-    hipLaunchKernelGGL((k_assemble_mfma<K, C, NP8, PX, WR, NW, NU, WPE, CT, SMIN, BIG, PSM>), dim3(blocks), dim3(F::NT), 0, st, a);
+    // as many workgroups as stay resident (WPE wavefronts per SIMD); strip form: a segment per wavefront
+    const long long want = STRIP ? (nt + NW - 1) / NW : nt;
+    const int blocks = want < cap ? (int)want : cap;
+    walk_of(a, (int)nt, blocks, STRIP ? NW : 1);
+    hipLaunchKernelGGL((k_assemble_mfma<K, C, NP8, PX, WR, NW, NU, WPE, CT, SMIN, BIG, PSM, STRIP>), dim3(blocks), dim3(F::NT), 0, st, a);
     return hipGetLastError();
+}
+
+// Whether a call goes to the strip form (strips of `sw` columns) where it is built next to tiles of tw x th pixels in
+// workgroups of four wavefronts: the form that leaves the fullest SIMD with fewer rows; at about the same number the strips,
+// which up-sample no row twice, once a segment is long enough to pay for its own first rows (scale 3: dearer rows).
+// Measured, both forms in one run (us, tiles / strips; rows of the fullest SIMD; rows of a segment):
+//   fewer rows: 720p x4 fp16 34.1 / 30.6 (12 / 8; 4), 540 x 960 x2 fp16 28.5 / 23.5 (8 / 6; 3), 480 x 640 x2 fp32 32.7 / 27.0 (8 / 6; 3)
+//   about the same: 4K x4, 8 atoms 79 / 62 (64 / 66; 22), 1080p x2 65.0 / 63.5 (16 / 16; 8), 720p x4 fp32 61.3 / 60.6 (16 / 16; 8), 4K x3 256 / 251
+//   (64 / 64; 32), but 1080p x3 63.1 / 65.9 (16 / 16; 8), 512 x 512 fp32 22.3 / 24.1 (4 / 4; 2), 512 x 512 fp16 14.4 / 14.9 (2 / 2; 1).
+inline bool strip_form(const AssembleArgs& a, int sw, int tw, int th, int wpe = 2) {
+    const long long simds = 4ll * compute_units(), strips = (long long)((a.W + sw - 1) / sw) * a.N;
+    const long long per_strip = strips < simds * wpe ? simds * wpe / strips : 1;
+    const long long rows = (a.H + per_strip - 1) / per_strip, segments = strips * ((a.H + rows - 1) / rows);
+    const long long tiles = (long long)((a.W + tw - 1) / tw) * ((a.H + th - 1) / th) * a.N;
+    const long long strip_rows = (segments + simds - 1) / simds * rows;
+    const long long tile_rows = (4 * tiles + simds - 1) / simds * (tw * th / (4 * sw));
+    return strip_rows < tile_rows || (10 * strip_rows <= 11 * tile_rows && rows >= (a.s == 3 ? 16 : 6));
+}
+
+// The strip form: workgroups of four wavefronts, WPE of them per CU.
+template <int K, int C, int NP8, int PX, int WPE, int CT = CT_F16, int PSM = 0>
+hipError_t launch_strip(const AssembleArgs& a, hipStream_t st) {
+    constexpr int WPE2 = WPE < 3 ? WPE : 2;             // (scales 2 and 3: the LR rows of twelve wavefronts do not fit the LDS)
+    switch (a.s) {
+    case 2:  return launch_one<K, C, NP8, PX, 1, 4, 1, WPE2, CT, 2, false, PSM, 2>(a, st);
+    case 3:  return launch_one<K, C, NP8, PX, 1, 4, 1, WPE2, CT, 3, false, PSM, 3>(a, st);
+    case 4:  return launch_one<K, C, NP8, PX, 1, 4, 1, WPE, CT, 4, false, PSM, 4>(a, st);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 }  // namespace srd

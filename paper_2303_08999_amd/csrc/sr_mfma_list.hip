@@ -9,7 +9,7 @@ bool mfma_list_supported(const AssembleArgs& a, int k, bool value_f16) {
     if (k != 5 || a.C != 3 || !value_f16 || a.L > 128 || a.T < 1 || a.T > LIST_MAX_ENTRIES) return false;
     if (a.W < 4 || a.W % 4 != 0 || a.H < 1) return false;
     if ((unsigned long long)a.T * a.H * a.W >= (1ull << 32)) return false;             // 32-bit element offsets within an image
-    if ((unsigned long long)a.C * a.H * a.W * 4ull >= (1ull << 32)) return false;
+    if ((unsigned long long)a.C * a.H * a.W * 4ull > 0xffffffc0ull) return false;
     return true;
 }
 
@@ -18,7 +18,8 @@ bool mfma_list_supported(const AssembleArgs& a, int k, bool value_f16) {
 template <int CT>
 static hipError_t launch_ct(const AssembleArgs& a, hipStream_t st) {
     if (a.L <= 72) {
-        if (a.s == 4) return launch_one<5, 3, 9, 4, 1, 4, 4, 2, CT, 4>(a, st);
+        if (a.s == 4 && strip_form(a, 128, 128, 16)) return launch_one<5, 3, 9, 4, 1, 4, 1, 2, CT, 4, false, 0, 4>(a, st);
+        if (a.s == 3 && strip_form(a, 128, 128, 8)) return launch_one<5, 3, 9, 4, 1, 4, 1, 2, CT, 3, false, 0, 3>(a, st);
         return launch_one<5, 3, 9, 4, 1, 4, 2, 2, CT, 2>(a, st);
     }
     return launch_one<5, 3, 16, 4, 1, 4, 2, 2, CT, 2>(a, st);

@@ -1,0 +1,87 @@
+"""The strip form of the matrix-core kernel where it can go wrong: strips that stick out of the image or end it on an odd
+column, every scale (three ways of grouping the columns), first and last rows, several segments per wavefront, every pixel
+group and coefficient type.  The sizes are large enough that the library takes strips (fewer rows on the fullest SIMD than
+tiles, or long segments).  Against the generic kernel, whose up-sampled values are the same bit for bit, so that only the
+order of fp32 sums and the 16-bit dictionary operands differ: 5e-5 * max(1, max|out|) and 2^-10 of it for an fp16 image,
+bfloat16 coefficients 1e-4 (dictionary of 16 significant bits); and the pixels at the borders against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2303_08999_amd as sr
+import sr_synth
+from test_gpu_parity import DEV, GENERIC, MFMA, assert_parity, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    sr.load()
+
+
+@pytest.mark.parametrize("n, c, h, w, scale, L, k, coeff, image, kept", [
+    (1, 3, 270, 480, 4, 72, 5, "f16", "f32", None),      # whole strips
+    (1, 3, 271, 473, 4, 72, 5, "f16", "f16", None),      # the last strip sticks out of the image
+    (1, 3, 300, 333, 3, 72, 5, "f8", "f32", None),       # rows that are no whole pixel groups: the last strip is moved left
+    (1, 3, 301, 501, 2, 72, 5, "f16", "f32", None),
+    (1, 3, 400, 43, 3, 72, 5, "f16", "f32", None),       # 129 columns: two strips, almost the same
+    (2, 3, 301, 501, 2, 72, 5, "f32", "f16", None),
+    (1, 1, 501, 301, 3, 72, 5, "f32", "f32", None),
+    (3, 3, 190, 250, 4, 72, 5, "f16", "f32", 8),         # kept lists: the forms with few planes
+    (1, 3, 333, 502, 3, 72, 5, "f8", "f32", 8),
+    (1, 3, 301, 502, 2, 72, 5, "bf16", "f32", 13),
+    (1, 1, 333, 401, 3, 72, 5, "bf16", "f32", None),
+    (1, 3, 250, 330, 4, 128, 5, "f16", "f32", None),     # two pixels per lane
+    (1, 3, 250, 331, 3, 128, 7, "f16", "f16", None),     # eight ring rows, groups before the image's first column
+    (1, 1, 251, 401, 2, 72, 7, "bf16", "f32", None),
+    (1, 3, 251, 401, 2, 72, 7, "f32", "f32", None),
+    (1, 3, 333, 401, 3, 40, 3, "f32", "f32", None),      # four ring rows
+    (1, 3, 333, 500, 2, 72, 3, "f8", "f16", None),
+    (1, 3, 251, 401, 4, 128, 3, "f16", "f32", 30),
+    (2300, 3, 4, 16, 2, 72, 5, "f16", "f32", None),      # more strips than wavefronts: several segments one after the other
+])
+def test_strips(oracle, n, c, h, w, scale, L, k, coeff, image, kept):
+    wl = sr_synth.Workload("strips", 60, n, c, h, w, scale, L, k, coeff, image)
+    inp = sr_synth.make_inputs(wl, DEV)
+    rng = np.random.default_rng(h)
+    lst = None if kept is None else rng.permutation(L)[:kept].astype(np.int32)
+    gamma = None if kept is None else rng.uniform(0.5, 1.5, size=kept).astype(np.float32)
+    got = run_gpu(inp, wl, MFMA, lst, gamma).float()
+    want = run_gpu(inp, wl, GENERIC, lst, gamma).float()
+    assert torch.isfinite(got).all(), "some output pixel was never written"
+    tol = ((1e-4 if coeff == "bf16" else 5e-5) + (2.0 ** -10 if image == "f16" else 0.0)) * max(1.0, float(want.abs().max()))
+    assert float((got - want).abs().max()) <= tol
+    if n == 1:
+        rows = sorted({0, 1, 2, wl.H // 2, wl.H - 3, wl.H - 2, wl.H - 1})
+        pts = np.array([(0, y, x) for y in rows for x in (0, 1, 2, 127, min(128, wl.W - 1), wl.W - 3, wl.W - 2, wl.W - 1)])
+        ref = oracle.assemble_points(oracle.bicubic(inp["lr"].cpu().numpy(), scale), sr_synth.stored_numpy(inp["coeff"]),
+                                     inp["dict"].cpu().numpy(), pts, kept=lst, gamma=gamma)
+        have = got[0].cpu().numpy()[:, pts[:, 1], pts[:, 2]].T
+        assert_parity(have, ref, coeff, image == "f16", "borders")
+
+
+@pytest.mark.parametrize("h, w, scale, entries, image", [(270, 480, 4, 8, "f32"), (301, 500, 3, 5, "f16"), (270, 477, 4, 16, "f32"), (301, 500, 3, 13, "f32")])
+def test_strips_of_lists(h, w, scale, entries, image):
+    wl = sr_synth.Workload("strips", 61, 1, 3, h, w, scale, 72, 5, "f16", image)
+    inp = sr_synth.make_inputs(wl, DEV)
+    index, value = sr_synth.to_list(inp["coeff"], entries)
+    out = [torch.full((1, 3, wl.H, wl.W), float("nan"), device=DEV, dtype=inp["lr"].dtype) for _ in range(2)]
+    for o, kernel in zip(out, (MFMA, GENERIC)):
+        sr.sr_dict_assemble_list_ex(inp["lr"], index, value, inp["dict"], 72, 5, scale, 3, entries, o, kernel=kernel)
+    got, want = out[0].float(), out[1].float()
+    assert torch.isfinite(got).all()
+    assert float((got - want).abs().max()) <= (5e-5 + (2.0 ** -10 if image == "f16" else 0.0)) * max(1.0, float(want.abs().max()))
+
+
+@pytest.mark.parametrize("h, w, scale, coeff", [(271, 473, 4, "f16"), (301, 501, 2, "bf16"), (333, 400, 3, "f16")])
+def test_strips_of_logits(h, w, scale, coeff):
+    """Same fp32 evaluation of the exponentials in both kernels (see test_gpu_logits.py)."""
+    wl = sr_synth.Workload("strips", 62, 1, 3, h, w, scale, 72, 5, coeff, "f32")
+    lr, z, d = sr_synth.make_lr(wl, DEV), sr_synth.make_logits(wl, DEV), sr_synth.make_dictionary(wl, DEV)
+    out = [torch.full((1, 3, wl.H, wl.W), float("nan"), device=DEV) for _ in range(2)]
+    for o, kernel in zip(out, (MFMA, GENERIC)):
+        sr.sr_dict_assemble_ex(lr, z, d, 72, 5, scale, 3, o, opts=sr.make_options(kernel, coeff_kind=sr.SR_COEFF_LOGITS))
+    assert torch.isfinite(out[0]).all()
+    assert float((out[0] - out[1]).abs().max()) <= 5e-5
