@@ -77,7 +77,7 @@
 // agent-scope release fence, which the compiler turns into the L2 write-back instruction and a wait): the writes
 // reach memory in bursts and the reads in between run undisturbed.  Measured: 4K frame 254 -> 241 us, the blocked
 // order 240 -> 231 us, 1080p 68 -> 65.5 us, sixteen video frames 1.80 -> 1.72 ms, 58 kept atoms 224 -> 215 us; neutral
-// at 43 kept atoms and for 720p fp32, 1-2 % slower with fewer atoms and with 8-bit coefficients, which are not bound
+// at 43 kept atoms and for 720p fp32, 1-2 % slower with fewer atoms and with 8-bit coefficients in tiles, which are not bound
 // by the stream: those instantiations are launched without it.  The period was swept from 4 to 48 us (8 us and
 // less cost time, beyond 32 us the gain fades; sixteen video frames of 7x7 atoms: 1.72 ms at 16 us, 1.69 at 24 to 32,
 // hence 28 us there); results are bit-identical.  -DSR_NO_L2_WRITEBACK builds without it.
@@ -1815,9 +1815,11 @@ hipError_t launch_one(const AssembleArgs& a0, hipStream_t st) {
     if ((PSM == 2 || PSM == 3 || PSM == 4) && (a0.s != PSM || a0.w % 4 != 0)) return hipErrorInvalidValue;
     AssembleArgs a = a0;
 #ifndef SR_NO_L2_WRITEBACK
-    // L2 write-back pacing where the coefficient stream is the bound: 49 atoms and more, not the 8-bit and list forms
-    // (measured neutral at 43 kept atoms, 1-2 % slower below and with 8-bit coefficients)
-    if (NP8 >= 9 && CT != CT_F8 && !F::LIST) {
+    // L2 write-back pacing where the coefficient stream is the bound: 49 atoms and more, not the list forms nor 8-bit
+    // coefficients in tiles (measured neutral at 43 kept atoms, 1-2 % slower below and for 8-bit tiles).  In strips 8-bit
+    // coefficients are near the stream too: 4K 149.9 -> 146.4 us, 1080p x3 the same; strips with 8 atoms 60.8 -> 64.5 and lists
+    // of 8 108 -> 111.5 with it, 4K fp16 strips 258 -> 245.
+    if (NP8 >= 9 && (CT != CT_F8 || STRIP) && !F::LIST) {
         // 16 us of the constant-rate clock the kernel reads (7x7 atoms: 28 us, measured); one asking workgroup per XCD
         // (32 CUs each: eight on the whole device, fewer on a partition of it)
         a.wb_ticks = (int)((K == 7 ? 28LL : 16LL) * wall_clock_khz() / 1000);
