@@ -898,15 +898,16 @@ void k_assemble_mfma(const AssembleArgs a) {
                         dst[swrite[i] + (q % F::SW) * NG + q / F::SW] = u;
                     }
                 }
-            // columns outside the image are copies of its first and last column
+            // columns outside the image are copies of its first and last column (ring column i is image column X0 - R + i; a last strip
+            // that was moved left may start at a column other than 0 and still look over the left edge: 129 columns, X0 = 1)
             const int X0 = tile_x0(sg.tx);
-            if (X0 == 0 || X0 + F::TW + F::R > a.W) {
+            if (X0 < F::R || X0 + F::TW + F::R > a.W) {
                 strip_fence();
                 int le = lane;                          // (these few addresses are not worth registers held over the rows)
                 asm volatile("" : "+v"(le));
                 const int side = le / (C * F::R), c = le / F::R % C, i = le % F::R;
-                const int from = side == 0 ? F::R : a.W - 1 - X0 + F::R, to = side == 0 ? i : a.W - X0 + F::R + i;
-                if (side == 0 ? X0 == 0 : side == 1 && to < UW)
+                const int from = side == 0 ? F::R - X0 : a.W - 1 - X0 + F::R, to = side == 0 ? i : a.W - X0 + F::R + i;
+                if (side == 0 ? i < F::R - X0 : side == 1 && to < UW)
                     dst[c * P + (to % F::SW) * NG + to / F::SW] = dst[c * P + (from % F::SW) * NG + from / F::SW];
             }
         }

@@ -10,7 +10,7 @@ import torch
 
 import paper_2303_08999_amd as sr
 import sr_synth
-from test_gpu_parity import DEV, GENERIC, MFMA, assert_parity, run_gpu
+from test_gpu_parity import DEV, GENERIC, MFMA, assert_parity, check_full, run_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -83,5 +83,39 @@ def test_strips_of_logits(h, w, scale, coeff):
     out = [torch.full((1, 3, wl.H, wl.W), float("nan"), device=DEV) for _ in range(2)]
     for o, kernel in zip(out, (MFMA, GENERIC)):
         sr.sr_dict_assemble_ex(lr, z, d, 72, 5, scale, 3, o, opts=sr.make_options(kernel, coeff_kind=sr.SR_COEFF_LOGITS))
+    assert torch.isfinite(out[0]).all()
+    assert float((out[0] - out[1]).abs().max()) <= 5e-5
+
+
+@pytest.mark.parametrize("n, c, h, L, coeff, image, kept", [
+    (1, 1, 43, 72, "f16", "f32", None),
+    (1, 1, 7, 72, "bf16", "f16", None),
+    (1, 3, 43, 72, "f16", "f32", 30),                    # kept lists that take strips at this size
+    (1, 3, 43, 72, "bf16", "f32", 41),
+    (1, 3, 43, 72, "f8", "f32", 30),
+    (32, 3, 43, 72, "f16", "f32", None),                 # batches: five rows to a segment
+    (32, 3, 43, 72, "f8", "f32", None),
+])
+def test_last_strip_moved_to_column_one(oracle, n, c, h, L, coeff, image, kept):
+    """43 columns at x3 are 129: the last strip starts at column 1 and looks one column over the left edge, where the image
+    is continued by copies of column 0.  Both strips write the same pixels, so they have to agree."""
+    wl = sr_synth.Workload("moved", 63, n, c, h, 43, 3, L, 5, coeff, image)
+    inp = sr_synth.make_inputs(wl, DEV)
+    inp["lr"][..., 0] = 1.0                               # a step at the left edge, where the two continuations differ most
+    inp["lr"][..., 1:3] = 0.0
+    rng = np.random.default_rng(h)
+    lst = None if kept is None else rng.permutation(L)[:kept].astype(np.int32)
+    gamma = None if kept is None else rng.uniform(0.5, 1.5, size=kept).astype(np.float32)
+    check_full(oracle, wl, MFMA, kept=lst, gamma=gamma, inp=inp)
+
+
+@pytest.mark.parametrize("coeff", ["f16", "bf16"])
+def test_last_strip_moved_to_column_one_logits(coeff):
+    wl = sr_synth.Workload("moved", 64, 1, 3, 43, 43, 3, 72, 5, coeff, "f32")
+    lr, z, d = sr_synth.make_lr(wl, DEV), sr_synth.make_logits(wl, DEV), sr_synth.make_dictionary(wl, DEV)
+    lr[..., 0], lr[..., 1:3] = 1.0, 0.0
+    out = [torch.full((1, 3, wl.H, wl.W), float("nan"), device=DEV) for _ in range(2)]
+    for o, kernel in zip(out, (MFMA, GENERIC)):
+        sr.sr_dict_assemble_ex(lr, z, d, 72, 5, 3, 3, o, opts=sr.make_options(kernel, coeff_kind=sr.SR_COEFF_LOGITS))
     assert torch.isfinite(out[0]).all()
     assert float((out[0] - out[1]).abs().max()) <= 5e-5
