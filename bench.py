@@ -551,7 +551,10 @@ def main():
         for t, ms in tune.sweep_tiles(inp["lr"], coeffs[0], inp["dict"], wl.L, wl.k, wl.scale, wl.c, outs[0], kept=kept, reps=15):
             shape = sr.sr_dict_assemble_launch_shape(inp["lr"], coeffs[0], inp["dict"], wl.L, wl.k, wl.scale, wl.c, outs[0],
                                                      kept=kept, opts=sr.make_options(sr.SR_KERNEL_MFMA, t))[1]
-            rows.append({"index": t, "tile": f"{shape[0]}x{shape[1]}", "wavefronts_per_workgroup": shape[2],
+            walk = sr.sr_dict_assemble_walk(inp["lr"], coeffs[0], inp["dict"], wl.L, wl.k, wl.scale, wl.c, outs[0],
+                                            kept=kept, opts=sr.make_options(sr.SR_KERNEL_MFMA, t))[1]
+            name = f"strips of {walk[1]} in segments of {walk[2]} rows" if walk[0] == 2 else f"{shape[0]}x{shape[1]}"
+            rows.append({"index": t, "tile": name, "wavefronts_per_workgroup": shape[2],
                          "workgroups_per_cu": shape[3], "median_us_single_launch": round(ms * 1e3, 1)})
         result["tile_sweep"] = rows
     if not args.no_cpu and not args.pre_shuffle:      # the oracle leg is timed on the planar layout only

@@ -226,8 +226,8 @@ int sr_dict_assemble_selective(const sr_tensor* lr, const sr_tensor* coeff, cons
  *
  * opts->tile (the launch-shape search of section III-B, Eq. 11-12, as a small set of compiled
  * tile shapes): index 0 is the library's default for the frame and is always accepted.  (By
- * default large frames may be walked in strips of 128 columns instead of tiles; index 0 then reports the
- * tile shape it would take otherwise.)  Other
+ * default a frame may be walked in strips of 128 columns instead of tiles, see sr_dict_assemble_walk; sr_dict_assemble_tile
+ * and sr_dict_assemble_launch_shape then report for index 0 the tile shape it would take otherwise.)  Other
  * indices exist only where alternative shapes are built - k = 5, C = 3, 65 to 72 folded f16
  * atoms, byte offsets: 1 = 64x8, 2 = 128x4, 3 = 64x16, 4 = 128x8, 5 = 64x32, 6 = 128x16,
  * 7 = 128x24 (scale 4 only) HR pixels per workgroup, i.e. 1, 1, 2, 2, 4, 4, 6 row groups per
@@ -307,6 +307,21 @@ int sr_dict_assemble_launch_shape(const sr_tensor* lr, const sr_tensor* coeff, c
                                   const sr_tensor* out,
                                   const int* kept, int n_kept, const sr_options* opts,
                                   int shape[4]);
+
+/* How the matrix-core kernel would walk the images of this call on the current device (256 CUs where there is none):
+ * walk[0] = 1: tiles of walk[1] x walk[2] HR pixels, each of a workgroup's wavefronts together; walk[0] = 2: strips of
+ * walk[1] columns in segments of walk[2] rows, each of one wavefront alone; walk[3] = tiles or segments of the call, walk[4]
+ * = workgroups launched, walk[5] = wavefronts of each.  All zero with the generic kernel and for an empty call.  Returns as
+ * sr_dict_assemble_plan.  Host only. */
+int sr_dict_assemble_walk(const sr_tensor* lr, const sr_tensor* coeff, const sr_tensor* dict,
+                          int L, int k, int scale, int channels,
+                          const sr_tensor* out,
+                          const int* kept, int n_kept, const sr_options* opts,
+                          int walk[6]);
+/* ... and of a list call (kernel as in sr_dict_assemble_list_ex). */
+int sr_dict_assemble_list_walk(const sr_tensor* lr, const sr_tensor* index, const sr_tensor* value,
+                               const sr_tensor* dict, int L, int k, int scale, int channels, int entries,
+                               const sr_tensor* out, int kernel, int walk[6]);
 
 /* Static, NUL-terminated description of a status code. */
 const char* sr_strerror(int status);

@@ -20,7 +20,7 @@ SR_COEFF_VALUES, SR_COEFF_LOGITS = 0, 1
 SR_MAX_ATOMS = 256
 
 EXPORTS = ("sr_dict_assemble", "sr_dict_assemble_selective", "sr_dict_assemble_ex", "sr_dict_assemble_list", "sr_dict_assemble_list_ex",
-           "sr_bicubic_upsample", "sr_dict_assemble_plan", "sr_dict_assemble_tile", "sr_dict_assemble_launch_shape", "sr_strerror", "sr_version",
+           "sr_bicubic_upsample", "sr_dict_assemble_plan", "sr_dict_assemble_tile", "sr_dict_assemble_launch_shape", "sr_dict_assemble_walk", "sr_dict_assemble_list_walk", "sr_strerror", "sr_version",
            "sr_probe_read", "sr_probe_mix", "sr_probe_mix_tiled", "sr_probe_mix_tiled_bytes", "sr_probe_mix_tiled_paced", "sr_probe_stream", "sr_probe_pattern", "sr_probe_policy", "sr_probe_policy_bits",
            "sr_atom_gram_workspace_bytes", "sr_atom_gram", "sr_atom_gram_static", "sr_select_atoms")
 
@@ -66,6 +66,8 @@ def load():
     lib.sr_dict_assemble_tile.argtypes = [T, T, T, i, i, i, i, T, ip, i, O, ip, ip]
     lib.sr_dict_assemble_launch_shape.argtypes = [T, T, T, i, i, i, i, T, ip, i, O, ip]
     lib.sr_dict_assemble_launch_shape.restype = i
+    lib.sr_dict_assemble_walk.argtypes = [T, T, T, i, i, i, i, T, ip, i, O, ip]
+    lib.sr_dict_assemble_list_walk.argtypes = [T, T, T, T, i, i, i, i, i, T, i, ip]
     lib.sr_bicubic_upsample.argtypes = [T, i, i, T, vp]
     lib.sr_strerror.argtypes = [i]
     lib.sr_probe_read.argtypes = [vp, ctypes.c_size_t, vp, vp]
@@ -254,6 +256,24 @@ def sr_dict_assemble_launch_shape(lr, coeff, dict, L, k, scale, channels, out, k
     shape = (ctypes.c_int * 4)()
     st = load().sr_dict_assemble_launch_shape(a, b, c, L, k, scale, channels, o, ka, n, op, shape)
     return st, tuple(shape)
+
+
+def sr_dict_assemble_walk(lr, coeff, dict, L, k, scale, channels, out, kept=None, n_kept=None, opts=None):
+    """(kernel or negative status, (form, width, rows, pieces, workgroups, wavefronts of a workgroup)); see the header."""
+    a, b, c, o = describe(lr), describe_coeff(coeff, opts), describe(_dict4(dict)), describe(out)
+    ka, n, _ga, _keep = _host_lists(kept, None)
+    n = n if n_kept is None else int(n_kept)
+    op = ctypes.byref(opts) if opts is not None else None
+    walk = (ctypes.c_int * 6)()
+    st = load().sr_dict_assemble_walk(a, b, c, L, k, scale, channels, o, ka, n, op, walk)
+    return st, tuple(walk)
+
+
+def sr_dict_assemble_list_walk(lr, index, value, dict, L, k, scale, channels, entries, out, kernel=SR_KERNEL_AUTO):
+    walk = (ctypes.c_int * 6)()
+    st = load().sr_dict_assemble_list_walk(describe(lr), describe(index), describe(value), describe(_dict4(dict)),
+                                           L, k, scale, channels, entries, describe(out), int(kernel), walk)
+    return st, tuple(walk)
 
 
 def sr_bicubic_upsample(lr, scale, channels, out, stream=None):

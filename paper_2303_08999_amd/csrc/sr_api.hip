@@ -187,6 +187,20 @@ __attribute__((visibility("default"))) int sr_dict_assemble_launch_shape(const s
     return p.kernel;
 }
 
+__attribute__((visibility("default"))) int sr_dict_assemble_walk(const sr_tensor* lr, const sr_tensor* coeff, const sr_tensor* dict,
+                          int L, int k, int scale, int channels, const sr_tensor* out,
+                          const int* kept, int n_kept, const sr_options* opts, int walk[6]) {
+    if (!walk) return SR_ERR_NULL;
+    Plan p;
+    make_plan(p, lr, coeff, dict, L, k, scale, channels, out, kept, n_kept, nullptr, opts);
+    if (p.status != SR_OK) return p.status;
+    Walk w = {};
+    if (p.kernel == SR_KERNEL_MFMA && !p.empty && launch_mfma(p.args, k, lr->dtype == SR_F16, p.tile, LaunchTo(&w)) != hipSuccess)
+        return SR_ERR_LAUNCH;
+    memcpy(walk, &w, sizeof(w));
+    return p.kernel;
+}
+
 __attribute__((visibility("default"))) int sr_bicubic_upsample(const sr_tensor* lr, int scale, int channels, sr_tensor* out, void* stream) {
     if (!lr || !out) return SR_ERR_NULL;
     if (!dtype_ok(lr->dtype) || !dtype_ok(out->dtype)) return SR_ERR_UNSUPPORTED;

@@ -8,12 +8,23 @@ namespace srd {
 hipError_t launch_generic(const AssembleArgs& a, int k, bool io_f16, hipStream_t st);   // coefficient dtype: a.coeff_dtype
 hipError_t launch_bicubic(const BicubicArgs& a, bool in_f16, bool out_f16, hipStream_t st);
 
+// How a matrix-core launch walks the images: 1 = tiles, 2 = strips (0: not said); HR columns x rows of a tile or of a strip's segment;
+// how many there are; workgroups, and wavefronts of each (a tile belongs to a workgroup, a segment to a wavefront).
+struct Walk { int form, width, rows, pieces, workgroups, waves; };
+// Where such a launch goes: to a stream, or (walk given) nowhere: the walk is written down instead.
+struct LaunchTo {
+    hipStream_t stream;
+    Walk* walk;
+    LaunchTo(hipStream_t st) : stream(st), walk(nullptr) {}
+    explicit LaunchTo(Walk* w) : stream(nullptr), walk(w) {}
+};
+
 // Matrix-core kernel.  mfma_supported() is a pure host-side predicate.
 bool mfma_supported(const AssembleArgs& a, int k, int coeff_dtype, int tile);
-hipError_t launch_mfma(const AssembleArgs& a, int k, bool io_f16, int tile, hipStream_t st);
+hipError_t launch_mfma(const AssembleArgs& a, int k, bool io_f16, int tile, const LaunchTo& st);
 // Per-pixel list form (sr_dict_assemble_list) on the matrix cores: a.coeff = values, a.index, a.T set; kept = identity.
 bool mfma_list_supported(const AssembleArgs& a, int k, bool value_f16);
-hipError_t launch_mfma_list(const AssembleArgs& a, hipStream_t st);
+hipError_t launch_mfma_list(const AssembleArgs& a, const LaunchTo& st);
 bool mfma_tile_shape(const AssembleArgs& a, int k, int coeff_dtype, int tile, int* tw, int* th, int* waves = nullptr,
                      int* groups = nullptr);
 

@@ -157,11 +157,12 @@ hipError_t launch_list(const ListArgs& a, int k, hipStream_t st) {
 using namespace srd;
 
 static int assemble_list(const sr_tensor* lr, const sr_tensor* index, const sr_tensor* value, const sr_tensor* dict,
-                         int L, int k, int scale, int channels, int entries, sr_tensor* out, void* stream, int force_kernel) {
+                         int L, int k, int scale, int channels, int entries, const sr_tensor* out, void* stream, int force_kernel,
+                         Walk* walk = nullptr, int* kernel = nullptr) {
     if (!lr || !index || !value || !dict || !out) return SR_ERR_NULL;
     if ((lr->dtype != SR_F32 && lr->dtype != SR_F16) || out->dtype != lr->dtype || index->dtype != SR_U8 ||
         (value->dtype != SR_F32 && value->dtype != SR_F16) || dict->dtype != SR_F32) return SR_ERR_UNSUPPORTED;
-    for (const sr_tensor* t : {lr, index, value, dict, (const sr_tensor*)out})
+    for (const sr_tensor* t : {lr, index, value, dict, out})
         if (t->n < 0 || t->c < 0 || t->h < 0 || t->w < 0) return SR_ERR_SHAPE;
     if ((k != 3 && k != 5 && k != 7) || scale < 2 || scale > 4 || L < 1 || L > SR_MAX_ATOMS || channels < 1 ||
         channels > SR_MAX_CHANNELS || entries < 1 || entries > SR_MAX_ATOMS) return SR_ERR_UNSUPPORTED;
@@ -194,11 +195,13 @@ static int assemble_list(const sr_tensor* lr, const sr_tensor* index, const sr_t
         m.n_fold = L; m.identity = 1; m.io_f16 = lr->dtype == SR_F16; m.coeff_dtype = SR_F16;
         for (int i = 0; i < L; ++i) { m.kept[i] = i; m.gamma[i] = 1.0f; }
         if (force_kernel != SR_KERNEL_GENERIC && mfma_list_supported(m, k, value->dtype == SR_F16)) {
-            e = launch_mfma_list(m, st);
+            if (kernel) *kernel = SR_KERNEL_MFMA;
+            e = launch_mfma_list(m, walk ? LaunchTo(walk) : LaunchTo(st));
             return e == hipSuccess ? SR_OK : SR_ERR_LAUNCH;
         }
         if (force_kernel == SR_KERNEL_MFMA) return SR_ERR_UNSUPPORTED;
     }
+    if (walk) return SR_OK;
     if (value->dtype == SR_F16)
         e = lr->dtype == SR_F16 ? launch_list<__half, __half>(a, k, st) : launch_list<__half, float>(a, k, st);
     else
@@ -217,4 +220,17 @@ int sr_dict_assemble_list_ex(const sr_tensor* lr, const sr_tensor* index, const 
                              int L, int k, int scale, int channels, int entries, sr_tensor* out, void* stream, int kernel) {
     if (kernel < SR_KERNEL_AUTO || kernel > SR_KERNEL_MFMA) return SR_ERR_UNSUPPORTED;
     return assemble_list(lr, index, value, dict, L, k, scale, channels, entries, out, stream, kernel);
+}
+
+extern "C" __attribute__((visibility("default")))
+int sr_dict_assemble_list_walk(const sr_tensor* lr, const sr_tensor* index, const sr_tensor* value, const sr_tensor* dict,
+                               int L, int k, int scale, int channels, int entries, const sr_tensor* out, int kernel, int walk[6]) {
+    if (!walk) return SR_ERR_NULL;
+    if (kernel < SR_KERNEL_AUTO || kernel > SR_KERNEL_MFMA) return SR_ERR_UNSUPPORTED;
+    Walk w = {};
+    int runs = SR_KERNEL_GENERIC;
+    const int status = assemble_list(lr, index, value, dict, L, k, scale, channels, entries, out, nullptr, kernel, &w, &runs);
+    if (status != SR_OK) return status;
+    memcpy(walk, &w, sizeof(w));
+    return runs;
 }

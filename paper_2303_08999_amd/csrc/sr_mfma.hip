@@ -5,20 +5,20 @@
 
 namespace srd {
 
-hipError_t launch_mfma_k3(const AssembleArgs& a, int np8, hipStream_t st);
-hipError_t launch_mfma_k5(const AssembleArgs& a, int np8, int shape, hipStream_t st);
+hipError_t launch_mfma_k3(const AssembleArgs& a, int np8, const LaunchTo& st);
+hipError_t launch_mfma_k5(const AssembleArgs& a, int np8, int shape, const LaunchTo& st);
 bool tile_shape_k5(const AssembleArgs& a, int shape, int* tw, int* th, int* waves, int* groups);
-hipError_t launch_mfma_k7(const AssembleArgs& a, int np8, int shape, hipStream_t st);
-hipError_t launch_mfma_k5_f32(const AssembleArgs& a, int np8, hipStream_t st);
-hipError_t launch_mfma_k7_f32(const AssembleArgs& a, int np8, hipStream_t st);
-hipError_t launch_mfma_k5_f8(const AssembleArgs& a, int np8, hipStream_t st);
-hipError_t launch_mfma_k7_f8(const AssembleArgs& a, int np8, hipStream_t st);
-hipError_t launch_mfma_k5_big(const AssembleArgs& a, int np8, hipStream_t st);
-hipError_t launch_mfma_bf16(const AssembleArgs& a, int k, int np8, hipStream_t st);
-hipError_t launch_mfma_k5_ps(const AssembleArgs& a, int np8, hipStream_t st);
-hipError_t launch_mfma_k5_pm(const AssembleArgs& a, hipStream_t st);
-hipError_t launch_mfma_k5_lg(const AssembleArgs& a, hipStream_t st);
-hipError_t launch_mfma_k5_blk(const AssembleArgs& a, hipStream_t st);
+hipError_t launch_mfma_k7(const AssembleArgs& a, int np8, int shape, const LaunchTo& st);
+hipError_t launch_mfma_k5_f32(const AssembleArgs& a, int np8, const LaunchTo& st);
+hipError_t launch_mfma_k7_f32(const AssembleArgs& a, int np8, const LaunchTo& st);
+hipError_t launch_mfma_k5_f8(const AssembleArgs& a, int np8, const LaunchTo& st);
+hipError_t launch_mfma_k7_f8(const AssembleArgs& a, int np8, const LaunchTo& st);
+hipError_t launch_mfma_k5_big(const AssembleArgs& a, int np8, const LaunchTo& st);
+hipError_t launch_mfma_bf16(const AssembleArgs& a, int k, int np8, const LaunchTo& st);
+hipError_t launch_mfma_k5_ps(const AssembleArgs& a, int np8, const LaunchTo& st);
+hipError_t launch_mfma_k5_pm(const AssembleArgs& a, const LaunchTo& st);
+hipError_t launch_mfma_k5_lg(const AssembleArgs& a, const LaunchTo& st);
+hipError_t launch_mfma_k5_blk(const AssembleArgs& a, const LaunchTo& st);
 
 namespace {
 
@@ -143,7 +143,7 @@ bool mfma_supported(const AssembleArgs& a, int k, int coeff_dtype, int tile) {
     return true;
 }
 
-hipError_t launch_mfma(const AssembleArgs& a, int k, bool io_f16, int tile, hipStream_t st) {
+hipError_t launch_mfma(const AssembleArgs& a, int k, bool io_f16, int tile, const LaunchTo& st) {
     (void)io_f16;
     const int np8 = np8_for(k, a.C, a.n_fold, a.coeff_dtype);
     if (a.blocked) return launch_mfma_k5_blk(a, st);

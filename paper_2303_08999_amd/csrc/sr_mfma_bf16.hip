@@ -9,7 +9,7 @@
 namespace srd {
 
 template <int C>
-static hipError_t launch_k5(const AssembleArgs& a, int np8, hipStream_t st) {
+static hipError_t launch_k5(const AssembleArgs& a, int np8, const LaunchTo& st) {
     const bool small = np8 == 9 && (long long)a.N * a.H * a.W <= 400000;
     if (np8 == 16 ? strip_form(a, 64, 64, a.s == 4 ? 24 : 16)
         : np8 <= 2 ? strip_form(a, 128, 64, a.s == 4 ? 32 : 16, a.s == 4 ? 3 : 2)
@@ -50,7 +50,7 @@ static hipError_t launch_k5(const AssembleArgs& a, int np8, hipStream_t st) {
 }
 
 template <int C>
-static hipError_t launch_k7(const AssembleArgs& a, int np8, hipStream_t st) {
+static hipError_t launch_k7(const AssembleArgs& a, int np8, const LaunchTo& st) {
     if (strip_form(a, 64, 64, a.s == 4 ? 24 : 16)) {
         switch (np8) {
         case 2:  return launch_strip<7, C, 2, 2, 2, CT_BF16>(a, st);
@@ -72,7 +72,7 @@ static hipError_t launch_k7(const AssembleArgs& a, int np8, hipStream_t st) {
     }
 }
 
-hipError_t launch_mfma_bf16(const AssembleArgs& a, int k, int np8, hipStream_t st) {
+hipError_t launch_mfma_bf16(const AssembleArgs& a, int k, int np8, const LaunchTo& st) {
     if (k == 5) {
         if (a.C == 3) return launch_k5<3>(a, np8, st);
         if (a.C == 1) return launch_k5<1>(a, np8, st);

@@ -7,7 +7,7 @@
 namespace srd {
 
 template <int C, int NP8, int CT>
-static hipError_t launch_k3(const AssembleArgs& a, hipStream_t st) {
+static hipError_t launch_k3(const AssembleArgs& a, const LaunchTo& st) {
     constexpr int PX = CT == CT_F32 ? 2 : 4;
     if (strip_form(a, 32 * PX, 32 * PX, a.s == 4 && CT != CT_F32 ? 24 : 16)) return launch_strip<3, C, NP8, PX, 2, CT>(a, st);
     if (a.s == 4 && CT != CT_F32) return launch_one<3, C, NP8, PX, 1, 4, 6, 2, CT, 4>(a, st);
@@ -15,7 +15,7 @@ static hipError_t launch_k3(const AssembleArgs& a, hipStream_t st) {
 }
 
 template <int C, int CT>
-static hipError_t launch_k3_np8(const AssembleArgs& a, int np8, hipStream_t st) {
+static hipError_t launch_k3_np8(const AssembleArgs& a, int np8, const LaunchTo& st) {
     switch (np8) {
     case 1:  return launch_k3<C, 1, CT>(a, st);
     case 4:  return launch_k3<C, 4, CT>(a, st);
@@ -29,7 +29,7 @@ static hipError_t launch_k3_np8(const AssembleArgs& a, int np8, hipStream_t st) 
 }
 
 // np8: capacity in groups of 8 folded atoms (8, 32, 72 or 128 atoms)
-hipError_t launch_mfma_k3(const AssembleArgs& a, int np8, hipStream_t st) {
+hipError_t launch_mfma_k3(const AssembleArgs& a, int np8, const LaunchTo& st) {
     if (a.coeff_dtype == SR_F32)
         return a.C == 3 ? launch_k3_np8<3, CT_F32>(a, np8, st) : launch_k3_np8<1, CT_F32>(a, np8, st);
     if (a.coeff_dtype == SR_F8E4M3)

@@ -37,7 +37,7 @@ bool tile_shape_k5(const AssembleArgs& a, int shape, int* tw, int* th, int* wave
 }
 
 // np8: capacity in groups of 8 folded atoms; shape: tile shape index (C = 3, np8 = 9 only)
-hipError_t launch_mfma_k5(const AssembleArgs& a, int np8, int shape, hipStream_t st) {
+hipError_t launch_mfma_k5(const AssembleArgs& a, int np8, int shape, const LaunchTo& st) {
     // Few atoms: the kernel is bound by up-sampling, filtering and the output
     // write rather than by the coefficient stream; the register budget then
     // allows three wavefronts per SIMD, which measured 25 % faster.

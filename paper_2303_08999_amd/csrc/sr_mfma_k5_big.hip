@@ -7,7 +7,7 @@
 namespace srd {
 
 template <int CT>
-static hipError_t launch_big(const AssembleArgs& a, int np8, hipStream_t st) {
+static hipError_t launch_big(const AssembleArgs& a, int np8, const LaunchTo& st) {
     switch (np8) {
     case 1:
         if (a.s == 4) return launch_one<5, 3, 1, 4, 2, 4, 4, 3, CT, 4, true>(a, st);     //  64 x 32
@@ -22,7 +22,7 @@ static hipError_t launch_big(const AssembleArgs& a, int np8, hipStream_t st) {
     }
 }
 
-hipError_t launch_mfma_k5_big(const AssembleArgs& a, int np8, hipStream_t st) {
+hipError_t launch_mfma_k5_big(const AssembleArgs& a, int np8, const LaunchTo& st) {
     if (a.C != 3) return hipErrorInvalidValue;
     if (a.coeff_dtype == SR_F16) return launch_big<CT_F16>(a, np8, st);
     if (a.coeff_dtype == SR_BF16) return launch_big<CT_BF16>(a, np8, st);

@@ -5,7 +5,7 @@
 namespace srd {
 
 // The tiles of the planar form: 128 x 24 at scale 4 (half the LR footprint), 128 x 16 below.
-hipError_t launch_mfma_k5_blk(const AssembleArgs& a, hipStream_t st) {
+hipError_t launch_mfma_k5_blk(const AssembleArgs& a, const LaunchTo& st) {
     if (a.C != 3 || a.L != 72) return hipErrorInvalidValue;
     if (a.coeff_dtype == SR_F8E4M3) {
         if (a.s == 4) return launch_one<5, 3, 9, 4, 1, 4, 6, 2, CT_F8, 4, false, 9>(a, st);

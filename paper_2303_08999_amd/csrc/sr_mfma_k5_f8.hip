@@ -9,7 +9,7 @@
 
 namespace srd {
 
-hipError_t launch_mfma_k5_f8(const AssembleArgs& a, int np8, hipStream_t st) {
+hipError_t launch_mfma_k5_f8(const AssembleArgs& a, int np8, const LaunchTo& st) {
     if (a.C == 3) {
         switch (np8) {
         case 1:

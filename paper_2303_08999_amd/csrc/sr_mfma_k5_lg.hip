@@ -9,7 +9,7 @@ namespace srd {
 // before the network's pixel-shuffle (what its last convolution writes): the permuted-slot forms of that layout,
 // LR widths that are multiples of 4.
 template <int CT>
-static hipError_t launch_lg(const AssembleArgs& a, hipStream_t st) {
+static hipError_t launch_lg(const AssembleArgs& a, const LaunchTo& st) {
     if (a.pre_shuffle) {
         if (a.w % 4 != 0) return hipErrorInvalidValue;
         if (a.s == 4) return launch_one<5, 3, 9, 4, 1, 4, 4, 2, CT, 4, false, 4>(a, st);   // 256 x 8
@@ -21,7 +21,7 @@ static hipError_t launch_lg(const AssembleArgs& a, hipStream_t st) {
     return launch_one<5, 3, 9, 4, 1, 4, 4, 2, CT, 2>(a, st);
 }
 
-hipError_t launch_mfma_k5_lg(const AssembleArgs& a, hipStream_t st) {
+hipError_t launch_mfma_k5_lg(const AssembleArgs& a, const LaunchTo& st) {
     if (a.C != 3 || a.L < 1 || a.L > 72) return hipErrorInvalidValue;
     if (a.coeff_dtype == SR_BF16) return launch_lg<CT_LOGIT_BF16>(a, st);
     if (a.coeff_dtype == SR_F16) return launch_lg<CT_LOGIT>(a, st);

@@ -5,7 +5,7 @@
 
 namespace srd {
 
-hipError_t launch_mfma_k5_ps(const AssembleArgs& a, int np8, hipStream_t st) {
+hipError_t launch_mfma_k5_ps(const AssembleArgs& a, int np8, const LaunchTo& st) {
     if (a.C != 3) return hipErrorInvalidValue;
     if (a.coeff_dtype == SR_BF16) {          // bfloat16 coefficients: the permuted-slot forms, 65 to 72 atoms
         if (np8 != 9 || a.w % 4 != 0) return hipErrorInvalidValue;

@@ -9,13 +9,13 @@
 namespace srd {
 
 template <int C, int NP8>
-static hipError_t launch_k7(const AssembleArgs& a, hipStream_t st) {
+static hipError_t launch_k7(const AssembleArgs& a, const LaunchTo& st) {
     if (strip_form(a, 64, 64, a.s == 4 ? 24 : 16)) return launch_strip<7, C, NP8, 2, 2>(a, st);
     if (a.s == 4) return launch_one<7, C, NP8, 2, 1, 4, 6, 2, CT_F16, 4>(a, st);
     return launch_one<7, C, NP8, 2, 1, 4, 4, 2>(a, st);
 }
 
-hipError_t launch_mfma_k7(const AssembleArgs& a, int np8, int shape, hipStream_t st) {
+hipError_t launch_mfma_k7(const AssembleArgs& a, int np8, int shape, const LaunchTo& st) {
     (void)shape;
     if (a.C == 3) {
         switch (np8) {

@@ -6,7 +6,7 @@
 
 namespace srd {
 
-hipError_t launch_mfma_k7_f8(const AssembleArgs& a, int np8, hipStream_t st) {
+hipError_t launch_mfma_k7_f8(const AssembleArgs& a, int np8, const LaunchTo& st) {
     if (a.C == 3) {
         switch (np8) {
         case 9:  return launch_one<7, 3, 9, 4, 1, 4, 4, 1, CT_F8>(a, st);

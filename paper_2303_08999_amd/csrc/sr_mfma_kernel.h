@@ -1801,7 +1801,7 @@ inline void walk_of(AssembleArgs& a, int ntiles, int blocks, int per_block) {
 
 template <int K, int C, int NP8, int PX, int WR, int NW, int NU, int WPE, int CT = CT_F16, int SMIN = 2, bool BIG = false,
           int PSM = 0, int STRIP = 0>
-hipError_t launch_one(const AssembleArgs& a0, hipStream_t st) {
+hipError_t launch_one(const AssembleArgs& a0, const LaunchTo& st) {
     using F = Cfg<K, C, NP8, PX, WR, NW, NU, CT, SMIN, (PSM == 4 ? 2 : (PSM == 3 ? 3 : 1)), (PSM == 8 ? 1 : 0), STRIP>;
     if (STRIP && a0.s != STRIP) return hipErrorInvalidValue;
     if (a0.s < SMIN) return hipErrorInvalidValue;       // its LDS footprint buffers would be too small
@@ -1850,7 +1850,11 @@ hipError_t launch_one(const AssembleArgs& a0, hipStream_t st) {
     const long long want = STRIP ? (nt + NW - 1) / NW : nt;
     const int blocks = want < cap ? (int)want : cap;
     walk_of(a, (int)nt, blocks, STRIP ? NW : 1);
-    hipLaunchKernelGGL((k_assemble_mfma<K, C, NP8, PX, WR, NW, NU, WPE, CT, SMIN, BIG, PSM, STRIP>), dim3(blocks), dim3(F::NT), 0, st, a);
+    if (st.walk) {
+        *st.walk = {STRIP ? 2 : 1, F::TW, a.seg_rows, (int)nt, blocks, NW};
+        return hipSuccess;
+    }
+    hipLaunchKernelGGL((k_assemble_mfma<K, C, NP8, PX, WR, NW, NU, WPE, CT, SMIN, BIG, PSM, STRIP>), dim3(blocks), dim3(F::NT), 0, st.stream, a);
     return hipGetLastError();
 }
 
@@ -1873,7 +1877,7 @@ inline bool strip_form(const AssembleArgs& a, int sw, int tw, int th, int wpe = 
 
 // The strip form: workgroups of four wavefronts, WPE of them per CU.
 template <int K, int C, int NP8, int PX, int WPE, int CT = CT_F16, int PSM = 0>
-hipError_t launch_strip(const AssembleArgs& a, hipStream_t st) {
+hipError_t launch_strip(const AssembleArgs& a, const LaunchTo& st) {
     constexpr int WPE2 = WPE < 3 ? WPE : 2;             // (scales 2 and 3: the LR rows of twelve wavefronts do not fit the LDS)
     switch (a.s) {
     case 2:  return launch_one<K, C, NP8, PX, 1, 4, 1, WPE2, CT, 2, false, PSM, 2>(a, st);

@@ -16,7 +16,7 @@ bool mfma_list_supported(const AssembleArgs& a, int k, bool value_f16) {
 // Up to 72 atoms: the dense form's operand steps (four of 16 atoms and one of 8) and its tiles; up to 128: eight
 // steps, 128 x 8 tiles at every scale (35 KB of scatter scratch).  Lists of up to 8 entries keep half the registers.
 template <int CT>
-static hipError_t launch_ct(const AssembleArgs& a, hipStream_t st) {
+static hipError_t launch_ct(const AssembleArgs& a, const LaunchTo& st) {
     if (a.L <= 72) {
         if (a.s == 4 && strip_form(a, 128, 128, 16)) return launch_one<5, 3, 9, 4, 1, 4, 1, 2, CT, 4, false, 0, 4>(a, st);
         if (a.s == 3 && strip_form(a, 128, 128, 8)) return launch_one<5, 3, 9, 4, 1, 4, 1, 2, CT, 3, false, 0, 3>(a, st);
@@ -25,7 +25,7 @@ static hipError_t launch_ct(const AssembleArgs& a, hipStream_t st) {
     return launch_one<5, 3, 16, 4, 1, 4, 2, 2, CT, 2>(a, st);
 }
 
-hipError_t launch_mfma_list(const AssembleArgs& a, hipStream_t st) {
+hipError_t launch_mfma_list(const AssembleArgs& a, const LaunchTo& st) {
     return a.T <= 8 ? launch_ct<CT_LIST8>(a, st) : launch_ct<CT_LIST16>(a, st);
 }
 

@@ -1,0 +1,88 @@
+"""What the host says about how a call is walked (sr_dict_assemble_walk, sr_dict_assemble_list_walk): tiles or strips, as
+launched.  No GPU and no launch: descriptors with fake, well-separated device addresses."""
+import ctypes
+
+import pytest
+
+import paper_2303_08999_amd as sr
+
+DT = {"f16": sr.SR_F16, "bf16": sr.SR_BF16, "f8": sr.SR_F8E4M3, "f32": sr.SR_F32}
+TILES, STRIPS = 1, 2
+
+
+def _far(*tensors):
+    return [sr.sr_tensor(0x1000000000 * (i + 1), *t) for i, t in enumerate(tensors)]
+
+
+def walk(n=1, C=3, H=2160, W=3840, s=4, L=72, k=5, cd="f16", kept=None, opts=None, kind=sr.SR_COEFF_VALUES, kernel=sr.SR_KERNEL_AUTO, tile=0):
+    lr, coeff, d, out = _far((sr.SR_F32, n, C, H // s, W // s), (DT[cd], n, L, H, W), (sr.SR_F32, 1, L, k, k), (sr.SR_F32, n, C, H, W))
+    ka = (ctypes.c_int * len(kept))(*kept) if kept else None
+    w = (ctypes.c_int * 6)(*[-1] * 6)
+    st = sr.load().sr_dict_assemble_walk(lr, coeff, d, L, k, s, C, out, ka, len(kept or ()),
+                                         ctypes.byref(opts or sr.make_options(kernel, tile, coeff_kind=kind)), w)
+    return st, tuple(w)
+
+
+def list_walk(n=1, H=2160, W=3840, s=4, L=72, entries=8, value="f16", kernel=sr.SR_KERNEL_AUTO):
+    ts = _far((sr.SR_F32, n, 3, H // s, W // s), (sr.SR_U8, n, entries, H, W), (DT[value], n, entries, H, W), (sr.SR_F32, 1, L, 5, 5),
+              (sr.SR_F32, n, 3, H, W))
+    w = (ctypes.c_int * 6)(*[-1] * 6)
+    st = sr.load().sr_dict_assemble_list_walk(*ts[:4], L, 5, s, 3, entries, ts[4], kernel, w)
+    return st, tuple(w)
+
+
+def _whole(w, n, H, W):
+    """The pieces cover the images, and the launch has work for all of its workgroups."""
+    form, width, rows, pieces, workgroups, waves = w
+    assert pieces == n * -(-W // width) * -(-H // rows)
+    assert workgroups * (waves if form == STRIPS else 1) < pieces + waves
+
+
+@pytest.mark.parametrize("cd", list(DT))
+@pytest.mark.parametrize("k, C, L", [(3, 1, 72), (3, 3, 128), (5, 1, 72), (5, 3, 8), (5, 3, 40), (5, 3, 72), (5, 3, 128), (7, 1, 72), (7, 3, 128)])
+@pytest.mark.parametrize("s", [2, 3, 4])
+def test_every_call_of_the_matrix_core_kernel_has_a_walk(cd, k, C, L, s):
+    forms = set()
+    for n, h, w in ((1, 8, 32), (1, 128, 128), (3, 77, 60), (1, 360, 640), (16, 270, 480), (1, 360, 641)):
+        H, W = h * s, w * s
+        kernel, got = walk(n=n, C=C, H=H, W=W, s=s, L=L, k=k, cd=cd)
+        if kernel == sr.SR_KERNEL_GENERIC:
+            assert got == (0,) * 6
+            continue
+        assert kernel == sr.SR_KERNEL_MFMA and got[0] in (TILES, STRIPS)
+        _whole(got, n, H, W)
+        forms.add(got[0])
+    assert forms or (k == 7 and L <= 16) or cd in ("f8", "f32")
+
+
+def test_a_tile_index_is_walked_in_its_tiles():
+    """Index 0 may be strips; every other index is the tile that sr_dict_assemble_launch_shape reports for it."""
+    for tile in range(1, 10):
+        lr, coeff, d, out = _far((sr.SR_F32, 1, 3, 540, 960), (sr.SR_F16, 1, 72, 2160, 3840), (sr.SR_F32, 1, 72, 5, 5),
+                                 (sr.SR_F32, 1, 3, 2160, 3840))
+        shape = (ctypes.c_int * 4)()
+        opts = sr.make_options(sr.SR_KERNEL_MFMA, tile)
+        assert sr.load().sr_dict_assemble_launch_shape(lr, coeff, d, 72, 5, 4, 3, out, None, 0, ctypes.byref(opts), shape) == sr.SR_KERNEL_MFMA
+        kernel, got = walk(opts=opts)
+        assert kernel == sr.SR_KERNEL_MFMA and got[:3] == (TILES, shape[0], shape[1]) and got[5] == shape[2]
+        _whole(got, 1, 2160, 3840)
+    assert walk()[1][:3] == (STRIPS, 128, 32)            # the 4K frame's default
+
+
+def test_walk_statuses():
+    assert walk(kernel=sr.SR_KERNEL_GENERIC) == (sr.SR_KERNEL_GENERIC, (0,) * 6)
+    assert walk(C=2, cd="f32") == (sr.SR_KERNEL_GENERIC, (0,) * 6)
+    assert walk(H=0) == (sr.SR_KERNEL_GENERIC, (0,) * 6)
+    assert walk(tile=10)[0] == walk(C=2, cd="f32", kernel=sr.SR_KERNEL_MFMA)[0] == -3
+    assert walk(kept=[72])[0] < 0
+    assert list_walk(kernel=sr.SR_KERNEL_GENERIC) == (sr.SR_KERNEL_GENERIC, (0,) * 6)
+    assert list_walk(value="f32") == (sr.SR_KERNEL_GENERIC, (0,) * 6)
+    assert list_walk(value="f32", kernel=sr.SR_KERNEL_MFMA)[0] == list_walk(kernel=3)[0] == -3
+    for s in (2, 3, 4):
+        for L in (72, 128):
+            for n, h, w in ((1, 8, 32), (1, 180, 320), (4, 270, 480)):
+                kernel, got = list_walk(n=n, H=h * s, W=w * s, s=s, L=L)
+                assert kernel == sr.SR_KERNEL_MFMA and got[0] in (TILES, STRIPS)
+                _whole(got, n, h * s, w * s)
+    lr, coeff, d, out = _far((sr.SR_F32, 1, 3, 8, 32), (sr.SR_F16, 1, 72, 32, 128), (sr.SR_F32, 1, 72, 5, 5), (sr.SR_F32, 1, 3, 32, 128))
+    assert sr.load().sr_dict_assemble_walk(lr, coeff, d, 72, 5, 4, 3, out, None, 0, None, None) == -1
