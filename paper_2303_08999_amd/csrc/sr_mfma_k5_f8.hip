@@ -30,6 +30,7 @@ hipError_t launch_mfma_k5_f8(const AssembleArgs& a, int np8, const LaunchTo& st)
             // for medium frames, which pays with fp16 coefficients, measured 3-7 % slower here
             if (strip_form(a, 128, 128, small ? 4 : a.s == 4 ? 24 : 16)) return launch_strip<5, 3, 9, 4, 2, CT_F8>(a, st);
             if (small) return launch_one<5, 3, 9, 4, 1, 4, 1, 2, CT_F8>(a, st);
+            if (a.s == 4) return launch_one<5, 3, 9, 4, 1, 4, 6, 2, CT_F8, 4>(a, st);    // 128 x 24
             return launch_one<5, 3, 9, 4, 1, 4, 4, 2, CT_F8>(a, st);
         }
         case 16: return launch_one<5, 3, 16, 4, 1, 4, 4, 1, CT_F8>(a, st);       // 73 to 128 atoms: one wavefront per SIMD, as 7x7

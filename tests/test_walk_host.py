@@ -86,3 +86,11 @@ def test_walk_statuses():
                 _whole(got, n, h * s, w * s)
     lr, coeff, d, out = _far((sr.SR_F32, 1, 3, 8, 32), (sr.SR_F16, 1, 72, 32, 128), (sr.SR_F32, 1, 72, 5, 5), (sr.SR_F32, 1, 3, 32, 128))
     assert sr.load().sr_dict_assemble_walk(lr, coeff, d, 72, 5, 4, 3, out, None, 0, None, None) == -1
+
+
+@pytest.mark.parametrize("H, W, s", [(720, 960, 4), (768, 1024, 4), (800, 800, 4), (540, 960, 4), (512, 1280, 4)])
+def test_8_bit_frames_that_strips_refuse_take_the_tile_they_were_compared_with(H, W, s):
+    """72 atoms, three channels, x4, about 0.4 to 0.8 Mpixel: strips and 128 x 24 tiles leave the fullest SIMD six rows;
+    128 x 16 tiles would leave it eight."""
+    kernel, got = walk(H=H, W=W, s=s, cd="f8")
+    assert kernel == sr.SR_KERNEL_MFMA and (got[0] == STRIPS or got[:3] == (TILES, 128, 24))
