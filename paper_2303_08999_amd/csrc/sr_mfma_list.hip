@@ -13,12 +13,15 @@ bool mfma_list_supported(const AssembleArgs& a, int k, bool value_f16) {
     return true;
 }
 
-// Up to 72 atoms: the dense form's operand steps (four of 16 atoms and one of 8) and its tiles; up to 128: eight
+// Up to 72 atoms: the dense form's operand steps (four of 16 atoms and one of 8); scale 4 in strips or 128 x 16 tiles, scale 3 in
+// strips or 128 x 8 tiles, scale 2 in 128 x 8 tiles.  Up to 128: eight
 // steps, 128 x 8 tiles at every scale (35 KB of scatter scratch).  Lists of up to 8 entries keep half the registers.
+// Frames that strips are refused for, lists of 8 (us, 128 x 8 / 128 x 16): 720 x 1280 x4 25.4 / 22.0, 800 x 1200 x4 25.5 / 22.7.
 template <int CT>
 static hipError_t launch_ct(const AssembleArgs& a, const LaunchTo& st) {
     if (a.L <= 72) {
         if (a.s == 4 && strip_form(a, 128, 128, 16)) return launch_one<5, 3, 9, 4, 1, 4, 1, 2, CT, 4, false, 0, 4>(a, st);
+        if (a.s == 4) return launch_one<5, 3, 9, 4, 1, 4, 4, 2, CT, 4>(a, st);
         if (a.s == 3 && strip_form(a, 128, 128, 8)) return launch_one<5, 3, 9, 4, 1, 4, 1, 2, CT, 3, false, 0, 3>(a, st);
         return launch_one<5, 3, 9, 4, 1, 4, 2, 2, CT, 2>(a, st);
     }

@@ -119,3 +119,31 @@ def test_last_strip_moved_to_column_one_logits(coeff):
         sr.sr_dict_assemble_ex(lr, z, d, 72, 5, 3, 3, o, opts=sr.make_options(kernel, coeff_kind=sr.SR_COEFF_LOGITS))
     assert torch.isfinite(out[0]).all()
     assert float((out[0] - out[1]).abs().max()) <= 5e-5
+
+
+def _assert_tile(walk, width, rows):
+    assert walk[0] == MFMA and walk[1][:3] == (1, width, rows), walk
+
+
+@pytest.mark.parametrize("image", ["f32", "f16"])
+def test_8_bit_tiles_where_strips_are_refused(oracle, image):
+    """720 x 960 at x4: 128 x 24 tiles (30 rows of them, whole; 7.5 tiles wide)."""
+    wl = sr_synth.Workload("tiles", 65, 1, 3, 180, 240, 4, 72, 5, "f8", image)
+    inp = sr_synth.make_inputs(wl, DEV)
+    out = torch.empty((1, 3, wl.H, wl.W), device=DEV, dtype=inp["lr"].dtype)
+    _assert_tile(sr.sr_dict_assemble_walk(inp["lr"], inp["coeff"], inp["dict"], 72, 5, 4, 3, out), 128, 24)
+    check_full(oracle, wl, MFMA, inp=inp)
+
+
+@pytest.mark.parametrize("h, entries", [(180, 8), (178, 16)])
+def test_list_tiles_where_strips_are_refused(h, entries):
+    """1280 columns at x4: 128 x 16 tiles; 712 rows are no whole number of them."""
+    wl = sr_synth.Workload("tiles", 66, 1, 3, h, 320, 4, 72, 5, "f16", "f32")
+    inp = sr_synth.make_inputs(wl, DEV)
+    index, value = sr_synth.to_list(inp["coeff"], entries)
+    out = [torch.full((1, 3, wl.H, wl.W), float("nan"), device=DEV) for _ in range(2)]
+    _assert_tile(sr.sr_dict_assemble_list_walk(inp["lr"], index, value, inp["dict"], 72, 5, 4, 3, entries, out[0]), 128, 16)
+    for o, kernel in zip(out, (MFMA, GENERIC)):
+        sr.sr_dict_assemble_list_ex(inp["lr"], index, value, inp["dict"], 72, 5, 4, 3, entries, o, kernel=kernel)
+    assert torch.isfinite(out[0]).all()
+    assert float((out[0] - out[1]).abs().max()) <= 5e-5 * max(1.0, float(out[1].abs().max()))

@@ -94,3 +94,10 @@ def test_8_bit_frames_that_strips_refuse_take_the_tile_they_were_compared_with(H
     128 x 16 tiles would leave it eight."""
     kernel, got = walk(H=H, W=W, s=s, cd="f8")
     assert kernel == sr.SR_KERNEL_MFMA and (got[0] == STRIPS or got[:3] == (TILES, 128, 24))
+
+
+@pytest.mark.parametrize("n, H, W", [(1, 720, 1280), (1, 800, 1200), (32, 128, 192)])
+@pytest.mark.parametrize("entries", [8, 16])
+def test_lists_that_strips_refuse_take_the_tile_they_were_compared_with(n, H, W, entries):
+    kernel, got = list_walk(n=n, H=H, W=W, entries=entries)
+    assert kernel == sr.SR_KERNEL_MFMA and (got[0] == STRIPS or got[:3] == (TILES, 128, 16))
