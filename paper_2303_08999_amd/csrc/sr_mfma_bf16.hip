@@ -11,9 +11,9 @@ namespace srd {
 template <int C>
 static hipError_t launch_k5(const AssembleArgs& a, int np8, const LaunchTo& st) {
     const bool small = np8 == 9 && (long long)a.N * a.H * a.W <= 400000;
-    if (np8 == 16 ? strip_form(a, 64, 64, a.s == 4 ? 24 : 16)
-        : np8 <= 2 ? strip_form(a, 128, 64, a.s == 4 ? 32 : 16, a.s == 4 ? 3 : 2)
-                   : strip_form(a, 128, 128, small ? 4 : a.s == 4 ? 24 : 16)) {
+    if (np8 == 16 ? strip_form(a, np8, 64, 64, a.s == 4 ? 24 : 16)
+        : np8 <= 2 ? strip_form(a, np8, 128, 64, a.s == 4 ? 32 : 16, a.s == 4 ? 3 : 2)
+                   : strip_form(a, np8, 128, 128, small ? 4 : a.s == 4 ? 24 : 16)) {
         switch (np8) {
         case 1: return launch_strip<5, C, 1, 4, 3, CT_BF16>(a, st);
         case 2: if (C == 3) return launch_strip<5, 3, 2, 4, 3, CT_BF16>(a, st); break;
@@ -51,7 +51,7 @@ static hipError_t launch_k5(const AssembleArgs& a, int np8, const LaunchTo& st) 
 
 template <int C>
 static hipError_t launch_k7(const AssembleArgs& a, int np8, const LaunchTo& st) {
-    if (strip_form(a, 64, 64, a.s == 4 ? 24 : 16)) {
+    if (strip_form(a, np8, 64, 64, a.s == 4 ? 24 : 16)) {
         switch (np8) {
         case 2:  return launch_strip<7, C, 2, 2, 2, CT_BF16>(a, st);
         case 9:  return launch_strip<7, C, 9, 2, 2, CT_BF16>(a, st);

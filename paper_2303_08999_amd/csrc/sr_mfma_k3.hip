@@ -9,7 +9,7 @@ namespace srd {
 template <int C, int NP8, int CT>
 static hipError_t launch_k3(const AssembleArgs& a, const LaunchTo& st) {
     constexpr int PX = CT == CT_F32 ? 2 : 4;
-    if (strip_form(a, 32 * PX, 32 * PX, a.s == 4 && CT != CT_F32 ? 24 : 16)) return launch_strip<3, C, NP8, PX, 2, CT>(a, st);
+    if (strip_form(a, NP8, 32 * PX, 32 * PX, a.s == 4 && CT != CT_F32 ? 24 : 16)) return launch_strip<3, C, NP8, PX, 2, CT>(a, st);
     if (a.s == 4 && CT != CT_F32) return launch_one<3, C, NP8, PX, 1, 4, 6, 2, CT, 4>(a, st);
     return launch_one<3, C, NP8, PX, 1, 4, 4, 2, CT>(a, st);
 }

@@ -45,23 +45,23 @@ hipError_t launch_mfma_k5(const AssembleArgs& a, int np8, int shape, const Launc
         switch (np8) {
         case 1:
             // x4: 64 x 32 still fits three workgroups per CU (measured 11 % faster)
-            if (strip_form(a, 128, 64, a.s == 4 ? 32 : 16, a.s == 4 ? 3 : 2)) return launch_strip<5, 3, 1, 4, 3>(a, st);
+            if (strip_form(a, np8, 128, 64, a.s == 4 ? 32 : 16, a.s == 4 ? 3 : 2)) return launch_strip<5, 3, 1, 4, 3>(a, st);
             if (a.s == 4) return launch_one<5, 3, 1, 4, 2, 4, 4, 3, CT_F16, 4>(a, st);
             return launch_one<5, 3, 1, 4, 2, 4, 2, 3>(a, st);        //  64 x 16
         case 2:
-            if (strip_form(a, 128, 64, a.s == 4 ? 32 : 16, a.s == 4 ? 3 : 2)) return launch_strip<5, 3, 2, 4, 3>(a, st);
+            if (strip_form(a, np8, 128, 64, a.s == 4 ? 32 : 16, a.s == 4 ? 3 : 2)) return launch_strip<5, 3, 2, 4, 3>(a, st);
             if (a.s == 4) return launch_one<5, 3, 2, 4, 2, 4, 4, 3, CT_F16, 4>(a, st);
             return launch_one<5, 3, 2, 4, 2, 4, 2, 3>(a, st);
         case 4:
-            if (strip_form(a, 128, 128, a.s == 4 ? 24 : 16)) return launch_strip<5, 3, 4, 4, 2>(a, st);
+            if (strip_form(a, np8, 128, 128, a.s == 4 ? 24 : 16)) return launch_strip<5, 3, 4, 4, 2>(a, st);
             if (a.s == 4) return launch_one<5, 3, 4, 4, 1, 4, 6, 2, CT_F16, 4>(a, st);   // 128 x 24 (6-10 % faster)
             return launch_one<5, 3, 4, 4, 1, 4, 4, 2>(a, st);
         case 6:
-            if (strip_form(a, 128, 128, a.s == 4 ? 24 : 16)) return launch_strip<5, 3, 6, 4, 2>(a, st);
+            if (strip_form(a, np8, 128, 128, a.s == 4 ? 24 : 16)) return launch_strip<5, 3, 6, 4, 2>(a, st);
             if (a.s == 4) return launch_one<5, 3, 6, 4, 1, 4, 6, 2, CT_F16, 4>(a, st);
             return launch_one<5, 3, 6, 4, 1, 4, 4, 2>(a, st);
         case 9:
-            if (shape == 0 && strip_form(a, 128, kShapeW[resolve_shape_k5(a, 0)], kShapeH[resolve_shape_k5(a, 0)])) return launch_strip<5, 3, 9, 4, 2>(a, st);
+            if (shape == 0 && strip_form(a, np8, 128, kShapeW[resolve_shape_k5(a, 0)], kShapeH[resolve_shape_k5(a, 0)])) return launch_strip<5, 3, 9, 4, 2>(a, st);
             switch (resolve_shape_k5(a, shape)) {
             case 1:  return launch_one<5, 3, 9, 4, 2, 4, 1, 2>(a, st);    //  64 x 8
             case 2:  return launch_one<5, 3, 9, 4, 1, 4, 1, 2>(a, st);    // 128 x 4
@@ -75,7 +75,7 @@ hipError_t launch_mfma_k5(const AssembleArgs& a, int np8, int shape, const Launc
             default: return hipErrorInvalidValue;
             }
         case 16:
-            if (strip_form(a, 64, 64, a.s == 4 ? 24 : 16)) return launch_strip<5, 3, 16, 2, 2>(a, st);   // 73 to 128 atoms: two pixels per lane, as 7x7
+            if (strip_form(a, np8, 64, 64, a.s == 4 ? 24 : 16)) return launch_strip<5, 3, 16, 2, 2>(a, st);   // 73 to 128 atoms: two pixels per lane, as 7x7
             if (a.s == 4) return launch_one<5, 3, 16, 2, 1, 4, 6, 2, CT_F16, 4>(a, st);
             return launch_one<5, 3, 16, 2, 1, 4, 4, 2>(a, st);
         default: return hipErrorInvalidValue;
@@ -97,7 +97,7 @@ hipError_t launch_mfma_k5(const AssembleArgs& a, int np8, int shape, const Launc
         default: return hipErrorInvalidValue;
         }
     }
-    if (np8 == 16 ? strip_form(a, 64, 64, a.s == 4 ? 24 : 16) : strip_form(a, 128, 128, a.s == 4 && np8 == 9 ? 24 : 16)) {
+    if (np8 == 16 ? strip_form(a, np8, 64, 64, a.s == 4 ? 24 : 16) : strip_form(a, np8, 128, 128, a.s == 4 && np8 == 9 ? 24 : 16)) {
         switch (np8) {
         case 1:  return launch_strip<5, 1, 1, 4, 2>(a, st);
         case 4:  return launch_strip<5, 1, 4, 4, 2>(a, st);

@@ -12,7 +12,7 @@ static bool few_tiles(const AssembleArgs& a) { return (long long)a.N * a.H * a.W
 hipError_t launch_mfma_k5_f32(const AssembleArgs& a, int np8, const LaunchTo& st) {
     if (np8 == 9 && few_tiles(a))
         return a.C == 3 ? launch_one<5, 3, 9, 2, 1, 4, 1, 2, CT_F32>(a, st) : launch_one<5, 1, 9, 2, 1, 4, 1, 2, CT_F32>(a, st);
-    if (strip_form(a, 64, 64, a.C == 3 && np8 == 9 && a.s == 4 && (long long)a.N * a.H * a.W > 600000 ? 32 : 16)) {
+    if (strip_form(a, np8, 64, 64, a.C == 3 && np8 == 9 && a.s == 4 && (long long)a.N * a.H * a.W > 600000 ? 32 : 16)) {
         if (a.C == 3) {
             switch (np8) {
             case 1: return launch_strip<5, 3, 1, 2, 2, CT_F32>(a, st);
@@ -59,7 +59,7 @@ hipError_t launch_mfma_k5_f32(const AssembleArgs& a, int np8, const LaunchTo& st
 // register file of a SIMD (one wavefront per SIMD).  Lists of up to 16 atoms are
 // left to the generic kernel, which measured faster there (62 against 80 us at 1080p).
 hipError_t launch_mfma_k7_f32(const AssembleArgs& a, int np8, const LaunchTo& st) {
-    if (np8 == 9 && strip_form(a, 64, 64, 16))
+    if (np8 == 9 && strip_form(a, np8, 64, 64, 16))
         return a.C == 3 ? launch_strip<7, 3, 9, 2, 2, CT_F32>(a, st) : launch_strip<7, 1, 9, 2, 2, CT_F32>(a, st);
     if (a.C == 3) {
         switch (np8) {

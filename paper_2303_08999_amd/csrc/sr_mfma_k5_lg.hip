@@ -16,7 +16,7 @@ static hipError_t launch_lg(const AssembleArgs& a, const LaunchTo& st) {
         if (a.s == 3) return launch_one<5, 3, 9, 4, 1, 8, 3, 2, CT, 3, false, 3>(a, st);   // 384 x 8
         return launch_one<5, 3, 9, 4, 1, 4, 4, 2, CT, 2, false, 2>(a, st);                 // 128 x 16
     }
-    if (strip_form(a, 128, 128, a.s == 4 ? 24 : 16)) return launch_strip<5, 3, 9, 4, 2, CT>(a, st);
+    if (strip_form(a, 9, 128, 128, a.s == 4 ? 24 : 16)) return launch_strip<5, 3, 9, 4, 2, CT>(a, st);
     if (a.s == 4) return launch_one<5, 3, 9, 4, 1, 4, 6, 2, CT, 4>(a, st);
     return launch_one<5, 3, 9, 4, 1, 4, 4, 2, CT, 2>(a, st);
 }

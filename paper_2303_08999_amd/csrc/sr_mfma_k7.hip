@@ -10,7 +10,7 @@ namespace srd {
 
 template <int C, int NP8>
 static hipError_t launch_k7(const AssembleArgs& a, const LaunchTo& st) {
-    if (strip_form(a, 64, 64, a.s == 4 ? 24 : 16)) return launch_strip<7, C, NP8, 2, 2>(a, st);
+    if (strip_form(a, NP8, 64, 64, a.s == 4 ? 24 : 16)) return launch_strip<7, C, NP8, 2, 2>(a, st);
     if (a.s == 4) return launch_one<7, C, NP8, 2, 1, 4, 6, 2, CT_F16, 4>(a, st);
     return launch_one<7, C, NP8, 2, 1, 4, 4, 2>(a, st);
 }

@@ -1861,17 +1861,27 @@ hipError_t launch_one(const AssembleArgs& a0, const LaunchTo& st) {
 // Whether a call goes to the strip form (strips of `sw` columns) where it is built next to tiles of tw x th pixels in
 // workgroups of four wavefronts: the form that leaves the fullest SIMD with fewer rows; at about the same number the strips,
 // which up-sample no row twice, once a segment is long enough to pay for its own first rows (scale 3: dearer rows).
-// Measured, both forms in one run (us, tiles / strips; rows of the fullest SIMD; rows of a segment):
-//   fewer rows: 720p x4 fp16 34.1 / 30.6 (12 / 8; 4), 540 x 960 x2 fp16 28.5 / 23.5 (8 / 6; 3), 480 x 640 x2 fp32 32.7 / 27.0 (8 / 6; 3)
-//   about the same: 4K x4, 8 atoms 79 / 62 (64 / 66; 22), 1080p x2 65.0 / 63.5 (16 / 16; 8), 720p x4 fp32 61.3 / 60.6 (16 / 16; 8), 4K x3 256 / 251
-//   (64 / 64; 32), but 1080p x3 63.1 / 65.9 (16 / 16; 8), 512 x 512 fp32 22.3 / 24.1 (4 / 4; 2), 512 x 512 fp16 14.4 / 14.9 (2 / 2; 1).
-inline bool strip_form(const AssembleArgs& a, int sw, int tw, int th, int wpe = 2) {
+// Two cases in which the strips need more than that:
+//   rows that are no whole number of 128-byte lines, where the stream is the bound (np8, the capacity in groups of 8 atoms: 48 atoms
+//   and more; one channel 32 and more; lists: 0).  Neighbouring pieces of a row then share lines.  Tiles side by side ask for them at about
+//   the same time; wavefronts that walk strips drift apart, and the line comes from memory twice.  Strips have to save 15 % of the rows.
+//   scale 3, tiles of at most two rows per SIMD: a segment of one row up-samples K + 1 rows for it, one after the other.
+// Measured, both forms in one run (us, tiles / strips; profiles/strips_or_tiles.txt):
+//   fewer rows: 720p fp8 x4 34.4 / 25.0, 540 x 960 x2 fp16 28.8 / 23.5, 480 x 640 x2 fp32 33.0 / 28.0, 1080p x4 fp16 69.8 / 62.2
+//   about the same: 4K x4, 8 atoms 82.7 / 63.9, 1080p x2 fp16 66.2 / 64.8, 4K x3 fp16 246.9 / 244.2, but 1080p x3 fp16 64.9 / 67.0 (segments of 8 rows)
+//   rows of 2040 or 3816 columns: 1536 x 2040 x3 fp16 113.3 / 133.3, the same with 7x7 atoms and one channel 116.4 / 141.4, 4K less 24 columns x4 fp16 284.4 / 307.3,
+//   with one channel and 30 atoms 49.6 / 53.0; 1536 x 2040 x4 with three channels and 30 atoms 61.3 / 61.5 (neither is excluded there)
+//   segments of one row: 8 atoms, 240 x 312 x3 9.1 / 10.5; 144 x 192 x2 9.1 / 8.7 (not excluded)
+inline bool strip_form(const AssembleArgs& a, int np8, int sw, int tw, int th, int wpe = 2) {
     const long long simds = 4ll * compute_units(), strips = (long long)((a.W + sw - 1) / sw) * a.N;
     const long long per_strip = strips < simds * wpe ? simds * wpe / strips : 1;
     const long long rows = (a.H + per_strip - 1) / per_strip, segments = strips * ((a.H + rows - 1) / rows);
     const long long tiles = (long long)((a.W + tw - 1) / tw) * ((a.H + th - 1) / th) * a.N;
     const long long strip_rows = (segments + simds - 1) / simds * rows;
     const long long tile_rows = (4 * tiles + simds - 1) / simds * (tw * th / (4 * sw));
+    const long long row_bytes = (long long)a.W * (a.coeff_dtype == SR_F32 ? 4 : a.coeff_dtype == SR_F8E4M3 ? 1 : 2);
+    if (row_bytes % 128 != 0 && np8 >= (a.C == 1 ? 4 : 6) && 20 * strip_rows > 17 * tile_rows) return false;
+    if (a.s == 3 && rows == 1 && tile_rows <= 2) return false;
     return strip_rows < tile_rows || (10 * strip_rows <= 11 * tile_rows && rows >= (a.s == 3 ? 16 : 6));
 }
 

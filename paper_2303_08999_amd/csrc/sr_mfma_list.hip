@@ -20,9 +20,9 @@ bool mfma_list_supported(const AssembleArgs& a, int k, bool value_f16) {
 template <int CT>
 static hipError_t launch_ct(const AssembleArgs& a, const LaunchTo& st) {
     if (a.L <= 72) {
-        if (a.s == 4 && strip_form(a, 128, 128, 16)) return launch_one<5, 3, 9, 4, 1, 4, 1, 2, CT, 4, false, 0, 4>(a, st);
+        if (a.s == 4 && strip_form(a, 0, 128, 128, 16)) return launch_one<5, 3, 9, 4, 1, 4, 1, 2, CT, 4, false, 0, 4>(a, st);
         if (a.s == 4) return launch_one<5, 3, 9, 4, 1, 4, 4, 2, CT, 4>(a, st);
-        if (a.s == 3 && strip_form(a, 128, 128, 8)) return launch_one<5, 3, 9, 4, 1, 4, 1, 2, CT, 3, false, 0, 3>(a, st);
+        if (a.s == 3 && strip_form(a, 0, 128, 128, 8)) return launch_one<5, 3, 9, 4, 1, 4, 1, 2, CT, 3, false, 0, 3>(a, st);
         return launch_one<5, 3, 9, 4, 1, 4, 2, 2, CT, 2>(a, st);
     }
     return launch_one<5, 3, 16, 4, 1, 4, 2, 2, CT, 2>(a, st);
