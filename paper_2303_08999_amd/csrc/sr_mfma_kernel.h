@@ -1865,13 +1865,15 @@ hipError_t launch_one(const AssembleArgs& a0, const LaunchTo& st) {
 //   rows that are no whole number of 128-byte lines, where the stream is the bound (np8, the capacity in groups of 8 atoms: 48 atoms
 //   and more; one channel 32 and more; lists: 0).  Neighbouring pieces of a row then share lines.  Tiles side by side ask for them at about
 //   the same time; wavefronts that walk strips drift apart, and the line comes from memory twice.  Strips have to save 15 % of the rows.
-//   scale 3, tiles of at most two rows per SIMD: a segment of one row up-samples K + 1 rows for it, one after the other.
+//   scale 3, tiles of at most two rows per SIMD: a segment of one row up-samples K + 1 rows for it, one after the other; and the same
+//   with up to three rows where a row is cheap to fold (one channel, two pixels per lane) and strips save at most a quarter of them.
 // Measured, both forms in one run (us, tiles / strips; profiles/strips_or_tiles.txt):
 //   fewer rows: 720p fp8 x4 34.4 / 25.0, 540 x 960 x2 fp16 28.8 / 23.5, 480 x 640 x2 fp32 33.0 / 28.0, 1080p x4 fp16 69.8 / 62.2
 //   about the same: 4K x4, 8 atoms 82.7 / 63.9, 1080p x2 fp16 66.2 / 64.8, 4K x3 fp16 246.9 / 244.2, but 1080p x3 fp16 64.9 / 67.0 (segments of 8 rows)
 //   rows of 2040 or 3816 columns: 1536 x 2040 x3 fp16 113.3 / 133.3, the same with 7x7 atoms and one channel 116.4 / 141.4, 4K less 24 columns x4 fp16 284.4 / 307.3,
 //   with one channel and 30 atoms 49.6 / 53.0; 1536 x 2040 x4 with three channels and 30 atoms 61.3 / 61.5 (neither is excluded there)
-//   segments of one row: 8 atoms, 240 x 312 x3 9.1 / 10.5; 144 x 192 x2 9.1 / 8.7 (not excluded)
+//   segments of one row: 8 atoms, 240 x 312 x3 9.1 / 10.5; 144 x 192 x2 9.1 / 8.7 (not excluded); of three: one channel,
+//   fp32, 8 atoms, 444 x 714 x3 10.1 / 10.8
 inline bool strip_form(const AssembleArgs& a, int np8, int sw, int tw, int th, int wpe = 2) {
     const long long simds = 4ll * compute_units(), strips = (long long)((a.W + sw - 1) / sw) * a.N;
     const long long per_strip = strips < simds * wpe ? simds * wpe / strips : 1;
@@ -1882,6 +1884,7 @@ inline bool strip_form(const AssembleArgs& a, int np8, int sw, int tw, int th, i
     const long long row_bytes = (long long)a.W * (a.coeff_dtype == SR_F32 ? 4 : a.coeff_dtype == SR_F8E4M3 ? 1 : 2);
     if (row_bytes % 128 != 0 && np8 >= (a.C == 1 ? 4 : 6) && 20 * strip_rows > 17 * tile_rows) return false;
     if (a.s == 3 && rows == 1 && tile_rows <= 2) return false;
+    if (a.s == 3 && a.C == 1 && sw == 64 && rows <= 3 && 4 * strip_rows >= 3 * tile_rows) return false;
     return strip_rows < tile_rows || (10 * strip_rows <= 11 * tile_rows && rows >= (a.s == 3 ? 16 : 6));
 }
 

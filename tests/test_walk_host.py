@@ -115,6 +115,7 @@ def test_lists_that_strips_refuse_take_the_tile_they_were_compared_with(n, H, W,
     (dict(W=3816, kept=list(range(8))), STRIPS), (dict(H=1536, W=2040, kept=list(range(30))), STRIPS),
     # scale 3, segments of one row against tiles of two
     (dict(H=240, W=312, s=3, kept=[0, 9]), TILES), (dict(H=144, W=192, s=3, cd="f8", L=8), TILES),
+    (dict(H=444, W=714, s=3, C=1, cd="f32", L=8), TILES), (dict(H=444, W=714, s=3, cd="f32", L=8), STRIPS),
     (dict(H=240, W=312, s=2, kept=[0, 9]), STRIPS), (dict(H=240, W=312, s=3, L=40), STRIPS),
 ])
 def test_which_form_a_call_takes(call, form):
