@@ -96,11 +96,12 @@ def test_8_bit_frames_that_strips_refuse_take_the_tile_they_were_compared_with(H
     assert kernel == sr.SR_KERNEL_MFMA and (got[0] == STRIPS or got[:3] == (TILES, 128, 24))
 
 
-@pytest.mark.parametrize("n, H, W", [(1, 720, 1280), (1, 800, 1200), (32, 128, 192)])
+@pytest.mark.parametrize("n, H, W", [(1, 4, 4), (1, 480, 640), (1, 720, 1280), (1, 800, 1200), (32, 128, 192), (1, 2160, 3840), (4000, 8, 16)])
 @pytest.mark.parametrize("entries", [8, 16])
-def test_lists_that_strips_refuse_take_the_tile_they_were_compared_with(n, H, W, entries):
+def test_lists_of_up_to_72_atoms_at_scale_4_take_strips(n, H, W, entries):
     kernel, got = list_walk(n=n, H=H, W=W, entries=entries)
-    assert kernel == sr.SR_KERNEL_MFMA and (got[0] == STRIPS or got[:3] == (TILES, 128, 16))
+    assert kernel == sr.SR_KERNEL_MFMA and got[:2] == (STRIPS, 128)
+    _whole(got, n, H, W)
 
 
 @pytest.mark.parametrize("call, form", [
