@@ -59,7 +59,7 @@ hipError_t launch_mfma_k5_f32(const AssembleArgs& a, int np8, const LaunchTo& st
 // register file of a SIMD (one wavefront per SIMD).  Lists of up to 16 atoms are
 // left to the generic kernel, which measured faster there (62 against 80 us at 1080p).
 hipError_t launch_mfma_k7_f32(const AssembleArgs& a, int np8, const LaunchTo& st) {
-    if (np8 == 9 && strip_form(a, np8, 64, 64, 16))
+    if (np8 == 9 && strip_form(a, 0, 64, 64, 16))
         return a.C == 3 ? launch_strip<7, 3, 9, 2, 2, CT_F32>(a, st) : launch_strip<7, 1, 9, 2, 2, CT_F32>(a, st);
     if (a.C == 3) {
         switch (np8) {

@@ -1861,19 +1861,21 @@ hipError_t launch_one(const AssembleArgs& a0, const LaunchTo& st) {
 // Whether a call goes to the strip form (strips of `sw` columns) where it is built next to tiles of tw x th pixels in
 // workgroups of four wavefronts: the form that leaves the fullest SIMD with fewer rows; at about the same number the strips,
 // which up-sample no row twice, once a segment is long enough to pay for its own first rows (scale 3: dearer rows).
-// Two cases in which the strips need more than that:
-//   rows that are no whole number of 128-byte lines, where the stream is the bound (np8, the capacity in groups of 8 atoms: 48 atoms
-//   and more; one channel 32 and more; lists: 0).  Neighbouring pieces of a row then share lines.  Tiles side by side ask for them at about
-//   the same time; wavefronts that walk strips drift apart, and the line comes from memory twice.  Strips have to save 15 % of the rows.
-//   scale 3, tiles of at most two rows per SIMD: a segment of one row up-samples K + 1 rows for it, one after the other; and the same
-//   with up to three rows where a row is cheap to fold (one channel, two pixels per lane) and strips save at most a quarter of them.
+// np8: capacity of the instantiation in groups of 8 atoms, 0 where the coefficient stream is not the bound (lists; fp32 with 7x7 atoms).
+// Two cases in which strips are refused although the rows speak for them:
+//   Rows that start on no multiple of 64 bytes, where the stream is the bound: instantiations for 48 atoms and more (one channel: 32) filled to 97 % (90 %),
+//   more coefficients than the 256 MB memory-side cache can hold beside the rest (one channel, which has half the other work to hide a miss
+//   behind: half of it), and work for 94 % of the resident lanes.  Neighbouring pieces of a row then share lines.  Tiles side by side ask for them at
+//   about the same time; wavefronts that walk strips drift apart, the loads are streaming ones, and the line comes from memory twice (with loads that stay
+//   in the L2, 128 atoms 1536 x 2040 x3 262 -> 215 us, but whole lines 4K 239 -> 278).  Strips have to save 8 % of the rows.
+//   Scale 3, tiles of at most two rows per SIMD: a segment of one row up-samples K + 1 rows for it, one after the other; and the same
+//   with up to three rows where a row is cheap to fold (one channel, few atoms, two pixels per lane) and strips save at most a quarter of them.
 // Measured, both forms in one run (us, tiles / strips; profiles/strips_or_tiles.txt):
 //   fewer rows: 720p fp8 x4 34.4 / 25.0, 540 x 960 x2 fp16 28.8 / 23.5, 480 x 640 x2 fp32 33.0 / 28.0, 1080p x4 fp16 69.8 / 62.2
 //   about the same: 4K x4, 8 atoms 82.7 / 63.9, 1080p x2 fp16 66.2 / 64.8, 4K x3 fp16 246.9 / 244.2, but 1080p x3 fp16 64.9 / 67.0 (segments of 8 rows)
-//   rows of 2040 or 3816 columns: 1536 x 2040 x3 fp16 113.3 / 133.3, the same with 7x7 atoms and one channel 116.4 / 141.4, 4K less 24 columns x4 fp16 284.4 / 307.3,
-//   with one channel and 30 atoms 49.6 / 53.0; 1536 x 2040 x4 with three channels and 30 atoms 61.3 / 61.5 (neither is excluded there)
-//   segments of one row: 8 atoms, 240 x 312 x3 9.1 / 10.5; 144 x 192 x2 9.1 / 8.7 (not excluded); of three: one channel,
-//   fp32, 8 atoms, 444 x 714 x3 10.1 / 10.8
+//   rows that share lines: 1536 x 2040 x2 fp16 116.6 / 130.5, x3 with 7x7 atoms and one channel 116.4 / 141.4, 4K less 24 columns x4 fp16 284.4 / 307.3;
+//   not refused: 1200 x 1608 x4 83.5 / 70.7 (92 % of the lanes), 1536 x 2040 x4 with 30 atoms 61.3 / 61.5, 900 x 1600 x2 fp8 with 45 atoms 35.0 / 28.8
+//   segments of one row: 8 atoms, 240 x 312 x3 9.1 / 10.5, but 144 x 192 x2 9.1 / 8.7; of three: one channel, fp32, 8 atoms, 444 x 714 x3 10.1 / 10.8
 inline bool strip_form(const AssembleArgs& a, int np8, int sw, int tw, int th, int wpe = 2) {
     const long long simds = 4ll * compute_units(), strips = (long long)((a.W + sw - 1) / sw) * a.N;
     const long long per_strip = strips < simds * wpe ? simds * wpe / strips : 1;
@@ -1882,9 +1884,12 @@ inline bool strip_form(const AssembleArgs& a, int np8, int sw, int tw, int th, i
     const long long strip_rows = (segments + simds - 1) / simds * rows;
     const long long tile_rows = (4 * tiles + simds - 1) / simds * (tw * th / (4 * sw));
     const long long row_bytes = (long long)a.W * (a.coeff_dtype == SR_F32 ? 4 : a.coeff_dtype == SR_F8E4M3 ? 1 : 2);
-    if (row_bytes % 128 != 0 && np8 >= (a.C == 1 ? 4 : 6) && 20 * strip_rows > 17 * tile_rows) return false;
+    const bool stream = np8 >= (a.C == 1 ? 4 : 6) && 100 * a.n_fold >= (a.C == 1 ? 90 : 97) * 8 * np8 &&
+                        row_bytes * a.H * a.N * a.n_fold >= (a.C == 1 ? 128000000ll : 230000000ll) &&
+                        100 * segments * a.W >= (np8 == 16 ? 85 : 94) * simds * wpe * ((a.W + sw - 1) / sw * sw);
+    if (row_bytes % 64 != 0 && stream && 100 * strip_rows > 92 * tile_rows) return false;
     if (a.s == 3 && rows == 1 && tile_rows <= 2) return false;
-    if (a.s == 3 && a.C == 1 && sw == 64 && rows <= 3 && 4 * strip_rows >= 3 * tile_rows) return false;
+    if (a.s == 3 && a.C == 1 && np8 >= 1 && np8 <= 2 && sw == 64 && rows <= 3 && 4 * strip_rows >= 3 * tile_rows) return false;
     return strip_rows < tile_rows || (10 * strip_rows <= 11 * tile_rows && rows >= (a.s == 3 ? 16 : 6));
 }
 

@@ -107,16 +107,18 @@ def test_lists_of_up_to_72_atoms_at_scale_4_take_strips(n, H, W, entries):
 @pytest.mark.parametrize("call, form", [
     # rows of whole 128-byte lines: strips at about the same number of rows of the fullest SIMD
     (dict(), STRIPS), (dict(H=1536, W=2048, s=2), STRIPS), (dict(H=1536, W=2048, L=128, k=7), STRIPS), (dict(cd="f8"), STRIPS),
-    # rows that share lines, the stream as the bound: tiles unless strips save 15 %
+    # rows that share lines, the stream as the bound: tiles unless strips save 8 %
     (dict(W=3816), TILES), (dict(W=3816, cd="f8"), TILES), (dict(W=3816, cd="bf16", kind=sr.SR_COEFF_LOGITS), TILES),
-    (dict(H=1536, W=2040, s=3), TILES), (dict(H=1536, W=2040, s=3, k=7, C=1), TILES), (dict(H=1536, W=2040, s=3, cd="f32", C=1), TILES),
+    (dict(H=1536, W=2040, s=2), TILES), (dict(H=1536, W=2040, s=3, k=7, C=1), TILES), (dict(H=1536, W=2040, s=3, cd="f32", C=1), TILES),
     (dict(H=1200, W=1600, s=2, L=128), STRIPS), (dict(H=1200, W=1608, s=2, L=128), TILES), (dict(H=1536, W=2040, C=1, kept=list(range(30))), TILES),
-    (dict(H=540, W=936, s=2), STRIPS),                                          # 4 rows against 8
+    # ... not bound by it: half lines, fewer coefficients than the memory-side cache holds, wavefronts to spare, capacity to spare, fp32 with 7x7 atoms
+    (dict(H=1800, W=3232, L=128), STRIPS), (dict(H=540, W=936, s=2), STRIPS), (dict(H=900, W=1600, s=2, cd="f8", kept=list(range(45))), STRIPS),
+    (dict(H=1200, W=1608), STRIPS), (dict(H=1536, W=2040, s=2, L=52), STRIPS), (dict(H=1200, W=1596, s=3, k=7, cd="f32"), STRIPS),
     # ... few atoms, or three channels and 30 atoms: the up-sampling counts, strips as before
     (dict(W=3816, kept=list(range(8))), STRIPS), (dict(H=1536, W=2040, kept=list(range(30))), STRIPS),
     # scale 3, segments of one row against tiles of two
     (dict(H=240, W=312, s=3, kept=[0, 9]), TILES), (dict(H=144, W=192, s=3, cd="f8", L=8), TILES),
-    (dict(H=444, W=714, s=3, C=1, cd="f32", L=8), TILES), (dict(H=444, W=714, s=3, cd="f32", L=8), STRIPS),
+    (dict(H=444, W=714, s=3, C=1, cd="f32", L=8), TILES), (dict(H=444, W=714, s=3, cd="f32", L=8), STRIPS), (dict(H=480, W=636, s=3, C=1, k=7), STRIPS),
     (dict(H=240, W=312, s=2, kept=[0, 9]), STRIPS), (dict(H=240, W=312, s=3, L=40), STRIPS),
 ])
 def test_which_form_a_call_takes(call, form):
