@@ -898,16 +898,16 @@ void k_assemble_mfma(const AssembleArgs a) {
                         dst[swrite[i] + (q % F::SW) * NG + q / F::SW] = u;
                     }
                 }
-            // columns outside the image are copies of its first and last column (ring column i is image column X0 - R + i; a last strip
-            // that was moved left may start at a column other than 0 and still look over the left edge: 129 columns, X0 = 1)
+            // columns outside the image are copies of its first and last column (a strip that starts at a column from 1 to R - 1 would
+            // need them on the left too: not launched, see strip_form)
             const int X0 = tile_x0(sg.tx);
-            if (X0 < F::R || X0 + F::TW + F::R > a.W) {
+            if (X0 == 0 || X0 + F::TW + F::R > a.W) {
                 strip_fence();
                 int le = lane;                          // (these few addresses are not worth registers held over the rows)
                 asm volatile("" : "+v"(le));
                 const int side = le / (C * F::R), c = le / F::R % C, i = le % F::R;
-                const int from = side == 0 ? F::R - X0 : a.W - 1 - X0 + F::R, to = side == 0 ? i : a.W - X0 + F::R + i;
-                if (side == 0 ? i < F::R - X0 : side == 1 && to < UW)
+                const int from = side == 0 ? F::R : a.W - 1 - X0 + F::R, to = side == 0 ? i : a.W - X0 + F::R + i;
+                if (side == 0 ? X0 == 0 : side == 1 && to < UW)
                     dst[c * P + (to % F::SW) * NG + to / F::SW] = dst[c * P + (from % F::SW) * NG + from / F::SW];
             }
         }
@@ -1834,6 +1834,7 @@ hipError_t launch_one(const AssembleArgs& a0, const LaunchTo& st) {
     if (a.W % PX != 0) {                                // ragged rows: the last tile column ends at the image edge
         if (a.W < F::TW) return hipErrorInvalidValue;
         a.xlast = a.W - F::TW;
+        if (STRIP && a.xlast > 0 && a.xlast < F::R) return hipErrorInvalidValue;   // would look over the left edge, see strip_form
     }
     const int cap = compute_units() * (4 * WPE / NW > 0 ? 4 * WPE / NW : 1);
     a.seg_rows = F::TH;
@@ -1861,6 +1862,8 @@ hipError_t launch_one(const AssembleArgs& a0, const LaunchTo& st) {
 // Whether a call goes to the strip form (strips of `sw` columns) where it is built next to tiles of tw x th pixels in
 // workgroups of four wavefronts: the form that leaves the fullest SIMD with fewer rows; at about the same number the strips,
 // which up-sample no row twice, once a segment is long enough to pay for its own first rows (scale 3: dearer rows).
+// One column more than a strip is left to the tiles: its last strip would start at column 1 and see column -1, which the kernel continues
+// for strips that start at column 0 only (continuing it there for all cost the light forms 1 % at every size).
 // np8: capacity of the instantiation in groups of 8 atoms, 0 where the coefficient stream is not the bound (lists; fp32 with 7x7 atoms).
 // Two cases in which strips are refused although the rows speak for them:
 //   Rows that start on no multiple of 64 bytes, where the stream is the bound: instantiations for 48 atoms and more (one channel: 32) filled to 97 % (90 %),
@@ -1877,6 +1880,7 @@ hipError_t launch_one(const AssembleArgs& a0, const LaunchTo& st) {
 //   not refused: 1200 x 1608 x4 83.5 / 70.7 (92 % of the lanes), 1536 x 2040 x4 with 30 atoms 61.3 / 61.5, 900 x 1600 x2 fp8 with 45 atoms 35.0 / 28.8
 //   segments of one row: 8 atoms, 240 x 312 x3 9.1 / 10.5, but 144 x 192 x2 9.1 / 8.7; of three: one channel, fp32, 8 atoms, 444 x 714 x3 10.1 / 10.8
 inline bool strip_form(const AssembleArgs& a, int np8, int sw, int tw, int th, int wpe = 2) {
+    if (a.W == sw + 1) return false;                    // the moved last strip would start at column 1 and look over the left edge with R = 2
     const long long simds = 4ll * compute_units(), strips = (long long)((a.W + sw - 1) / sw) * a.N;
     const long long per_strip = strips < simds * wpe ? simds * wpe / strips : 1;
     const long long rows = (a.H + per_strip - 1) / per_strip, segments = strips * ((a.H + rows - 1) / rows);

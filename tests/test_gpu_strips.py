@@ -90,15 +90,16 @@ def test_strips_of_logits(h, w, scale, coeff):
 @pytest.mark.parametrize("n, c, h, L, coeff, image, kept", [
     (1, 1, 43, 72, "f16", "f32", None),
     (1, 1, 7, 72, "bf16", "f16", None),
-    (1, 3, 43, 72, "f16", "f32", 30),                    # kept lists that take strips at this size
+    (1, 3, 43, 72, "f16", "f32", 30),                    # the forms and batches whose other sizes about this one take strips
     (1, 3, 43, 72, "bf16", "f32", 41),
     (1, 3, 43, 72, "f8", "f32", 30),
-    (32, 3, 43, 72, "f16", "f32", None),                 # batches: five rows to a segment
+    (32, 3, 43, 72, "f16", "f32", None),
     (32, 3, 43, 72, "f8", "f32", None),
 ])
-def test_last_strip_moved_to_column_one(oracle, n, c, h, L, coeff, image, kept):
-    """43 columns at x3 are 129: the last strip starts at column 1 and looks one column over the left edge, where the image
-    is continued by copies of column 0.  Both strips write the same pixels, so they have to agree."""
+def test_one_column_more_than_a_strip(oracle, n, c, h, L, coeff, image, kept):
+    """43 columns at x3 are 129: a last strip moved left to end at the edge would start at column 1 and look one column over the
+    left edge, where the image is continued by copies of column 0 and the strip form has none there; both strips write the
+    same pixels.  Such images take tiles."""
     wl = sr_synth.Workload("moved", 63, n, c, h, 43, 3, L, 5, coeff, image)
     inp = sr_synth.make_inputs(wl, DEV)
     inp["lr"][..., 0] = 1.0                               # a step at the left edge, where the two continuations differ most
@@ -110,7 +111,7 @@ def test_last_strip_moved_to_column_one(oracle, n, c, h, L, coeff, image, kept):
 
 
 @pytest.mark.parametrize("coeff", ["f16", "bf16"])
-def test_last_strip_moved_to_column_one_logits(coeff):
+def test_one_column_more_than_a_strip_logits(coeff):
     wl = sr_synth.Workload("moved", 64, 1, 3, 43, 43, 3, 72, 5, coeff, "f32")
     lr, z, d = sr_synth.make_lr(wl, DEV), sr_synth.make_logits(wl, DEV), sr_synth.make_dictionary(wl, DEV)
     lr[..., 0], lr[..., 1:3] = 1.0, 0.0

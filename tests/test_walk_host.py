@@ -123,3 +123,16 @@ def test_lists_of_up_to_72_atoms_at_scale_4_take_strips(n, H, W, entries):
 ])
 def test_which_form_a_call_takes(call, form):
     assert walk(**call)[1][0] == form
+
+
+@pytest.mark.parametrize("cd", list(DT))
+@pytest.mark.parametrize("kind", [sr.SR_COEFF_VALUES, sr.SR_COEFF_LOGITS])
+def test_no_strip_starts_between_its_first_columns(cd, kind):
+    """A last strip that is moved left to end at the image edge starts at column 0 or at R or beyond: the strip form continues
+    the image on the left of column 0 for a strip that starts there only."""
+    for k, C, L in ((3, 1, 72), (3, 3, 8), (5, 1, 72), (5, 3, 8), (5, 3, 30), (5, 3, 72), (5, 3, 128), (7, 1, 72), (7, 3, 12)):
+        for n, h in ((1, 1), (1, 43), (32, 43), (400, 43), (1, 3000)):
+            for w in range(43, 68):
+                form, width = walk(n=n, C=C, H=3 * h, W=3 * w, s=3, L=L, k=k, cd=cd, kind=kind)[1][:2]
+                if form == STRIPS and (3 * w) % (width // 32) != 0:
+                    assert 3 * w - width == 0 or 3 * w - width >= k // 2, (k, C, L, n, h, w)
