@@ -8,6 +8,8 @@
 // This kernel is bound by the fp32 ALUs (L*k^2 multiply-adds per pixel), not by
 // HBM; the matrix-core kernel (sr_mfma_kernel.h) is the fast path wherever it
 // qualifies.
+#include <string.h>
+
 #include "sr_device.h"
 #include "sr_launch.h"
 
@@ -17,8 +19,21 @@ constexpr int GTW = 64;   // tile width  (HR pixels) = one wavefront per row
 constexpr int GTH = 4;    // tile height (HR pixels)
 constexpr int GNT = GTW * GTH;
 
+// What it reads of a call's arguments.  A struct of its own: with the matrix-core kernel's walk in front of the lists the kernel took 0.5 %
+// more time in the median of 2160 calls, 1.6 % at the ninth decile; like this 0.4 % less.
+struct GenericArgs {
+    const void*  lr;
+    const void*  coeff;
+    const float* dict;
+    void*        out;
+    int C, h, w, H, W, s, L, n_fold;
+    int pre_shuffle, pixel_major, blocked, logits;
+    int   kept[SR_MAX_ATOMS];
+    float gamma[SR_MAX_ATOMS];
+};
+
 template <typename TC, typename TIO, int K>
-__global__ __launch_bounds__(GNT) void k_assemble_generic(const AssembleArgs a) {
+__global__ __launch_bounds__(GNT) void k_assemble_generic(const GenericArgs a) {
     constexpr int KK = K * K;
     constexpr int R = (K - 1) / 2;
     constexpr int UW = GTW + K - 1;
@@ -225,8 +240,14 @@ __global__ __launch_bounds__(256) void k_bicubic(const BicubicArgs a) {
 }
 
 template <typename TC, typename TIO>
-static hipError_t launch_generic_k(const AssembleArgs& a, int k, hipStream_t st) {
-    const dim3 grid((a.W + GTW - 1) / GTW, (a.H + GTH - 1) / GTH, a.N);
+static hipError_t launch_generic_k(const AssembleArgs& c, int k, hipStream_t st) {
+    const dim3 grid((c.W + GTW - 1) / GTW, (c.H + GTH - 1) / GTH, c.N);
+    GenericArgs a;
+    a.lr = c.lr; a.coeff = c.coeff; a.dict = c.dict; a.out = c.out;
+    a.C = c.C; a.h = c.h; a.w = c.w; a.H = c.H; a.W = c.W; a.s = c.s; a.L = c.L; a.n_fold = c.n_fold;
+    a.pre_shuffle = c.pre_shuffle; a.pixel_major = c.pixel_major; a.blocked = c.blocked; a.logits = c.logits;
+    memcpy(a.kept, c.kept, sizeof(a.kept));
+    memcpy(a.gamma, c.gamma, sizeof(a.gamma));
     switch (k) {
     case 3: hipLaunchKernelGGL((k_assemble_generic<TC, TIO, 3>), grid, dim3(GNT), 0, st, a); break;
     case 5: hipLaunchKernelGGL((k_assemble_generic<TC, TIO, 5>), grid, dim3(GNT), 0, st, a); break;
