@@ -103,7 +103,7 @@ bool mfma_supported(const AssembleArgs& a, int k, int coeff_dtype, int tile) {
         !(k == 5 && a.C == 3 && (coeff_dtype == SR_F16 || coeff_dtype == SR_BF16) &&
           (unsigned long long)a.L * a.H * a.W < (1ull << 32)))
         return false;
-    if ((unsigned long long)a.C * a.H * a.W * 4ull > 0xffffffc0ull) return false;          // 32-bit offsets within an image (BEYOND in the kernel)
+    if ((unsigned long long)a.C * a.H * a.W * 4ull >= (1ull << 32)) return false;          // 32-bit offsets within an image
     const int np8 = np8_for(k, a.C, a.n_fold, coeff_dtype);
     if (np8 == 0) return false;
     // coefficients in the layout before the network's pixel-shuffle: one family built

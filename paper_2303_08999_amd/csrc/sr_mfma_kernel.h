@@ -291,9 +291,10 @@ __device__ __forceinline__ _Float16 __attribute__((ext_vector_type(2))) pk_max_f
 }
 
 // Output stores through a raw buffer resource of the image (fourth word: 32-bit data format), whose bounds check drops a lane
-// at BEYOND: no image has that many bytes (see mfma_supported), and BEYOND + 15 does not wrap.
+// at the end of the image or beyond.  Such a lane stores up to eight bytes (sixteen at scale 4, whose images are multiples of 64) from the
+// end on, and all of them have 32-bit offsets: every image below 4 GB, but fp32 ones of 2^30 - 1 pixels, whose pixel groups go in strips (see
+// strip_form), where every lane is inside the image.
 constexpr int RAW_BUFFER = 0x00020000;
-constexpr unsigned BEYOND = 0xffffffc0u;
 __device__ __forceinline__ void store16(__amdgpu_buffer_rsrc_t r, unsigned at, float v) {
     __builtin_amdgcn_raw_buffer_store_b16(__half_as_ushort(narrow_f16(v)), r, at, 0, 0);
 }
@@ -1531,14 +1532,15 @@ void k_assemble_mfma(const AssembleArgs a) {
                           : PERM ? (unsigned)y * (unsigned)a.W + x + hf * (2 * PSM) + (PSM == 4 ? 4 : 2) * (jc % 2)
                           : STRIP ? so0 : (unsigned)y * (unsigned)a.W + x + hf * (PX / 2);   // within the image
         char* const out_img = STRIP ? sout : (char*)a.out + (size_t)cur.n * C * ((size_t)plane_px * (a.io_f16 ? 2 : 4));
-        // Every lane stores, one outside the image beyond the end of the buffer, which drops it.  Behind a branch the compiler cannot
+        // Every lane stores, one outside the image at the end of the buffer, which drops it.  Behind a branch the compiler cannot
         // count the stores, and the next unit's fold, which waits for loads issued before them, waits for them as well.
         // 512 x 512 x4: 14.1 -> 13.3 us; no different where a unit is long.
-        const __amdgpu_buffer_rsrc_t out_rsrc = __builtin_amdgcn_make_buffer_rsrc(out_img, 0, (int)(C * plane_px * (a.io_f16 ? 2u : 4u)), RAW_BUFFER);
+        const unsigned out_bytes = C * plane_px * (a.io_f16 ? 2u : 4u);
+        const __amdgpu_buffer_rsrc_t out_rsrc = __builtin_amdgcn_make_buffer_rsrc(out_img, 0, (int)out_bytes, RAW_BUFFER);
 #ifdef SR_ABLATE_STORES
-        auto out_at = [&](unsigned e, unsigned size) -> unsigned { return valid && a.N < 0 ? e * size : BEYOND; };   // (never true)
+        auto out_at = [&](unsigned e, unsigned size) -> unsigned { return valid && a.N < 0 ? e * size : out_bytes; };   // (never true)
 #else
-        auto out_at = [&](unsigned e, unsigned size) -> unsigned { return valid ? e * size : BEYOND; };
+        auto out_at = [&](unsigned e, unsigned size) -> unsigned { return valid ? e * size : out_bytes; };
 #endif
 #pragma unroll
         for (int c = 0; c < C; ++c) {
@@ -1880,6 +1882,7 @@ hipError_t launch_one(const AssembleArgs& a0, const LaunchTo& st) {
 //   not refused: 1200 x 1608 x4 83.5 / 70.7 (92 % of the lanes), 1536 x 2040 x4 with 30 atoms 61.3 / 61.5, 900 x 1600 x2 fp8 with 45 atoms 35.0 / 28.8
 //   segments of one row: 8 atoms, 240 x 312 x3 9.1 / 10.5, but 144 x 192 x2 9.1 / 8.7; of three: one channel, fp32, 8 atoms, 444 x 714 x3 10.1 / 10.8
 inline bool strip_form(const AssembleArgs& a, int np8, int sw, int tw, int th, int wpe = 2) {
+    if ((long long)a.C * a.H * a.W == (1ll << 30) - 1) return true;         // see the stores
     if (a.W == sw + 1) return false;                    // the moved last strip would start at column 1 and look over the left edge with R = 2
     const long long simds = 4ll * compute_units(), strips = (long long)((a.W + sw - 1) / sw) * a.N;
     const long long per_strip = strips < simds * wpe ? simds * wpe / strips : 1;

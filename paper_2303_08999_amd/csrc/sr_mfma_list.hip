@@ -9,7 +9,7 @@ bool mfma_list_supported(const AssembleArgs& a, int k, bool value_f16) {
     if (k != 5 || a.C != 3 || !value_f16 || a.L > 128 || a.T < 1 || a.T > LIST_MAX_ENTRIES) return false;
     if (a.W < 4 || a.W % 4 != 0 || a.H < 1) return false;
     if ((unsigned long long)a.T * a.H * a.W >= (1ull << 32)) return false;             // 32-bit element offsets within an image
-    if ((unsigned long long)a.C * a.H * a.W * 4ull > 0xffffffc0ull) return false;
+    if ((unsigned long long)a.C * a.H * a.W * 4ull >= (1ull << 32)) return false;
     return true;
 }
 

@@ -148,3 +148,21 @@ def test_list_strips_of_few_rows(h, entries):
         sr.sr_dict_assemble_list_ex(inp["lr"], index, value, inp["dict"], 72, 5, 4, 3, entries, o, kernel=kernel)
     assert torch.isfinite(out[0]).all()
     assert float((out[0] - out[1]).abs().max()) <= 5e-5 * max(1.0, float(out[1].abs().max()))
+
+
+@pytest.mark.parametrize("h, w, scale, L", [(16383, 16385, 2, 1), (25487, 4681, 3, 1)])
+def test_images_of_just_below_4_gb(h, w, scale, L):
+    """fp32 images that end 16 and 4 bytes below 4 GB: lanes outside them store nowhere, those inside everywhere."""
+    n = h * scale * w * scale
+    assert (1 << 32) - 4 * n in (16, 4)
+    lr = torch.rand((1, 1, h, w), device=DEV)
+    coeff = torch.randint(0x28, 0x40, (1, L, h * scale, w * scale), device=DEV, dtype=torch.uint8).view(torch.float8_e4m3fn)
+    d = torch.randn((L, 5, 5), device=DEV) * 0.1
+    guard = torch.full((n + 1024,), float("nan"), device=DEV)
+    got = guard[:n].view(1, 1, h * scale, w * scale)
+    want = torch.empty_like(got)
+    for o, kernel in ((got, MFMA), (want, GENERIC)):
+        sr.sr_dict_assemble_ex(lr, coeff, d, L, 5, scale, 1, o, opts=sr.make_options(kernel))
+    assert torch.isnan(guard[n:]).all()
+    worst = max(float((a - b).abs().max()) for a, b in zip(got[0, 0].split(2048), want[0, 0].split(2048)))
+    assert worst <= 5e-5 * max(1.0, float(want.abs().max()))

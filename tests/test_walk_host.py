@@ -136,3 +136,18 @@ def test_no_strip_starts_between_its_first_columns(cd, kind):
                 form, width = walk(n=n, C=C, H=3 * h, W=3 * w, s=3, L=L, k=k, cd=cd, kind=kind)[1][:2]
                 if form == STRIPS and (3 * w) % (width // 32) != 0:
                     assert 3 * w - width == 0 or 3 * w - width >= k // 2, (k, C, L, n, h, w)
+
+
+def test_images_up_to_4_gb_are_the_matrix_core_kernels():
+    """The last 64 bytes below 4 GB included; an odd number of 2^30 - 1 pixels in strips, whose lanes are all inside the image."""
+    H, W = 2 * 16383, 2 * 16385
+    assert H * W == (1 << 30) - 4
+    for kernel in (sr.SR_KERNEL_AUTO, sr.SR_KERNEL_MFMA):
+        for cd, L in (("f8", 3), ("f16", 1), ("bf16", 1)):
+            assert walk(C=1, H=H, W=W, s=2, L=L, cd=cd, kernel=kernel)[0] == sr.SR_KERNEL_MFMA
+    H, W = 3 * 7 * 11 * 331, 3 * 31 * 151
+    assert H * W == (1 << 30) - 1
+    for k in (3, 5):
+        for cd, L in (("f8", 4), ("f16", 2), ("bf16", 2)):
+            assert walk(C=1, H=H, W=W, s=3, L=L, k=k, cd=cd, kernel=sr.SR_KERNEL_MFMA)[1][0] == STRIPS
+    assert walk(C=1, H=1 << 15, W=1 << 15, s=2, L=1, cd="f8", kernel=sr.SR_KERNEL_MFMA)[0] == -3
