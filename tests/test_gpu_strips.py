@@ -1,7 +1,8 @@
 """The strip form of the matrix-core kernel where it can go wrong: strips that stick out of the image or end it on an odd
-column, every scale (three ways of grouping the columns), first and last rows, several segments per wavefront, every pixel
-group and coefficient type.  The sizes are large enough that the library takes strips (fewer rows on the fullest SIMD than
-tiles, or long segments).  Against the generic kernel, whose up-sampled values are the same bit for bit, so that only the
+column, every scale (three ways of grouping the columns), first and last rows, rings that turn, several segments per wavefront,
+every pixel group and coefficient type; and tiles of about the same sizes.  Which form a call takes depends on the rows
+of the fullest SIMD: the first tests take either (frames of about the sizes that change over), those named as_launched
+ask sr_dict_assemble_walk first.  Against the generic kernel, whose up-sampled values are the same bit for bit, so that only the
 order of fp32 sums and the 16-bit dictionary operands differ: 5e-5 * max(1, max|out|) and 2^-10 of it for an fp16 image,
 bfloat16 coefficients 1e-4 (dictionary of 16 significant bits); and the pixels at the borders against the oracle."""
 import numpy as np
@@ -21,33 +22,21 @@ def _need_gpu():
     sr.load()
 
 
-@pytest.mark.parametrize("n, c, h, w, scale, L, k, coeff, image, kept", [
-    (1, 3, 270, 480, 4, 72, 5, "f16", "f32", None),      # whole strips
-    (1, 3, 271, 473, 4, 72, 5, "f16", "f16", None),      # the last strip sticks out of the image
-    (1, 3, 300, 333, 3, 72, 5, "f8", "f32", None),       # rows that are no whole pixel groups: the last strip is moved left
-    (1, 3, 301, 501, 2, 72, 5, "f16", "f32", None),
-    (1, 3, 400, 43, 3, 72, 5, "f16", "f32", None),       # 129 columns: two strips, almost the same
-    (2, 3, 301, 501, 2, 72, 5, "f32", "f16", None),
-    (1, 1, 501, 301, 3, 72, 5, "f32", "f32", None),
-    (3, 3, 190, 250, 4, 72, 5, "f16", "f32", 8),         # kept lists: the forms with few planes
-    (1, 3, 333, 502, 3, 72, 5, "f8", "f32", 8),
-    (1, 3, 301, 502, 2, 72, 5, "bf16", "f32", 13),
-    (1, 1, 333, 401, 3, 72, 5, "bf16", "f32", None),
-    (1, 3, 250, 330, 4, 128, 5, "f16", "f32", None),     # two pixels per lane
-    (1, 3, 250, 331, 3, 128, 7, "f16", "f16", None),     # eight ring rows, groups before the image's first column
-    (1, 1, 251, 401, 2, 72, 7, "bf16", "f32", None),
-    (1, 3, 251, 401, 2, 72, 7, "f32", "f32", None),
-    (1, 3, 333, 401, 3, 40, 3, "f32", "f32", None),      # four ring rows
-    (1, 3, 333, 500, 2, 72, 3, "f8", "f16", None),
-    (1, 3, 251, 401, 4, 128, 3, "f16", "f32", 30),
-    (2300, 3, 4, 16, 2, 72, 5, "f16", "f32", None),      # more strips than wavefronts: several segments one after the other
-])
-def test_strips(oracle, n, c, h, w, scale, L, k, coeff, image, kept):
+def _assert_strips(walk, rows, segments):
+    """Strips, of segments of at least so many rows, and at least so many of them to a wavefront."""
+    kernel, (form, _, got, pieces, workgroups, waves) = walk
+    assert kernel == MFMA and form == 2 and got >= rows and pieces > (segments - 1) * workgroups * waves, walk
+
+
+def _check(oracle, n, c, h, w, scale, L, k, coeff, image, kept, strip_rows=0, segments=0):
     wl = sr_synth.Workload("strips", 60, n, c, h, w, scale, L, k, coeff, image)
     inp = sr_synth.make_inputs(wl, DEV)
     rng = np.random.default_rng(h)
     lst = None if kept is None else rng.permutation(L)[:kept].astype(np.int32)
     gamma = None if kept is None else rng.uniform(0.5, 1.5, size=kept).astype(np.float32)
+    if strip_rows:
+        out = torch.empty((n, c, wl.H, wl.W), device=DEV, dtype=inp["lr"].dtype)
+        _assert_strips(sr.sr_dict_assemble_walk(inp["lr"], inp["coeff"], inp["dict"], L, k, scale, c, out, kept=lst), strip_rows, segments)
     got = run_gpu(inp, wl, MFMA, lst, gamma).float()
     want = run_gpu(inp, wl, GENERIC, lst, gamma).float()
     assert torch.isfinite(got).all(), "some output pixel was never written"
@@ -62,17 +51,87 @@ def test_strips(oracle, n, c, h, w, scale, L, k, coeff, image, kept):
         assert_parity(have, ref, coeff, image == "f16", "borders")
 
 
-@pytest.mark.parametrize("h, w, scale, entries, image", [(270, 480, 4, 8, "f32"), (301, 500, 3, 5, "f16"), (270, 477, 4, 16, "f32"), (301, 500, 3, 13, "f32")])
-def test_strips_of_lists(h, w, scale, entries, image):
-    wl = sr_synth.Workload("strips", 61, 1, 3, h, w, scale, 72, 5, "f16", image)
+@pytest.mark.parametrize("n, c, h, w, scale, L, k, coeff, image, kept", [
+    (1, 3, 270, 480, 4, 72, 5, "f16", "f32", None),      # whole strips
+    (1, 3, 271, 473, 4, 72, 5, "f16", "f16", None),      # the last strip sticks out of the image
+    (1, 3, 300, 333, 3, 72, 5, "f8", "f32", None),       # rows that are no whole pixel groups: the last tile or strip is moved left
+    (1, 3, 301, 501, 2, 72, 5, "f16", "f32", None),
+    (1, 3, 400, 43, 3, 72, 5, "f16", "f32", None),       # 129 columns: two pieces, almost the same
+    (2, 3, 301, 501, 2, 72, 5, "f32", "f16", None),
+    (1, 1, 501, 301, 3, 72, 5, "f32", "f32", None),
+    (3, 3, 190, 250, 4, 72, 5, "f16", "f32", 8),         # kept lists: the forms with few planes
+    (1, 3, 333, 502, 3, 72, 5, "f8", "f32", 8),
+    (1, 3, 301, 502, 2, 72, 5, "bf16", "f32", 13),
+    (1, 1, 333, 401, 3, 72, 5, "bf16", "f32", None),
+    (1, 3, 250, 330, 4, 128, 5, "f16", "f32", None),     # two pixels per lane
+    (1, 3, 250, 331, 3, 128, 7, "f16", "f16", None),     # two matrix blocks per slot
+    (1, 1, 251, 401, 2, 72, 7, "bf16", "f32", None),
+    (1, 3, 251, 401, 2, 72, 7, "f32", "f32", None),
+    (1, 3, 333, 401, 3, 40, 3, "f32", "f32", None),
+    (1, 3, 333, 500, 2, 72, 3, "f8", "f16", None),
+    (1, 3, 251, 401, 4, 128, 3, "f16", "f32", 30),
+    (2300, 3, 4, 16, 2, 72, 5, "f16", "f32", None),      # more strips than wavefronts: several segments one after the other
+])
+def test_strips(oracle, n, c, h, w, scale, L, k, coeff, image, kept):
+    _check(oracle, n, c, h, w, scale, L, k, coeff, image, kept)
+
+
+# (strip_rows: more than the ring has slots, four, six or eight, so that it turns)
+@pytest.mark.parametrize("n, c, h, w, scale, L, k, coeff, image, kept, strip_rows, segments", [
+    (1, 3, 419, 257, 3, 128, 7, "f16", "f16", None, 9, 1),     # eight ring rows, groups before the image's first column; the last strip moved left
+    (1, 3, 292, 387, 3, 72, 7, "f32", "f32", None, 9, 1),
+    (1, 1, 540, 640, 2, 72, 7, "bf16", "f32", None, 9, 1),
+    (1, 3, 540, 641, 2, 72, 7, "f32", "f32", None, 9, 1),
+    (1, 3, 374, 161, 4, 72, 7, "f16", "f32", 12, 9, 1),
+    (1, 3, 305, 171, 3, 40, 3, "f32", "f32", None, 5, 1),      # four ring rows
+    (1, 3, 400, 640, 3, 72, 3, "f16", "f16", None, 5, 1),
+    (1, 3, 420, 403, 3, 72, 5, "f8", "f32", None, 7, 1),       # six; the last strip moved left
+    (1, 3, 413, 398, 3, 72, 5, "f16", "f32", None, 7, 1),
+    (1, 1, 375, 215, 3, 72, 5, "f32", "f16", None, 7, 1),
+    (1, 3, 1000, 513, 3, 72, 5, "f8", "f32", 8, 7, 1),
+    (1, 3, 540, 961, 2, 72, 5, "bf16", "f32", 13, 7, 1),
+    (1, 1, 400, 640, 3, 72, 5, "bf16", "f32", None, 7, 1),
+    (2435, 3, 2, 4, 3, 72, 5, "f16", "f32", None, 6, 2),       # several segments one after the other: every wavefront of the launch walks one, some two
+    (2213, 3, 2, 4, 3, 72, 5, "f32", "f32", None, 6, 2),
+    (2125, 3, 2, 5, 2, 72, 7, "f16", "f16", None, 4, 2),
+    (4200, 1, 2, 5, 2, 72, 5, "f32", "f32", None, 4, 3),
+    (3135, 3, 2, 3, 4, 72, 5, "f16", "f32", 8, 8, 2),          # few planes: their offsets in registers, three wavefronts per SIMD
+    (1030, 3, 2, 33, 4, 72, 5, "f8", "f32", None, 8, 2),       # two strips to an image
+])
+def test_strips_as_launched(oracle, n, c, h, w, scale, L, k, coeff, image, kept, strip_rows, segments):
+    _check(oracle, n, c, h, w, scale, L, k, coeff, image, kept, strip_rows, segments)
+
+
+def _check_list(n, h, w, scale, entries, image, strip_rows=0, segments=0):
+    wl = sr_synth.Workload("strips", 61, n, 3, h, w, scale, 72, 5, "f16", image)
     inp = sr_synth.make_inputs(wl, DEV)
     index, value = sr_synth.to_list(inp["coeff"], entries)
-    out = [torch.full((1, 3, wl.H, wl.W), float("nan"), device=DEV, dtype=inp["lr"].dtype) for _ in range(2)]
+    out = [torch.full((n, 3, wl.H, wl.W), float("nan"), device=DEV, dtype=inp["lr"].dtype) for _ in range(2)]
+    if strip_rows:
+        _assert_strips(sr.sr_dict_assemble_list_walk(inp["lr"], index, value, inp["dict"], 72, 5, scale, 3, entries, out[0]), strip_rows, segments)
     for o, kernel in zip(out, (MFMA, GENERIC)):
         sr.sr_dict_assemble_list_ex(inp["lr"], index, value, inp["dict"], 72, 5, scale, 3, entries, o, kernel=kernel)
     got, want = out[0].float(), out[1].float()
     assert torch.isfinite(got).all()
     assert float((got - want).abs().max()) <= (5e-5 + (2.0 ** -10 if image == "f16" else 0.0)) * max(1.0, float(want.abs().max()))
+
+
+@pytest.mark.parametrize("h, w, scale, entries, image", [(270, 480, 4, 8, "f32"), (301, 500, 3, 5, "f16"), (270, 477, 4, 16, "f32"), (301, 500, 3, 13, "f32")])
+def test_strips_of_lists(h, w, scale, entries, image):
+    _check_list(1, h, w, scale, entries, image)
+
+
+@pytest.mark.parametrize("n, h, w, scale, entries, image, strip_rows, segments", [
+    (1, 600, 800, 3, 8, "f32", 7, 1),
+    (1, 601, 796, 3, 13, "f16", 7, 1),
+    (2343, 2, 4, 3, 5, "f32", 6, 2),            # the register sets change hands between segments: an even and an odd number of rows
+    (2400, 3, 4, 3, 13, "f32", 9, 2),
+    (2251, 2, 3, 4, 8, "f16", 8, 2),
+    (1030, 3, 34, 4, 16, "f32", 12, 2),
+    (6200, 3, 4, 3, 8, "f32", 9, 3),
+])
+def test_strips_of_lists_as_launched(n, h, w, scale, entries, image, strip_rows, segments):
+    _check_list(n, h, w, scale, entries, image, strip_rows, segments)
 
 
 @pytest.mark.parametrize("h, w, scale, coeff", [(271, 473, 4, "f16"), (301, 501, 2, "bf16"), (333, 400, 3, "f16")])
