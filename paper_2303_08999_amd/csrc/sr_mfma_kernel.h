@@ -85,7 +85,9 @@
 // Measurement builds (python -m paper_2303_08999_amd.build -o other.so -DSR_ABLATE_...): the
 // same launch with a part switched off, to see what that part costs.  SR_ABLATE_STORES keeps
 // every instruction but never executes the output stores; SR_ABLATE_STAGE1 skips the two
-// up-sampling passes (their barriers stay); results are then wrong by construction.
+// up-sampling passes (barriers and LR rows stay); results are then wrong by construction.
+// SR_STORES_WRITE_THROUGH writes the fp32 output of the four-pixel instantiations through the L2
+// (agent scope) instead of leaving dirty lines in it; results are unchanged.
 // The library built by default contains none of them.
 #pragma once
 #include <type_traits>
@@ -301,6 +303,14 @@ __device__ __forceinline__ void store16(__amdgpu_buffer_rsrc_t r, unsigned at, f
 __device__ __forceinline__ void store32(__amdgpu_buffer_rsrc_t r, unsigned at, unsigned v) { __builtin_amdgcn_raw_buffer_store_b32(v, r, at, 0, 0); }
 __device__ __forceinline__ void store64(__amdgpu_buffer_rsrc_t r, unsigned at, unsigned v0, unsigned v1) {
     __builtin_amdgcn_raw_buffer_store_b64(u32x2{v0, v1}, r, at, 0, 0);
+}
+#ifdef SR_STORES_WRITE_THROUGH
+constexpr int FP32_PAIR_POLICY = 16;                    // sc1: agent scope
+#else
+constexpr int FP32_PAIR_POLICY = 0;
+#endif
+__device__ __forceinline__ void store_fp32_pair(__amdgpu_buffer_rsrc_t r, unsigned at, float v0, float v1) {
+    __builtin_amdgcn_raw_buffer_store_b64(u32x2{__float_as_uint(v0), __float_as_uint(v1)}, r, at, 0, FP32_PAIR_POLICY);
 }
 __device__ __forceinline__ void store128(__amdgpu_buffer_rsrc_t r, unsigned at, const float (&v)[4]) {
     __builtin_amdgcn_raw_buffer_store_b128(u32x4{__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])}, r, at, 0, 0);
@@ -865,6 +875,9 @@ void k_assemble_mfma(const AssembleArgs a) {
             strip_load(f + 3, spre, io_f16);
             strip_fence();
         }
+#ifdef SR_ABLATE_STAGE1
+        if (a.N >= 0) return;
+#endif
         constexpr int PH = STRIP == 3 ? 0 : (F::R / S_ + 1) * S_ - F::R;     // a column with the phase of a group's first
         constexpr int NV = 4 + (F::GPX - 1 + S_ - 1) / S_;                   // (at most that many LR columns)
         float v[F::GIT][NV], r[LIT][4];
@@ -1108,10 +1121,10 @@ void k_assemble_mfma(const AssembleArgs a) {
     unsigned long long wb_last = a.wb_ticks > 0 ? __builtin_amdgcn_s_memrealtime() : 0ull;
     // A unit: stage 3, stage 4 and the store of WR rows of WC * PX pixels; `more_tiles`: the unit after the tile's last is unit 0 of `nxt`.
     // (slot0: strip form, ring slot of the first filter row; more_tiles and io_f16: booleans, or the types of known ones)
-    auto do_unit = [&](const int unit, const TilePos cur, const TilePos nxt, const auto more_tiles, const int tid, const int slot0, const auto io_f16) __attribute__((always_inline)) {
+    auto do_unit = [&](const int unit, const TilePos here, const TilePos nxt, const auto more_tiles, const int tid, const int slot0, const auto io_f16) __attribute__((always_inline)) {
         const int lane = tid & 63;
         const int hf = lane >> 5, j = lane & 31, jr = j / F::WC, jc = j % F::WC;
-        const int Y0 = cur.ty * F::TH, X0 = tile_x0(cur.tx);
+        const int Y0 = here.ty * F::TH, X0 = tile_x0(here.tx);
         const unsigned* pt = ptab + hf * F::NLOAD;
         const bool last_unit = STRIP || unit == NU - 1;
         const bool more = last_unit ? (bool)more_tiles : true;
@@ -1120,12 +1133,12 @@ void k_assemble_mfma(const AssembleArgs a) {
         if constexpr (STRIP != 0 && !BLK) {
             pix_next[0] = spix;
             cnext = snext;
-        } else if constexpr (!LIST && !PMAJ && !BLK) cnext = last_unit ? phi_base(nxt, 0, jr, jc, pix_next) : phi_base(cur, unit + 1, jr, jc, pix_next);
+        } else if constexpr (!LIST && !PMAJ && !BLK) cnext = last_unit ? phi_base(nxt, 0, jr, jc, pix_next) : phi_base(here, unit + 1, jr, jc, pix_next);
         const char* bimg = nullptr;                    // blocked: the next unit's image and offset
         unsigned boff = 0u;
         if constexpr (BLK) {
-            bimg = last_unit ? pm_image(nxt) : pm_image(cur);
-            boff = last_unit ? blk_offset(nxt, 0) : blk_offset(cur, unit + 1);
+            bimg = last_unit ? pm_image(nxt) : pm_image(here);
+            boff = last_unit ? blk_offset(nxt, 0) : blk_offset(here, unit + 1);
         }
 
         // (3) stage 3 on the matrix cores: atom steps outer, pixel slots inner
@@ -1141,7 +1154,7 @@ void k_assemble_mfma(const AssembleArgs a) {
             if (more) {
                 if constexpr (STRIP != 0) load_list_at(slist, spix, hf, lval[(unit + 1) & 1], lidx[(unit + 1) & 1]);
                 else if (last_unit) load_list(nxt, 0, jc, hf, lval[(unit + 1) & 1], lidx[(unit + 1) & 1]);
-                else load_list(cur, unit + 1, jc, hf, lval[(unit + 1) & 1], lidx[(unit + 1) & 1]);
+                else load_list(here, unit + 1, jc, hf, lval[(unit + 1) & 1], lidx[(unit + 1) & 1]);
             }
             const u32x2 (&val)[LH] = lval[unit & 1];
             const unsigned (&idx)[LH] = lidx[unit & 1];
@@ -1194,8 +1207,8 @@ void k_assemble_mfma(const AssembleArgs a) {
         }
         if constexpr (PMAJ) {
             static_assert(NMB == 1 || !PMAJ, "pixel-major: one block of MFMA rows");
-            const char* nimg = last_unit ? pm_image(nxt) : pm_image(cur);
-            const unsigned noff = last_unit ? pm_offset(nxt, 0, lane) : pm_offset(cur, unit + 1, lane);
+            const char* nimg = last_unit ? pm_image(nxt) : pm_image(here);
+            const unsigned noff = last_unit ? pm_offset(nxt, 0, lane) : pm_offset(here, unit + 1, lane);
             char* const scr = (char*)(pmscr + wave * 288);
             const char* const mine = scr + jc * (16 * NP8);            // the lane's pixel of the slot
             auto reload = [&](int i) {
@@ -1531,7 +1544,7 @@ void k_assemble_mfma(const AssembleArgs a) {
                           : PSM == 3 ? (unsigned)y * (unsigned)a.W + x + hf * 6
                           : PERM ? (unsigned)y * (unsigned)a.W + x + hf * (2 * PSM) + (PSM == 4 ? 4 : 2) * (jc % 2)
                           : STRIP ? so0 : (unsigned)y * (unsigned)a.W + x + hf * (PX / 2);   // within the image
-        char* const out_img = STRIP ? sout : (char*)a.out + (size_t)cur.n * C * ((size_t)plane_px * (a.io_f16 ? 2 : 4));
+        char* const out_img = STRIP ? sout : (char*)a.out + (size_t)here.n * C * ((size_t)plane_px * (a.io_f16 ? 2 : 4));
         // Every lane stores, one outside the image at the end of the buffer, which drops it.  Behind a branch the compiler cannot
         // count the stores, and the next unit's fold, which waits for loads issued before them, waits for them as well.
         // 512 x 512 x4: 14.1 -> 13.3 us; no different where a unit is long.
@@ -1614,7 +1627,7 @@ void k_assemble_mfma(const AssembleArgs a) {
                 }
             } else if constexpr (PX == 4) {
                 if (a.io_f16) store32(out_rsrc, out_at(oe, 2u), pack_f16(tot[0], tot[1]));
-                else store64(out_rsrc, out_at(oe, 4u), __float_as_uint(tot[0]), __float_as_uint(tot[1]));
+                else store_fp32_pair(out_rsrc, out_at(oe, 4u), tot[0], tot[1]);
             } else {
                 static_assert(PX == 2, "two or four pixels per lane");
                 if (a.io_f16) store16(out_rsrc, out_at(oe, 2u), tot[0]);
