@@ -1549,11 +1549,14 @@ void k_assemble_mfma(const AssembleArgs a) {
         // count the stores, and the next unit's fold, which waits for loads issued before them, waits for them as well.
         // 512 x 512 x4: 14.1 -> 13.3 us; no different where a unit is long.
         const unsigned out_bytes = C * plane_px * (a.io_f16 ? 2u : 4u);
+        // (images of the forms with PSM >= 2 are multiples of 192 bytes or more: none ends in the last 64 bytes below 4 GB, and the constant
+        //  saves a scalar register there: 1080p logits before the pixel-shuffle 80.4 -> 80.0 us)
+        const unsigned beyond = PSM >= 2 ? 0xffffffc0u : out_bytes;
         const __amdgpu_buffer_rsrc_t out_rsrc = __builtin_amdgcn_make_buffer_rsrc(out_img, 0, (int)out_bytes, RAW_BUFFER);
 #ifdef SR_ABLATE_STORES
-        auto out_at = [&](unsigned e, unsigned size) -> unsigned { return valid && a.N < 0 ? e * size : out_bytes; };   // (never true)
+        auto out_at = [&](unsigned e, unsigned size) -> unsigned { return valid && a.N < 0 ? e * size : beyond; };   // (never true)
 #else
-        auto out_at = [&](unsigned e, unsigned size) -> unsigned { return valid ? e * size : out_bytes; };
+        auto out_at = [&](unsigned e, unsigned size) -> unsigned { return valid ? e * size : beyond; };
 #endif
 #pragma unroll
         for (int c = 0; c < C; ++c) {
@@ -1888,12 +1891,12 @@ hipError_t launch_one(const AssembleArgs& a0, const LaunchTo& st) {
 //   in the L2, 128 atoms 1536 x 2040 x3 262 -> 215 us, but whole lines 4K 239 -> 278).  Strips have to save 8 % of the rows.
 //   Scale 3, tiles of at most two rows per SIMD: a segment of one row up-samples K + 1 rows for it, one after the other; and the same
 //   with up to three rows where a row is cheap to fold (one channel, few atoms, two pixels per lane) and strips save at most a quarter of them.
-// Measured, both forms in one run (us, tiles / strips; profiles/strips_or_tiles.txt):
-//   fewer rows: 720p fp8 x4 34.4 / 25.0, 540 x 960 x2 fp16 28.8 / 23.5, 480 x 640 x2 fp32 33.0 / 28.0, 1080p x4 fp16 69.8 / 62.2
-//   about the same: 4K x4, 8 atoms 82.7 / 63.9, 1080p x2 fp16 66.2 / 64.8, 4K x3 fp16 246.9 / 244.2, but 1080p x3 fp16 64.9 / 67.0 (segments of 8 rows)
-//   rows that share lines: 1536 x 2040 x2 fp16 116.6 / 130.5, x3 with 7x7 atoms and one channel 116.4 / 141.4, 4K less 24 columns x4 fp16 284.4 / 307.3;
-//   not refused: 1200 x 1608 x4 83.5 / 70.7 (92 % of the lanes), 1536 x 2040 x4 with 30 atoms 61.3 / 61.5, 900 x 1600 x2 fp8 with 45 atoms 35.0 / 28.8
-//   segments of one row: 8 atoms, 240 x 312 x3 9.1 / 10.5, but 144 x 192 x2 9.1 / 8.7; of three: one channel, fp32, 8 atoms, 444 x 714 x3 10.1 / 10.8
+// Measured, both forms in one run (us, tiles / strips; profiles/strips_or_tiles.txt has them and more):
+//   fewer rows: 720p fp8 x4 34.2 / 24.8, 540 x 960 x2 fp16 29.1 / 23.9, 480 x 640 x2 fp32 33.3 / 28.5, 1080p x4 fp16 70.5 / 63.2
+//   about the same: 4K x4, 8 atoms 80.2 / 62.7, 1080p x2 fp16 66.4 / 65.5, 4K x3 fp16 246.1 / 244.2, but 1080p x3 fp16 64.7 / 67.2 (segments of 8 rows)
+//   rows that share lines: 1536 x 2040 x2 fp16 119.4 / 132.6, x3 with 7x7 atoms and one channel 119.8 / 144.3, 4K less 24 columns x4 fp16 287.8 / 308.8;
+//   not refused: 1200 x 1608 x4 85.2 / 71.5 (92 % of the lanes), 1536 x 2040 x4 with 30 atoms 62.0 / 62.1, 900 x 1600 x2 fp8 with 45 atoms 34.5 / 28.7
+//   segments of one row: 8 atoms, 240 x 312 x3 9.1 / 10.5, but 144 x 192 x2 9.1 / 8.7; of three: one channel, fp32, 8 atoms, 444 x 714 x3 10.2 / 11.2
 inline bool strip_form(const AssembleArgs& a, int np8, int sw, int tw, int th, int wpe = 2) {
     if ((long long)a.C * a.H * a.W == (1ll << 30) - 1) return true;         // see the stores
     if (a.W == sw + 1) return false;                    // the moved last strip would start at column 1 and look over the left edge with R = 2
