@@ -60,7 +60,7 @@ def empirical_ceilings(sr, torch, wl, coeffs, outs, kernel_ms, inp_lr, inp_dict)
     t_read = timed(lambda i: sr.sr_probe_read(coeffs[i % len(coeffs)][0], sink))
     t_mix = timed(lambda i: sr.sr_probe_mix(coeffs[i % len(coeffs)][0], wl.L, px, outs[i % 2][0], wl.c)) if eb == 2 else None
     mix_bytes = coeff_bytes + wl.c * px * 4
-    # the same requests in the kernel's own order: its tiles (height reported by the library, 16 where it reports none),
+    # the same requests in the order of the kernel's tile form: its tiles (height reported by the library, 16 where it reports none),
     # its split of the tiles over the XCDs, its rows per wavefront
     t_tiled = None
     if wl.W % 128 == 0:
@@ -85,8 +85,8 @@ def empirical_ceilings(sr, torch, wl, coeffs, outs, kernel_ms, inp_lr, inp_dict)
             "independent_mix_GBps": round(mix_bytes / t_stream / 1e6, 1), "independent_mix_ms": round(t_stream, 4),
             "kernel_time_over_independent_mix_time": round(kernel_ms * 1.0 / (t_stream * wl.n), 3),
             "note": "streaming probes of the same library on one frame's coefficient planes: read-only; the kernel's "
-                    "own read + write pattern with no arithmetic, run by run (mix) and in the kernel's own tile order (tiled_mix: what is "
-                    "left of the kernel when only its memory requests remain; tiled_mix_paced: with the kernel's L2 write-back "
+                    "own read + write pattern with no arithmetic, run by run (mix) and in the order of its tile form (tiled_mix: what is "
+                    "left of that form when only its memory requests remain, a call in strips asks in another order; tiled_mix_paced: with the kernel's L2 write-back "
                     "pacing, every 16 us, among them); and the same bytes with 16-byte accesses by "
                     "separate reader and writer workgroups (independent_mix), whose writers finish before its readers, so "
                     "that part of the reading runs undisturbed"}
