@@ -86,8 +86,8 @@ def empirical_ceilings(sr, torch, wl, coeffs, outs, kernel_ms, inp_lr, inp_dict)
             "kernel_time_over_independent_mix_time": round(kernel_ms * 1.0 / (t_stream * wl.n), 3),
             "note": "streaming probes of the same library on one frame's coefficient planes: read-only; the kernel's "
                     "own read + write pattern with no arithmetic, run by run (mix) and in the order of its tile form (tiled_mix: what is "
-                    "left of that form when only its memory requests remain, a call in strips asks in another order; tiled_mix_paced: with the kernel's L2 write-back "
-                    "pacing, every 16 us, among them); and the same bytes with 16-byte accesses by "
+                    "left of that form when only its memory requests remain, a call in strips asks in another order; "
+                    "tiled_mix_paced: with the kernel's L2 write-back pacing, every 16 us, among them); and the same bytes with 16-byte accesses by "
                     "separate reader and writer workgroups (independent_mix), whose writers finish before its readers, so "
                     "that part of the reading runs undisturbed"}
 

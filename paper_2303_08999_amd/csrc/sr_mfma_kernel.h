@@ -1121,7 +1121,8 @@ void k_assemble_mfma(const AssembleArgs a) {
     unsigned long long wb_last = a.wb_ticks > 0 ? __builtin_amdgcn_s_memrealtime() : 0ull;
     // A unit: stage 3, stage 4 and the store of WR rows of WC * PX pixels; `more_tiles`: the unit after the tile's last is unit 0 of `nxt`.
     // (slot0: strip form, ring slot of the first filter row; more_tiles and io_f16: booleans, or the types of known ones)
-    auto do_unit = [&](const int unit, const TilePos here, const TilePos nxt, const auto more_tiles, const int tid, const int slot0, const auto io_f16) __attribute__((always_inline)) {
+    auto do_unit = [&](const int unit, const TilePos here, const TilePos nxt, const auto more_tiles, const int tid, const int slot0,
+                       const auto io_f16) __attribute__((always_inline)) {
         const int lane = tid & 63;
         const int hf = lane >> 5, j = lane & 31, jr = j / F::WC, jc = j % F::WC;
         const int Y0 = here.ty * F::TH, X0 = tile_x0(here.tx);
@@ -1880,23 +1881,31 @@ hipError_t launch_one(const AssembleArgs& a0, const LaunchTo& st) {
 // Whether a call goes to the strip form (strips of `sw` columns) where it is built next to tiles of tw x th pixels in
 // workgroups of four wavefronts: the form that leaves the fullest SIMD with fewer rows; at about the same number the strips,
 // which up-sample no row twice, once a segment is long enough to pay for its own first rows (scale 3: dearer rows).
-// One column more than a strip is left to the tiles: its last strip would start at column 1 and see column -1, which the kernel continues
-// for strips that start at column 0 only (continuing it there for all cost the light forms 1 % at every size).
-// np8: capacity of the instantiation in groups of 8 atoms, 0 where the coefficient stream is not the bound (lists; fp32 with 7x7 atoms).
+// One column more than a strip is left to the tiles: its last strip would start at column 1 and see column -1, which the kernel
+// continues for strips that start at column 0 only (continuing it there for all cost the light forms 1 % at every size).
+// np8: capacity of the instantiation in groups of 8 atoms, 0 where the coefficient stream is not the bound (lists; fp32 with
+// 7x7 atoms).
 // Two cases in which strips are refused although the rows speak for them:
-//   Rows that start on no multiple of 64 bytes, where the stream is the bound: instantiations for 48 atoms and more (one channel: 32) filled to 97 % (90 %),
-//   more coefficients than the 256 MB memory-side cache can hold beside the rest (one channel, which has half the other work to hide a miss
-//   behind: half of it), and work for 94 % of the resident lanes.  Neighbouring pieces of a row then share lines.  Tiles side by side ask for them at
-//   about the same time; wavefronts that walk strips drift apart, the loads are streaming ones, and the line comes from memory twice (with loads that stay
-//   in the L2, 128 atoms 1536 x 2040 x3 262 -> 215 us, but whole lines 4K 239 -> 278).  Strips have to save 8 % of the rows.
-//   Scale 3, tiles of at most two rows per SIMD: a segment of one row up-samples K + 1 rows for it, one after the other; and the same
-//   with up to three rows where a row is cheap to fold (one channel, few atoms, two pixels per lane) and strips save at most a quarter of them.
+//   Rows that start on no multiple of 64 bytes, where the stream is the bound: instantiations for 48 atoms and more (one
+//   channel: 32) filled to 97 % (90 %), more coefficients than the 256 MB memory-side cache can hold beside the rest (one
+//   channel, which has half the other work to hide a miss behind: half of it), and work for 94 % of the resident lanes (128 atoms: 85 %).
+//   Neighbouring pieces of a row then share lines.  Tiles side by side ask for them at about the same time; wavefronts that
+//   walk strips drift apart, the loads are streaming ones, and the line comes from memory twice (with loads that stay in the
+//   L2, 128 atoms 1536 x 2040 x3 263 -> 215 us, but whole lines 4K 239 -> 278).  Strips have to save 8 % of the rows.
+//   Scale 3, tiles of at most two rows per SIMD: a segment of one row up-samples K + 1 rows for it, one after the other; and
+//   the same with up to three rows where a row is cheap to fold (one channel, few atoms, two pixels per lane) and strips save
+//   at most a quarter of them.
 // Measured, both forms in one run (us, tiles / strips; profiles/strips_or_tiles.txt has them and more):
-//   fewer rows: 720p fp8 x4 34.2 / 24.8, 540 x 960 x2 fp16 29.1 / 23.9, 480 x 640 x2 fp32 33.3 / 28.5, 1080p x4 fp16 70.5 / 63.2
-//   about the same: 4K x4, 8 atoms 80.2 / 62.7, 1080p x2 fp16 66.4 / 65.5, 4K x3 fp16 246.1 / 244.2, but 1080p x3 fp16 64.7 / 67.2 (segments of 8 rows)
-//   rows that share lines: 1536 x 2040 x2 fp16 119.4 / 132.6, x3 with 7x7 atoms and one channel 119.8 / 144.3, 4K less 24 columns x4 fp16 287.8 / 308.8;
-//   not refused: 1200 x 1608 x4 85.2 / 71.5 (92 % of the lanes), 1536 x 2040 x4 with 30 atoms 62.0 / 62.1, 900 x 1600 x2 fp8 with 45 atoms 34.5 / 28.7
-//   segments of one row: 8 atoms, 240 x 312 x3 9.1 / 10.5, but 144 x 192 x2 9.1 / 8.7; of three: one channel, fp32, 8 atoms, 444 x 714 x3 10.2 / 11.2
+//   fewer rows: 720p fp8 x4 34.2 / 24.8, 540 x 960 x2 fp16 29.1 / 23.9, 480 x 640 x2 fp32 33.3 / 28.5, 1080p x4 fp16 70.5 /
+//   63.2
+//   about the same: 4K x4, 8 atoms 80.2 / 62.7, 1080p x2 fp16 66.4 / 65.5, 4K x3 fp16 246.1 / 244.2, but 1080p x3 fp16 64.7 /
+//   67.2 (segments of 8 rows)
+//   rows that share lines: 1536 x 2040 x2 fp16 119.4 / 132.6, x3 with 7x7 atoms and one channel 119.8 / 144.3, 4K less 24
+//   columns x4 fp16 287.8 / 308.8;
+//   not refused: 1200 x 1608 x4 85.2 / 71.5 (92 % of the lanes), 1536 x 2040 x4 with 30 atoms 62.0 / 62.1, 900 x 1600 x2 fp8
+//   with 45 atoms 34.5 / 28.7
+//   segments of one row: 8 atoms, 240 x 312 x3 9.1 / 10.5, but 144 x 192 x2 9.1 / 8.7; of three: one channel, fp32, 8 atoms,
+//   444 x 714 x3 10.2 / 11.2
 inline bool strip_form(const AssembleArgs& a, int np8, int sw, int tw, int th, int wpe = 2) {
     if ((long long)a.C * a.H * a.W == (1ll << 30) - 1) return true;         // see the stores
     if (a.W == sw + 1) return false;                    // the moved last strip would start at column 1 and look over the left edge with R = 2

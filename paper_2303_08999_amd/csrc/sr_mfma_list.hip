@@ -16,9 +16,10 @@ bool mfma_list_supported(const AssembleArgs& a, int k, bool value_f16) {
 // Up to 72 atoms: the dense form's operand steps (four of 16 atoms and one of 8); scale 4 in strips, scale 3 in strips or 128 x 8
 // tiles, scale 2 in 128 x 8 tiles.  Up to 128: eight steps, 128 x 8 tiles at every scale (35 KB of scatter scratch).  Lists of up to 8
 // entries keep half the registers.
-// Scale 4 in one run of three forms, lists of 8 (us, 128 x 16 tiles with the scale-4 footprint / 128 x 8 / strips): 240 x 320 15.4 / - / 9.3,
-// 480 x 640 16.3 / 14.4 / 13.7, 720 x 1280 22.0 / 25.4 / 21.1, 800 x 1200 22.7 / 25.5 / 21.4, 4K 142.2 / - / 107.5, 32 images of 128 x 192 21.5 / 24.8 / 21.0;
-// no size was found where tiles are faster, also not where strips leave the fullest SIMD as many rows.
+// Scale 4 in one run of three forms, lists of 8 (us, 128 x 16 tiles with the scale-4 footprint / 128 x 8 / strips):
+// 240 x 320 15.4 / - / 9.3, 480 x 640 16.3 / 14.4 / 13.7, 720 x 1280 22.0 / 25.4 / 21.1, 800 x 1200 22.7 / 25.5 /
+// 21.4, 4K 142.2 / - / 107.5, 32 images of 128 x 192 21.5 / 24.8 / 21.0; no size was found where tiles are faster,
+// also not where strips leave the fullest SIMD as many rows.
 template <int CT>
 static hipError_t launch_ct(const AssembleArgs& a, const LaunchTo& st) {
     if (a.L <= 72) {
