@@ -293,8 +293,8 @@ __device__ __forceinline__ _Float16 __attribute__((ext_vector_type(2))) pk_max_f
 }
 
 // Output stores through a raw buffer resource of the image (fourth word: 32-bit data format), whose bounds check drops a lane
-// at the end of the image or beyond.  Such a lane stores up to eight bytes (sixteen at scale 4, whose images are multiples of 64) from the
-// end on, and all of them have 32-bit offsets: every image below 4 GB, but fp32 ones of 2^30 - 1 pixels, whose pixel groups go in strips (see
+// at the end of the image or beyond.  Such a lane stores up to eight bytes from the end on (or sixteen 64 bytes below 4 GB), and all of
+// them have 32-bit offsets: every image below 4 GB, but fp32 ones of 2^30 - 1 pixels, whose pixel groups go in strips (see
 // strip_form), where every lane is inside the image.
 constexpr int RAW_BUFFER = 0x00020000;
 __device__ __forceinline__ void store16(__amdgpu_buffer_rsrc_t r, unsigned at, float v) {
@@ -1550,9 +1550,11 @@ void k_assemble_mfma(const AssembleArgs a) {
         // count the stores, and the next unit's fold, which waits for loads issued before them, waits for them as well.
         // 512 x 512 x4: 14.1 -> 13.3 us; no different where a unit is long.
         const unsigned out_bytes = C * plane_px * (a.io_f16 ? 2u : 4u);
-        // (images of the forms with PSM >= 2 are multiples of 192 bytes or more: none ends in the last 64 bytes below 4 GB, and the constant
-        //  saves a scalar register there: 1080p logits before the pixel-shuffle 80.4 -> 80.0 us)
-        const unsigned beyond = PSM >= 2 ? 0xffffffc0u : out_bytes;
+        // (where no image can end in the last 64 bytes below 4 GB - scale 4, three channels at scale 3, lists and the forms with PSM >= 2, whose
+        //  images are multiples of 64, 108, 96 and 192 bytes - a constant, which saves a scalar register: 1080p logits before the
+        //  pixel-shuffle 80.4 -> 80.0 us)
+        constexpr bool EVEN_END = LIST || PSM >= 2 || SMIN == 4 || (SMIN == 3 && C == 3);
+        const unsigned beyond = EVEN_END ? 0xffffffc0u : out_bytes;
         const __amdgpu_buffer_rsrc_t out_rsrc = __builtin_amdgcn_make_buffer_rsrc(out_img, 0, (int)out_bytes, RAW_BUFFER);
 #ifdef SR_ABLATE_STORES
         auto out_at = [&](unsigned e, unsigned size) -> unsigned { return valid && a.N < 0 ? e * size : beyond; };   // (never true)
