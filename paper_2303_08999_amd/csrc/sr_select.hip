@@ -13,10 +13,11 @@
 // each workgroup leaves its partial sums in the caller's scratch and a second kernel
 // adds them in a fixed order.
 //
-// Two forms of the first kernel.  k_atom_gram_rows (lattice strides up to 4): runs
+// Three forms of the first kernel.  k_atom_gram_tri (up to 79 atoms): every wavefront forms responses and contracts them
+// in its own registers.  k_atom_gram_rows (more atoms, lattice strides up to 4): runs
 // are segments of one lattice row, eight wavefronts per workgroup split into four
 // that form responses (their dot products on the matrix cores too) and four that
-// contract, all global loads coalesced and parked in LDS.  k_atom_gram (any stride):
+// contract, all global loads coalesced and parked in LDS.  k_atom_gram (what is left):
 // runs are 64 consecutive samples in lattice order, one thread per sample gathers
 // its neighbourhood, the dictionary row comes through scalar loads, and the same
 // four wavefronts form the responses and contract them.
@@ -27,6 +28,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/sr_select.h"
@@ -59,6 +61,17 @@ __device__ __forceinline__ float widen(__half v) { return __half2float(v); }
 __device__ __forceinline__ float widen(e4m3 v) { return __builtin_amdgcn_cvt_f32_fp8((int)v.bits, 0); }
 struct bf16v { unsigned short bits; };      // bfloat16 storage: the upper half of a binary32
 __device__ __forceinline__ float widen(bf16v v) { return __uint_as_float((unsigned)v.bits << 16); }
+// a coefficient as stored (loaded as an integer, which a load widens by itself), and back
+template <int BYTES> struct BitsOf;
+template <> struct BitsOf<4> { typedef unsigned type; };
+template <> struct BitsOf<2> { typedef unsigned short type; };
+template <> struct BitsOf<1> { typedef unsigned char type; };
+template <typename TC>
+__device__ __forceinline__ TC from_bits(unsigned b) {
+    if constexpr (sizeof(TC) == 4) return __builtin_bit_cast(TC, b);
+    else if constexpr (sizeof(TC) == 2) return __builtin_bit_cast(TC, (unsigned short)b);
+    else return __builtin_bit_cast(TC, (unsigned char)b);
+}
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
 // q-th block of the upper triangle of an n x n block matrix, row-major: (bi, bj) with bi <= bj
@@ -69,19 +82,18 @@ __device__ __forceinline__ void block_of(int q, int n, int& bi, int& bj) {
     bj = r + (q - start);
 }
 
-// N16: 16-column blocks the LDS tile has room for (2, 5 or 9; the frame's own count
-// a.n16 may be smaller: the columns beyond it are computed as zeros and never read).
-// Up to 5 blocks there are two LDS tiles, so that one barrier per run and channel is
-// enough.  The response loop has no branches: atoms past L read the last dictionary
+// N16: 16-column blocks the LDS tile has room for (9; the frame's own count a.n16 may be smaller: the columns beyond it are
+// computed as zeros and never read).
+// The response loop has no branches: atoms past L read the last dictionary
 // row with a zero coefficient, so the scalar loads of one atom's row overlap the
 // multiply-adds of the one before.
 template <int K, typename TC, int N16>
-__global__ __launch_bounds__(NT, (N16 <= 5 && K <= 5) ? 2 : 1) void k_atom_gram(const GramArgs a) {
+__global__ __launch_bounds__(NT, 1) void k_atom_gram(const GramArgs a) {
     constexpr int KK = K * K, R = (K - 1) / 2;
-    constexpr int NTW = N16 == 2 ? 1 : (N16 == 5 ? 4 : 12);     // blocks per wavefront
-    constexpr int NBUF = N16 <= 5 ? 2 : 1;
+    constexpr int NTW = 12;                           // blocks per wavefront
+    static_assert(N16 * (N16 + 1) / 2 <= 4 * NTW, "every block has its wavefront");
     constexpr int NPHI = N16 * 4;                     // columns per thread (one wavefront takes every fourth)
-    __shared__ float tile[NBUF][N16 * 16 * TSS];
+    __shared__ float T[N16 * 16 * TSS];
 
     const int tid = threadIdx.x, si = tid & 63, c16 = tid & 15, kq = (tid >> 4) & 3;
     const int g = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -166,10 +178,9 @@ __global__ __launch_bounds__(NT, (N16 <= 5 && K <= 5) ? 2 : 1) void k_atom_gram(
         hval_n = 0.0f;
 #pragma unroll
         for (int j = 0; j < KK; ++j) patch_n[j] = 0.0f;
-        int c = 0, buf = 0;
+        int c = 0;
         for (;;) {
             // (1) responses of every atom at this thread's sample, plus the target column
-            float* T = tile[buf];
             // (the dictionary row of the next atom is requested before the multiply-adds
             // of this one: scalar loads return out of order, so a wait is always for all
             // of them, and the scheduling fences keep the request one atom ahead)
@@ -237,8 +248,7 @@ __global__ __launch_bounds__(NT, (N16 <= 5 && K <= 5) ? 2 : 1) void k_atom_gram(
             for (int t = 0; t < NTW; ++t)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) dacc[t][e] += (double)acc[t][e];
-            if (NBUF == 1) __syncthreads();
-            else buf ^= 1;
+            __syncthreads();
             if (!more) break;
             if (c_n == 0) {
                 smp = smp_n;
@@ -262,8 +272,337 @@ __global__ __launch_bounds__(NT, (N16 <= 5 && K <= 5) ? 2 : 1) void k_atom_gram(
 }
 
 // ---------------------------------------------------------------------------
-// Second form of the kernel, for lattice strides up to 4 (every pixel down to every
-// fourth): workgroups of eight wavefronts, one or two per CU.  Four wavefronts form the
+// Up to 79 atoms (five 16-column blocks; the paper's 72 among them): every wavefront forms the whole upper
+// triangle for samples of its own, in registers.
+//
+// Bound: the fp32 matrix instructions.  Of an item (16 samples of one lattice row, one channel) they take, for 72 atoms of
+// 5x5: 35 for the responses (7 steps of 4 taps x 5 blocks of atoms) and 60 for the triangle (15 blocks x 4 steps).  What makes
+// this form possible is that v_mfma_f32_16x16x4 leaves its result as it takes its operands: lane (c16, kq) receives the
+// responses of atom 16 nb + c16 at samples 4 kq .. 4 kq + 3, and as an operand of step e it has to supply row (column) c16 at
+// sample kq of the four of that step, i.e. sample 4 kq + e: its e-th response as it stands, for both operands (the order of
+// the samples does not matter to the sum).  So nothing passes through LDS between the two contractions and no wavefront waits for
+// another before the end; two of them per SIMD take turns on the matrix pipe.  A block's sum over the 16 samples of
+// an item is fp32 and is added to a double at once.
+// Loads: the patch operands (one image element per lane and step) and the targets go out one item ahead, the coefficients,
+// which the channels of 16 samples share, as soon as the last channel has used the ones before; all of them
+// straight from global memory, whose lines neighbouring items share.
+// Items are dealt to the wavefronts in contiguous runs, channel fastest.  At the end a workgroup's eight wavefronts add up in LDS.
+//
+// fp32 matrix and vector instructions share their units on this device (measured: one fp32 multiply-add beside each matrix
+// instruction adds its 4 cycles, a double-precision one 8 to 13), so every vector instruction counts: patch and sample offsets move
+// by a constant from segment to segment, four adjacent coefficients are one load, doubles are added every fourth item only.  The
+// fp32 sums (60 registers for 72 atoms) and the doubles (120) leave no room for the rest at two wavefronts per SIMD, so half of the
+// doubles live in LDS; one wavefront per SIMD holds all in registers but waits for memory (865 us against 660 below).
+// Before, eight wavefronts per workgroup in two roles passed 64-sample tiles through LDS, a barrier per channel.  Up-sampling and
+// normal equations, 72 atoms of 5x5, before / now, us: 1920 x 1080 x3 fp16 766 / 659 (the 35 + 60 matrix instructions of
+// every item are 480 of it), 1304 x 1134 x3 fp8 636 / 486, 160 x 112 x3 every second pixel 32.5 / 22; 60 atoms 1302 x 1227 x1 328 /
+// 149; 40 atoms 268 x 218 x3 53 / 25.
+// ---------------------------------------------------------------------------
+constexpr int NTT = 512;         // at most eight wavefronts
+constexpr int GRIDT = 256;       // at most one workgroup per CU
+
+// block b of the upper triangle of an N x N block matrix, row-major
+template <int N>
+struct UpperBlocks {
+    int row[N * (N + 1) / 2], col[N * (N + 1) / 2];
+    constexpr UpperBlocks() : row(), col() {
+        int b = 0;
+        for (int i = 0; i < N; ++i)
+            for (int j = i; j < N; ++j) { row[b] = i; col[b] = j; ++b; }
+    }
+};
+
+template <int K, typename TC, int N16>
+__global__ __launch_bounds__(NTT, 2) void k_atom_gram_tri(const GramArgs a, unsigned long long items) {
+    constexpr int KK = K * K, R = (K - 1) / 2, KS = (KK + 3) / 4;     // KS: 4-tap steps of the responses
+    constexpr int NB = N16 * (N16 + 1) / 2;
+    constexpr UpperBlocks<N16> ub;
+    // Sums of a wavefront's triangle in double: the first BR blocks in registers, the others, which with the fp32 sums would
+    // not fit there, in LDS (each lane its own words).
+    constexpr int BL = N16 == 5 ? 8 : (N16 == 4 ? 5 : 0), BR = NB - BL;
+    constexpr int MAXB = BL > BR ? BL : BR;
+    constexpr int BDQ = (N16 * KS + 3) / 4;
+    __shared__ double part[8 * MAXB * 256];
+    __shared__ float4 Bd[BDQ * 64];                                   // dictionary operand, four (block, step) pairs of a lane side by side
+
+    const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, kq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const unsigned plane = (unsigned)a.H * (unsigned)a.W;             // below 2^30, see atom_gram
+    const int nseg = (a.nx + 15) / 16;
+
+    // this wavefront's items
+    const int nwaves = blockDim.x >> 6, NTH = blockDim.x;
+    const unsigned nw = gridDim.x * nwaves, w = blockIdx.x * nwaves + wave;
+    unsigned long long first, per;
+    if (items <= 0xffffffffull) {
+        const unsigned p = (unsigned)items / nw, rem = (unsigned)items - p * nw;
+        first = (unsigned long long)w * p + (w < rem ? w : rem);
+        per = p + (w < rem ? 1 : 0);
+    } else {
+        const unsigned long long p = items / nw, rem = items - p * nw;
+        first = w * p + (w < rem ? w : rem);
+        per = p + (w < rem ? 1 : 0);
+    }
+    int c, seg, iy, n;
+    {
+        const unsigned ipr = (unsigned)nseg * (unsigned)a.C;          // items of a lattice row (at most 2^16 x 16)
+        unsigned long long row;
+        unsigned r;
+        if (first <= 0xffffffffull) {
+            row = (unsigned)first / ipr;
+            r = (unsigned)first - (unsigned)row * ipr;
+        } else {
+            row = first / ipr;
+            r = (unsigned)(first - row * ipr);
+        }
+        seg = (int)(r / (unsigned)a.C);
+        c = (int)(r - (unsigned)seg * (unsigned)a.C);
+        n = row <= 0xffffffffull ? (int)((unsigned)row / (unsigned)a.ny) : (int)(row / (unsigned)a.ny);
+        iy = (int)(row - (unsigned long long)n * (unsigned)a.ny);
+    }
+
+    // dictionary operand: (block nb, step ks) of lane (c16, kq) is tap 4 ks + kq of atom 16 nb + c16
+    for (int e = tid; e < BDQ * 64; e += NTH) {
+        const int l64 = e & 63;
+        float v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int i = 4 * (e >> 6) + j, ks = i / N16, tap = 4 * ks + (l64 >> 4), l = 16 * (i - ks * N16) + (l64 & 15);
+            v[j] = (i < N16 * KS && l < a.L && tap < KK) ? a.dict[l * KK + tap] : 0.0f;
+        }
+        Bd[e] = make_float4(v[0], v[1], v[2], v[3]);
+    }
+
+    double dacc[BR][4];
+#pragma unroll
+    for (int b = 0; b < BR; ++b)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dacc[b][e] = 0.0;
+    double* const mine = part + wave * (MAXB * 256) + lane;
+#pragma unroll
+    for (int i = 0; i < 4 * BL; ++i) mine[64 * i] = 0.0;
+
+    const bool last_tap = 4 * (KS - 1) + kq < KK;                     // of the last step: the others are padding
+    const bool holds_target = c16 == (a.L & 15);                      // column L is the target: this lane's, in block L / 16
+    const int tblk = a.L >> 4;
+
+    // Element offsets within a plane: the patch operands (lane: sample c16, tap 4 ks + kq) and the lane's four samples.  Samples
+    // past the end of the row are clamped to its last one and their responses zeroed.
+    unsigned aoff[KS], soff[4];
+    int left = 0;                                                     // samples of the item that exist, from 4 kq on
+    // (from a segment of the row to the next, nothing clamped in either: all of them move by as much)
+    auto place = [&](int iy_, int seg_, const auto moved) {
+        const int Y = iy_ * a.stride, x0 = seg_ * 16, xl = a.nx - 1;
+        left = a.nx - (x0 + 4 * kq);
+        if (moved && seg_ >= 2 && x0 + 15 <= xl && (x0 + 15) * a.stride + R < a.W) {
+            const unsigned by = 16u * (unsigned)a.stride;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) aoff[ks] += by;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) soff[e] += by;
+            return;
+        }
+        const int Xc = (x0 + c16 < xl ? x0 + c16 : xl) * a.stride;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const int tap = 4 * ks + kq, t = tap < KK ? tap : 0, dy = t / K, dx = t - dy * K;
+            aoff[ks] = (unsigned)clampi(Y + dy - R, 0, a.H - 1) * (unsigned)a.W + (unsigned)clampi(Xc + dx - R, 0, a.W - 1);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int x = x0 + 4 * kq + e;
+            soff[e] = (unsigned)Y * (unsigned)a.W + (unsigned)((x < xl ? x : xl) * a.stride);
+        }
+    };
+    float av[KS], h[4];
+    auto fetch = [&](int n_, int c_) {                                // an item's patch operands and targets
+        const size_t pl = ((size_t)n_ * a.C + c_) * plane;
+        const char* const up = (const char*)(a.up + pl);
+        const char* const tg = (const char*)(a.target + pl);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) av[ks] = *(const float*)(up + 4u * aoff[ks]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) h[e] = *(const float*)(tg + 4u * soff[e]);
+    };
+    unsigned phi[N16][4];                                             // as stored
+    typedef typename BitsOf<sizeof(TC)>::type Bits;
+    constexpr int VW = sizeof(TC);                                    // words of four side by side
+    typedef unsigned words __attribute__((ext_vector_type(VW == 1 ? 2 : VW), aligned(sizeof(TC))));
+    // the lane's four samples side by side in memory (stride 1, all of them in the row, of every lane): one load
+    auto adjacent = [&](int left_) { return a.stride == 1 && __builtin_amdgcn_ballot_w64(left_ < 4) == 0; };
+    // Elements from a block's first plane to the lane's; 16 planes stay below 4 GB, see atom_gram.  Lanes past the last atom
+    // take its plane (the last block may hold the target column only: its first plane is the last atom's then).
+    const int last_block = 16 * (N16 - 1) < a.L ? 16 * (N16 - 1) : a.L - 1;
+    const unsigned plane_off = (unsigned)c16 * plane, plane_off_last = (unsigned)(last_block + c16 < a.L ? c16 : a.L - 1 - last_block) * plane;
+    auto fetch_phi = [&](int n_) {                                    // the coefficients of the lane's atoms and samples
+        const Bits* const img = (const Bits*)a.coeff + (size_t)n_ * a.L * plane;
+        auto at = [&](int nb, int e) -> const char* {
+            return (const char*)(img + (size_t)(nb == N16 - 1 ? last_block : 16 * nb) * plane) + ((nb == N16 - 1 ? plane_off_last : plane_off) + soff[e]) * (unsigned)sizeof(TC);
+        };
+        if (adjacent(left)) {
+#pragma unroll
+            for (int nb = 0; nb < N16; ++nb) {
+                if constexpr (VW == 1) {
+                    struct __attribute__((packed, aligned(1))) word { unsigned v; };
+                    phi[nb][0] = ((const word*)at(nb, 0))->v;
+                } else {
+                    const words v = *(const words*)at(nb, 0);
+#pragma unroll
+                    for (int i = 0; i < VW; ++i) phi[nb][i] = v[i];
+                }
+            }
+            return;
+        }
+#pragma unroll
+        for (int nb = 0; nb < N16; ++nb)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) phi[nb][e] = *(const Bits*)at(nb, e);
+    };
+    if (per) {
+        place(iy, seg, std::false_type{});
+        fetch(n, c);
+        fetch_phi(n);
+    }
+    __syncthreads();                                                  // the dictionary operand is written
+    // The triangle's sums, in fp32 over up to 64 samples and channels (four items), then added to the doubles.
+    f32x4 acc[NB];
+    auto zero_acc = [&]() {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    };
+    auto flush = [&]() {
+#pragma unroll
+        for (int b = 0; b < BR; ++b)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) dacc[b][e] += (double)acc[b][e];
+#pragma unroll
+        for (int b = 0; b < BL; ++b)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) mine[64 * (4 * b + e)] += (double)acc[BR + b][e];
+        zero_acc();
+    };
+    zero_acc();
+    int items_in = 0;
+    // an item; `last_channel`: the type of a known one
+    auto item = [&](const auto last_channel) __attribute__((always_inline)) {
+        f32x4 dot[N16];
+#pragma unroll
+        for (int nb = 0; nb < N16; ++nb) dot[nb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        // (a few steps' dictionary operands at a time, requested one group ahead: all at once they take registers the triangle needs)
+        constexpr int QC = 2;
+        float bd[2][4 * QC];
+        auto read_bd = [&](int q0) {
+#pragma unroll
+            for (int q = 0; q < QC; ++q)
+                if (q0 + q < BDQ) {
+                    const float4 v = Bd[(q0 + q) * 64 + lane];
+                    float* const d = &bd[(q0 / QC) & 1][4 * q];
+                    d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
+                }
+        };
+        read_bd(0);
+#pragma unroll
+        for (int q0 = 0; q0 < BDQ; q0 += QC) {
+            if (q0 + QC < BDQ) read_bd(q0 + QC);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 4 * q0; i < 4 * (q0 + QC) && i < N16 * KS; ++i) {
+                const int ks = i / N16, nb = i - ks * N16;
+                dot[nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(ks < KS - 1 || last_tap ? av[ks] : 0.0f, bd[(q0 / QC) & 1][i - 4 * q0], dot[nb], 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        const int here = left;
+        const bool adj = adjacent(here);
+        const float ht[4] = {h[0], h[1], h[2], h[3]};
+        // the next item: its patch operands now, its coefficients once this item's last use of the old ones is over (after the
+        // wavefront's last item: the same again, unused)
+        --per;
+        if (per != 0) {
+            if constexpr (last_channel.value) {
+                c = 0;
+                if (++seg == nseg) {
+                    seg = 0;
+                    if (++iy == a.ny) { iy = 0; ++n; }
+                }
+                place(iy, seg, std::true_type{});
+            } else {
+                ++c;
+            }
+        }
+        fetch(n, c);
+        float r[N16][4];
+#pragma unroll
+        for (int nb = 0; nb < N16; ++nb)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) asm volatile("" : "+v"(phi[nb][e]));   // (widened anew for each channel)
+        if (sizeof(TC) != 4 && adj) {
+#pragma unroll
+            for (int nb = 0; nb < N16; ++nb)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    r[nb][e] = widen(from_bits<TC>(phi[nb][e * VW / 4] >> (8 * (e * VW % 4)))) * dot[nb][e];
+        } else {
+#pragma unroll
+            for (int nb = 0; nb < N16; ++nb)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) r[nb][e] = widen(from_bits<TC>(phi[nb][e])) * dot[nb][e];
+        }
+#pragma unroll
+        for (int nb = 0; nb < N16; ++nb)
+            if (nb == tblk) {                                         // wave-uniform
+#pragma unroll
+                for (int e = 0; e < 4; ++e) r[nb][e] = holds_target ? ht[e] : r[nb][e];
+            }
+        if constexpr (last_channel.value) fetch_phi(n);
+        if (__builtin_amdgcn_ballot_w64(here < 4)) {                  // the end of a row
+#pragma unroll
+            for (int nb = 0; nb < N16; ++nb)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) r[nb][e] = e < here ? r[nb][e] : 0.0f;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+                acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(r[ub.row[b]][e], r[ub.col[b]][e], acc[b], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (++items_in == 4) {
+            items_in = 0;
+            flush();
+        }
+    };
+    while (per != 0) {
+        while (c + 1 < a.C && per != 0) item(std::false_type{});
+        if (per != 0) item(std::true_type{});
+    }
+    flush();
+
+    // The workgroup's sum, wavefront by wavefront: the blocks in LDS, then, in their place, those in registers.
+    // Lane (c16, kq), register e of block (bi, bj) holds row 16 bi + 4 kq + e, column 16 bj + c16.
+    auto add_up = [&](int first_block, int blocks) {
+        __syncthreads();
+        for (int i = tid; i < blocks * 256; i += NTH) {
+            double sum = 0.0;
+            for (int v = 0; v < nwaves; ++v) sum += part[v * (MAXB * 256) + i];
+            a.ws[((size_t)blockIdx.x * NB + first_block) * 256 + (size_t)(i >> 8) * 256 + (i & 63) * 4 + ((i >> 6) & 3)] = sum;
+        }
+    };
+    if constexpr (BL != 0) {
+        add_up(BR, BL);
+        __syncthreads();
+    }
+#pragma unroll
+    for (int b = 0; b < BR; ++b)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) mine[64 * (4 * b + e)] = dacc[b][e];
+    add_up(0, BR);
+}
+
+// ---------------------------------------------------------------------------
+// More than 79 atoms, lattice strides up to 4 (every pixel down to every
+// fourth): workgroups of eight wavefronts, one per CU.  Four wavefronts form the
 // responses of one (run, channel) while the other four contract the tile of the
 // one before; two LDS tiles, one barrier per iteration.  A run is 64 consecutive
 // lattice samples of ONE lattice row, so the k image rows it needs are contiguous
@@ -280,7 +619,7 @@ __global__ __launch_bounds__(NT, (N16 <= 5 && K <= 5) ? 2 : 1) void k_atom_gram(
 // whose latency a single wavefront per SIMD cannot hide.
 // ---------------------------------------------------------------------------
 constexpr int NT2 = 512;         // four response + four contraction wavefronts
-constexpr int GRID2 = 256;       // one workgroup per CU (two where registers and LDS allow)
+constexpr int GRID2 = 256;       // one workgroup per CU
 constexpr int STMAX = 4;         // largest lattice stride whose row segments are staged
 
 // floats of dynamic LDS: tile[2], coefficients of a run [1 or 2], its targets [2], staged segments [2]
@@ -289,48 +628,11 @@ constexpr size_t rows_lds_floats(int k, int n16, int channels) {
            2 * (((size_t)k * (63 * STMAX + k) + 3) & ~(size_t)3);
 }
 
-// Five column blocks (64 to 79 atoms, the paper's 72 among them): the 15 blocks of
-// the upper triangle dealt to the four contracting wavefronts so that a wavefront's
-// blocks share their operands.  Wavefront w reads the column blocks col[w][0 .. nc)
-// of the tile (one 16-byte LDS load each per 16 samples: 14 loads for the 15 blocks,
-// where separate operands for every block would take 30) and block t multiplies
-// operand u[w][t] by operand v[w][t]; q is the block's row-major number in the
-// upper triangle.
-struct Deal5 { int nc, nb, col[4], u[4], v[4], q[4]; };
-constexpr Deal5 deal5(int w) {
-    return w == 0 ? Deal5{3, 4, {0, 1, 2, 0}, {0, 0, 1, 0}, {0, 1, 1, 2}, {0, 1, 5, 2}}        // 00 01 11 02
-         : w == 1 ? Deal5{3, 4, {1, 2, 3, 0}, {1, 1, 2, 0}, {1, 2, 2, 1}, {9, 10, 12, 6}}      // 22 23 33 12
-         : w == 2 ? Deal5{4, 4, {1, 2, 3, 4}, {3, 2, 1, 0}, {3, 3, 3, 3}, {14, 13, 11, 8}}     // 44 34 24 14
-                  : Deal5{4, 3, {0, 1, 3, 4}, {0, 0, 1, 0}, {2, 3, 2, 0}, {3, 4, 7, 0}};       // 03 04 13
-}
-template <int W>
-__device__ __forceinline__ void contract5(const float* T, int c16, int kq, f32x4 (&acc)[4]) {
-    constexpr Deal5 d = deal5(W);
-#pragma unroll
-    for (int sg = 0; sg < RUN / 16; ++sg) {
-        float4 x[4];
-#pragma unroll
-        for (int i = 0; i < d.nc; ++i) x[i] = *(const float4*)&T[(16 * d.col[i] + c16) * TSS + 16 * sg + 4 * kq];
-#pragma unroll
-        for (int t = 0; t < d.nb; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[d.u[t]].x, x[d.v[t]].x, acc[t], 0, 0, 0);
-#pragma unroll
-        for (int t = 0; t < d.nb; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[d.u[t]].y, x[d.v[t]].y, acc[t], 0, 0, 0);
-#pragma unroll
-        for (int t = 0; t < d.nb; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[d.u[t]].z, x[d.v[t]].z, acc[t], 0, 0, 0);
-#pragma unroll
-        for (int t = 0; t < d.nb; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[d.u[t]].w, x[d.v[t]].w, acc[t], 0, 0, 0);
-    }
-}
-// block number of slot t of wavefront w in that deal, -1: none
-__device__ __forceinline__ int deal5_block(int w, int t) {
-    const Deal5 d = w == 0 ? deal5(0) : (w == 1 ? deal5(1) : (w == 2 ? deal5(2) : deal5(3)));
-    return t < d.nb ? d.q[t] : -1;
-}
-
 template <int K, typename TC, int N16>
-__global__ __launch_bounds__(NT2, (N16 <= 5 && K <= 5) ? 4 : 2) void k_atom_gram_rows(const GramArgs a) {
+__global__ __launch_bounds__(NT2, 2) void k_atom_gram_rows(const GramArgs a) {
     constexpr int KK = K * K, R = (K - 1) / 2;
-    constexpr int NTW = N16 == 2 ? 1 : (N16 == 5 ? 4 : 12);     // blocks per contracting wavefront
+    constexpr int NTW = 12;                           // blocks per contracting wavefront
+    static_assert(N16 * (N16 + 1) / 2 <= 4 * NTW, "every block has its wavefront");
     constexpr int NPW = N16 * 4;                      // atoms whose coefficients one contracting wavefront fetches
     constexpr int TILE = N16 * 16 * TSS;
     constexpr int PSZ = (K * (63 * STMAX + K) + 3) & ~3;   // staged row segments of one run and channel (whole 16 bytes)
@@ -574,7 +876,6 @@ __global__ __launch_bounds__(NT2, (N16 <= 5 && K <= 5) ? 4 : 2) void k_atom_gram
     for (int t = 0; t < NTW; ++t)
 #pragma unroll
         for (int e = 0; e < 4; ++e) dacc[t][e] = 0.0;
-    const bool shared_operands = N16 == 5 && a.n16 == 5;     // the deal of deal5() instead
 
     // The run whose coefficients are requested next, the first iteration that reads them
     // and the copy they go to.  Requested in iteration ia - 3, parked in iteration ia - 2
@@ -618,37 +919,25 @@ __global__ __launch_bounds__(NT2, (N16 <= 5 && K <= 5) ? 4 : 2) void k_atom_gram
         f32x4 acc[NTW];
 #pragma unroll
         for (int t = 0; t < NTW; ++t) acc[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        constexpr int TG = NTW < 4 ? NTW : 4;           // blocks go four at a time, their steps interleaved
-        if constexpr (N16 == 5) {
-            if (shared_operands) {
-                switch (g) {
-                case 0:  contract5<0>(T, c16, kq, acc); break;
-                case 1:  contract5<1>(T, c16, kq, acc); break;
-                case 2:  contract5<2>(T, c16, kq, acc); break;
-                default: contract5<3>(T, c16, kq, acc); break;
+        constexpr int TG = 4;                           // blocks go four at a time, their steps interleaved
+#pragma unroll
+        for (int sg = 0; sg < RUN / 16; ++sg) {
+#pragma unroll
+            for (int t0 = 0; t0 < NTW; t0 += TG) {
+                float4 u[TG], v[TG];
+#pragma unroll
+                for (int t = 0; t < TG; ++t) {
+                    u[t] = *(const float4*)&T[(16 * bi[t0 + t] + c16) * TSS + 16 * sg + 4 * kq];
+                    v[t] = *(const float4*)&T[(16 * bj[t0 + t] + c16) * TSS + 16 * sg + 4 * kq];
                 }
-            }
-        }
-        if (!shared_operands) {
 #pragma unroll
-            for (int sg = 0; sg < RUN / 16; ++sg) {
+                for (int t = 0; t < TG; ++t) acc[t0 + t] = __builtin_amdgcn_mfma_f32_16x16x4f32(u[t].x, v[t].x, acc[t0 + t], 0, 0, 0);
 #pragma unroll
-                for (int t0 = 0; t0 < NTW; t0 += TG) {
-                    float4 u[TG], v[TG];
+                for (int t = 0; t < TG; ++t) acc[t0 + t] = __builtin_amdgcn_mfma_f32_16x16x4f32(u[t].y, v[t].y, acc[t0 + t], 0, 0, 0);
 #pragma unroll
-                    for (int t = 0; t < TG; ++t) {
-                        u[t] = *(const float4*)&T[(16 * bi[t0 + t] + c16) * TSS + 16 * sg + 4 * kq];
-                        v[t] = *(const float4*)&T[(16 * bj[t0 + t] + c16) * TSS + 16 * sg + 4 * kq];
-                    }
+                for (int t = 0; t < TG; ++t) acc[t0 + t] = __builtin_amdgcn_mfma_f32_16x16x4f32(u[t].z, v[t].z, acc[t0 + t], 0, 0, 0);
 #pragma unroll
-                    for (int t = 0; t < TG; ++t) acc[t0 + t] = __builtin_amdgcn_mfma_f32_16x16x4f32(u[t].x, v[t].x, acc[t0 + t], 0, 0, 0);
-#pragma unroll
-                    for (int t = 0; t < TG; ++t) acc[t0 + t] = __builtin_amdgcn_mfma_f32_16x16x4f32(u[t].y, v[t].y, acc[t0 + t], 0, 0, 0);
-#pragma unroll
-                    for (int t = 0; t < TG; ++t) acc[t0 + t] = __builtin_amdgcn_mfma_f32_16x16x4f32(u[t].z, v[t].z, acc[t0 + t], 0, 0, 0);
-#pragma unroll
-                    for (int t = 0; t < TG; ++t) acc[t0 + t] = __builtin_amdgcn_mfma_f32_16x16x4f32(u[t].w, v[t].w, acc[t0 + t], 0, 0, 0);
-                }
+                for (int t = 0; t < TG; ++t) acc[t0 + t] = __builtin_amdgcn_mfma_f32_16x16x4f32(u[t].w, v[t].w, acc[t0 + t], 0, 0, 0);
             }
         }
 #pragma unroll
@@ -659,12 +948,8 @@ __global__ __launch_bounds__(NT2, (N16 <= 5 && K <= 5) ? 4 : 2) void k_atom_gram
     // lane (c16, kq), register e of block (bi, bj) holds row 16 bi + 4 kq + e, column 16 bj + c16
 #pragma unroll
     for (int t = 0; t < NTW; ++t) {
-        int q = g + 4 * t;
-        if (q >= a.ntile) q = -1;
-        if constexpr (N16 == 5) {
-            if (shared_operands) q = deal5_block(g, t);
-        }
-        if (q >= 0) {
+        const int q = g + 4 * t;
+        if (q < a.ntile) {
             double* dst = a.ws + ((size_t)blockIdx.x * a.ntile + q) * 256 + si * 4;
 #pragma unroll
             for (int e = 0; e < 4; ++e) dst[e] = dacc[t][e];
@@ -676,7 +961,7 @@ __global__ __launch_bounds__(NT2, (N16 <= 5 && K <= 5) ? 4 : 2) void k_atom_gram
 // also stores the sample count.  Sixteen threads share an entry: thread p adds the
 // partial sums of workgroups p, p + 16, ... in that order and the first thread then
 // adds the sixteen results in order, so the sum depends on the launch shape only.
-constexpr int RED_PARTS = 16, RED_ITEMS = NT / RED_PARTS;
+constexpr int RED_PARTS = 16, RED_ITEMS = NT / RED_PARTS, RED_BATCH = 16;   // (a thread's sixteen partial sums of a launch of 256 workgroups are requested together)
 __global__ __launch_bounds__(NT) void k_gram_reduce(const double* __restrict__ ws, int grid, int ntile, int n16, int L,
                                                     double M, double* __restrict__ normal) {
     __shared__ double part_sum[RED_PARTS][RED_ITEMS];
@@ -690,7 +975,17 @@ __global__ __launch_bounds__(NT) void k_gram_reduce(const double* __restrict__ w
     const bool wanted = row <= col && col <= L;         // diagonal blocks hold both triangles: keep the upper one
     double sum = 0.0;
     if (wanted)
-        for (int w = part; w < grid; w += RED_PARTS) sum += ws[((size_t)w * ntile + q) * 256 + (idx & 255)];
+        for (int w0 = part; w0 < grid; w0 += RED_BATCH * RED_PARTS) {
+            double v[RED_BATCH];
+#pragma unroll
+            for (int i = 0; i < RED_BATCH; ++i) {
+                const int w = w0 + i * RED_PARTS;
+                v[i] = ws[((size_t)(w < grid ? w : w0) * ntile + q) * 256 + (idx & 255)];
+            }
+#pragma unroll
+            for (int i = 0; i < RED_BATCH; ++i)
+                if (w0 + i * RED_PARTS < grid) sum += v[i];
+        }
     part_sum[part][item] = sum;
     __syncthreads();
     if (part != 0 || !wanted) return;
@@ -921,30 +1216,38 @@ int atom_gram(const sr_tensor* up, const sr_tensor* coeff, const sr_tensor* dict
     a.n16 = column_blocks(L);
     a.ntile = upper_blocks(a.n16);
     const hipStream_t st = (hipStream_t)stream;
-    // staged row segments (32-bit offsets within a plane; LDS for the tiles), else per-lane gathers
-    const bool rows_ok = stride <= STMAX && (int64_t)up->h * up->w < (1 << 30);
-    bool rows = false;
+    // Up to five column blocks (79 atoms) a wavefront's registers hold the whole triangle: k_atom_gram_tri, any stride.  More:
+    // staged row segments (strides up to 4, LDS for the tiles).  Both with 32-bit offsets within a plane; else per-lane gathers.
+    const bool offsets32 = (int64_t)up->h * up->w < (1 << 30);
+    const bool tri = a.n16 <= 5 && (uint64_t)up->h * up->w * 16 * (coeff->dtype == SR_F32 ? 4 : coeff->dtype == SR_F8E4M3 ? 1 : 2) < (1ull << 32);
     int grid = GRID;
-#define SR_GRAM_LAUNCH_N(KS, TC, N16)                                                                      \
-    do {                                                                                                    \
-        const size_t lds = rows_lds_floats(KS, N16, channels) * sizeof(float);                              \
-        rows = rows_ok && lds <= 160 * 1024;                                                                \
-        if (rows) {                                                                                         \
-            if (lds > 65536 &&                                                                              \
-                hipFuncSetAttribute((const void*)k_atom_gram_rows<KS, TC, N16>,                             \
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)    \
-                return SR_ERR_LAUNCH;                                                                       \
-            grid = ((N16) <= 5 && (KS) <= 5 && 2 * lds <= 160 * 1024) ? 2 * GRID2 : GRID2;                  \
-            hipLaunchKernelGGL((k_atom_gram_rows<KS, TC, N16>), dim3(grid), dim3(NT2), lds, st, a);         \
-        } else {                                                                                            \
-            hipLaunchKernelGGL((k_atom_gram<KS, TC, N16>), dim3(GRID), dim3(NT), 0, st, a);                 \
-        }                                                                                                   \
-    } while (0)
+    const unsigned long long items = (unsigned long long)a.N * a.ny * ((a.nx + 15) / 16) * a.C;
+#define SR_GRAM_TRI(KS, TC, N16)                                                                           \
+    hipLaunchKernelGGL((k_atom_gram_tri<KS, TC, N16>), dim3(grid), dim3(64 * waves), 0, st, a, items)
 #define SR_GRAM_LAUNCH_T(KS, TC)                                                                           \
     do {                                                                                                    \
-        if (a.n16 <= 2) SR_GRAM_LAUNCH_N(KS, TC, 2);                                                        \
-        else if (a.n16 <= 5) SR_GRAM_LAUNCH_N(KS, TC, 5);                                                   \
-        else SR_GRAM_LAUNCH_N(KS, TC, 9);                                                                   \
+        const size_t lds = rows_lds_floats(KS, 9, channels) * sizeof(float);                                \
+        if (tri) {                                                                                          \
+            /* few items: a wavefront has its SIMD to itself */                                            \
+            const int waves = items <= 4ull * GRIDT ? 4 : 8;                                                \
+            grid = items >= (unsigned)waves * (unsigned long long)GRIDT ? GRIDT : (items == 0 ? 1 : (int)((items + waves - 1) / waves)); \
+            switch (a.n16) {                                                                                \
+            case 1:  SR_GRAM_TRI(KS, TC, 1); break;                                                         \
+            case 2:  SR_GRAM_TRI(KS, TC, 2); break;                                                         \
+            case 3:  SR_GRAM_TRI(KS, TC, 3); break;                                                         \
+            case 4:  SR_GRAM_TRI(KS, TC, 4); break;                                                         \
+            default: SR_GRAM_TRI(KS, TC, 5); break;                                                         \
+            }                                                                                               \
+        } else if (offsets32 && stride <= STMAX && lds <= 160 * 1024) {                                     \
+            if (lds > 65536 &&                                                                              \
+                hipFuncSetAttribute((const void*)k_atom_gram_rows<KS, TC, 9>,                               \
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)    \
+                return SR_ERR_LAUNCH;                                                                       \
+            grid = GRID2;                                                                                   \
+            hipLaunchKernelGGL((k_atom_gram_rows<KS, TC, 9>), dim3(grid), dim3(NT2), lds, st, a);           \
+        } else {                                                                                            \
+            hipLaunchKernelGGL((k_atom_gram<KS, TC, 9>), dim3(GRID), dim3(NT), 0, st, a);                   \
+        }                                                                                                   \
     } while (0)
 #define SR_GRAM_LAUNCH(KS)                                                                                  \
     do {                                                                                                    \
@@ -960,11 +1263,11 @@ int atom_gram(const sr_tensor* up, const sr_tensor* coeff, const sr_tensor* dict
     }
 #undef SR_GRAM_LAUNCH
 #undef SR_GRAM_LAUNCH_T
-#undef SR_GRAM_LAUNCH_N
+#undef SR_GRAM_TRI
     if (hipGetLastError() != hipSuccess) return SR_ERR_LAUNCH;
     const double M = (double)a.N * a.ny * a.nx * a.C;
-    const int items = a.ntile * 256;
-    hipLaunchKernelGGL(k_gram_reduce, dim3(items / RED_ITEMS), dim3(NT), 0, st,
+    const int entries = a.ntile * 256;
+    hipLaunchKernelGGL(k_gram_reduce, dim3(entries / RED_ITEMS), dim3(NT), 0, st,
                        (const double*)workspace, grid, a.ntile, a.n16, L, M, normal);
     return hipGetLastError() == hipSuccess ? SR_OK : SR_ERR_LAUNCH;
 }

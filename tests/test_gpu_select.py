@@ -99,6 +99,31 @@ def test_normal_equations_on_random_shapes(oracle):
         assert abs(hh - hh0) <= 1e-6 * hh0, case
 
 
+# The form that keeps the whole triangle in a wavefront's registers: the last item of a row with 1, 15, 16 and 17 samples, rows
+# that start on odd elements (four coefficients are one load), every number of column blocks, fewer items than wavefronts
+# and several per wavefront, a stride that leaves one sample
+@pytest.mark.parametrize("N,C,h,w,s,L,k,cd,stride", [
+    (1, 1, 8, 8, 2, 72, 5, "f16", 16), (1, 3, 9, 11, 3, 79, 5, "bf16", 2), (1, 1, 13, 31, 3, 63, 3, "f8", 1), (2, 3, 40, 37, 3, 15, 7, "f16", 1),
+    (1, 2, 60, 49, 3, 47, 5, "f32", 3), (1, 3, 50, 83, 3, 72, 5, "f8", 1), (1, 4, 33, 17, 4, 72, 7, "f16", 4),
+    (1, 1, 20, 33, 2, 16, 5, "f16", 1), (1, 3, 21, 30, 2, 64, 3, "f32", 2)])          # the last block holds the target only
+def test_triangle_in_registers(N, C, h, w, s, L, k, cd, stride):
+    wl, inp, up, target = _inputs((N, C, h, w, s, L, k, cd, stride))
+    got = sr.sr_atom_gram(up, inp["coeff"], inp["dict"], target, L, k, C, stride).cpu().numpy()
+    G0, b0, hh0, M0 = so.normal_equations(up.cpu().numpy().astype(np.float64), sr_synth.stored_numpy(inp["coeff"]),
+                                          inp["dict"].cpu().numpy(), target.cpu().numpy(), stride)
+    ref = np.concatenate([G0.reshape(-1), b0, [hh0, M0]])
+    # fp32 responses of k^2 products (2^-24 each, partial sums a few times the result) and fp32 sums over at most 64 samples
+    tol = 1e-5 * np.sqrt(np.concatenate([np.outer(np.diag(G0), np.diag(G0)).reshape(-1), np.diag(G0) * hh0, [hh0 ** 2, M0 ** 2]]))
+    assert (np.abs(got - ref) <= tol + 1e-12).all()
+    if cd in ("f16", "f32"):                        # what is not a number stays within its atom
+        inp["coeff"][0, L - 1, 0, 0] = float("nan")
+        bad = sr.sr_atom_gram(up, inp["coeff"], inp["dict"], target, L, k, C, stride).cpu().numpy()
+        mine = np.zeros((L, L), bool)
+        mine[L - 1], mine[:, L - 1] = True, True
+        mine = np.concatenate([mine.reshape(-1), np.arange(L) == L - 1, [False, False]])
+        assert np.isnan(bad[mine]).all() and np.array_equal(bad[~mine], got[~mine])
+
+
 def test_empty_batch_and_undersized_scratch():
     wl, inp, up, target = _inputs(CASES[0])
     z = torch.empty((0, 3, wl.H, wl.W), device=DEV)
