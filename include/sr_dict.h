@@ -283,7 +283,11 @@ int sr_dict_assemble_list_ex(const sr_tensor* lr, const sr_tensor* index, const 
 
 /* Which kernel sr_dict_assemble_ex would run for these arguments
  * (SR_KERNEL_GENERIC or SR_KERNEL_MFMA), or a negative sr_status.  Launches
- * nothing. */
+ * nothing.
+ * (SR_KERNEL_GENERIC means: outside the streaming matrix-core kernel.  With SR_KERNEL_AUTO most of what the generic kernel was
+ * asked for - coefficients before the pixel-shuffle and logits of every type, up to 128 folded atoms, one to three
+ * channels - runs on a second matrix-core kernel of its own; SR_KERNEL_GENERIC given by the caller is always the
+ * vector-ALU kernel.) */
 int sr_dict_assemble_plan(const sr_tensor* lr, const sr_tensor* coeff, const sr_tensor* dict,
                           int L, int k, int scale, int channels,
                           const sr_tensor* out,

@@ -31,6 +31,7 @@ struct Plan {
     int status;      // SR_OK or an error
     int kernel;      // SR_KERNEL_GENERIC | SR_KERNEL_MFMA
     int tile;
+    bool slots;      // SR_KERNEL_GENERIC by the library's own choice, not the caller's: k_assemble_slots where it takes the call
     bool empty;      // nothing to do
     AssembleArgs args;
 };
@@ -42,6 +43,7 @@ void make_plan(Plan& p, const sr_tensor* lr, const sr_tensor* coeff, const sr_te
     p.status = SR_OK;
     p.kernel = SR_KERNEL_GENERIC;
     p.tile = 0;
+    p.slots = false;
     p.empty = false;
     if (!lr || !coeff || !dict || !out) { p.status = SR_ERR_NULL; return; }
     if (!dtype_ok(lr->dtype) || !coeff_dtype_ok(coeff->dtype) || !dtype_ok(out->dtype) ||
@@ -119,6 +121,7 @@ void make_plan(Plan& p, const sr_tensor* lr, const sr_tensor* coeff, const sr_te
     if ((want == SR_KERNEL_MFMA || (tile != 0 && want != SR_KERNEL_GENERIC)) && !can_mfma) { p.status = SR_ERR_UNSUPPORTED; return; }
     p.kernel = (want == SR_KERNEL_GENERIC || !can_mfma) ? SR_KERNEL_GENERIC : SR_KERNEL_MFMA;
     p.tile = tile;
+    p.slots = !p.empty && p.kernel == SR_KERNEL_GENERIC && want == SR_KERNEL_AUTO && slots_supported(a, k);
 }
 
 }  // namespace
@@ -136,7 +139,7 @@ __attribute__((visibility("default"))) int sr_dict_assemble_ex(const sr_tensor* 
     const bool io_f16 = lr->dtype == SR_F16;
     hipError_t e = (p.kernel == SR_KERNEL_MFMA)
                        ? launch_mfma(p.args, k, io_f16, p.tile, st)
-                       : launch_generic(p.args, k, io_f16, st);
+                       : p.slots ? launch_slots(p.args, k, st) : launch_generic(p.args, k, io_f16, st);
     return e == hipSuccess ? SR_OK : SR_ERR_LAUNCH;
 }
 

@@ -1,0 +1,8 @@
+// k_assemble_slots for 3x3 atoms and one channel (sr_slots.h)
+#include "sr_slots.h"
+
+namespace srd {
+
+hipError_t launch_slots_k3c1(const AssembleArgs& a, hipStream_t st) { return launch_slots_t<3, 1>(a, st); }
+
+}  // namespace srd

@@ -1,0 +1,8 @@
+// k_assemble_slots for 5x5 atoms and two or three channels (sr_slots.h)
+#include "sr_slots.h"
+
+namespace srd {
+
+hipError_t launch_slots_k5c3(const AssembleArgs& a, hipStream_t st) { return launch_slots_t<5, 3>(a, st); }
+
+}  // namespace srd

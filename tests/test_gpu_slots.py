@@ -1,0 +1,129 @@
+"""Calls that no instantiation of the streaming matrix-core kernel holds (coefficients before the pixel-shuffle and logits in
+most types and sizes): the library's own choice of kernel against the oracle, against the generic kernel over all the forms that
+both take, and its distance from 64-bit arithmetic, which must not exceed the generic kernel's."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2303_08999_amd as sr
+import sr_synth
+from test_gpu_parity import DEV, GENERIC, host, tolerance_ok
+from test_gpu_logits import assert_logits_parity
+
+pytestmark = pytest.mark.gpu
+AUTO = sr.SR_KERNEL_AUTO
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    sr.load()
+
+
+def run(inp, wl, coeff, kernel, pre, logits, kept=None, gamma=None):
+    out = torch.full((wl.n, wl.c, wl.H, wl.W), float("nan"), device=DEV, dtype=inp["lr"].dtype)
+    opts = sr.make_options(kernel, 0, sr.SR_COEFF_PRE_SHUFFLE if pre else sr.SR_COEFF_PLANAR,
+                           sr.SR_COEFF_LOGITS if logits else sr.SR_COEFF_VALUES)
+    sr.sr_dict_assemble_ex(inp["lr"], coeff, inp["dict"], wl.L, wl.k, wl.scale, wl.c, out, kept=kept, gamma=gamma, opts=opts)
+    torch.cuda.synchronize()
+    return out
+
+
+def planned(inp, wl, coeff, pre, logits, kept):
+    opts = sr.make_options(AUTO, 0, sr.SR_COEFF_PRE_SHUFFLE if pre else sr.SR_COEFF_PLANAR,
+                           sr.SR_COEFF_LOGITS if logits else sr.SR_COEFF_VALUES)
+    out = torch.empty((wl.n, wl.c, wl.H, wl.W), device=DEV, dtype=inp["lr"].dtype)
+    return sr.sr_dict_assemble_plan(inp["lr"], coeff, inp["dict"], wl.L, wl.k, wl.scale, wl.c, out, kept=kept, opts=opts)
+
+
+def make(wl, pre, logits):
+    inp = sr_synth.make_inputs(wl, DEV)
+    flat = sr_synth.make_logits(wl, DEV) if logits else inp["coeff"]
+    return inp, flat, sr_synth.to_pre_shuffle(flat, wl.scale) if pre else flat
+
+
+# words of one, two and four pixels at the end of rows that are no whole number of them; rows of one word; every scale, filter size,
+# number of parts of the dictionary; capacities full and with one atom; one to three channels; both image types; kept lists
+CASES = [
+    # (N, C, h, w, scale, L, k, coeff, image, pre-shuffle, logits, kept)
+    (1, 3, 9, 65, 2, 72, 5, "f16", "f32", True, False, None), (1, 1, 5, 33, 4, 128, 5, "f16", "f16", True, False, None),
+    (2, 2, 7, 31, 3, 33, 7, "bf16", "f32", True, False, None), (1, 3, 11, 67, 3, 72, 5, "f8", "f32", True, False, None),
+    (1, 1, 6, 130, 4, 40, 7, "f8", "f16", True, False, 17), (1, 3, 9, 35, 2, 100, 3, "f32", "f32", True, False, None),
+    (1, 3, 4, 2, 4, 1, 5, "bf16", "f32", True, False, None), (1, 1, 3, 4, 2, 8, 3, "f8", "f32", True, False, None),
+    (1, 3, 19, 61, 4, 72, 7, "f32", "f16", True, False, 30), (1, 2, 10, 1, 3, 16, 5, "f32", "f32", True, False, None),
+    (1, 1, 13, 47, 3, 72, 5, "f16", "f32", False, True, None), (1, 3, 8, 25, 4, 128, 7, "bf16", "f16", False, True, None),
+    (2, 3, 9, 50, 2, 50, 3, "f32", "f32", False, True, None), (1, 3, 6, 33, 4, 96, 5, "f16", "f32", True, True, None),
+    (1, 1, 12, 29, 3, 72, 7, "f32", "f32", True, True, None), (1, 3, 7, 70, 2, 9, 5, "bf16", "f32", True, True, None),
+    (1, 3, 11, 17, 3, 72, 7, "f8", "f32", False, False, 9), (1, 2, 30, 65, 2, 72, 5, "f8", "f32", False, False, None),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "N%dC%dh%dw%ds%dL%dk%d%s%s-%d%d-%s" % c)
+def test_against_the_oracle(oracle, case):
+    N, C, h, w, s, L, k, cd, io, pre, logits, nk = case
+    wl = sr_synth.Workload("slots", 70, N, C, h, w, s, L, k, cd, io, 0.0, 1.5)
+    inp, flat, coeff = make(wl, pre, logits)
+    kept = gamma = None
+    if nk:
+        rng = np.random.default_rng(nk)
+        kept = np.sort(rng.choice(L, size=nk, replace=False)).astype(np.int32)
+        gamma = rng.uniform(0.5, 1.5, size=nk).astype(np.float32)
+    assert planned(inp, wl, coeff, pre, logits, kept) == GENERIC           # (what the plan calls everything outside the streaming kernel)
+    got = run(inp, wl, coeff, AUTO, pre, logits, kept, gamma)
+    hi = host(inp)
+    phi = oracle.softmax_logits(sr_synth.stored_numpy(flat)) if logits else sr_synth.stored_numpy(flat)
+    ref = oracle.assemble(oracle.bicubic(hi["lr"], s), phi, hi["dict"], kept=kept, gamma=gamma)
+    if logits:
+        assert_logits_parity(got.float().cpu().numpy(), ref, io == "f16", case)
+    else:
+        # (fp32 bounds for every type: the dictionary's parts carry 22 bits and more)
+        worst, tol, ok = tolerance_ok(got.float().cpu().numpy(), ref, "f16" if cd == "bf16" else cd, io == "f16")
+        assert ok, (case, worst, tol)
+    if io == "f32":
+        # no further from 64-bit arithmetic than the generic kernel: both are a few roundings of fp32, so a tenth for chance
+        gen = run(inp, wl, coeff, GENERIC, pre, logits, kept, gamma)
+        rms = lambda x: float(np.sqrt(np.mean((x.double().cpu().numpy() - ref) ** 2)))
+        assert rms(got) <= 1.1 * rms(gen) + 1e-9, (case, rms(got), rms(gen))
+
+
+def test_random_shapes_against_the_generic_kernel():
+    """Everything that both take: orders, types, sizes, kept lists, batches."""
+    rng = np.random.default_rng(11)
+    compared = 0
+    for index in range(260):
+        pre, logits = bool(rng.integers(2)), bool(rng.integers(2))
+        cd = str(rng.choice(["f16", "bf16", "f32"] if logits else ["f16", "bf16", "f32", "f8"]))
+        k, s, C, N = int(rng.choice([3, 5, 7])), int(rng.choice([2, 3, 4])), int(rng.choice([1, 2, 3])), int(rng.choice([1, 1, 2, 5]))
+        L = int(rng.choice([72, 128, int(rng.integers(1, 129))]))
+        big = index % 10 == 0
+        h, w = int(rng.integers(1, 160 if big else 30)), int(rng.integers(1, 300 if big else 80))
+        if N * h * w * s * s * L > 60e6:
+            continue
+        wl = sr_synth.Workload("slotsr", 700 + index, N, C, h, w, s, L, k, cd, str(rng.choice(["f32", "f16"])), 0.0, 1.5)
+        inp, flat, coeff = make(wl, pre, logits)
+        kept = gamma = None
+        if not logits and rng.random() < 0.4:
+            nk = int(rng.integers(1, L + 1))
+            kept = np.sort(rng.choice(L, size=nk, replace=False)).astype(np.int32)
+            gamma = rng.uniform(0.5, 1.5, size=nk).astype(np.float32)
+        if planned(inp, wl, coeff, pre, logits, kept) != GENERIC:
+            continue
+        a = run(inp, wl, coeff, AUTO, pre, logits, kept, gamma).float()
+        b = run(inp, wl, coeff, GENERIC, pre, logits, kept, gamma).float()
+        what = (wl, pre, logits, kept)
+        assert torch.isfinite(a).all(), what
+        # fp32 rounding order, half a step of an fp16 image; logits: an exponential next to a tie may round the other way on one side
+        tol = (2.5e-4 if logits else 5e-5) + (2.0 ** -10 if wl.lr_dtype == "f16" else 0.0)
+        err = float((a - b).abs().max())
+        assert err <= tol * max(1.0, float(b.abs().max())), (what, err)
+        compared += 1
+    assert compared >= 150, compared
+
+
+def test_an_infinite_image_value_stays_within_its_patches():
+    """The halves of a filter have unequal numbers of rows: the one that pads the second must not reach beyond the patch."""
+    wl = sr_synth.Workload("slotsi", 71, 1, 1, 12, 40, 2, 72, 5, "f32", "f32", 0.0, 1.5)
+    inp, flat, coeff = make(wl, True, False)
+    inp["lr"][0, 0, 6, 20] = float("inf")
+    a, b = (run(inp, wl, coeff, kernel, True, False) for kernel in (AUTO, GENERIC))
+    assert torch.equal(torch.isfinite(a), torch.isfinite(b)) and not torch.isfinite(b).all()
