@@ -24,7 +24,8 @@ bool mfma_supported(const AssembleArgs& a, int k, int coeff_dtype, int tile);
 hipError_t launch_mfma(const AssembleArgs& a, int k, bool io_f16, int tile, const LaunchTo& st);
 // Matrix-core kernel for calls the one above has no instantiation for (coefficient dtype: a.coeff_dtype)
 bool slots_supported(const AssembleArgs& a, int k);
-hipError_t launch_slots(const AssembleArgs& a, int k, hipStream_t st);
+bool slots_faster(const AssembleArgs& a, int k);       // ... and those that it has one for but serves slower
+hipError_t launch_slots(const AssembleArgs& a, int k, const LaunchTo& st);
 // Per-pixel list form (sr_dict_assemble_list) on the matrix cores: a.coeff = values, a.index, a.T set; kept = identity.
 bool mfma_list_supported(const AssembleArgs& a, int k, bool value_f16);
 hipError_t launch_mfma_list(const AssembleArgs& a, const LaunchTo& st);

@@ -51,8 +51,8 @@ int np8_for(int k, int channels, int n_fold, int coeff_dtype) {
     }
     // fp16 and bfloat16 coefficients
     static const int k5c3[] = {1, 2, 4, 6, 9, 16, 0}, k5c1[] = {1, 4, 6, 9, 16, 0};
-    static const int k7c3[] = {2, 9, 16, 0}, k7c1[] = {2, 9, 16, 0};
-    const int* built = k == 5 ? (channels == 3 ? k5c3 : k5c1) : (channels == 3 ? k7c3 : k7c1);
+    static const int k7[] = {2, 4, 9, 16, 0};
+    const int* built = k == 5 ? (channels == 3 ? k5c3 : k5c1) : k7;
     for (; *built; ++built)
         if (*built >= need) return *built;
     return 0;
@@ -146,6 +146,7 @@ bool mfma_supported(const AssembleArgs& a, int k, int coeff_dtype, int tile) {
 hipError_t launch_mfma(const AssembleArgs& a, int k, bool io_f16, int tile, const LaunchTo& st) {
     (void)io_f16;
     const int np8 = np8_for(k, a.C, a.n_fold, a.coeff_dtype);
+    if (tile == 0 && slots_faster(a, k)) return launch_slots(a, k, st);
     if (a.blocked) return launch_mfma_k5_blk(a, st);
     if (a.logits) return launch_mfma_k5_lg(a, st);
     if (a.pixel_major) return launch_mfma_k5_pm(a, st);

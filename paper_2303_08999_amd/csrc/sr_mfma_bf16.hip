@@ -2,7 +2,7 @@
 // the same flow and tiles as fp16 coefficients, with the fold on the bfloat16 matrix
 // instructions and the dictionary split into two bfloat16 operands.
 // The capacities built for fp16: 5x5 atoms with 8, 16 (three channels), 32, 48 and 72 atoms
-// (two or four channels: 32 and 72); 7x7 atoms with 16, 72 and 128.  (3x3 atoms:
+// (two or four channels: 32 and 72); 7x7 atoms with 16, 32, 72 and 128.  (3x3 atoms:
 // sr_mfma_k3.hip.)
 #include "sr_mfma_kernel.h"
 
@@ -54,6 +54,7 @@ static hipError_t launch_k7(const AssembleArgs& a, int np8, const LaunchTo& st) 
     if (strip_form(a, np8, 64, 64, a.s == 4 ? 24 : 16)) {
         switch (np8) {
         case 2:  return launch_strip<7, C, 2, 2, 2, CT_BF16>(a, st);
+        case 4:  return launch_strip<7, C, 4, 2, 2, CT_BF16>(a, st);
         case 9:  return launch_strip<7, C, 9, 2, 2, CT_BF16>(a, st);
         case 16: return launch_strip<7, C, 16, 2, 2, CT_BF16>(a, st);
         }
@@ -62,6 +63,9 @@ static hipError_t launch_k7(const AssembleArgs& a, int np8, const LaunchTo& st) 
     case 2:
         if (a.s == 4) return launch_one<7, C, 2, 2, 1, 4, 6, 2, CT_BF16, 4>(a, st);
         return launch_one<7, C, 2, 2, 1, 4, 4, 2, CT_BF16>(a, st);
+    case 4:
+        if (a.s == 4) return launch_one<7, C, 4, 2, 1, 4, 6, 2, CT_BF16, 4>(a, st);
+        return launch_one<7, C, 4, 2, 1, 4, 4, 2, CT_BF16>(a, st);
     case 9:
         if (a.s == 4) return launch_one<7, C, 9, 2, 1, 4, 6, 2, CT_BF16, 4>(a, st);
         return launch_one<7, C, 9, 2, 1, 4, 4, 2, CT_BF16>(a, st);

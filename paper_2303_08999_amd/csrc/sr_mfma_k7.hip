@@ -20,6 +20,7 @@ hipError_t launch_mfma_k7(const AssembleArgs& a, int np8, int shape, const Launc
     if (a.C == 3) {
         switch (np8) {
         case 2:  return launch_k7<3, 2>(a, st);
+        case 4:  return launch_k7<3, 4>(a, st);
         case 9:  return launch_k7<3, 9>(a, st);
         case 16: return launch_k7<3, 16>(a, st);
         default: return hipErrorInvalidValue;
@@ -27,6 +28,7 @@ hipError_t launch_mfma_k7(const AssembleArgs& a, int np8, int shape, const Launc
     }
     switch (np8) {
     case 2:  return launch_k7<1, 2>(a, st);
+    case 4:  return launch_k7<1, 4>(a, st);
     case 9:  return launch_k7<1, 9>(a, st);
     case 16: return launch_k7<1, 16>(a, st);
     default: return hipErrorInvalidValue;

@@ -99,15 +99,17 @@ void k_assemble_slots(const SlotArgs a) {
     if (t >= t_end) return;
     // units of a tile row, column classes of the tile and the stride between them (planar: known when compiled)
     const int upr = PRE ? a.upr : 4 / P, sw = PRE ? a.sw : P, ng = PRE ? a.ng : 32 * (4 / P) + (K - 2) / P + 1;
-    const int units = a.th * upr, TW = 32 * P * upr;
+    const int TW = 32 * P * upr;
     const int wb = PRE ? a.w : a.W;                   // pixels of a row of a coefficient plane
     const unsigned plane_b = (unsigned)a.H * (unsigned)a.W * CB;          // bytes of an atom's coefficients (below 4 GB for all of them)
 
-    struct Tile { int n, Y0, X0; };
+    // (upr: units of a row of this tile; planar: those that hold any of the image)
+    struct Tile { int n, Y0, X0, upr; };
     auto tile_of = [&](int i) -> Tile {
         const unsigned per = (unsigned)a.tiles_x * (unsigned)a.tiles_y, n = (unsigned)i / per, r = (unsigned)i - n * per;
         const unsigned ty = r / (unsigned)a.tiles_x;
-        return {(int)n, (int)ty * a.th, (int)(r - ty * (unsigned)a.tiles_x) * TW};
+        const int X0 = (int)(r - ty * (unsigned)a.tiles_x) * TW;
+        return {(int)n, (int)ty * a.th, X0, PRE ? upr : min(upr, (wb - X0 + 32 * P - 1) / (32 * P))};
     };
     // ---- tables and operands, as in sr_mfma_kernel.h: everything is requested before anything is waited for
     auto load_atom = [&](int i, int h) -> int {
@@ -176,16 +178,11 @@ void k_assemble_slots(const SlotArgs a) {
     };
 
     // A unit of a tile: its row, the first pixel of its words in a coefficient row, its sub-pixel column (planar: none)
-    struct Unit { int row, x, jx; };
+    struct Unit { int row, x, jx, col; };             // (col: its first group of columns in the tile)
     auto unit_of = [&](const Tile tp, int u) -> Unit {
         int row = 0, r = u;
-        if constexpr (PRE) {
-            while (r >= upr) { r -= upr; ++row; }                          // (at most 32 units)
-        } else {
-            row = r / upr;
-            r -= row * upr;
-        }
-        return PRE ? Unit{row, tp.X0 / a.s, r} : Unit{row, tp.X0 + 32 * P * r, 0};
+        while (r >= tp.upr) { r -= tp.upr; ++row; }                        // (at most 32 units)
+        return PRE ? Unit{row, tp.X0 / a.s, r, 0} : Unit{row, tp.X0 + 32 * P * r, 0, 32 * r};
     };
     unsigned raw[NLOAD], pix = 0u, sh = 0u;
     const char* cimg = nullptr;
@@ -211,7 +208,7 @@ void k_assemble_slots(const SlotArgs a) {
     Tile cur = tile_of(t);
     load_lr(cur);
     __syncthreads();                                                       // the table of plane offsets is written
-    if (wave < units) {
+    if (wave < a.th * cur.upr) {
         point_at(cur, unit_of(cur, wave));
 #pragma unroll
         for (int i = 0; i < NLOAD; ++i) raw[i] = load_word(i);
@@ -369,6 +366,7 @@ void k_assemble_slots(const SlotArgs a) {
         const Tile nxt = more ? tile_of(t + a.stride) : cur;
         if (more) load_lr(nxt);
 
+        const int units = a.th * cur.upr;
         for (int u = wave; u < units; u += 4) {
             const Unit un = unit_of(cur, u);
             const unsigned ush = sh;
@@ -430,7 +428,7 @@ void k_assemble_slots(const SlotArgs a) {
             const int se = PRE ? a.s : 1;
             // Half 1 has one filter row less: its last one meets weights that are zero, and reads a row of the patch again (a row further
             // down may hold what no weight of zero makes harmless).
-            const float* const ub = U + (un.row + hf * RH0) * PITCH + j + (PRE ? 0 : 32 * (u - un.row * upr));
+            const float* const ub = U + (un.row + hf * RH0) * PITCH + j + un.col;
             const float* const ub_last = ub + (RH0 - 1 - hf) * PITCH;
 #pragma unroll
             for (int q0 = 0; q0 < P; q0 += QG) {
@@ -529,16 +527,13 @@ void k_assemble_slots(const SlotArgs a) {
                         float sum[QG];
 #pragma unroll
                         for (int q = 0; q < QG; ++q) {
+                            // (row by row, as the streaming kernel: the same sums where the fold is the same)
                             sum[q] = 0.0f;
 #pragma unroll
-                            for (int dx = 0; dx < K; ++dx) {
-                                const float* const col = ub + at[q][dx];
-                                const float* const last = ub_last + at[q][dx];
-#pragma unroll
-                                for (int dy = 0; dy < RH0; ++dy) {
-                                    const int v = dy * K + dx;
-                                    sum[q] = fmaf(acc[q][v / 16][0][v % 16], dy + 1 < RH0 ? col[(c * UH + dy) * PITCH] : last[c * UH * PITCH], sum[q]);
-                                }
+                            for (int v = 0; v < NSLOT; ++v) {
+                                const int dy = v / K, dx = v % K;
+                                const float u = dy + 1 < RH0 ? ub[at[q][dx] + (c * UH + dy) * PITCH] : ub_last[at[q][dx] + c * UH * PITCH];
+                                sum[q] = fmaf(acc[q][v / 16][0][v % 16], u, sum[q]);
                             }
                             if constexpr (LG) sum[q] *= rsum[q];
                         }
@@ -564,7 +559,7 @@ void k_assemble_slots(const SlotArgs a) {
 }
 
 template <int K, int CM, int CT, int NP8, bool LG, bool PRE>
-static hipError_t launch_slots_p(const AssembleArgs& c, hipStream_t st) {
+static hipError_t launch_slots_p(const AssembleArgs& c, const LaunchTo& st) {
     using F = SlotCfg<K, CM, CT, NP8, LG, PRE>;
     SlotArgs a;
     a.lr = c.lr; a.coeff = c.coeff; a.dict = c.dict; a.out = c.out;
@@ -602,24 +597,28 @@ static hipError_t launch_slots_p(const AssembleArgs& c, hipStream_t st) {
     const int groups = 1 << a.group_shift;
     a.share = (a.ntiles + groups - 1) / groups;
     a.stride = blocks / groups;
-    hipLaunchKernelGGL((k_assemble_slots<K, CM, CT, NP8, LG, PRE>), dim3(blocks), dim3(256), 0, st, a);
+    if (st.walk) {
+        *st.walk = {1, tw, a.th, a.ntiles, blocks, 4};
+        return hipSuccess;
+    }
+    hipLaunchKernelGGL((k_assemble_slots<K, CM, CT, NP8, LG, PRE>), dim3(blocks), dim3(256), 0, st.stream, a);
     return hipGetLastError();
 }
 
 template <int K, int CM, int CT, int NP8, bool LG>
-static hipError_t launch_slots_n(const AssembleArgs& a, hipStream_t st) {
+static hipError_t launch_slots_n(const AssembleArgs& a, const LaunchTo& st) {
     return a.pre_shuffle ? launch_slots_p<K, CM, CT, NP8, LG, true>(a, st) : launch_slots_p<K, CM, CT, NP8, LG, false>(a, st);
 }
 
 template <int K, int CM, int CT, bool LG>
-static hipError_t launch_slots_k(const AssembleArgs& a, hipStream_t st) {
+static hipError_t launch_slots_k(const AssembleArgs& a, const LaunchTo& st) {
     if (a.n_fold <= 32) return launch_slots_n<K, CM, CT, 4, LG>(a, st);
     if (a.n_fold <= 72) return launch_slots_n<K, CM, CT, 9, LG>(a, st);
     return launch_slots_n<K, CM, CT, 16, LG>(a, st);
 }
 
 template <int K, int CM>
-static hipError_t launch_slots_t(const AssembleArgs& a, hipStream_t st) {
+static hipError_t launch_slots_t(const AssembleArgs& a, const LaunchTo& st) {
     switch (a.coeff_dtype) {
     case SR_F16:  return a.logits ? launch_slots_k<K, CM, CT_F16, true>(a, st) : launch_slots_k<K, CM, CT_F16, false>(a, st);
     case SR_BF16: return a.logits ? launch_slots_k<K, CM, CT_BF16, true>(a, st) : launch_slots_k<K, CM, CT_BF16, false>(a, st);

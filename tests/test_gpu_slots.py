@@ -120,6 +120,33 @@ def test_random_shapes_against_the_generic_kernel():
     assert compared >= 150, compared
 
 
+# Planar coefficients that the streaming kernel has an instantiation for and that go here all the same, and their neighbours on the
+# other side of each line: the result is the matrix-core kernel's either way
+@pytest.mark.parametrize("n, c, h, w, s, L, k, cd, io, slots", [
+    (1, 3, 60, 70, 3, 100, 5, "f8", "f32", True), (1, 1, 3, 5, 2, 128, 3, "f32", "f16", True), (2, 1, 40, 25, 4, 73, 5, "f32", "f32", True),
+    (1, 3, 82, 155, 2, 72, 7, "f8", "f32", True), (1, 3, 250, 260, 2, 72, 7, "f8", "f32", False), (1, 1, 64, 64, 2, 72, 5, "f32", "f32", True),
+    (1, 1, 100, 110, 2, 72, 5, "f32", "f32", False), (1, 3, 93, 187, 3, 50, 5, "f32", "f16", True), (1, 3, 90, 120, 4, 72, 5, "f32", "f32", False),
+    (1, 3, 125, 131, 2, 128, 3, "f16", "f32", True), (1, 3, 150, 311, 3, 72, 3, "f16", "f32", True), (1, 3, 150, 320, 3, 72, 3, "f16", "f32", False), (1, 3, 150, 311, 3, 72, 5, "f16", "f32", False),
+    (1, 1, 109, 152, 3, 72, 5, "f16", "f16", True), (1, 3, 300, 301, 3, 128, 5, "bf16", "f32", True), (1, 3, 10, 56, 2, 72, 3, "f16", "f32", True), (1, 3, 10, 40, 2, 72, 5, "f16", "f32", False)])
+def test_planar_calls_that_are_faster_here(oracle, n, c, h, w, s, L, k, cd, io, slots):
+    wl = sr_synth.Workload("slotsp", 72, n, c, h, w, s, L, k, cd, io, 0.0, 1.5)
+    inp = sr_synth.make_inputs(wl, DEV)
+    out = torch.empty((n, c, wl.H, wl.W), device=DEV, dtype=inp["lr"].dtype)
+    kernel, walk = sr.sr_dict_assemble_walk(inp["lr"], inp["coeff"], inp["dict"], L, k, s, c, out)
+    # (its tiles have up to eight rows and 128 columns; the streaming kernel's of that width have four, sixteen or twenty-four)
+    assert kernel == sr.SR_KERNEL_MFMA and (walk[0] == 1 and walk[1] == 128 and walk[2] in (1, 2, 4, 8)) >= slots
+    got = run(inp, wl, inp["coeff"], sr.SR_KERNEL_MFMA, False, False)
+    gen = run(inp, wl, inp["coeff"], GENERIC, False, False)
+    assert torch.isfinite(got).all()
+    tol = (5e-5 if cd != "bf16" else 1e-4) + (2.0 ** -10 if io == "f16" else 0.0)
+    assert float((got.float() - gen.float()).abs().max()) <= tol * max(1.0, float(gen.float().abs().max()))
+    if n == 1 and wl.H * wl.W * L < 30e6:
+        hi = host(inp)
+        ref = oracle.assemble(oracle.bicubic(hi["lr"], s), sr_synth.stored_numpy(inp["coeff"]), hi["dict"])
+        worst, t, ok = tolerance_ok(got.float().cpu().numpy(), ref, cd, io == "f16")
+        assert ok, (worst, t)
+
+
 def test_an_infinite_image_value_stays_within_its_patches():
     """The halves of a filter have unequal numbers of rows: the one that pads the second must not reach beyond the patch."""
     wl = sr_synth.Workload("slotsi", 71, 1, 1, 12, 40, 2, 72, 5, "f32", "f32", 0.0, 1.5)
