@@ -72,6 +72,18 @@ __device__ __forceinline__ TC from_bits(unsigned b) {
     else if constexpr (sizeof(TC) == 2) return __builtin_bit_cast(TC, (unsigned short)b);
     else return __builtin_bit_cast(TC, (unsigned char)b);
 }
+// x times the coefficient in bits 8 AT .. of a word (fp16: the half is widened by the multiplication itself)
+template <typename TC, int AT>
+__device__ __forceinline__ float times_stored(unsigned word, float x) {
+    if constexpr (std::is_same<TC, __half>::value) {
+        float r;
+        if constexpr (AT == 0) asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel_hi:[1,0,0]" : "=v"(r) : "v"(word), "v"(x));
+        else asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(word), "v"(x));
+        return r;
+    } else {
+        return widen(from_bits<TC>(word >> (8 * AT))) * x;
+    }
+}
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
 // q-th block of the upper triangle of an n x n block matrix, row-major: (bi, bj) with bi <= bj
@@ -294,8 +306,8 @@ __global__ __launch_bounds__(NT, 1) void k_atom_gram(const GramArgs a) {
 // fp32 sums (60 registers for 72 atoms) and the doubles (120) leave no room for the rest at two wavefronts per SIMD, so half of the
 // doubles live in LDS; one wavefront per SIMD holds all in registers but waits for memory (865 us against 660 below).
 // Before, eight wavefronts per workgroup in two roles passed 64-sample tiles through LDS, a barrier per channel.  Up-sampling and
-// normal equations, 72 atoms of 5x5, before / now, us: 1920 x 1080 x3 fp16 766 / 659 (the 35 + 60 matrix instructions of
-// every item are 480 of it), 1304 x 1134 x3 fp8 636 / 486, 160 x 112 x3 every second pixel 32.5 / 22; 60 atoms 1302 x 1227 x1 328 /
+// normal equations, 72 atoms of 5x5, before / now, us: 1920 x 1080 x3 fp16 766 / 645 (the 35 + 60 matrix instructions of
+// every item are 480 of it), 1304 x 1134 x3 fp8 636 / 485, 160 x 112 x3 every second pixel 32.5 / 22; 60 atoms 1302 x 1227 x1 328 /
 // 149; 40 atoms 268 x 218 x3 53 / 25.
 // ---------------------------------------------------------------------------
 constexpr int NTT = 512;         // at most eight wavefronts
@@ -386,7 +398,7 @@ __global__ __launch_bounds__(NTT, 2) void k_atom_gram_tri(const GramArgs a, unsi
     const bool holds_target = c16 == (a.L & 15);                      // column L is the target: this lane's, in block L / 16
     const int tblk = a.L >> 4;
 
-    // Element offsets within a plane: the patch operands (lane: sample c16, tap 4 ks + kq) and the lane's four samples.  Samples
+    // Offsets within a plane: the patch operands in bytes (lane: sample c16, tap 4 ks + kq), the lane's four samples in elements.  Samples
     // past the end of the row are clamped to its last one and their responses zeroed.
     unsigned aoff[KS], soff[4];
     int left = 0;                                                     // samples of the item that exist, from 4 kq on
@@ -397,7 +409,7 @@ __global__ __launch_bounds__(NTT, 2) void k_atom_gram_tri(const GramArgs a, unsi
         if (moved && seg_ >= 2 && x0 + 15 <= xl && (x0 + 15) * a.stride + R < a.W) {
             const unsigned by = 16u * (unsigned)a.stride;
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) aoff[ks] += by;
+            for (int ks = 0; ks < KS; ++ks) aoff[ks] += 4u * by;
 #pragma unroll
             for (int e = 0; e < 4; ++e) soff[e] += by;
             return;
@@ -406,7 +418,7 @@ __global__ __launch_bounds__(NTT, 2) void k_atom_gram_tri(const GramArgs a, unsi
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             const int tap = 4 * ks + kq, t = tap < KK ? tap : 0, dy = t / K, dx = t - dy * K;
-            aoff[ks] = (unsigned)clampi(Y + dy - R, 0, a.H - 1) * (unsigned)a.W + (unsigned)clampi(Xc + dx - R, 0, a.W - 1);
+            aoff[ks] = 4u * ((unsigned)clampi(Y + dy - R, 0, a.H - 1) * (unsigned)a.W + (unsigned)clampi(Xc + dx - R, 0, a.W - 1));
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -414,22 +426,29 @@ __global__ __launch_bounds__(NTT, 2) void k_atom_gram_tri(const GramArgs a, unsi
             soff[e] = (unsigned)Y * (unsigned)a.W + (unsigned)((x < xl ? x : xl) * a.stride);
         }
     };
+    // the lane's four samples side by side in memory (stride 1, all of them in the row, of every lane): one load
+    auto adjacent = [&](int left_) { return a.stride == 1 && __builtin_amdgcn_ballot_w64(left_ < 4) == 0; };
     float av[KS], h[4];
     auto fetch = [&](int n_, int c_) {                                // an item's patch operands and targets
         const size_t pl = ((size_t)n_ * a.C + c_) * plane;
         const char* const up = (const char*)(a.up + pl);
         const char* const tg = (const char*)(a.target + pl);
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) av[ks] = *(const float*)(up + 4u * aoff[ks]);
+        for (int ks = 0; ks < KS; ++ks) av[ks] = *(const float*)(up + aoff[ks]);
+        if (adjacent(left)) {
+            typedef float four __attribute__((ext_vector_type(4), aligned(4)));
+            const four v = *(const four*)(tg + 4u * soff[0]);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) h[e] = *(const float*)(tg + 4u * soff[e]);
+            for (int e = 0; e < 4; ++e) h[e] = v[e];
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) h[e] = *(const float*)(tg + 4u * soff[e]);
+        }
     };
     unsigned phi[N16][4];                                             // as stored
     typedef typename BitsOf<sizeof(TC)>::type Bits;
     constexpr int VW = sizeof(TC);                                    // words of four side by side
     typedef unsigned words __attribute__((ext_vector_type(VW == 1 ? 2 : VW), aligned(sizeof(TC))));
-    // the lane's four samples side by side in memory (stride 1, all of them in the row, of every lane): one load
-    auto adjacent = [&](int left_) { return a.stride == 1 && __builtin_amdgcn_ballot_w64(left_ < 4) == 0; };
     // Elements from a block's first plane to the lane's; 16 planes stay below 4 GB, see atom_gram.  Lanes past the last atom
     // take its plane (the last block may hold the target column only: its first plane is the last atom's then).
     const int last_block = 16 * (N16 - 1) < a.L ? 16 * (N16 - 1) : a.L - 1;
@@ -538,15 +557,17 @@ __global__ __launch_bounds__(NTT, 2) void k_atom_gram_tri(const GramArgs a, unsi
             for (int e = 0; e < 4; ++e) asm volatile("" : "+v"(phi[nb][e]));   // (widened anew for each channel)
         if (sizeof(TC) != 4 && adj) {
 #pragma unroll
-            for (int nb = 0; nb < N16; ++nb)
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    r[nb][e] = widen(from_bits<TC>(phi[nb][e * VW / 4] >> (8 * (e * VW % 4)))) * dot[nb][e];
+            for (int nb = 0; nb < N16; ++nb) {
+                r[nb][0] = times_stored<TC, 0>(phi[nb][0], dot[nb][0]);
+                r[nb][1] = times_stored<TC, VW % 4>(phi[nb][VW / 4], dot[nb][1]);
+                r[nb][2] = times_stored<TC, 2 * VW % 4>(phi[nb][2 * VW / 4], dot[nb][2]);
+                r[nb][3] = times_stored<TC, 3 * VW % 4>(phi[nb][3 * VW / 4], dot[nb][3]);
+            }
         } else {
 #pragma unroll
             for (int nb = 0; nb < N16; ++nb)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) r[nb][e] = widen(from_bits<TC>(phi[nb][e])) * dot[nb][e];
+                for (int e = 0; e < 4; ++e) r[nb][e] = times_stored<TC, 0>(phi[nb][e], dot[nb][e]);
         }
 #pragma unroll
         for (int nb = 0; nb < N16; ++nb)
