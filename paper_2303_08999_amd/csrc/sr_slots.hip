@@ -18,8 +18,15 @@ bool slots_supported(const AssembleArgs& a, int k) {
     // Few atoms: the generic kernel's time grows with them, this one's hardly below the 32 that its smallest instantiation
     // folds.  Before the pixel-shuffle, generic / this, us: 1060 x 1020 x1 fp32 5x5 14 atoms 34 / 39, 24 atoms 55 / 39; 7x7 24 atoms 64 / 65;
     // x3 fp8 5x5 24 atoms 52 / 54, 7x7 24 atoms 72 / 82, 3x3 14 atoms 33 / 34; bfloat16 5x5 6 atoms 29 / 36, 14 atoms 40 / 36.
-    if (!a.logits && a.n_fold <= (a.coeff_dtype == SR_F32 ? (k == 7 ? 26 : 16)
+    if (!a.logits && a.n_fold <= (a.coeff_dtype == SR_F32 ? (k == 7 ? 26 : k == 3 ? 22 : 16)
                                   : a.coeff_dtype == SR_F8E4M3 ? (a.C == 1 ? 10 : k == 3 ? 14 : k == 5 ? 25 : 32) : 12)) return false;
+    // 7x7 atoms before the pixel-shuffle, beyond small frames: the two blocks of matrix instructions of every slot and the wide tiles
+    // cost more than the generic kernel's fold until there are many atoms.  1350 thousand pixels x3 fp8 33 atoms 121 / 252, 60 atoms 189 /
+    // 252, all of 128 390 / 279; fp32 33 atoms 124 / 165, 60 atoms 195 / 164, 80 atoms 255 / 266; but 103 thousand fp8 33 atoms 32 / 25.
+    if (!a.logits && a.pre_shuffle && k == 7 && (long long)a.N * a.H * a.W > 150000) {
+        if (a.coeff_dtype == SR_F8E4M3 && a.C != 1 && a.n_fold <= 90) return false;
+        if (a.coeff_dtype == SR_F32 && (a.n_fold <= 48 || (a.C != 1 && a.n_fold > 72 && a.n_fold <= 84))) return false;
+    }
     if (a.logits && (a.n_fold != a.L || a.coeff_dtype == SR_F8E4M3)) return false;
     if ((a.pre_shuffle ? a.w : a.W) < 4 / cb || a.H < 1) return false;
     if ((unsigned long long)a.L * a.H * a.W * cb >= (1ull << 32)) return false;
