@@ -6,8 +6,8 @@
 // Eq. 3 are never written to memory.
 //
 // This kernel is bound by the fp32 ALUs (L*k^2 multiply-adds per pixel), not by
-// HBM; the matrix-core kernel (sr_mfma_kernel.h) is the fast path wherever it
-// qualifies.
+// HBM; the matrix-core kernels (sr_mfma_kernel.h, sr_slots.h) are the fast path
+// wherever they qualify.
 #include <string.h>
 
 #include "sr_device.h"
