@@ -367,6 +367,15 @@ void k_assemble_slots(const SlotArgs a) {
         if (more) load_lr(nxt);
 
         const int units = a.th * cur.upr;
+        // A wavefront's first words of the next tile are requested with its last unit of this one.  The last tile of a row can have fewer
+        // units than wavefronts: one that has none here requests them now.
+        if constexpr (!PRE && P < 4) {
+            if (more && wave >= units) {
+                point_at(nxt, unit_of(nxt, wave));
+#pragma unroll
+                for (int i = 0; i < NLOAD; ++i) raw[i] = load_word(i);
+            }
+        }
         for (int u = wave; u < units; u += 4) {
             const Unit un = unit_of(cur, u);
             const unsigned ush = sh;

@@ -154,3 +154,20 @@ def test_an_infinite_image_value_stays_within_its_patches():
     inp["lr"][0, 0, 6, 20] = float("inf")
     a, b = (run(inp, wl, coeff, kernel, True, False) for kernel in (AUTO, GENERIC))
     assert torch.equal(torch.isfinite(a), torch.isfinite(b)) and not torch.isfinite(b).all()
+
+
+# More tiles than workgroups, tiles of one or two rows, and a last tile of a row with fewer units than a workgroup has wavefronts: those
+# that sit it out still have to fetch their first unit of the next tile
+@pytest.mark.parametrize("n, c, h, w, s, L, k, cd, logits", [
+    (1, 1, 104, 69, 4, 128, 5, "f32", False), (1, 3, 119, 135, 4, 100, 3, "f32", False), (1, 3, 164, 143, 4, 128, 7, "f32", False),
+    (1, 3, 280, 611, 2, 128, 7, "f32", False), (1, 1, 123, 289, 2, 56, 7, "f32", False), (4, 3, 131, 321, 2, 100, 3, "f32", False),
+    (1, 1, 172, 129, 2, 73, 5, "f32", False), (400, 1, 1, 260, 2, 72, 5, "f32", True), (400, 2, 1, 260, 2, 40, 5, "f16", True),
+    (1, 1, 219, 402, 2, 72, 3, "bf16", True), (1, 1, 146, 575, 3, 55, 3, "f16", True)])
+def test_wavefronts_without_a_unit_in_a_partial_tile(n, c, h, w, s, L, k, cd, logits):
+    wl = sr_synth.Workload("slotst", 73, n, c, h, w, s, L, k, cd, "f32", 0.0, 1.5)
+    inp, flat, coeff = make(wl, False, logits)
+    got = run(inp, wl, coeff, AUTO, False, logits)
+    gen = run(inp, wl, coeff, GENERIC, False, logits)
+    assert torch.isfinite(got).all()
+    tol = 2.5e-4 if logits else (5e-5 if cd != "bf16" else 1e-4)
+    assert float((got - gen).abs().max()) <= tol * max(1.0, float(gen.abs().max()))
