@@ -322,7 +322,22 @@ int sr_dict_assemble_walk(const sr_tensor* lr, const sr_tensor* coeff, const sr_
                           const sr_tensor* out,
                           const int* kept, int n_kept, const sr_options* opts,
                           int walk[6]);
-/* ... and of a list call (kernel as in sr_dict_assemble_list_ex). */
+/* The kernel that sr_dict_assemble_ex launches for these arguments, and its walk as above for either matrix-core kernel.  Negative:
+ * sr_status.  Host only. */
+typedef enum {
+    SR_RUNS_NOTHING   = 0,     /* an empty batch or image                          */
+    SR_RUNS_GENERIC   = 1,     /* the vector-ALU kernel                            */
+    SR_RUNS_STREAMING = 2,     /* the streaming matrix-core kernel                 */
+    SR_RUNS_SLOTS     = 3      /* the second matrix-core kernel, which serves most
+                                  of what sr_dict_assemble_plan calls generic and
+                                  some planar calls of the streaming kernel        */
+} sr_runs;
+int sr_dict_assemble_runs(const sr_tensor* lr, const sr_tensor* coeff, const sr_tensor* dict,
+                          int L, int k, int scale, int channels,
+                          const sr_tensor* out,
+                          const int* kept, int n_kept, const sr_options* opts,
+                          int walk[6]);
+/* sr_dict_assemble_walk of a list call (kernel as in sr_dict_assemble_list_ex). */
 int sr_dict_assemble_list_walk(const sr_tensor* lr, const sr_tensor* index, const sr_tensor* value,
                                const sr_tensor* dict, int L, int k, int scale, int channels, int entries,
                                const sr_tensor* out, int kernel, int walk[6]);

@@ -17,10 +17,11 @@ SR_F32, SR_F16, SR_F8E4M3, SR_BF16, SR_U8 = 0, 1, 2, 3, 4
 SR_KERNEL_AUTO, SR_KERNEL_GENERIC, SR_KERNEL_MFMA = 0, 1, 2
 SR_COEFF_PLANAR, SR_COEFF_PRE_SHUFFLE, SR_COEFF_PIXEL_MAJOR, SR_COEFF_BLOCKED = 0, 1, 2, 3
 SR_COEFF_VALUES, SR_COEFF_LOGITS = 0, 1
+SR_RUNS_NOTHING, SR_RUNS_GENERIC, SR_RUNS_STREAMING, SR_RUNS_SLOTS = 0, 1, 2, 3
 SR_MAX_ATOMS = 256
 
 EXPORTS = ("sr_dict_assemble", "sr_dict_assemble_selective", "sr_dict_assemble_ex", "sr_dict_assemble_list", "sr_dict_assemble_list_ex",
-           "sr_bicubic_upsample", "sr_dict_assemble_plan", "sr_dict_assemble_tile", "sr_dict_assemble_launch_shape", "sr_dict_assemble_walk", "sr_dict_assemble_list_walk", "sr_strerror", "sr_version",
+           "sr_bicubic_upsample", "sr_dict_assemble_plan", "sr_dict_assemble_tile", "sr_dict_assemble_launch_shape", "sr_dict_assemble_walk", "sr_dict_assemble_runs", "sr_dict_assemble_list_walk", "sr_strerror", "sr_version",
            "sr_probe_read", "sr_probe_mix", "sr_probe_mix_tiled", "sr_probe_mix_tiled_bytes", "sr_probe_mix_tiled_paced", "sr_probe_stream", "sr_probe_pattern", "sr_probe_policy", "sr_probe_policy_bits",
            "sr_atom_gram_workspace_bytes", "sr_atom_gram", "sr_atom_gram_static", "sr_select_atoms")
 
@@ -67,6 +68,7 @@ def load():
     lib.sr_dict_assemble_launch_shape.argtypes = [T, T, T, i, i, i, i, T, ip, i, O, ip]
     lib.sr_dict_assemble_launch_shape.restype = i
     lib.sr_dict_assemble_walk.argtypes = [T, T, T, i, i, i, i, T, ip, i, O, ip]
+    lib.sr_dict_assemble_runs.argtypes = [T, T, T, i, i, i, i, T, ip, i, O, ip]
     lib.sr_dict_assemble_list_walk.argtypes = [T, T, T, T, i, i, i, i, i, T, i, ip]
     lib.sr_bicubic_upsample.argtypes = [T, i, i, T, vp]
     lib.sr_strerror.argtypes = [i]
@@ -266,6 +268,17 @@ def sr_dict_assemble_walk(lr, coeff, dict, L, k, scale, channels, out, kept=None
     op = ctypes.byref(opts) if opts is not None else None
     walk = (ctypes.c_int * 6)()
     st = load().sr_dict_assemble_walk(a, b, c, L, k, scale, channels, o, ka, n, op, walk)
+    return st, tuple(walk)
+
+
+def sr_dict_assemble_runs(lr, coeff, dict, L, k, scale, channels, out, kept=None, n_kept=None, opts=None):
+    """(the kernel that is launched, SR_RUNS_*, or negative status; its walk); see the header."""
+    a, b, c, o = describe(lr), describe_coeff(coeff, opts), describe(_dict4(dict)), describe(out)
+    ka, n, _ga, _keep = _host_lists(kept, None)
+    n = n if n_kept is None else int(n_kept)
+    op = ctypes.byref(opts) if opts is not None else None
+    walk = (ctypes.c_int * 6)()
+    st = load().sr_dict_assemble_runs(a, b, c, L, k, scale, channels, o, ka, n, op, walk)
     return st, tuple(walk)
 
 

@@ -31,7 +31,7 @@ struct Plan {
     int status;      // SR_OK or an error
     int kernel;      // SR_KERNEL_GENERIC | SR_KERNEL_MFMA
     int tile;
-    bool slots;      // SR_KERNEL_GENERIC by the library's own choice, not the caller's: k_assemble_slots where it takes the call
+    bool slots;      // k_assemble_slots runs it: in place of the generic kernel (SR_KERNEL_AUTO only), or of the streaming one (its default tile only)
     bool empty;      // nothing to do
     AssembleArgs args;
 };
@@ -121,7 +121,13 @@ void make_plan(Plan& p, const sr_tensor* lr, const sr_tensor* coeff, const sr_te
     if ((want == SR_KERNEL_MFMA || (tile != 0 && want != SR_KERNEL_GENERIC)) && !can_mfma) { p.status = SR_ERR_UNSUPPORTED; return; }
     p.kernel = (want == SR_KERNEL_GENERIC || !can_mfma) ? SR_KERNEL_GENERIC : SR_KERNEL_MFMA;
     p.tile = tile;
-    p.slots = !p.empty && p.kernel == SR_KERNEL_GENERIC && want == SR_KERNEL_AUTO && slots_supported(a, k);
+    if (!p.empty) p.slots = p.kernel == SR_KERNEL_MFMA ? tile == 0 && slots_faster(a, k) : want == SR_KERNEL_AUTO && slots_supported(a, k);
+}
+
+// Launches a valid, non-empty plan, or says how it would be walked (see LaunchTo).
+hipError_t launch(const Plan& p, int k, const LaunchTo& st) {
+    if (p.slots) return launch_slots(p.args, k, st);
+    return p.kernel == SR_KERNEL_MFMA ? launch_mfma(p.args, k, p.args.io_f16, p.tile, st) : launch_generic(p.args, k, p.args.io_f16, st.stream);
 }
 
 }  // namespace
@@ -135,12 +141,7 @@ __attribute__((visibility("default"))) int sr_dict_assemble_ex(const sr_tensor* 
     make_plan(p, lr, coeff, dict, L, k, scale, channels, out, kept, n_kept, gamma, opts);
     if (p.status != SR_OK) return p.status;
     if (p.empty) return SR_OK;
-    const hipStream_t st = (hipStream_t)stream;
-    const bool io_f16 = lr->dtype == SR_F16;
-    hipError_t e = (p.kernel == SR_KERNEL_MFMA)
-                       ? launch_mfma(p.args, k, io_f16, p.tile, st)
-                       : p.slots ? launch_slots(p.args, k, st) : launch_generic(p.args, k, io_f16, st);
-    return e == hipSuccess ? SR_OK : SR_ERR_LAUNCH;
+    return launch(p, k, LaunchTo((hipStream_t)stream)) == hipSuccess ? SR_OK : SR_ERR_LAUNCH;
 }
 
 __attribute__((visibility("default"))) int sr_dict_assemble(const sr_tensor* lr, const sr_tensor* coeff, const sr_tensor* dict,
@@ -198,10 +199,23 @@ __attribute__((visibility("default"))) int sr_dict_assemble_walk(const sr_tensor
     make_plan(p, lr, coeff, dict, L, k, scale, channels, out, kept, n_kept, nullptr, opts);
     if (p.status != SR_OK) return p.status;
     Walk w = {};
-    if (p.kernel == SR_KERNEL_MFMA && !p.empty && launch_mfma(p.args, k, lr->dtype == SR_F16, p.tile, LaunchTo(&w)) != hipSuccess)
-        return SR_ERR_LAUNCH;
+    if (p.kernel == SR_KERNEL_MFMA && !p.empty && launch(p, k, LaunchTo(&w)) != hipSuccess) return SR_ERR_LAUNCH;
     memcpy(walk, &w, sizeof(w));
     return p.kernel;
+}
+
+__attribute__((visibility("default"))) int sr_dict_assemble_runs(const sr_tensor* lr, const sr_tensor* coeff, const sr_tensor* dict,
+                          int L, int k, int scale, int channels, const sr_tensor* out,
+                          const int* kept, int n_kept, const sr_options* opts, int walk[6]) {
+    if (!walk) return SR_ERR_NULL;
+    Plan p;
+    make_plan(p, lr, coeff, dict, L, k, scale, channels, out, kept, n_kept, nullptr, opts);
+    if (p.status != SR_OK) return p.status;
+    Walk w = {};
+    const bool matrix = !p.empty && (p.slots || p.kernel == SR_KERNEL_MFMA);
+    if (matrix && launch(p, k, LaunchTo(&w)) != hipSuccess) return SR_ERR_LAUNCH;
+    memcpy(walk, &w, sizeof(w));
+    return p.empty ? SR_RUNS_NOTHING : p.slots ? SR_RUNS_SLOTS : p.kernel == SR_KERNEL_MFMA ? SR_RUNS_STREAMING : SR_RUNS_GENERIC;
 }
 
 __attribute__((visibility("default"))) int sr_bicubic_upsample(const sr_tensor* lr, int scale, int channels, sr_tensor* out, void* stream) {

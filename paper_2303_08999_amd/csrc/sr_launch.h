@@ -22,7 +22,7 @@ struct LaunchTo {
 // Matrix-core kernel.  mfma_supported() is a pure host-side predicate.
 bool mfma_supported(const AssembleArgs& a, int k, int coeff_dtype, int tile);
 hipError_t launch_mfma(const AssembleArgs& a, int k, bool io_f16, int tile, const LaunchTo& st);
-// Matrix-core kernel for calls the one above has no instantiation for (coefficient dtype: a.coeff_dtype)
+// Matrix-core kernel for calls the one above has no instantiation for (coefficient dtype: a.coeff_dtype); make_plan chooses
 bool slots_supported(const AssembleArgs& a, int k);
 bool slots_faster(const AssembleArgs& a, int k);       // ... and those that it has one for but serves slower
 hipError_t launch_slots(const AssembleArgs& a, int k, const LaunchTo& st);

@@ -146,7 +146,6 @@ bool mfma_supported(const AssembleArgs& a, int k, int coeff_dtype, int tile) {
 hipError_t launch_mfma(const AssembleArgs& a, int k, bool io_f16, int tile, const LaunchTo& st) {
     (void)io_f16;
     const int np8 = np8_for(k, a.C, a.n_fold, a.coeff_dtype);
-    if (tile == 0 && slots_faster(a, k)) return launch_slots(a, k, st);
     if (a.blocked) return launch_mfma_k5_blk(a, st);
     if (a.logits) return launch_mfma_k5_lg(a, st);
     if (a.pixel_major) return launch_mfma_k5_pm(a, st);

@@ -29,11 +29,12 @@ def run(inp, wl, coeff, kernel, pre, logits, kept=None, gamma=None):
     return out
 
 
-def planned(inp, wl, coeff, pre, logits, kept):
+def runs(inp, wl, coeff, pre, logits, kept=None):
+    """The kernel that AUTO launches, and its walk."""
     opts = sr.make_options(AUTO, 0, sr.SR_COEFF_PRE_SHUFFLE if pre else sr.SR_COEFF_PLANAR,
                            sr.SR_COEFF_LOGITS if logits else sr.SR_COEFF_VALUES)
     out = torch.empty((wl.n, wl.c, wl.H, wl.W), device=DEV, dtype=inp["lr"].dtype)
-    return sr.sr_dict_assemble_plan(inp["lr"], coeff, inp["dict"], wl.L, wl.k, wl.scale, wl.c, out, kept=kept, opts=opts)
+    return sr.sr_dict_assemble_runs(inp["lr"], coeff, inp["dict"], wl.L, wl.k, wl.scale, wl.c, out, kept=kept, opts=opts)
 
 
 def make(wl, pre, logits):
@@ -55,7 +56,11 @@ CASES = [
     (2, 3, 9, 50, 2, 50, 3, "f32", "f32", False, True, None), (1, 3, 6, 33, 4, 96, 5, "f16", "f32", True, True, None),
     (1, 1, 12, 29, 3, 72, 7, "f32", "f32", True, True, None), (1, 3, 7, 70, 2, 9, 5, "bf16", "f32", True, True, None),
     (1, 3, 11, 17, 3, 72, 7, "f8", "f32", False, False, 9), (1, 2, 30, 65, 2, 72, 5, "f8", "f32", False, False, None),
+    (1, 3, 4, 2, 4, 13, 5, "bf16", "f32", True, False, None), (1, 1, 3, 4, 2, 11, 3, "f8", "f32", True, False, None),
+    (1, 2, 10, 1, 3, 17, 5, "f32", "f32", True, False, None), (1, 3, 11, 17, 3, 72, 7, "f8", "f32", False, False, 33),
 ]
+# those that are left to the generic kernel, and the same with one atom more than its lists have (above)
+FEW_ATOMS = [c for c in CASES if (c[5], c[6], c[7], c[11]) in ((1, 5, "bf16", None), (8, 3, "f8", None), (16, 5, "f32", None), (72, 7, "f8", 9))]
 
 
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "N%dC%dh%dw%ds%dL%dk%d%s%s-%d%d-%s" % c)
@@ -68,7 +73,7 @@ def test_against_the_oracle(oracle, case):
         rng = np.random.default_rng(nk)
         kept = np.sort(rng.choice(L, size=nk, replace=False)).astype(np.int32)
         gamma = rng.uniform(0.5, 1.5, size=nk).astype(np.float32)
-    assert planned(inp, wl, coeff, pre, logits, kept) == GENERIC           # (what the plan calls everything outside the streaming kernel)
+    assert runs(inp, wl, coeff, pre, logits, kept)[0] == (sr.SR_RUNS_GENERIC if case in FEW_ATOMS else sr.SR_RUNS_SLOTS)
     got = run(inp, wl, coeff, AUTO, pre, logits, kept, gamma)
     hi = host(inp)
     phi = oracle.softmax_logits(sr_synth.stored_numpy(flat)) if logits else sr_synth.stored_numpy(flat)
@@ -106,7 +111,7 @@ def test_random_shapes_against_the_generic_kernel():
             nk = int(rng.integers(1, L + 1))
             kept = np.sort(rng.choice(L, size=nk, replace=False)).astype(np.int32)
             gamma = rng.uniform(0.5, 1.5, size=nk).astype(np.float32)
-        if planned(inp, wl, coeff, pre, logits, kept) != GENERIC:
+        if runs(inp, wl, coeff, pre, logits, kept)[0] != sr.SR_RUNS_SLOTS:
             continue
         a = run(inp, wl, coeff, AUTO, pre, logits, kept, gamma).float()
         b = run(inp, wl, coeff, GENERIC, pre, logits, kept, gamma).float()
@@ -131,10 +136,7 @@ def test_random_shapes_against_the_generic_kernel():
 def test_planar_calls_that_are_faster_here(oracle, n, c, h, w, s, L, k, cd, io, slots):
     wl = sr_synth.Workload("slotsp", 72, n, c, h, w, s, L, k, cd, io, 0.0, 1.5)
     inp = sr_synth.make_inputs(wl, DEV)
-    out = torch.empty((n, c, wl.H, wl.W), device=DEV, dtype=inp["lr"].dtype)
-    kernel, walk = sr.sr_dict_assemble_walk(inp["lr"], inp["coeff"], inp["dict"], L, k, s, c, out)
-    # (its tiles have up to eight rows and 128 columns; the streaming kernel's of that width have four, sixteen or twenty-four)
-    assert kernel == sr.SR_KERNEL_MFMA and (walk[0] == 1 and walk[1] == 128 and walk[2] in (1, 2, 4, 8)) >= slots
+    assert runs(inp, wl, inp["coeff"], False, False)[0] == (sr.SR_RUNS_SLOTS if slots else sr.SR_RUNS_STREAMING)
     got = run(inp, wl, inp["coeff"], sr.SR_KERNEL_MFMA, False, False)
     gen = run(inp, wl, inp["coeff"], GENERIC, False, False)
     assert torch.isfinite(got).all()
@@ -166,6 +168,9 @@ def test_an_infinite_image_value_stays_within_its_patches():
 def test_wavefronts_without_a_unit_in_a_partial_tile(n, c, h, w, s, L, k, cd, logits):
     wl = sr_synth.Workload("slotst", 73, n, c, h, w, s, L, k, cd, "f32", 0.0, 1.5)
     inp, flat, coeff = make(wl, False, logits)
+    kernel, (form, width, rows, tiles, workgroups, waves) = runs(inp, wl, coeff, False, logits)
+    units = rows * -(-(wl.W % width) // (32 if cd == "f32" else 64))         # of a partial tile
+    assert kernel == sr.SR_RUNS_SLOTS and tiles > workgroups and 0 < units < waves
     got = run(inp, wl, coeff, AUTO, False, logits)
     gen = run(inp, wl, coeff, GENERIC, False, logits)
     assert torch.isfinite(got).all()

@@ -151,3 +151,29 @@ def test_images_up_to_4_gb_are_the_matrix_core_kernels():
         for cd, L in (("f8", 4), ("f16", 2), ("bf16", 2)):
             assert walk(C=1, H=H, W=W, s=3, L=L, k=k, cd=cd, kernel=sr.SR_KERNEL_MFMA)[1][0] == STRIPS
     assert walk(C=1, H=1 << 15, W=1 << 15, s=2, L=1, cd="f8", kernel=sr.SR_KERNEL_MFMA)[0] == -3
+
+
+def runs(n=1, C=3, H=2160, W=3840, s=4, L=72, k=5, cd="f16", kept=None, pre=False, logits=False, kernel=sr.SR_KERNEL_AUTO, tile=0):
+    lr, coeff, d, out = _far((sr.SR_F32, n, C, H // s, W // s), (DT[cd], n, L * s * s, H // s, W // s) if pre else (DT[cd], n, L, H, W),
+                             (sr.SR_F32, 1, L, k, k), (sr.SR_F32, n, C, H, W))
+    opts = sr.make_options(kernel, tile, sr.SR_COEFF_PRE_SHUFFLE if pre else sr.SR_COEFF_PLANAR, sr.SR_COEFF_LOGITS if logits else sr.SR_COEFF_VALUES)
+    ka = (ctypes.c_int * len(kept))(*kept) if kept else None
+    w = (ctypes.c_int * 6)(*[-1] * 6)
+    return sr.load().sr_dict_assemble_runs(lr, coeff, d, L, k, s, C, out, ka, len(kept or ()), ctypes.byref(opts), w), tuple(w)
+
+
+def test_the_kernel_that_is_launched():
+    """Where sr_dict_assemble_plan knows two answers, sr_dict_assemble_runs knows three, and the walk of both matrix-core kernels."""
+    assert runs() == (sr.SR_RUNS_STREAMING, walk()[1])
+    assert runs(kernel=sr.SR_KERNEL_GENERIC) == (sr.SR_RUNS_GENERIC, (0,) * 6)
+    assert runs(H=0) == (sr.SR_RUNS_NOTHING, (0,) * 6)
+    assert runs(tile=10)[0] == runs(C=2, cd="f32", kernel=sr.SR_KERNEL_MFMA)[0] == -3 and runs(kept=[72])[0] < 0
+    for call in (dict(C=2, cd="f32"), dict(pre=True, cd="f8"), dict(logits=True, k=3), dict(logits=True, cd="f32", pre=True)):
+        kernel, got = runs(**call)
+        assert kernel == sr.SR_RUNS_SLOTS and got[0] == TILES
+        assert runs(**call, kernel=sr.SR_KERNEL_GENERIC) == (sr.SR_RUNS_GENERIC, (0,) * 6)
+    small = dict(C=1, H=128, W=128, s=2, cd="f32")       # a planar call that it has from the streaming kernel
+    assert runs(**small) == runs(**small, kernel=sr.SR_KERNEL_MFMA) == (sr.SR_RUNS_SLOTS, walk(**small)[1])
+    assert runs(C=5, cd="f16") == runs(L=200) == (sr.SR_RUNS_GENERIC, (0,) * 6)
+    lr, coeff, d, out = _far(*[(sr.SR_F32, 1, 3, 8, 8)] * 4)
+    assert sr.load().sr_dict_assemble_runs(lr, coeff, d, 72, 5, 4, 3, out, None, 0, None, None) == -1
