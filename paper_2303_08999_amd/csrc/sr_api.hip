@@ -126,7 +126,7 @@ void make_plan(Plan& p, const sr_tensor* lr, const sr_tensor* coeff, const sr_te
 
 // Launches a valid, non-empty plan, or says how it would be walked (see LaunchTo).
 hipError_t launch(const Plan& p, int k, const LaunchTo& st) {
-    if (p.slots) return launch_slots(p.args, k, st);
+    if (p.slots) return launch_slots(p.args, k, p.kernel == SR_KERNEL_MFMA, st);
     return p.kernel == SR_KERNEL_MFMA ? launch_mfma(p.args, k, p.args.io_f16, p.tile, st) : launch_generic(p.args, k, p.args.io_f16, st.stream);
 }
 

@@ -25,7 +25,7 @@ hipError_t launch_mfma(const AssembleArgs& a, int k, bool io_f16, int tile, cons
 // Matrix-core kernel for calls the one above has no instantiation for (coefficient dtype: a.coeff_dtype); make_plan chooses
 bool slots_supported(const AssembleArgs& a, int k);
 bool slots_faster(const AssembleArgs& a, int k);       // ... and those that it has one for but serves slower
-hipError_t launch_slots(const AssembleArgs& a, int k, const LaunchTo& st);
+hipError_t launch_slots(const AssembleArgs& a, int k, bool streamed, const LaunchTo& st);      // streamed: with the streaming kernel's bits
 // Per-pixel list form (sr_dict_assemble_list) on the matrix cores: a.coeff = values, a.index, a.T set; kept = identity.
 bool mfma_list_supported(const AssembleArgs& a, int k, bool value_f16);
 hipError_t launch_mfma_list(const AssembleArgs& a, const LaunchTo& st);

@@ -1,6 +1,7 @@
 // Matrix-core kernel for calls that the streaming kernel (sr_mfma_kernel.h) has no instantiation for: coefficients before the
 // network's pixel-shuffle and logits, for every coefficient type, atom size and scale, one to three channels, up to 128 folded
-// atoms, any width; and planar coefficients in the few cases that are left.  They ran on the generic kernel, which folds on the
+// atoms, any width; planar coefficients in two channels, narrow ragged frames and the like; and planar calls of the streaming kernel that are
+// faster here (slots_faster).  All but the last ran on the generic kernel, which folds on the
 // vector ALUs and reads a pixel's coefficients eight at a time, one memory latency after the other: that is what bounded all but the
 // largest of them.  Here a wavefront takes a UNIT, 32 lanes times the pixels of a 32-bit word of coefficients, requests all of its
 // coefficients at once, and folds it on the matrix cores.
@@ -21,7 +22,8 @@
 //
 // Precision: fp32 coefficients go through v_mfma_f32_32x32x2_f32 (products and sums fp32).  16- and 8-bit ones and the
 // exponentials of logits meet the dictionary as 16-bit parts: fp16, the first part and the rest scaled by 2^11 into a sum of its own, 22
-// significant bits also where the rest alone would be subnormal; bfloat16 three parts, 24 bits.  Against 64-bit arithmetic two drawn calls went from
+// significant bits also where the rest alone would be subnormal; bfloat16 three parts, 24 bits.  (Calls of the streaming kernel: its parts, its
+// order, its bits.)  Against 64-bit arithmetic two drawn calls went from
 // 1.0e-7 and 1.1e-7 in the generic kernel to 7.6e-8 and 6.8e-8.
 #pragma once
 #include <string.h>
@@ -44,14 +46,20 @@ struct SlotArgs {
     float gamma[SR_MAX_ATOMS];
 };
 
-template <int K, int CM, int CT, int NP8, bool LG, bool PRE>
+// What a call brings: coefficients or logits, whose dictionary keeps (nearly) all bits of fp32 as in the generic kernel, which served them
+// before; or coefficients that the streaming kernel has an instantiation for too: its two parts in one sum, in its order, so that these calls have
+// its bits, whichever kernel their size sends them to.
+constexpr int SLOT_VALUES = 0, SLOT_LOGITS = 1, SLOT_STREAMED = 2;
+
+template <int K, int CM, int CT, int NP8, int KIND, bool PRE>
 struct SlotCfg {
+    static constexpr bool LG = KIND == SLOT_LOGITS, ST = KIND == SLOT_STREAMED;
     static constexpr int KK = K * K, R = (K - 1) / 2, RH0 = (K + 1) / 2, NSLOT = RH0 * K, NMB = (NSLOT + 15) / 16;
     static constexpr int CB = CT == CT_F32 ? 4 : (CT == CT_F8 ? 1 : 2), P = 4 / CB;      // bytes of a coefficient, pixels of a word
     static constexpr bool F32 = CT == CT_F32 && !LG;                   // fp32 matrix instructions
     static constexpr bool BF = CT == CT_BF16 && !LG;                   // bfloat16 ones (logits: fp16, whatever they are stored as)
-    static constexpr int NPART = F32 ? 1 : (BF ? 3 : 2);               // 16-bit parts of a dictionary entry
-    static constexpr int NACC = F32 || BF ? 1 : 2;                     // sums: fp16's second part has its own
+    static constexpr int NPART = F32 ? 1 : (BF && !ST ? 3 : 2);        // 16-bit parts of a dictionary entry
+    static constexpr int NACC = F32 || BF || ST ? 1 : 2;               // sums: fp16's second part has its own
     static constexpr int QG = P * NMB * NACC <= 4 ? P : (NMB * NACC <= 2 ? 2 : 1);   // slots folded together (registers)
     static constexpr int QGP = QG < P ? QG : P;
     static constexpr int N16 = F32 ? 0 : NP8 / 2, N8 = F32 ? 0 : NP8 % 2, N2 = F32 ? 4 * NP8 : 0;
@@ -70,10 +78,11 @@ struct SlotCfg {
 
 constexpr float SLOT_LO = 2048.0f;       // scale of fp16's second part
 
-template <int K, int CM, int CT, int NP8, bool LG, bool PRE>
-__global__ __launch_bounds__(256, (SlotCfg<K, CM, CT, NP8, LG, PRE>::WPE))
+template <int K, int CM, int CT, int NP8, int KIND, bool PRE>
+__global__ __launch_bounds__(256, (SlotCfg<K, CM, CT, NP8, KIND, PRE>::WPE))
 void k_assemble_slots(const SlotArgs a) {
-    using F = SlotCfg<K, CM, CT, NP8, LG, PRE>;
+    using F = SlotCfg<K, CM, CT, NP8, KIND, PRE>;
+    constexpr bool LG = F::LG;
     constexpr int KK = F::KK, R = F::R, RH0 = F::RH0, NSLOT = F::NSLOT, NMB = F::NMB, P = F::P, NPART = F::NPART, NACC = F::NACC;
     constexpr int N16 = F::N16, N8 = F::N8, NLOAD = F::NLOAD, UH = F::UH, PITCH = F::PITCH, MAXLRX = F::MAXLRX, MAXLRY = F::MAXLRY, QG = F::QGP;
     constexpr unsigned CB = F::CB;
@@ -242,7 +251,7 @@ void k_assemble_slots(const SlotArgs a) {
             } else if constexpr (!F::F32) {
                 const _Float16 v = (_Float16)d[i];
                 b[0][i] = __builtin_bit_cast(unsigned short, v);
-                b[1][i] = __builtin_bit_cast(unsigned short, (_Float16)((d[i] - (float)v) * SLOT_LO));
+                b[1][i] = __builtin_bit_cast(unsigned short, (_Float16)((d[i] - (float)v) * (NACC == 2 ? SLOT_LO : 1.0f)));
             }
         }
 #pragma unroll
@@ -567,9 +576,9 @@ void k_assemble_slots(const SlotArgs a) {
     }
 }
 
-template <int K, int CM, int CT, int NP8, bool LG, bool PRE>
+template <int K, int CM, int CT, int NP8, int KIND, bool PRE>
 static hipError_t launch_slots_p(const AssembleArgs& c, const LaunchTo& st) {
-    using F = SlotCfg<K, CM, CT, NP8, LG, PRE>;
+    using F = SlotCfg<K, CM, CT, NP8, KIND, PRE>;
     SlotArgs a;
     a.lr = c.lr; a.coeff = c.coeff; a.dict = c.dict; a.out = c.out;
     a.N = c.N; a.C = c.C; a.h = c.h; a.w = c.w; a.H = c.H; a.W = c.W; a.s = c.s; a.L = c.L;
@@ -610,29 +619,40 @@ static hipError_t launch_slots_p(const AssembleArgs& c, const LaunchTo& st) {
         *st.walk = {1, tw, a.th, a.ntiles, blocks, 4};
         return hipSuccess;
     }
-    hipLaunchKernelGGL((k_assemble_slots<K, CM, CT, NP8, LG, PRE>), dim3(blocks), dim3(256), 0, st.stream, a);
+    hipLaunchKernelGGL((k_assemble_slots<K, CM, CT, NP8, KIND, PRE>), dim3(blocks), dim3(256), 0, st.stream, a);
     return hipGetLastError();
 }
 
-template <int K, int CM, int CT, int NP8, bool LG>
+template <int K, int CM, int CT, int NP8, int KIND>
 static hipError_t launch_slots_n(const AssembleArgs& a, const LaunchTo& st) {
-    return a.pre_shuffle ? launch_slots_p<K, CM, CT, NP8, LG, true>(a, st) : launch_slots_p<K, CM, CT, NP8, LG, false>(a, st);
+    if constexpr (KIND != SLOT_STREAMED)
+        if (a.pre_shuffle) return launch_slots_p<K, CM, CT, NP8, KIND, true>(a, st);
+    return launch_slots_p<K, CM, CT, NP8, KIND, false>(a, st);
 }
 
-template <int K, int CM, int CT, bool LG>
+template <int K, int CM, int CT, int KIND>
 static hipError_t launch_slots_k(const AssembleArgs& a, const LaunchTo& st) {
-    if (a.n_fold <= 32) return launch_slots_n<K, CM, CT, 4, LG>(a, st);
-    if (a.n_fold <= 72) return launch_slots_n<K, CM, CT, 9, LG>(a, st);
-    return launch_slots_n<K, CM, CT, 16, LG>(a, st);
+    if (a.n_fold <= 32) return launch_slots_n<K, CM, CT, 4, KIND>(a, st);
+    if (a.n_fold <= 72) return launch_slots_n<K, CM, CT, 9, KIND>(a, st);
+    return launch_slots_n<K, CM, CT, 16, KIND>(a, st);
+}
+
+template <int K, int CM, int CT>
+static hipError_t launch_slots_v(const AssembleArgs& a, bool streamed, const LaunchTo& st) {
+    if constexpr (CT != CT_F32)                        // (fp32 matrix instructions: one part, the same bits)
+        if (streamed) return launch_slots_k<K, CM, CT, SLOT_STREAMED>(a, st);
+    if constexpr (CT != CT_F8)
+        if (a.logits) return launch_slots_k<K, CM, CT, SLOT_LOGITS>(a, st);
+    return launch_slots_k<K, CM, CT, SLOT_VALUES>(a, st);
 }
 
 template <int K, int CM>
-static hipError_t launch_slots_t(const AssembleArgs& a, const LaunchTo& st) {
+static hipError_t launch_slots_t(const AssembleArgs& a, bool streamed, const LaunchTo& st) {
     switch (a.coeff_dtype) {
-    case SR_F16:  return a.logits ? launch_slots_k<K, CM, CT_F16, true>(a, st) : launch_slots_k<K, CM, CT_F16, false>(a, st);
-    case SR_BF16: return a.logits ? launch_slots_k<K, CM, CT_BF16, true>(a, st) : launch_slots_k<K, CM, CT_BF16, false>(a, st);
-    case SR_F32:  return a.logits ? launch_slots_k<K, CM, CT_F32, true>(a, st) : launch_slots_k<K, CM, CT_F32, false>(a, st);
-    default:      return launch_slots_k<K, CM, CT_F8, false>(a, st);
+    case SR_F16:  return launch_slots_v<K, CM, CT_F16>(a, streamed, st);
+    case SR_BF16: return launch_slots_v<K, CM, CT_BF16>(a, streamed, st);
+    case SR_F32:  return launch_slots_v<K, CM, CT_F32>(a, streamed, st);
+    default:      return launch_slots_v<K, CM, CT_F8>(a, streamed, st);
     }
 }
 }  // namespace srd

@@ -3,12 +3,12 @@
 
 namespace srd {
 
-hipError_t launch_slots_k3c1(const AssembleArgs& a, const LaunchTo& st);
-hipError_t launch_slots_k3c3(const AssembleArgs& a, const LaunchTo& st);
-hipError_t launch_slots_k5c1(const AssembleArgs& a, const LaunchTo& st);
-hipError_t launch_slots_k5c3(const AssembleArgs& a, const LaunchTo& st);
-hipError_t launch_slots_k7c1(const AssembleArgs& a, const LaunchTo& st);
-hipError_t launch_slots_k7c3(const AssembleArgs& a, const LaunchTo& st);
+hipError_t launch_slots_k3c1(const AssembleArgs& a, bool streamed, const LaunchTo& st);
+hipError_t launch_slots_k3c3(const AssembleArgs& a, bool streamed, const LaunchTo& st);
+hipError_t launch_slots_k5c1(const AssembleArgs& a, bool streamed, const LaunchTo& st);
+hipError_t launch_slots_k5c3(const AssembleArgs& a, bool streamed, const LaunchTo& st);
+hipError_t launch_slots_k7c1(const AssembleArgs& a, bool streamed, const LaunchTo& st);
+hipError_t launch_slots_k7c3(const AssembleArgs& a, bool streamed, const LaunchTo& st);
 
 // Up to 128 folded atoms, one to three channels, every atom's coefficients of an image within 4 GB, rows of at least one word of
 // coefficients; the generic kernel takes what is left.
@@ -72,11 +72,11 @@ bool slots_faster(const AssembleArgs& a, int k) {
     return (k == 3 ? n > 32 : a.C == 1 && n > 48 && f16) && px > 180000 && px <= 600000 && (a.s != 4 || px <= 320000);
 }
 
-hipError_t launch_slots(const AssembleArgs& a, int k, const LaunchTo& st) {
+hipError_t launch_slots(const AssembleArgs& a, int k, bool streamed, const LaunchTo& st) {
     switch (k) {
-    case 3:  return a.C == 1 ? launch_slots_k3c1(a, st) : launch_slots_k3c3(a, st);
-    case 5:  return a.C == 1 ? launch_slots_k5c1(a, st) : launch_slots_k5c3(a, st);
-    case 7:  return a.C == 1 ? launch_slots_k7c1(a, st) : launch_slots_k7c3(a, st);
+    case 3:  return a.C == 1 ? launch_slots_k3c1(a, streamed, st) : launch_slots_k3c3(a, streamed, st);
+    case 5:  return a.C == 1 ? launch_slots_k5c1(a, streamed, st) : launch_slots_k5c3(a, streamed, st);
+    case 7:  return a.C == 1 ? launch_slots_k7c1(a, streamed, st) : launch_slots_k7c3(a, streamed, st);
     default: return hipErrorInvalidValue;
     }
 }

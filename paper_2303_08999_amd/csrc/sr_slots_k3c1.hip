@@ -3,6 +3,6 @@
 
 namespace srd {
 
-hipError_t launch_slots_k3c1(const AssembleArgs& a, const LaunchTo& st) { return launch_slots_t<3, 1>(a, st); }
+hipError_t launch_slots_k3c1(const AssembleArgs& a, bool streamed, const LaunchTo& st) { return launch_slots_t<3, 1>(a, streamed, st); }
 
 }  // namespace srd

@@ -3,6 +3,6 @@
 
 namespace srd {
 
-hipError_t launch_slots_k3c3(const AssembleArgs& a, const LaunchTo& st) { return launch_slots_t<3, 3>(a, st); }
+hipError_t launch_slots_k3c3(const AssembleArgs& a, bool streamed, const LaunchTo& st) { return launch_slots_t<3, 3>(a, streamed, st); }
 
 }  // namespace srd
