@@ -21,9 +21,9 @@
 // atoms of 3x3 118 / 49, 1152 x 945 x3 fp16 128 atoms of 7x7 342 / 96.
 //
 // Precision: fp32 coefficients go through v_mfma_f32_32x32x2_f32 (products and sums fp32).  16- and 8-bit ones and the
-// exponentials of logits meet the dictionary as 16-bit parts: fp16, the first part and the rest scaled by 2^11 into a sum of its own, 22
-// significant bits also where the rest alone would be subnormal; bfloat16 three parts, 24 bits.  (Calls of the streaming kernel: its parts, its
-// order, its bits.)  Against 64-bit arithmetic two drawn calls went from
+// exponentials of logits meet the dictionary as 16-bit parts: fp16, of the dictionary scaled by one power of two, the first part and the
+// rest times 2^11 into a sum of its own, 22 significant bits of every entry down to 2^-29 of the largest; bfloat16 three parts, 24 bits.
+// (Calls of the streaming kernel: its parts, its order, its bits.)  Against 64-bit arithmetic two drawn calls went from
 // 1.0e-7 and 1.1e-7 in the generic kernel to 7.6e-8 and 6.8e-8.
 #pragma once
 #include <string.h>
@@ -60,6 +60,9 @@ struct SlotCfg {
     static constexpr bool BF = CT == CT_BF16 && !LG;                   // bfloat16 ones (logits: fp16, whatever they are stored as)
     static constexpr int NPART = F32 ? 1 : (BF && !ST ? 3 : 2);        // 16-bit parts of a dictionary entry
     static constexpr int NACC = F32 || BF || ST ? 1 : 2;               // sums: fp16's second part has its own
+    // fp16 parts: of the dictionary times a power of two that brings its largest entry below 2^15.  Unscaled, entries of 65520 and more overflow and
+    // small ones keep 2^-35 at best.
+    static constexpr bool SCALED = NACC == 2;
     static constexpr int QG = P * NMB * NACC <= 4 ? P : (NMB * NACC <= 2 ? 2 : 1);   // slots folded together (registers)
     static constexpr int QGP = QG < P ? QG : P;
     static constexpr int N16 = F32 ? 0 : NP8 / 2, N8 = F32 ? 0 : NP8 % 2, N2 = F32 ? 4 * NP8 : 0;
@@ -98,6 +101,7 @@ void k_assemble_slots(const SlotArgs a) {
     __shared__ unsigned ptab[2 * NLOAD];              // byte offset of the plane each lane half loads
     __shared__ int ktab[8 * NP8];
     __shared__ float gtab[8 * NP8];
+    __shared__ unsigned dmax[4];                      // bits of the dictionary's largest magnitude, of each wavefront's part
     float* const lrT = U;
 
     const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5, j = lane & 31;
@@ -233,6 +237,42 @@ void k_assemble_slots(const SlotArgs a) {
         const int blk = wave + 4 * m, mb = blk % NMB, st = blk / NMB;
         if (blk < F::NB32) A32[blk * 64 + lane] = dict_value(2 * st + hf, tap_of_row<K>(j, mb), dv32[m]);
     }
+    // the values of the operands, and (SCALED) the exponent of the power of two that the dictionary is multiplied by
+#pragma unroll
+    for (int m = 0; m < M16; ++m) {
+        const int blk = wave + 4 * m < F::NB16 ? wave + 4 * m : F::NB16 - 1, mb = blk % NMB, c16 = blk / NMB;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) dv16[m][i] = dict_value(16 * c16 + 8 * hf + i, tap_of_row<K>(j, mb), dv16[m][i]);
+    }
+#pragma unroll
+    for (int m = 0; m < M8; ++m) {
+        const int mb = wave + 4 * m < F::NB8 ? wave + 4 * m : F::NB8 - 1;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) dv8[m][i] = dict_value(16 * N16 + 4 * hf + i, tap_of_row<K>(j, mb), dv8[m][i]);
+    }
+    int scale = 0;
+    if constexpr (F::SCALED) {
+        unsigned m = 0u;
+#pragma unroll
+        for (int b = 0; b < M16; ++b)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) m = max(m, __float_as_uint(fabsf(dv16[b][i])));
+#pragma unroll
+        for (int b = 0; b < M8; ++b)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) m = max(m, __float_as_uint(fabsf(dv8[b][i])));
+        m = max(m, (unsigned)__builtin_amdgcn_update_dpp(0, (int)m, 0xB1, 0xf, 0xf, false));       // neighbours, pairs, quads, halves of a row
+        m = max(m, (unsigned)__builtin_amdgcn_update_dpp(0, (int)m, 0x4E, 0xf, 0xf, false));
+        m = max(m, (unsigned)__builtin_amdgcn_update_dpp(0, (int)m, 0x141, 0xf, 0xf, false));
+        m = max(m, (unsigned)__builtin_amdgcn_update_dpp(0, (int)m, 0x140, 0xf, 0xf, false));
+        m = max(m, (unsigned)__builtin_amdgcn_update_dpp(0, (int)m, 0x142, 0xa, 0xf, false));      // rows 1 and 3 from the row before, then
+        m = max(m, (unsigned)__builtin_amdgcn_update_dpp(0, (int)m, 0x143, 0xc, 0xf, false));      // the upper half from lane 31: lane 63 has all
+        if (lane == 63) dmax[wave] = m;
+        __syncthreads();
+        const unsigned all = max(max(dmax[0], dmax[1]), max(dmax[2], dmax[3]));
+        scale = 14 + 127 - (int)(__builtin_amdgcn_readfirstlane(all) >> 23);
+    }
+    auto scaled = [&](float v) -> float { return F::SCALED ? ldexpf(v, scale) : v; };
     // N dictionary values as NPART operands
     auto parts = [&](auto& dst, int blk, const auto& d) {
         using Vec = typename std::remove_reference<decltype(dst[0])>::type;
@@ -272,7 +312,7 @@ void k_assemble_slots(const SlotArgs a) {
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
                     const int at = 16 * c16 + 8 * hf + i;
-                    d[i] = ones ? (at < a.n_fold ? 1.0f : 0.0f) : dict_value(at, tap_of_row<K>(j, mb), dv16[m][i]);
+                    d[i] = ones ? (at < a.n_fold ? 1.0f : 0.0f) : scaled(dv16[m][i]);
                 }
                 parts(A16, blk, d);
             }
@@ -286,7 +326,7 @@ void k_assemble_slots(const SlotArgs a) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int at = 16 * N16 + 4 * hf + i;
-                    d[i] = ones ? (at < a.n_fold ? 1.0f : 0.0f) : dict_value(at, tap_of_row<K>(j, mb), dv8[m][i]);
+                    d[i] = ones ? (at < a.n_fold ? 1.0f : 0.0f) : scaled(dv8[m][i]);
                 }
                 parts(A8, mb, d);
             }
@@ -554,6 +594,7 @@ void k_assemble_slots(const SlotArgs a) {
                                 sum[q] = fmaf(acc[q][v / 16][0][v % 16], u, sum[q]);
                             }
                             if constexpr (LG) sum[q] *= rsum[q];
+                            if constexpr (F::SCALED) sum[q] = ldexpf(sum[q], -scale);
                         }
                         constexpr int NS = QG == 4 ? 2 : 1;                // pixels a lane stores: half hf has slots NS hf + i (one slot: half 0)
 #pragma unroll

@@ -194,3 +194,38 @@ def test_frames_of_a_batch_have_the_bits_of_single_ones(k, c, L, cd, io):
         coeff = inp["coeff"][i:i + 1].contiguous()
         assert runs(single, one, coeff, False, False)[0] == sr.SR_RUNS_SLOTS
         assert torch.equal(run(single, one, coeff, AUTO, False, False), batch[i:i + 1])
+
+
+# The dictionary's 16-bit parts: a power of two goes through every form without a trace, and small atoms beside large ones keep their bits
+FORMS = [(3, 72, 5, "f16", True, False), (1, 40, 3, "f8", True, False), (1, 128, 7, "bf16", True, False), (3, 100, 5, "f32", True, False),
+         (3, 72, 3, "f16", False, True), (1, 100, 5, "bf16", False, True), (2, 30, 7, "f32", True, True), (2, 72, 5, "f8", False, False)]
+
+
+@pytest.mark.parametrize("c, L, k, cd, pre, logits", FORMS)
+@pytest.mark.parametrize("power", [20, 60, -22, -60])
+def test_dictionaries_of_any_magnitude(c, L, k, cd, pre, logits, power):
+    wl = sr_synth.Workload("slotsm", 75, 1, c, 15, 67, 2, L, k, cd, "f32", 0.0, 1.5)
+    inp, flat, coeff = make(wl, pre, logits)
+    assert runs(inp, wl, coeff, pre, logits)[0] == sr.SR_RUNS_SLOTS
+    ref = run(inp, wl, coeff, AUTO, pre, logits)
+    got = run(dict(inp, dict=inp["dict"] * 2.0 ** power), wl, coeff, AUTO, pre, logits)
+    assert torch.equal(got, ref * 2.0 ** power)
+    if not logits:                                  # the same as a scale of the kept atoms
+        kept, gamma = np.arange(L, dtype=np.int32), np.full(L, 2.0 ** power, np.float32)
+        assert torch.equal(run(inp, wl, coeff, AUTO, pre, logits, kept, gamma), got)
+
+
+@pytest.mark.parametrize("c, L, k, cd, pre, logits", FORMS)
+def test_small_atoms_beside_large_ones(c, L, k, cd, pre, logits):
+    """Only the last atom, of entries around 1e-7 of the others', takes part: 22 bits of it and more are asked for, i.e. what the bound of
+    fp32 sums leaves."""
+    wl = sr_synth.Workload("slotsm", 76, 1, c, 15, 67, 2, L, k, cd, "f32", 0.0, 1.5)
+    inp, flat, coeff = make(wl, pre, logits)
+    only = torch.full(flat.shape, -float("inf") if logits else 0.0, device=DEV)
+    only[:, L - 1] = 1.0
+    flat = only.to(flat.dtype)
+    coeff = sr_synth.to_pre_shuffle(flat, wl.scale) if pre else flat
+    inp["dict"][..., L - 1, :, :] *= 1e-7
+    got, gen = (run(inp, wl, coeff, kernel, pre, logits) for kernel in (AUTO, GENERIC))
+    # (k^2 products of an entry that is off by 2^-23 of itself at most, sums of them in another order)
+    assert float((got - gen).abs().max()) <= 2e-6 * float(gen.abs().max())
