@@ -79,6 +79,12 @@ struct SlotCfg {
     static_assert(CM * MAXLRY * MAXLRX <= CM * UH * PITCH, "the LR rows fit where the tile goes");
 };
 
+template <int CT> struct StoredAs;      // a coefficient in memory
+template <> struct StoredAs<CT_F16> { typedef __half type; };
+template <> struct StoredAs<CT_F32> { typedef float type; };
+template <> struct StoredAs<CT_F8> { typedef f8e4m3 type; };
+template <> struct StoredAs<CT_BF16> { typedef bf16raw type; };
+
 constexpr float SLOT_LO = 2048.0f;       // scale of fp16's second part
 
 template <int K, int CM, int CT, int NP8, int KIND, bool PRE>
@@ -580,6 +586,8 @@ void k_assemble_slots(const SlotArgs a) {
                 // Every lane stores, for every channel that there is room for: what is outside the image goes where the buffer drops it.
                 // Behind a branch the compiler cannot count the stores, and the next unit, which waits for loads issued before them,
                 // waits for them as well.
+                constexpr int NS = QG == 4 ? 2 : 1;                        // pixels a lane stores: half hf has slots NS hf + i (one slot: half 0)
+                unsigned odd = 0u;                                         // bit c NS + i: what the lane stores there is not finite
 #pragma unroll
                 for (int c = 0; c < CM; ++c) {
                         float sum[QG];
@@ -596,7 +604,6 @@ void k_assemble_slots(const SlotArgs a) {
                             if constexpr (LG) sum[q] *= rsum[q];
                             if constexpr (F::SCALED) sum[q] = ldexpf(sum[q], -scale);
                         }
-                        constexpr int NS = QG == 4 ? 2 : 1;                // pixels a lane stores: half hf has slots NS hf + i (one slot: half 0)
 #pragma unroll
                         for (int i = 0; i < NS; ++i) {
                             const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(sum[i]), __float_as_uint(sum[QG == 1 ? 0 : i + NS]), false, false);
@@ -606,6 +613,77 @@ void k_assemble_slots(const SlotArgs a) {
                             const unsigned px = (unsigned)c * plane_px + (unsigned)y * (unsigned)a.W + (unsigned)(se * x + un.jx);
                             if (a.io_f16) store16(out_rsrc, valid ? 2u * px : BEYOND, v);
                             else store32(out_rsrc, valid ? 4u * px : BEYOND, __float_as_uint(v));
+                            if constexpr (!F::ST) odd |= valid && __builtin_amdgcn_classf(v, 0x207) ? 1u << (c * NS + i) : 0u;      // NaN, infinity
+                        }
+                    }
+                // An infinite coefficient, logit, image value or dictionary entry meets the zeros of the padding and the dictionary's second part here and gives
+                // NaN also where the plain sums give infinity, or a number (logits).  Such pixels are taken again, one by one, as in the generic kernel.
+                if constexpr (!F::ST)
+                    if (__builtin_expect(__builtin_amdgcn_ballot_w64(odd != 0u) != 0, 0)) {
+                        using TC = typename StoredAs<CT>::type;
+#pragma unroll 1
+                        for (int i = 0; i < NS; ++i) {
+                            const int q = q0 + (QG == 1 ? 0 : NS * hf + i), x = x0 + q;
+                            const bool mine = ((odd >> i) & (NS == 2 ? 0x15u : 0x7u)) != 0u;
+                            unsigned at = 0u;                              // the pixel's place in a coefficient plane
+                            if (mine) {
+                                if constexpr (PRE) {
+                                    int ly, iy;
+                                    divmod_scale(y, a.s, ly, iy);
+                                    at = (unsigned)(iy * a.s + un.jx) * ((unsigned)a.h * (unsigned)a.w) + (unsigned)ly * (unsigned)a.w + (unsigned)x;
+                                } else {
+                                    at = (unsigned)y * (unsigned)a.W + (unsigned)x;
+                                }
+                            }
+                            const TC* const base = (const TC*)a.coeff + (size_t)cur.n * a.L * plane_px + at;
+                            auto stored = [&](int atom) -> float { return ld_as_float(base, (size_t)atom * plane_px); };
+                            float Fk[KK], esum = 0.0f, shift = 0.0f;
+#pragma unroll
+                            for (int t = 0; t < KK; ++t) Fk[t] = 0.0f;
+                            if constexpr (LG) {
+                                float m = stored(0);
+#pragma unroll 4
+                                for (int l = 1; l < a.n_fold; ++l) m = fmaxf(m, stored(l));
+                                shift = logit_shift(m);
+                            }
+                            constexpr int NB = 8;                          // coefficients requested together
+#pragma unroll 1
+                            for (int l0 = 0; l0 < a.n_fold; l0 += NB) {
+                                float phi[NB];
+#pragma unroll
+                                for (int b = 0; b < NB; ++b) {
+                                    const int l = l0 + b < a.n_fold ? l0 + b : a.n_fold - 1;
+                                    phi[b] = stored(a.kept[l]) * a.gamma[l];
+                                }
+#pragma unroll
+                                for (int b = 0; b < NB; ++b)
+                                    if (l0 + b < a.n_fold) {               // wave-uniform
+                                        float p = phi[b];
+                                        if constexpr (LG) {
+                                            p = __half2float(__float2half_rn(logit_exp(p, shift)));
+                                            esum += p;
+                                        }
+                                        const float* const d = a.dict + (size_t)a.kept[l0 + b] * KK;
+#pragma unroll
+                                        for (int t = 0; t < KK; ++t) Fk[t] = fmaf(p, d[t], Fk[t]);
+                                    }
+                            }
+#pragma unroll 1
+                            for (int c = 0; c < a.C; ++c) {
+                                float v = 0.0f;
+#pragma unroll
+                                for (int dy = 0; dy < K; ++dy)
+#pragma unroll
+                                    for (int dx = 0; dx < K; ++dx) {
+                                        const unsigned e = (unsigned)(se * q + (PRE ? un.jx : 0) + dx), g = PRE ? (e * a.inv_sw) >> 16 : e / P;
+                                        v = fmaf(Fk[dy * K + dx], U[(c * UH + un.row + dy) * PITCH + j + un.col + (e - g * (unsigned)sw) * (unsigned)ng + g], v);
+                                    }
+                                if constexpr (LG) v = v * (1.0f / esum);
+                                const bool again = ((odd >> (c * NS + i)) & 1u) != 0u;
+                                const unsigned px = (unsigned)c * plane_px + (unsigned)y * (unsigned)a.W + (unsigned)(se * x + un.jx);
+                                if (a.io_f16) store16(out_rsrc, again ? 2u * px : BEYOND, v);
+                                else store32(out_rsrc, again ? 4u * px : BEYOND, __float_as_uint(v));
+                            }
                         }
                     }
             }

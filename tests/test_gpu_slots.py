@@ -229,3 +229,36 @@ def test_small_atoms_beside_large_ones(c, L, k, cd, pre, logits):
     got, gen = (run(inp, wl, coeff, kernel, pre, logits) for kernel in (AUTO, GENERIC))
     # (k^2 products of an entry that is off by 2^-23 of itself at most, sums of them in another order)
     assert float((got - gen).abs().max()) <= 2e-6 * float(gen.abs().max())
+
+
+@pytest.mark.parametrize("c, L, k, cd, pre, logits", FORMS + [(1, 72, 5, "f16", True, False), (3, 17, 7, "bf16", True, False), (1, 72, 5, "f32", False, False),
+                                                              (1, 72, 7, "f32", False, True), (3, 128, 3, "f8", True, False)])
+@pytest.mark.parametrize("io", ["f32", "f16"])
+def test_infinities_and_nan_as_in_the_generic_kernel(c, L, k, cd, pre, logits, io):
+    wl = sr_synth.Workload("slotsn", 77, 2, c, 14, 71, 3, L, k, cd, io, 0.0, 1.5)
+    inp, flat, coeff = make(wl, pre, logits)
+    assert runs(inp, wl, coeff, pre, logits)[0] == sr.SR_RUNS_SLOTS
+    inf, nan = float("inf"), float("nan")
+    changed = flat.float()
+    values = [-inf] if logits else [inf, -inf, nan] if cd != "f8" else [nan]
+    if cd == "bf16" and logits:
+        values += [-1e37, -3e38]
+    for i in range(60):                             # the first and the last atom, and any; edges of rows and units, and any
+        atom = (0, L - 1, (7 * i) % L)[i % 3]
+        y, x = ((0, 0), (wl.H - 1, wl.W - 1), ((11 * i) % wl.H, (37 * i) % wl.W))[(i // 3) % 3]
+        changed[i % 2, atom, y, x] = values[(i // 2) % len(values)]
+    if logits:
+        changed[0, :, 5, 6] = -inf                  # no atom is left
+    changed = changed.to(flat.dtype)
+    changed = sr_synth.to_pre_shuffle(changed, wl.scale) if pre else changed
+    image, entry = inp["lr"].clone(), inp["dict"].clone()
+    image[1, c - 1, 6, 20], image[0, 0, 0, 0], image[0, 0, 13, 70] = inf, -inf, nan
+    entry[..., L // 2, k // 2, 0] = inf
+    for what, other, phi in (("coefficients", inp, changed), ("image", dict(inp, lr=image), coeff), ("dictionary", dict(inp, dict=entry), coeff)):
+        got, gen = (run(other, wl, phi, kernel, pre, logits).float() for kernel in (AUTO, GENERIC))
+        odd = ~torch.isfinite(gen)
+        assert odd.any() or (logits and what == "coefficients"), what
+        assert torch.equal(torch.isfinite(got), ~odd), what
+        assert torch.equal(torch.nan_to_num(got[odd], 7.0), torch.nan_to_num(gen[odd], 7.0)), what
+        tol = (2.5e-4 if logits else 5e-5) + (2.0 ** -10 if io == "f16" else 0.0)
+        assert not (~odd).any() or float((got - gen)[~odd].abs().max()) <= tol * max(1.0, float(gen[~odd].abs().max())), what
