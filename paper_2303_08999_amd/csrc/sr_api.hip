@@ -1,5 +1,5 @@
 // C ABI of the library: argument validation, kernel choice, launch.
-// Everything here runs on the host; all checks precede any HIP call.
+// Everything here runs on the host; all checks precede any HIP call but the question for the device's size.
 #include <stdint.h>
 #include <string.h>
 
@@ -36,7 +36,7 @@ struct Plan {
     AssembleArgs args;
 };
 
-// Validate everything and build the kernel arguments.  No HIP calls.
+// Validate everything and build the kernel arguments.  No HIP calls but for the device's compute units.
 void make_plan(Plan& p, const sr_tensor* lr, const sr_tensor* coeff, const sr_tensor* dict,
                int L, int k, int scale, int channels, const sr_tensor* out,
                const int* kept, int n_kept, const float* gamma, const sr_options* opts) {
@@ -116,6 +116,7 @@ void make_plan(Plan& p, const sr_tensor* lr, const sr_tensor* coeff, const sr_te
 
     const int want = opts ? opts->kernel : SR_KERNEL_AUTO;
     const int tile = opts ? opts->tile : 0;
+    if (!p.empty && want != SR_KERNEL_GENERIC) a.cus = compute_units();
     const bool can_mfma = !p.empty && mfma_supported(a, k, coeff->dtype, tile);
     // a tile index other than 0 is an option of the matrix-core kernel: it never falls back silently
     if ((want == SR_KERNEL_MFMA || (tile != 0 && want != SR_KERNEL_GENERIC)) && !can_mfma) { p.status = SR_ERR_UNSUPPORTED; return; }

@@ -48,6 +48,7 @@ struct AssembleArgs {
     int logits;           // `coeff` holds logits: the coefficients are their per-pixel softmax over the atoms
     int   kept[SR_MAX_ATOMS];    // plane read for folded atom i (identity when dense)
     float gamma[SR_MAX_ATOMS];   // its scale (1 when dense)
+    int cus;              // compute units of the device, asked for once per call (0: not yet)
 };
 
 struct BicubicArgs {

@@ -5,6 +5,23 @@
 
 namespace srd {
 
+// ---------------------------------------------------------------------------
+// Host side: launch of one instantiation on a persistent grid.
+// ---------------------------------------------------------------------------
+// CUs of the current device (asked once per device and thread)
+inline int compute_units() {
+    static thread_local int known[64];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+    if (known[dev] == 0) {
+        int cus = 0;
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 256;
+        known[dev] = cus;
+    }
+    return known[dev];
+}
+inline int units_of(const AssembleArgs& a) { return a.cus ? a.cus : compute_units(); }
+
 hipError_t launch_generic(const AssembleArgs& a, int k, bool io_f16, hipStream_t st);   // coefficient dtype: a.coeff_dtype
 hipError_t launch_bicubic(const BicubicArgs& a, bool in_f16, bool out_f16, hipStream_t st);
 
@@ -21,6 +38,7 @@ struct LaunchTo {
 
 // Matrix-core kernel.  mfma_supported() is a pure host-side predicate.
 bool mfma_supported(const AssembleArgs& a, int k, int coeff_dtype, int tile);
+int mfma_capacity(const AssembleArgs& a, int k);        // of the instantiation that takes the call, in groups of 8 atoms
 hipError_t launch_mfma(const AssembleArgs& a, int k, bool io_f16, int tile, const LaunchTo& st);
 // Matrix-core kernel for calls the one above has no instantiation for (coefficient dtype: a.coeff_dtype); make_plan chooses
 bool slots_supported(const AssembleArgs& a, int k);

@@ -143,6 +143,8 @@ bool mfma_supported(const AssembleArgs& a, int k, int coeff_dtype, int tile) {
     return true;
 }
 
+int mfma_capacity(const AssembleArgs& a, int k) { return np8_for(k, a.C, a.n_fold, a.coeff_dtype); }
+
 hipError_t launch_mfma(const AssembleArgs& a, int k, bool io_f16, int tile, const LaunchTo& st) {
     (void)io_f16;
     const int np8 = np8_for(k, a.C, a.n_fold, a.coeff_dtype);

@@ -21,9 +21,9 @@ static hipError_t launch_k3_np8(const AssembleArgs& a, int np8, const LaunchTo& 
     case 4:  return launch_k3<C, 4, CT>(a, st);
     case 9:  return launch_k3<C, 9, CT>(a, st);
     case 16:                                         // 73 to 128 atoms, as the 5x5 and 7x7 instantiations of that size:
-        // 16-bit coefficients, two pixels per lane (the others: slots_faster)
-        if constexpr (CT == CT_F16 || CT == CT_BF16) return launch_one<3, C, 16, 2, 1, 4, 4, 2, CT>(a, st);
-        else return hipErrorInvalidValue;
+        // two pixels per lane; fp32 coefficients with one wavefront per SIMD, 8-bit ones nowhere (slots_faster)
+        if constexpr (CT == CT_F8) return hipErrorInvalidValue;
+        else return launch_one<3, C, 16, 2, 1, 4, 4, CT == CT_F32 ? 1 : 2, CT>(a, st);
     default: return hipErrorInvalidValue;
     }
 }

@@ -1773,22 +1773,6 @@ void k_assemble_mfma(const AssembleArgs a) {
     }
 }
 
-// ---------------------------------------------------------------------------
-// Host side: launch of one instantiation on a persistent grid.
-// ---------------------------------------------------------------------------
-// CUs of the current device (asked once per device and thread)
-inline int compute_units() {
-    static thread_local int known[64];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-    if (known[dev] == 0) {
-        int cus = 0;
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 256;
-        known[dev] = cus;
-    }
-    return known[dev];
-}
-
 // rate of the constant clock s_memrealtime reads, in kHz (asked once per device and thread; 100 MHz if the runtime
 // does not say)
 inline long long wall_clock_khz() {
@@ -1835,6 +1819,30 @@ hipError_t launch_one(const AssembleArgs& a0, const LaunchTo& st) {
     if (PSM == 9 && (a0.W % 128 != 0 || a0.L != 8 * NP8 || a0.n_fold != a0.L)) return hipErrorInvalidValue;
     // permuted pixel slots: a lane owns four whole LR columns, the image must end on such a group
     if ((PSM == 2 || PSM == 3 || PSM == 4) && (a0.s != PSM || a0.w % 4 != 0)) return hipErrorInvalidValue;
+    const int tiles_x = (a0.W + F::TW - 1) / F::TW;
+    int tiles_y = (a0.H + F::TH - 1) / F::TH, xlast = (tiles_x - 1) * F::TW, seg_rows = F::TH;
+    if (a0.W % PX != 0) {                               // ragged rows: the last tile column ends at the image edge
+        if (a0.W < F::TW) return hipErrorInvalidValue;
+        xlast = a0.W - F::TW;
+        if (STRIP && xlast > 0 && xlast < F::R) return hipErrorInvalidValue;   // would look over the left edge, see strip_form
+    }
+    const int cap = units_of(a0) * (4 * WPE / NW > 0 ? 4 * WPE / NW : 1);
+    if (STRIP) {
+        // as many segments as there are wavefronts, or one per strip
+        const long long strips = (long long)tiles_x * a0.N, waves = (long long)cap * NW;
+        const int per_strip = (int)(strips < waves ? waves / strips : 1);
+        seg_rows = (a0.H + per_strip - 1) / per_strip;
+        tiles_y = (a0.H + seg_rows - 1) / seg_rows;
+    }
+    const long long nt = (long long)tiles_x * tiles_y * a0.N;
+    if (nt > 0x7fffffffLL) return hipErrorInvalidValue;
+    // as many workgroups as stay resident (WPE wavefronts per SIMD); strip form: a segment per wavefront
+    const long long want = STRIP ? (nt + NW - 1) / NW : nt;
+    const int blocks = want < cap ? (int)want : cap;
+    if (st.walk) {
+        *st.walk = {STRIP ? 2 : 1, F::TW, seg_rows, (int)nt, blocks, NW};
+        return hipSuccess;
+    }
     AssembleArgs a = a0;
 #ifndef SR_NO_L2_WRITEBACK
     // L2 write-back pacing where the coefficient stream is the bound: 49 atoms and more, not the list forms nor 8-bit
@@ -1845,37 +1853,15 @@ hipError_t launch_one(const AssembleArgs& a0, const LaunchTo& st) {
         // 16 us of the constant-rate clock the kernel reads (7x7 atoms: 28 us, measured); one asking workgroup per XCD
         // (32 CUs each: eight on the whole device, fewer on a partition of it)
         a.wb_ticks = (int)((K == 7 ? 28LL : 16LL) * wall_clock_khz() / 1000);
-        const int xcds = compute_units() / 32;
+        const int xcds = units_of(a0) / 32;
         a.wb_flushers = xcds < 1 ? 1 : (xcds > 8 ? 8 : xcds);
     }
 #endif
-    a.tiles_x = (a.W + F::TW - 1) / F::TW;
-    a.tiles_y = (a.H + F::TH - 1) / F::TH;
-    a.xlast = (a.tiles_x - 1) * F::TW;
-    if (a.W % PX != 0) {                                // ragged rows: the last tile column ends at the image edge
-        if (a.W < F::TW) return hipErrorInvalidValue;
-        a.xlast = a.W - F::TW;
-        if (STRIP && a.xlast > 0 && a.xlast < F::R) return hipErrorInvalidValue;   // would look over the left edge, see strip_form
-    }
-    const int cap = compute_units() * (4 * WPE / NW > 0 ? 4 * WPE / NW : 1);
-    a.seg_rows = F::TH;
-    if (STRIP) {
-        // as many segments as there are wavefronts, or one per strip
-        const long long strips = (long long)a.tiles_x * a.N, waves = (long long)cap * NW;
-        const int per_strip = (int)(strips < waves ? waves / strips : 1);
-        a.seg_rows = (a.H + per_strip - 1) / per_strip;
-        a.tiles_y = (a.H + a.seg_rows - 1) / a.seg_rows;
-    }
-    const long long nt = (long long)a.tiles_x * a.tiles_y * a.N;
-    if (nt > 0x7fffffffLL) return hipErrorInvalidValue;
-    // as many workgroups as stay resident (WPE wavefronts per SIMD); strip form: a segment per wavefront
-    const long long want = STRIP ? (nt + NW - 1) / NW : nt;
-    const int blocks = want < cap ? (int)want : cap;
+    a.tiles_x = tiles_x;
+    a.tiles_y = tiles_y;
+    a.xlast = xlast;
+    a.seg_rows = seg_rows;
     walk_of(a, (int)nt, blocks, STRIP ? NW : 1);
-    if (st.walk) {
-        *st.walk = {STRIP ? 2 : 1, F::TW, a.seg_rows, (int)nt, blocks, NW};
-        return hipSuccess;
-    }
     hipLaunchKernelGGL((k_assemble_mfma<K, C, NP8, PX, WR, NW, NU, WPE, CT, SMIN, BIG, PSM, STRIP>), dim3(blocks), dim3(F::NT), 0, st.stream, a);
     return hipGetLastError();
 }
@@ -1911,7 +1897,7 @@ hipError_t launch_one(const AssembleArgs& a0, const LaunchTo& st) {
 inline bool strip_form(const AssembleArgs& a, int np8, int sw, int tw, int th, int wpe = 2) {
     if ((long long)a.C * a.H * a.W == (1ll << 30) - 1) return true;         // see the stores
     if (a.W == sw + 1) return false;                    // the moved last strip would start at column 1 and look over the left edge with R = 2
-    const long long simds = 4ll * compute_units(), strips = (long long)((a.W + sw - 1) / sw) * a.N;
+    const long long simds = 4ll * units_of(a), strips = (long long)((a.W + sw - 1) / sw) * a.N;
     const long long per_strip = strips < simds * wpe ? simds * wpe / strips : 1;
     const long long rows = (a.H + per_strip - 1) / per_strip, segments = strips * ((a.H + rows - 1) / rows);
     const long long tiles = (long long)((a.W + tw - 1) / tw) * ((a.H + th - 1) / th) * a.N;

@@ -702,13 +702,11 @@ static hipError_t launch_slots_p(const AssembleArgs& c, const LaunchTo& st) {
     a.lr = c.lr; a.coeff = c.coeff; a.dict = c.dict; a.out = c.out;
     a.N = c.N; a.C = c.C; a.h = c.h; a.w = c.w; a.H = c.H; a.W = c.W; a.s = c.s; a.L = c.L;
     a.n_fold = c.n_fold; a.io_f16 = c.io_f16; a.identity = c.identity;
-    memcpy(a.kept, c.kept, sizeof(a.kept));
-    memcpy(a.gamma, c.gamma, sizeof(a.gamma));
     a.upr = PRE ? a.s : 4 / F::P;                      // planar: tiles of 128 columns
     a.sw = F::P * (PRE ? a.s : 1);
     a.ng = 32 * a.upr * F::P / a.sw + (K - 2) / a.sw + 1;
     a.inv_sw = (65536u + (unsigned)a.sw - 1) / (unsigned)a.sw;
-    const int tw = 32 * F::P * a.upr, cus = compute_units(), cap = F::WPE * cus;
+    const int tw = 32 * F::P * a.upr, cus = units_of(c), cap = F::WPE * cus;
     a.tiles_x = (a.W + tw - 1) / tw;
     // Rows of a tile, by the cycles of the fullest CU's SIMDs: units of a wavefront (matrix instructions and filtering) and the
     // up-sampling of th + K - 1 rows, times its tiles; or, where that is more, what a workgroup's tiles take one after the other with the
@@ -738,6 +736,8 @@ static hipError_t launch_slots_p(const AssembleArgs& c, const LaunchTo& st) {
         *st.walk = {1, tw, a.th, a.ntiles, blocks, 4};
         return hipSuccess;
     }
+    memcpy(a.kept, c.kept, sizeof(a.kept));
+    memcpy(a.gamma, c.gamma, sizeof(a.gamma));
     hipLaunchKernelGGL((k_assemble_slots<K, CM, CT, NP8, KIND, PRE>), dim3(blocks), dim3(256), 0, st.stream, a);
     return hipGetLastError();
 }
@@ -745,8 +745,11 @@ static hipError_t launch_slots_p(const AssembleArgs& c, const LaunchTo& st) {
 template <int K, int CM, int CT, int NP8, int KIND>
 static hipError_t launch_slots_n(const AssembleArgs& a, const LaunchTo& st) {
     if constexpr (KIND != SLOT_STREAMED)
-        if (a.pre_shuffle) return launch_slots_p<K, CM, CT, NP8, KIND, true>(a, st);
-    return launch_slots_p<K, CM, CT, NP8, KIND, false>(a, st);
+        return a.pre_shuffle ? launch_slots_p<K, CM, CT, NP8, KIND, true>(a, st) : launch_slots_p<K, CM, CT, NP8, KIND, false>(a, st);
+    else if constexpr (NP8 == 16 || (CT == CT_F8 ? K == 7 : K != 5 || CM == 1))        // (what slots_faster sends here)
+        return launch_slots_p<K, CM, CT, NP8, KIND, false>(a, st);
+    else
+        return hipErrorInvalidValue;
 }
 
 template <int K, int CM, int CT, int KIND>

@@ -1,5 +1,6 @@
 // Which calls k_assemble_slots (sr_slots.h) takes, and its instantiation for one.
 #include "sr_launch.h"
+#include "sr_mfma_kernel.h"
 
 namespace srd {
 
@@ -34,42 +35,50 @@ bool slots_supported(const AssembleArgs& a, int k) {
     return true;
 }
 
-// Planar coefficients that the streaming kernel has an instantiation for and this one is faster with.  Three reasons:
-//   8-bit and fp32 coefficients of more than 72 atoms (and 8-bit ones of 7x7 atoms) fill the register file of a SIMD with one
-//   wavefront there, in tiles of sixteen rows; here two or three share it and a small frame is cut finer.  Streaming / this, us: fp8 100
-//   atoms 162 x 108 x3 21 / 10, 1548 x 1032 x3 86 / 58, 2112 x 1416 x3 125 / 102; fp32 100 atoms 162 x 108 x1 27 / 9, 1096 x 724 x3
-//   114 / 97; fp8 7x7 164 x 108 x3 23 / 14, 824 x 548 x3 27 / 30; fp32 7x7 100 atoms 1096 x 724 x1 158 / 150, 1548 x 1032 x1
-//   272 / 296.
-//   fp32 coefficients of a few hundred units of sixteen rows, whose fullest SIMD has four and here two or three: 366 x 243 x3 18 /
-//   14.5, 464 x 308 x3 21 / 18.5, but 548 x 364 x3 23 / 23.5; between 32 and 64 thousand pixels the streaming kernel's 64 x 4 tiles are as
-//   good.
-//   16-bit coefficients of one channel and of the smallest frames, for the same reason (few instantiations have tiles of four rows): 5x5
-//   72 atoms fp16 546 x 363 x1 14 / 12.4, 162 x 108 x1 9 / 8, 3x3 162 x 108 x3 9 / 8.2; 128 atoms 456 x 327 x1 17 / 16, but at scale 4 516 x 384 x1 17 / 18; 7x7 363 x 243 x1
-//   12 / 10, but 546 x 363 x1 14 / 14.7.
-//   16-bit coefficients in rows that start on no multiple of 32 bytes (of 64 bytes: no difference): neighbouring pieces share memory lines, which the streaming
-//   loads there take from memory twice and the ordinary ones here once: 3x3, 72 atoms, 822 x 548 x3
-//   28 / 24, 5x5 669 x 441 x1 18 / 14.5; 128 atoms 1554 x 1030 x3 119 / 102; with whole lines 794 / 800 thousand pixels 32 / 35, 3 million 91 /
-//   104.  3x3 atoms of 128 have no strips there: 540 x 360 x3 37 / 30.
+// Planar coefficients that the streaming kernel has an instantiation for and this one is faster with (and gives the same bits).  Both launches are
+// known before either is made, and what decides is the work of the fullest CU.  Counted in pixels: those of its tiles or of its
+// wavefronts' strip segments, plus 9 for each of the k - 1 rows that a tile, or each wavefront's segment, up-samples beyond its own
+// (per 128 columns), plus 24 for what a tile costs whatever its size.  `ratio` is the streaming kernel's count over this one's.  The limits were
+// read off 2401 drawn calls of 2 thousand to 4 million pixels, timed on both in turn with rotating inputs (in brackets: streaming us /
+// this us of the calls from the limit on, smallest .. largest; with them the drawn calls take 0.84 of the streaming kernel's time, geometric mean):
+//   tiles of one or two rows: 1.03 (0.91 .. 1.6), 3x3 0.97 (0.94 .. 1.4).  For more than 72 atoms, which take two pixels per lane there, 0.86
+//   (0.96 .. 2.1); 7x7 in one channel 0.88 (1.0 .. 1.6), in three 1.06, 1.03 for more than 72 (0.96 .. 1.3).
+//   tiles of four and eight rows: 1.13 (1.02 .. 1.4); from 0.9 to there 0.7 .. 1.15: strips win the large frames.
+//   16-bit rows that start on no multiple of 32 bytes, whose streaming loads take the shared lines twice: 3x3, launches of one round, 1.04 (0.97 ..
+//   1.4), three channels at scales 2 and 3 0.97 (0.93 .. 1.4); more than 72 atoms 0.855 (0.92 .. 1.5), 7x7 0.9 (0.97 .. 1.3); but frames of few
+//   tiles at scale 4, where the streaming tiles are larger: 1.05 (1.02 .. 1.3), against those of 24 rows and three channels 0.72 (0.97 .. 1.26).
+//   More than 72 atoms of 3x3 (no strips there), in tiles of four rows or such rows: 0.95 (0.97 .. 1.7); more than 72 of fp32 (one wavefront per
+//   SIMD, tiles of sixteen rows): 0.925 in tiles of four and eight rows, 0.95 in lower ones (0.94 .. 3.2), 7x7 0.76 (0.95 .. 3.2).
+//   fp32 atoms of 7x7, 27 to 32 of them, in the streaming kernel's capacity of 72: 0.85 (1.4 .. 1.9).
+//   One tile for a CU at most: always (1.0 .. 3.2).  8-bit coefficients of 7x7, and of more than 72 atoms: always (0.96 .. 2.3).
+// Left out: capacities that this kernel has not (5x5: 8, 16 and 48; 3x3: 8); 5x5 atoms of three channels up to 72 in 16 bits, whose default tile is one of
+// the shapes that a caller can ask for.
 bool slots_faster(const AssembleArgs& a, int k) {
     if (a.pre_shuffle || a.pixel_major || a.blocked || a.logits || a.C == 2 || !slots_supported(a, k)) return false;
-    if (a.n_fold > 72 && k != 7 && (a.coeff_dtype == SR_F8E4M3 || a.coeff_dtype == SR_F32)) return true;      // (none is built there)
-    if (a.W < 100) return false;                       // its planar tiles have 128 columns
-    const long long px = (long long)a.N * a.H * a.W;
-    const int n = a.n_fold;
-    if (a.coeff_dtype == SR_F8E4M3) return k == 7 && (px <= 250000 || (a.C == 1 && n <= 72 && px > 700000));
-    if (a.coeff_dtype == SR_F32) {
-        if (n > 72) return px <= 700000;
-        return px <= 32768 || (px > 65536 && px <= (k != 7 ? 170000 : a.C == 1 ? 150000 : 110000));
-    }
-    const bool f16 = a.coeff_dtype == SR_F16;
-    if (a.C == 1 && (k == 3 ? n > 32 && px <= 320000 : k == 7 ? n > 16 && a.s != 4 && px <= 100000 : n > 72 ? a.s != 4 && px <= 160000 : n > 48 && f16 && px <= 320000)) return true;
-    if (px <= 32768 && f16 && k == 3 && n > 32) return true;
-    const bool shared_lines = (long long)a.W * 2 % 32 != 0;
-    if (k == 3 && n > 72) return shared_lines || px <= 500000;
-    if (k == 7 || !shared_lines) return false;
-    if (n > 72) return px > 350000 || (px > 180000 && (a.s == 4 || px < 250000));
-    // (5x5 atoms, three channels, up to 72 atoms: the streaming kernel takes them in several storage orders and gives the same bits in all)
-    return (k == 3 ? n > 32 : a.C == 1 && n > 48 && f16) && px > 180000 && px <= 600000 && (a.s != 4 || px <= 320000);
+    const int n = a.n_fold, built = n <= 32 ? 4 : n <= 72 ? 9 : 16, streaming = mfma_capacity(a, k);
+    if (a.coeff_dtype == SR_F8E4M3) return k == 7 || n > 72;               // (of more than 72 atoms of 3x3 and 5x5 none is built there)
+    const bool f32 = a.coeff_dtype == SR_F32;
+    if (k == 5 && a.C == 3 && n <= 72 && !f32) return false;
+    const long long cus = units_of(a);
+    if ((a.W + 127ll) / 128 * a.H * a.N <= cus) return true;               // (single rows)
+    if (built > streaming) return false;
+    Walk s, t;
+    if (launch_mfma(a, k, a.io_f16, 0, LaunchTo(&s)) != hipSuccess || launch_slots(a, k, true, LaunchTo(&t)) != hipSuccess) return false;
+    // in half pixels
+    const long long halo = 18ll * (k - 1), fixed = 48, wide = 2ll * s.width * s.rows + halo * s.width / 128;
+    const long long there = s.form == 1 ? (s.pieces + cus - 1) / cus * (wide + fixed)
+                                        : ((s.pieces + s.waves - 1) / s.waves + cus - 1) / cus * s.waves * wide;
+    const int word = f32 ? 1 : 2, width = t.rows >= 4 && a.W < 128 ? (a.W + 32 * word - 1) / (32 * word) * 32 * word : 128;      // (a narrow image: its units only)
+    const long long here = (t.pieces + cus - 1) / cus * (2ll * width * t.rows + halo * width / 128 + fixed);
+    const bool shared_lines = !f32 && a.W % 16 != 0, many = n > 72;
+    const int limit = built < streaming                       ? 850         // thousandths
+                      : many && f32                           ? (k == 7 ? 760 : t.rows >= 4 ? 925 : 950)
+                      : t.rows <= 2                           ? (k == 7 && a.C == 3 ? (many ? 1030 : 1060) : many ? 860 : k == 7 ? 880 : k == 3 ? 970 : 1030)
+                      : many && k == 3 && (shared_lines || t.rows == 4) ? 950
+                      : shared_lines && many                  ? (a.s == 4 && t.pieces <= 2 * cus ? (s.rows == 24 && a.C == 3 ? 720 : 1050) : k == 7 ? 900 : 855)
+                      : shared_lines && k == 3 && t.pieces <= 3 * cus ? (a.C == 3 && a.s != 4 && t.pieces <= 2 * cus ? 970 : 1040)
+                                                              : 1130;
+    return 1000 * there >= limit * here;
 }
 
 hipError_t launch_slots(const AssembleArgs& a, int k, bool streamed, const LaunchTo& st) {

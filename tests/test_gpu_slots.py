@@ -130,8 +130,9 @@ def test_random_shapes_against_the_generic_kernel():
 # other side of each line: the result is the matrix-core kernel's either way
 @pytest.mark.parametrize("n, c, h, w, s, L, k, cd, io, slots", [
     (1, 3, 60, 70, 3, 100, 5, "f8", "f32", True), (1, 1, 3, 5, 2, 128, 3, "f32", "f16", True), (2, 1, 40, 25, 4, 73, 5, "f32", "f32", True),
-    (1, 3, 82, 155, 2, 72, 7, "f8", "f32", True), (1, 3, 250, 260, 2, 72, 7, "f8", "f32", False), (1, 1, 64, 64, 2, 72, 5, "f32", "f32", True),
-    (1, 1, 100, 110, 2, 72, 5, "f32", "f32", False), (1, 3, 93, 187, 3, 50, 5, "f32", "f16", True), (1, 3, 90, 120, 4, 72, 5, "f32", "f32", False),
+    (1, 3, 82, 155, 2, 72, 7, "f8", "f32", True), (1, 3, 250, 260, 2, 72, 7, "f8", "f32", True), (1, 1, 64, 64, 2, 72, 5, "f32", "f32", True),
+    (1, 1, 100, 110, 2, 72, 5, "f32", "f32", False), (1, 3, 93, 187, 3, 50, 5, "f32", "f16", True), (1, 3, 90, 120, 4, 72, 5, "f32", "f32", True), (1, 3, 90, 120, 4, 48, 5, "f32", "f32", False), (1, 1, 173, 352, 2, 115, 3, "f32", "f16", False),
+    (1, 1, 3000, 4, 4, 98, 5, "f32", "f16", True), (1, 3, 60, 140, 4, 30, 7, "f32", "f32", True), (1, 3, 170, 175, 4, 128, 5, "bf16", "f16", False),
     (1, 3, 125, 131, 2, 128, 3, "f16", "f32", True), (1, 3, 150, 311, 3, 72, 3, "f16", "f32", True), (1, 3, 150, 320, 3, 72, 3, "f16", "f32", False), (1, 3, 150, 311, 3, 72, 5, "f16", "f32", False),
     (1, 1, 109, 152, 3, 72, 5, "f16", "f16", True), (1, 3, 300, 301, 3, 128, 5, "bf16", "f32", True), (1, 3, 10, 56, 2, 72, 3, "f16", "f32", True), (1, 3, 10, 40, 2, 72, 5, "f16", "f32", False)])
 def test_planar_calls_that_are_faster_here(oracle, n, c, h, w, s, L, k, cd, io, slots):
@@ -162,8 +163,8 @@ def test_an_infinite_image_value_stays_within_its_patches():
 # More tiles than workgroups, tiles of one or two rows, and a last tile of a row with fewer units than a workgroup has wavefronts: those
 # that sit it out still have to fetch their first unit of the next tile
 @pytest.mark.parametrize("n, c, h, w, s, L, k, cd, logits", [
-    (1, 1, 104, 69, 4, 128, 5, "f32", False), (1, 3, 119, 135, 4, 100, 3, "f32", False), (1, 3, 164, 143, 4, 128, 7, "f32", False),
-    (1, 3, 280, 611, 2, 128, 7, "f32", False), (1, 1, 123, 289, 2, 56, 7, "f32", False), (4, 3, 131, 321, 2, 100, 3, "f32", False),
+    (1, 1, 104, 69, 4, 128, 5, "f32", False), (1, 3, 119, 135, 4, 100, 3, "f32", False), (1, 2, 164, 143, 4, 128, 7, "f32", False),
+    (1, 2, 280, 611, 2, 128, 7, "f32", False), (1, 1, 123, 289, 2, 56, 7, "f32", False), (4, 2, 131, 321, 2, 100, 3, "f32", False),
     (1, 1, 172, 129, 2, 73, 5, "f32", False), (400, 1, 1, 260, 2, 72, 5, "f32", True), (400, 2, 1, 260, 2, 40, 5, "f16", True),
     (1, 1, 219, 402, 2, 72, 3, "bf16", True), (1, 1, 146, 575, 3, 55, 3, "f16", True)])
 def test_wavefronts_without_a_unit_in_a_partial_tile(n, c, h, w, s, L, k, cd, logits):
