@@ -122,7 +122,7 @@ void make_plan(Plan& p, const sr_tensor* lr, const sr_tensor* coeff, const sr_te
     if ((want == SR_KERNEL_MFMA || (tile != 0 && want != SR_KERNEL_GENERIC)) && !can_mfma) { p.status = SR_ERR_UNSUPPORTED; return; }
     p.kernel = (want == SR_KERNEL_GENERIC || !can_mfma) ? SR_KERNEL_GENERIC : SR_KERNEL_MFMA;
     p.tile = tile;
-    if (!p.empty) p.slots = p.kernel == SR_KERNEL_MFMA ? tile == 0 && slots_faster(a, k) : want == SR_KERNEL_AUTO && slots_supported(a, k);
+    if (!p.empty) p.slots = p.kernel == SR_KERNEL_MFMA ? tile == 0 && slots_faster(a, k) : want == SR_KERNEL_AUTO && slots_supported(a, k) && !generic_faster(a, k);
 }
 
 // Launches a valid, non-empty plan, or says how it would be walked (see LaunchTo).

@@ -42,6 +42,7 @@ int mfma_capacity(const AssembleArgs& a, int k);        // of the instantiation 
 hipError_t launch_mfma(const AssembleArgs& a, int k, bool io_f16, int tile, const LaunchTo& st);
 // Matrix-core kernel for calls the one above has no instantiation for (coefficient dtype: a.coeff_dtype); make_plan chooses
 bool slots_supported(const AssembleArgs& a, int k);
+bool generic_faster(const AssembleArgs& a, int k);     // ... but are faster on the generic kernel
 bool slots_faster(const AssembleArgs& a, int k);       // ... and those that it has one for but serves slower
 hipError_t launch_slots(const AssembleArgs& a, int k, bool streamed, const LaunchTo& st);      // streamed: with the streaming kernel's bits
 // Per-pixel list form (sr_dict_assemble_list) on the matrix cores: a.coeff = values, a.index, a.T set; kept = identity.

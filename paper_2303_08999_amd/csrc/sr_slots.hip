@@ -11,28 +11,49 @@ hipError_t launch_slots_k5c3(const AssembleArgs& a, bool streamed, const LaunchT
 hipError_t launch_slots_k7c1(const AssembleArgs& a, bool streamed, const LaunchTo& st);
 hipError_t launch_slots_k7c3(const AssembleArgs& a, bool streamed, const LaunchTo& st);
 
+// Few atoms: the generic kernel's time grows with them, this one's hardly below the 32 that its smallest instantiation
+// folds.  Before the pixel-shuffle, generic / this, us: 1060 x 1020 x1 fp32 5x5 14 atoms 34 / 39, 24 atoms 55 / 39; 7x7 24 atoms 64 / 65;
+// planar 881 thousand x2 fp32 18 atoms 34 / 42; x3 fp8 5x5 24 atoms 52 / 54, 7x7 24 atoms 72 / 82, 3x3 248 thousand 16 atoms 10.7 / 14;
+// bfloat16 x1 5x5 6 atoms 29 / 36, 14 atoms 40 / 36; fp16 x2 5x5 323 thousand 13 atoms 15 / 22.  Logits (800 drawn calls of 1 to 28
+// atoms; generic over this): one channel up to 8 atoms 0.5 .. 1.07, 9 atoms 1.0 .. 1.33; two and three up to 11 atoms (3x3 12, 7x7 14)
+// 0.5 .. 1.33, from there 0.9 .. 2.
+static bool few_atoms(const AssembleArgs& a, int k) {
+    const int n = a.n_fold;
+    if (a.logits) return n <= (a.C == 1 ? 8 : k == 3 ? 12 : k == 5 ? 11 : 14);
+    if (a.coeff_dtype == SR_F32) return n <= (k == 7 ? 26 : k == 3 ? 22 : a.C == 1 ? 16 : 20);
+    if (a.coeff_dtype == SR_F8E4M3) return n <= (a.C == 1 ? (k == 3 ? 14 : 10) : k == 3 ? 24 : k == 5 ? 25 : 32);
+    return n <= (a.C == 1 ? 12 : 16);
+}
+
 // Up to 128 folded atoms, one to three channels, every atom's coefficients of an image within 4 GB, rows of at least one word of
 // coefficients; the generic kernel takes what is left.
 bool slots_supported(const AssembleArgs& a, int k) {
     const int cb = a.coeff_dtype == SR_F32 ? 4 : (a.coeff_dtype == SR_F8E4M3 ? 1 : 2);
     if ((k != 3 && k != 5 && k != 7) || a.C < 1 || a.C > 3 || a.n_fold < 1 || a.n_fold > 128 || a.pixel_major || a.blocked) return false;
-    // Few atoms: the generic kernel's time grows with them, this one's hardly below the 32 that its smallest instantiation
-    // folds.  Before the pixel-shuffle, generic / this, us: 1060 x 1020 x1 fp32 5x5 14 atoms 34 / 39, 24 atoms 55 / 39; 7x7 24 atoms 64 / 65;
-    // x3 fp8 5x5 24 atoms 52 / 54, 7x7 24 atoms 72 / 82, 3x3 14 atoms 33 / 34; bfloat16 5x5 6 atoms 29 / 36, 14 atoms 40 / 36.
-    if (!a.logits && a.n_fold <= (a.coeff_dtype == SR_F32 ? (k == 7 ? 26 : k == 3 ? 22 : 16)
-                                  : a.coeff_dtype == SR_F8E4M3 ? (a.C == 1 ? 10 : k == 3 ? 14 : k == 5 ? 25 : 32) : 12)) return false;
-    // 7x7 atoms before the pixel-shuffle, beyond small frames: the two blocks of matrix instructions of every slot and the wide tiles
-    // cost more than the generic kernel's fold until there are many atoms.  1350 thousand pixels x3 fp8 33 atoms 121 / 252, 60 atoms 189 /
-    // 252, all of 128 390 / 279; fp32 33 atoms 124 / 165, 60 atoms 195 / 164, 80 atoms 255 / 266; but 103 thousand fp8 33 atoms 32 / 25.
-    if (!a.logits && a.pre_shuffle && k == 7 && (long long)a.N * a.H * a.W > 150000) {
-        if (a.coeff_dtype == SR_F8E4M3 && a.C != 1 && a.n_fold <= 90) return false;
-        if (a.coeff_dtype == SR_F32 && (a.n_fold <= 48 || (a.C != 1 && a.n_fold > 72 && a.n_fold <= 84))) return false;
-    }
     if (a.logits && (a.n_fold != a.L || a.coeff_dtype == SR_F8E4M3)) return false;
     if ((a.pre_shuffle ? a.w : a.W) < 4 / cb || a.H < 1) return false;
     if ((unsigned long long)a.L * a.H * a.W * cb >= (1ull << 32)) return false;
     if ((unsigned long long)a.C * a.H * a.W * 4ull > 0xffffffc0ull) return false;      // lanes outside the image store from there on
-    return true;
+    return !few_atoms(a, k);
+}
+
+// The calls among them that the generic kernel serves faster: its fold grows with the atoms, this kernel's in steps (32, 72, 128), and
+// beyond small frames the filtering and the wide tiles weigh.  Generic / this, us:
+//   7x7 before the pixel-shuffle, x3 fp8 1350 thousand pixels 33 atoms 121 / 252, 60 atoms 189 / 252, all of 128 390 / 279, 337 thousand
+//   97 atoms 92 / 110, 95 thousand at scale 3 36 atoms 23 / 44, but 103 thousand 33 atoms 32 / 25; fp32 1350 thousand 33 atoms 124 / 165, 60 atoms
+//   195 / 164, 80 atoms 255 / 266; planar 560 thousand x2 fp32 28 atoms 45 / 49; 319 thousand x2 bfloat16 33 atoms 33 / 36.
+//   fp32 just above 32 atoms: 3x3 1615 thousand x3 37 atoms 74 / 108, 196 thousand x1 33 atoms 18 / 21, 924 thousand x3 40 atoms
+//   0.96 of each other, but 63 thousand 40 atoms 1.07; 5x5 283 thousand x2 34 atoms 24 / 26, 1638 thousand x2 40 atoms 99 / 118.
+bool generic_faster(const AssembleArgs& a, int k) {
+    const long long px = (long long)a.N * a.H * a.W;
+    const int n = a.n_fold;
+    if (a.logits) return false;
+    if (k == 7) {
+        if (a.coeff_dtype == SR_F32) return px > 150000 && (n <= 48 || (a.pre_shuffle && a.C != 1 && n > 72 && n <= 84));
+        if (!a.pre_shuffle || a.C == 1) return false;
+        return a.coeff_dtype == SR_F8E4M3 ? n <= 100 && px > (a.s == 3 ? 25000 : 110000) : n > 32 && n <= 36 && px > 150000;
+    }
+    return a.coeff_dtype == SR_F32 && px > 120000 && n > 32 && n <= (k == 3 || a.C != 1 ? 42 : 36);
 }
 
 // Planar coefficients that the streaming kernel has an instantiation for and this one is faster with (and gives the same bits).  Both launches are
@@ -68,7 +89,7 @@ bool slots_faster(const AssembleArgs& a, int k) {
     const long long halo = 18ll * (k - 1), fixed = 48, wide = 2ll * s.width * s.rows + halo * s.width / 128;
     const long long there = s.form == 1 ? (s.pieces + cus - 1) / cus * (wide + fixed)
                                         : ((s.pieces + s.waves - 1) / s.waves + cus - 1) / cus * s.waves * wide;
-    const int word = f32 ? 1 : 2, width = t.rows >= 4 && a.W < 128 ? (a.W + 32 * word - 1) / (32 * word) * 32 * word : 128;      // (a narrow image: its units only)
+    const int width = f32 && t.rows >= 4 && a.W < 128 ? (a.W + 31) / 32 * 32 : 128;      // (a narrow image: its units only)
     const long long here = (t.pieces + cus - 1) / cus * (2ll * width * t.rows + halo * width / 128 + fixed);
     const bool shared_lines = !f32 && a.W % 16 != 0, many = n > 72;
     const int limit = built < streaming                       ? 850         // thousandths

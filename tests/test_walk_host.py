@@ -177,3 +177,18 @@ def test_the_kernel_that_is_launched():
     assert runs(C=5, cd="f16") == runs(L=200) == (sr.SR_RUNS_GENERIC, (0,) * 6)
     lr, coeff, d, out = _far(*[(sr.SR_F32, 1, 3, 8, 8)] * 4)
     assert sr.load().sr_dict_assemble_runs(lr, coeff, d, 72, 5, 4, 3, out, None, 0, None, None) == -1
+
+
+# calls that the generic kernel serves faster, and the same on the other side of the line
+@pytest.mark.parametrize("call, atoms", [
+    (dict(C=1, H=600, W=600, s=2, k=5, logits=True), (8, 9)), (dict(C=1, H=600, W=600, s=3, k=7, cd="f32", logits=True, pre=True), (8, 9)),
+    (dict(C=2, H=600, W=600, s=4, k=7, cd="bf16", logits=True), (14, 15)), (dict(C=2, H=600, W=600, s=2, k=5, pre=True), (16, 17)),
+    (dict(C=1, H=600, W=600, s=2, k=3, cd="bf16", pre=True), (12, 13)), (dict(C=3, H=600, W=600, s=2, k=3, cd="f32", pre=True), (22, 23)),
+    (dict(C=3, H=600, W=600, s=2, k=3, cd="f32", pre=True), (33, 32)), (dict(C=3, H=600, W=600, s=2, k=3, cd="f32", pre=True), (42, 43)),
+    (dict(C=2, H=600, W=600, s=2, k=5, cd="f32"), (42, 43)), (dict(C=2, H=600, W=600, s=2, k=5, cd="f32"), (20, 21)), (dict(C=2, H=600, W=600, s=2, k=7, cd="f32"), (48, 49)),
+    (dict(C=3, H=600, W=600, s=2, k=7, cd="bf16", pre=True), (36, 37)), (dict(C=3, H=600, W=600, s=2, k=7, cd="f8", pre=True), (100, 101))])
+def test_calls_that_the_generic_kernel_serves_faster(call, atoms):
+    assert runs(L=atoms[0], **call) == (sr.SR_RUNS_GENERIC, (0,) * 6)
+    assert runs(L=atoms[1], **call)[0] == sr.SR_RUNS_SLOTS
+    if call.get("cd") in ("f32", "f8") and atoms[0] > 25:     # (a small frame: not)
+        assert runs(L=atoms[0], **dict(call, H=48, W=72))[0] == sr.SR_RUNS_SLOTS
