@@ -34,6 +34,7 @@ bool slots_supported(const AssembleArgs& a, int k) {
     if ((a.pre_shuffle ? a.w : a.W) < 4 / cb || a.H < 1) return false;
     if ((unsigned long long)a.L * a.H * a.W * cb >= (1ull << 32)) return false;
     if ((unsigned long long)a.C * a.H * a.W * 4ull > 0xffffffc0ull) return false;      // lanes outside the image store from there on
+    if ((long long)a.N * a.H * ((a.W + 31) / 32) > 0x3fffffffLL) return false;         // tiles are counted in 32 bits
     return !few_atoms(a, k);
 }
 

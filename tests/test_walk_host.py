@@ -153,8 +153,13 @@ def test_images_up_to_4_gb_are_the_matrix_core_kernels():
     assert walk(C=1, H=1 << 15, W=1 << 15, s=2, L=1, cd="f8", kernel=sr.SR_KERNEL_MFMA)[0] == -3
 
 
+def _apart(*tensors):
+    """_far for tensors of many terabytes."""
+    return [sr.sr_tensor((i + 1) << 52, *t) for i, t in enumerate(tensors)]
+
+
 def runs(n=1, C=3, H=2160, W=3840, s=4, L=72, k=5, cd="f16", kept=None, pre=False, logits=False, kernel=sr.SR_KERNEL_AUTO, tile=0):
-    lr, coeff, d, out = _far((sr.SR_F32, n, C, H // s, W // s), (DT[cd], n, L * s * s, H // s, W // s) if pre else (DT[cd], n, L, H, W),
+    lr, coeff, d, out = _apart((sr.SR_F32, n, C, H // s, W // s), (DT[cd], n, L * s * s, H // s, W // s) if pre else (DT[cd], n, L, H, W),
                              (sr.SR_F32, 1, L, k, k), (sr.SR_F32, n, C, H, W))
     opts = sr.make_options(kernel, tile, sr.SR_COEFF_PRE_SHUFFLE if pre else sr.SR_COEFF_PLANAR, sr.SR_COEFF_LOGITS if logits else sr.SR_COEFF_VALUES)
     ka = (ctypes.c_int * len(kept))(*kept) if kept else None
@@ -192,3 +197,10 @@ def test_calls_that_the_generic_kernel_serves_faster(call, atoms):
     assert runs(L=atoms[1], **call)[0] == sr.SR_RUNS_SLOTS
     if call.get("cd") in ("f32", "f8") and atoms[0] > 25:     # (a small frame: not)
         assert runs(L=atoms[0], **dict(call, H=48, W=72))[0] == sr.SR_RUNS_SLOTS
+
+
+def test_more_tiles_than_32_bits_count():
+    """Thin images in their largest number: the generic kernel, as before, and no refusal."""
+    for call in (dict(pre=True, cd="f8"), dict(logits=True, C=1), dict(C=2, cd="f32")):
+        assert runs(n=65535, H=262140, W=8, s=2, L=72, **call) == (sr.SR_RUNS_GENERIC, (0,) * 6)
+        assert runs(n=600, H=262140, W=8, s=2, L=72, **call)[0] == sr.SR_RUNS_SLOTS
