@@ -1251,7 +1251,7 @@ int atom_gram(const sr_tensor* up, const sr_tensor* coeff, const sr_tensor* dict
         if (tri) {                                                                                          \
             /* few items: a wavefront has its SIMD to itself */                                            \
             const int waves = items <= 4ull * GRIDT ? 4 : 8;                                                \
-            grid = items >= (unsigned)waves * (unsigned long long)GRIDT ? GRIDT : (items == 0 ? 1 : (int)((items + waves - 1) / waves)); \
+            grid = items >= (unsigned)waves * (unsigned long long)GRIDT ? GRIDT : (int)((items + waves - 1) / waves); \
             switch (a.n16) {                                                                                \
             case 1:  SR_GRAM_TRI(KS, TC, 1); break;                                                         \
             case 2:  SR_GRAM_TRI(KS, TC, 2); break;                                                         \
@@ -1277,7 +1277,8 @@ int atom_gram(const sr_tensor* up, const sr_tensor* coeff, const sr_tensor* dict
         else if (coeff->dtype == SR_BF16) SR_GRAM_LAUNCH_T(KS, bf16v);                                      \
         else SR_GRAM_LAUNCH_T(KS, e4m3);                                                                    \
     } while (0)
-    switch (k) {
+    if (empty) grid = 0;                                   // no sums: zeros (the pointers may be null, and nothing divides by an empty row)
+    else switch (k) {
     case 3:  SR_GRAM_LAUNCH(3); break;
     case 5:  SR_GRAM_LAUNCH(5); break;
     default: SR_GRAM_LAUNCH(7); break;

@@ -137,6 +137,20 @@ def test_empty_batch_and_undersized_scratch():
     assert err.value.status == -2
 
 
+@pytest.mark.parametrize("n, h, w, L", [(0, 8, 8, 72), (3, 0, 40, 72), (2, 40, 0, 15), (1, 0, 0, 100)])
+@pytest.mark.parametrize("cd", [sr.SR_F16, sr.SR_F32])
+def test_empty_images_read_nothing(n, h, w, L, cd):
+    """An empty call need not bring any tensor: the normal equations are zero, and no kernel looks at a pointer."""
+    shapes = [(sr.SR_F32, n, 3, h, w), (cd, n, L, h, w), (sr.SR_F32, 1, L, 5, 5), (sr.SR_F32, n, 3, h, w)]
+    up, coeff, d, target = [sr.sr_tensor(None, *s) for s in shapes]
+    size = sr.sr_atom_gram_workspace_bytes(L)
+    workspace = torch.full((size // 8,), float("nan"), device=DEV, dtype=torch.float64)
+    normal = torch.full((L * L + L + 2,), float("nan"), device=DEV, dtype=torch.float64)
+    assert sr.load().sr_atom_gram(up, coeff, d, target, L, 5, 3, 1, workspace.data_ptr(), size, normal.data_ptr(), 0) == 0
+    torch.cuda.synchronize()
+    assert not normal.cpu().numpy().any()
+
+
 def test_whole_chain_recovers_a_planted_selection(oracle):
     """The target is what the path itself produces from 6 of 40 atoms with known scales;
     the selection must find exactly them, and assembling with what it returns must
