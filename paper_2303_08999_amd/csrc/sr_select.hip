@@ -324,7 +324,8 @@ struct UpperBlocks {
     }
 };
 
-template <int K, typename TC, int N16>
+// WIDE: planes so large that 16 of them, or one's patch operands, pass 4 GB: offsets within a row, and 64 bits for the lane's plane.
+template <int K, typename TC, int N16, bool WIDE>
 __global__ __launch_bounds__(NTT, 2) void k_atom_gram_tri(const GramArgs a, unsigned long long items) {
     constexpr int KK = K * K, R = (K - 1) / 2, KS = (KK + 3) / 4;     // KS: 4-tap steps of the responses
     constexpr int NB = N16 * (N16 + 1) / 2;
@@ -339,7 +340,8 @@ __global__ __launch_bounds__(NTT, 2) void k_atom_gram_tri(const GramArgs a, unsi
 
     const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, kq = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const unsigned plane = (unsigned)a.H * (unsigned)a.W;             // below 2^30, see atom_gram
+    typedef typename std::conditional<WIDE, size_t, unsigned>::type Plane;
+    const Plane plane = (Plane)a.H * (Plane)a.W;                      // (WIDE or below 2^28 elements, see atom_gram)
     const int nseg = (a.nx + 15) / 16;
 
     // this wavefront's items
@@ -398,9 +400,10 @@ __global__ __launch_bounds__(NTT, 2) void k_atom_gram_tri(const GramArgs a, unsi
     const bool holds_target = c16 == (a.L & 15);                      // column L is the target: this lane's, in block L / 16
     const int tblk = a.L >> 4;
 
-    // Offsets within a plane: the patch operands in bytes (lane: sample c16, tap 4 ks + kq), the lane's four samples in elements.  Samples
-    // past the end of the row are clamped to its last one and their responses zeroed.
+    // Offsets within a plane (WIDE: from the first of the k image rows, from the lattice row): the patch operands in bytes (lane: sample c16,
+    // tap 4 ks + kq), the lane's four samples in elements.  Samples past the end of the row are clamped to its last one and their responses zeroed.
     unsigned aoff[KS], soff[4];
+    int top = 0, lattice_row = 0;                                     // WIDE: these rows
     int left = 0;                                                     // samples of the item that exist, from 4 kq on
     // (from a segment of the row to the next, nothing clamped in either: all of them move by as much)
     auto place = [&](int iy_, int seg_, const auto moved) {
@@ -415,15 +418,19 @@ __global__ __launch_bounds__(NTT, 2) void k_atom_gram_tri(const GramArgs a, unsi
             return;
         }
         const int Xc = (x0 + c16 < xl ? x0 + c16 : xl) * a.stride;
+        if constexpr (WIDE) {
+            top = Y > R ? Y - R : 0;
+            lattice_row = Y;
+        }
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             const int tap = 4 * ks + kq, t = tap < KK ? tap : 0, dy = t / K, dx = t - dy * K;
-            aoff[ks] = 4u * ((unsigned)clampi(Y + dy - R, 0, a.H - 1) * (unsigned)a.W + (unsigned)clampi(Xc + dx - R, 0, a.W - 1));
+            aoff[ks] = 4u * ((unsigned)(clampi(Y + dy - R, 0, a.H - 1) - top) * (unsigned)a.W + (unsigned)clampi(Xc + dx - R, 0, a.W - 1));
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int x = x0 + 4 * kq + e;
-            soff[e] = (unsigned)Y * (unsigned)a.W + (unsigned)((x < xl ? x : xl) * a.stride);
+            soff[e] = (unsigned)(Y - lattice_row) * (unsigned)a.W + (unsigned)((x < xl ? x : xl) * a.stride);
         }
     };
     // the lane's four samples side by side in memory (stride 1, all of them in the row, of every lane): one load
@@ -431,8 +438,8 @@ __global__ __launch_bounds__(NTT, 2) void k_atom_gram_tri(const GramArgs a, unsi
     float av[KS], h[4];
     auto fetch = [&](int n_, int c_) {                                // an item's patch operands and targets
         const size_t pl = ((size_t)n_ * a.C + c_) * plane;
-        const char* const up = (const char*)(a.up + pl);
-        const char* const tg = (const char*)(a.target + pl);
+        const char* const up = (const char*)(a.up + pl + (size_t)top * a.W);
+        const char* const tg = (const char*)(a.target + pl + (size_t)lattice_row * a.W);
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) av[ks] = *(const float*)(up + aoff[ks]);
         if (adjacent(left)) {
@@ -449,14 +456,14 @@ __global__ __launch_bounds__(NTT, 2) void k_atom_gram_tri(const GramArgs a, unsi
     typedef typename BitsOf<sizeof(TC)>::type Bits;
     constexpr int VW = sizeof(TC);                                    // words of four side by side
     typedef unsigned words __attribute__((ext_vector_type(VW == 1 ? 2 : VW), aligned(sizeof(TC))));
-    // Elements from a block's first plane to the lane's; 16 planes stay below 4 GB, see atom_gram.  Lanes past the last atom
+    // Elements from a block's first plane to the lane's (not WIDE: 16 planes stay below 4 GB).  Lanes past the last atom
     // take its plane (the last block may hold the target column only: its first plane is the last atom's then).
     const int last_block = 16 * (N16 - 1) < a.L ? 16 * (N16 - 1) : a.L - 1;
-    const unsigned plane_off = (unsigned)c16 * plane, plane_off_last = (unsigned)(last_block + c16 < a.L ? c16 : a.L - 1 - last_block) * plane;
+    const Plane plane_off = (Plane)c16 * plane, plane_off_last = (Plane)(last_block + c16 < a.L ? c16 : a.L - 1 - last_block) * plane;
     auto fetch_phi = [&](int n_) {                                    // the coefficients of the lane's atoms and samples
-        const Bits* const img = (const Bits*)a.coeff + (size_t)n_ * a.L * plane;
+        const Bits* const img = (const Bits*)a.coeff + (size_t)n_ * a.L * plane + (size_t)lattice_row * a.W;
         auto at = [&](int nb, int e) -> const char* {
-            return (const char*)(img + (size_t)(nb == N16 - 1 ? last_block : 16 * nb) * plane) + ((nb == N16 - 1 ? plane_off_last : plane_off) + soff[e]) * (unsigned)sizeof(TC);
+            return (const char*)(img + (size_t)(nb == N16 - 1 ? last_block : 16 * nb) * plane) + ((nb == N16 - 1 ? plane_off_last : plane_off) + soff[e]) * (Plane)sizeof(TC);
         };
         if (adjacent(left)) {
 #pragma unroll
@@ -1237,14 +1244,17 @@ int atom_gram(const sr_tensor* up, const sr_tensor* coeff, const sr_tensor* dict
     a.n16 = column_blocks(L);
     a.ntile = upper_blocks(a.n16);
     const hipStream_t st = (hipStream_t)stream;
-    // Up to five column blocks (79 atoms) a wavefront's registers hold the whole triangle: k_atom_gram_tri, any stride.  More:
-    // staged row segments (strides up to 4, LDS for the tiles).  Both with 32-bit offsets within a plane; else per-lane gathers.
-    const bool offsets32 = (int64_t)up->h * up->w < (1 << 30);
-    const bool tri = a.n16 <= 5 && (uint64_t)up->h * up->w * 16 * (coeff->dtype == SR_F32 ? 4 : coeff->dtype == SR_F8E4M3 ? 1 : 2) < (1ull << 32);
+    // Up to five column blocks (79 atoms) a wavefront's registers hold the whole triangle: k_atom_gram_tri, any stride and plane.  More:
+    // staged row segments (strides up to 4, LDS for the tiles, 32-bit offsets within a plane), else per-lane gathers.
+    const bool offsets32 = (int64_t)up->h * up->w < (1 << 30), tri = a.n16 <= 5;
+    const bool wide = (uint64_t)up->h * up->w * 16 * (coeff->dtype == SR_F32 ? 4 : coeff->dtype == SR_F8E4M3 ? 1 : 2) >= (1ull << 32);
     int grid = GRID;
     const unsigned long long items = (unsigned long long)a.N * a.ny * ((a.nx + 15) / 16) * a.C;
 #define SR_GRAM_TRI(KS, TC, N16)                                                                           \
-    hipLaunchKernelGGL((k_atom_gram_tri<KS, TC, N16>), dim3(grid), dim3(64 * waves), 0, st, a, items)
+    do {                                                                                                    \
+        if (wide) hipLaunchKernelGGL((k_atom_gram_tri<KS, TC, N16, true>), dim3(grid), dim3(64 * waves), 0, st, a, items); \
+        else hipLaunchKernelGGL((k_atom_gram_tri<KS, TC, N16, false>), dim3(grid), dim3(64 * waves), 0, st, a, items); \
+    } while (0)
 #define SR_GRAM_LAUNCH_T(KS, TC)                                                                           \
     do {                                                                                                    \
         const size_t lds = rows_lds_floats(KS, 9, channels) * sizeof(float);                                \

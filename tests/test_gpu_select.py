@@ -137,6 +137,35 @@ def test_empty_batch_and_undersized_scratch():
     assert err.value.status == -2
 
 
+# Planes of 2^26 fp32, 2^27 16-bit and 2^28 8-bit elements and more: 16 of them pass 4 GB; and of 2^30, whose patch operands do
+@pytest.mark.parametrize("c, h, w, L, k, cd, stride", [(2, 8192, 8192, 18, 5, torch.float32, 61), (1, 8192, 8201, 2, 3, torch.float32, 1),
+                                                       (2, 11600, 11603, 16, 7, torch.float16, 53), (1, 32768, 32771, 2, 3, torch.float8_e4m3fn, 127)])
+def test_planes_beyond_32_bit_offsets(c, h, w, L, k, cd, stride):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(78)
+    up, target = (torch.rand((1, c, h, w), generator=g, device=DEV) for _ in range(2))
+    coeff = torch.empty((1, L, h, w), device=DEV, dtype=cd)
+    for l in range(L):
+        coeff[0, l] = torch.rand((h, w), generator=g, device=DEV).to(cd)
+    d = torch.rand((L, k, k), generator=g, device=DEV)
+    got = sr.sr_atom_gram(up, coeff, d, target, L, k, c, stride).cpu().numpy()
+    ref = torch.zeros((L + 1, L + 1), device=DEV, dtype=torch.float64)
+    xs, r = torch.arange(0, w, stride, device=DEV), (k - 1) // 2
+    for ys in torch.arange(0, h, stride, device=DEV).split(64):
+        phi = coeff[0, :, ys][:, :, xs].double().reshape(L, -1) if cd != torch.float8_e4m3fn else torch.stack(
+            [coeff[0, l].view(torch.uint8)[ys][:, xs].view(cd).double().reshape(-1) for l in range(L)])
+        for ch in range(c):
+            taps = [up[0, ch][(ys + i // k - r).clamp(0, h - 1)][:, (xs + i % k - r).clamp(0, w - 1)].double().reshape(-1) for i in range(k * k)]
+            resp = torch.cat([(d.reshape(L, -1).double() @ torch.stack(taps)) * phi, target[0, ch][ys][:, xs].double().reshape(1, -1)])
+            ref += resp @ resp.T.contiguous()
+    ref = ref.cpu().numpy()
+    G, b, hh = got[:L * L].reshape(L, L), got[L * L:L * L + L], got[L * L + L]
+    assert got[-1] == c * len(range(0, h, stride)) * len(range(0, w, stride))
+    size = np.sqrt(np.diag(ref))                    # (the bound of test_triangle_in_registers)
+    assert (np.abs(G - ref[:L, :L]) <= 1e-5 * np.outer(size[:L], size[:L])).all()
+    assert (np.abs(b - ref[:L, L]) <= 1e-5 * size[:L] * size[L]).all() and abs(hh - ref[L, L]) <= 1e-5 * ref[L, L]
+
+
 @pytest.mark.parametrize("n, h, w, L", [(0, 8, 8, 72), (3, 0, 40, 72), (2, 40, 0, 15), (1, 0, 0, 100)])
 @pytest.mark.parametrize("cd", [sr.SR_F16, sr.SR_F32])
 def test_empty_images_read_nothing(n, h, w, L, cd):
