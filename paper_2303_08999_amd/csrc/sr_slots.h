@@ -746,7 +746,7 @@ template <int K, int CM, int CT, int NP8, int KIND>
 static hipError_t launch_slots_n(const AssembleArgs& a, const LaunchTo& st) {
     if constexpr (KIND != SLOT_STREAMED)
         return a.pre_shuffle ? launch_slots_p<K, CM, CT, NP8, KIND, true>(a, st) : launch_slots_p<K, CM, CT, NP8, KIND, false>(a, st);
-    else if constexpr (NP8 == 16 || (CT == CT_F8 ? K == 7 : K != 5 || CM == 1))        // (what slots_faster sends here)
+    else if constexpr (NP8 == 16 || (CT == CT_F8 ? K == 7 : CT == CT_F32 || K != 5 || CM == 1))      // (what slots_faster sends here)
         return launch_slots_p<K, CM, CT, NP8, KIND, false>(a, st);
     else
         return hipErrorInvalidValue;
@@ -761,8 +761,7 @@ static hipError_t launch_slots_k(const AssembleArgs& a, const LaunchTo& st) {
 
 template <int K, int CM, int CT>
 static hipError_t launch_slots_v(const AssembleArgs& a, bool streamed, const LaunchTo& st) {
-    if constexpr (CT != CT_F32)                        // (fp32 matrix instructions: one part, the same bits)
-        if (streamed) return launch_slots_k<K, CM, CT, SLOT_STREAMED>(a, st);
+    if (streamed) return launch_slots_k<K, CM, CT, SLOT_STREAMED>(a, st);
     if constexpr (CT != CT_F8)
         if (a.logits) return launch_slots_k<K, CM, CT, SLOT_LOGITS>(a, st);
     return launch_slots_k<K, CM, CT, SLOT_VALUES>(a, st);
