@@ -151,8 +151,12 @@ typedef struct {
  *
  * Supported: k in {3,5,7}; scale in {2,3,4}; 1 <= L <= SR_MAX_ATOMS;
  * 1 <= C <= SR_MAX_CHANNELS; N >= 0 (N = 0 or an empty image is a no-op
- * returning SR_OK).  With f16 or f8 coefficients the dictionary entries must
- * be finite in fp16 (|D| < 65504); f8 NaN codes give unspecified results.
+ * returning SR_OK).  Where the streaming matrix-core kernel runs (see
+ * sr_dict_assemble_runs) and the coefficients are f16, f8 or logits, the dictionary
+ * entries, times gamma where there is one, must be finite in fp16 (below 65504),
+ * and infinite coefficients may give NaN; the other kernels take any finite value
+ * and give infinities and NaN as plain fp32 sums do.  f8 NaN codes give
+ * unspecified results.
  */
 int sr_dict_assemble(const sr_tensor* lr, const sr_tensor* coeff, const sr_tensor* dict,
                      int L, int k, int scale, int channels,
@@ -190,15 +194,19 @@ int sr_dict_assemble_selective(const sr_tensor* lr, const sr_tensor* coeff, cons
  *   f8  coefficients: as f32, and lr->data 4-byte aligned with an even number of
  *                     elements if the image is f16;
  *   images beyond 4 GB of coefficients (element offsets): at most 72 folded atoms.
- * Every other supported case runs on the generic kernel.
+ * Of these planar calls a second matrix-core kernel serves those that it is faster with, with the same bits (f8
+ * coefficients of more than 72 atoms with k = 3 or 5, which the first has no instantiation for, and of k = 7: all of them).
+ * With SR_KERNEL_AUTO it also serves most other cases of the planar order and the one before the pixel-shuffle: C up to 3, at
+ * most 128 folded atoms, but few atoms.  The generic kernel runs what is left, and whatever SR_KERNEL_GENERIC asks for.
+ * sr_dict_assemble_runs says which one a call gets.
  *
  * opts->coeff_layout = SR_COEFF_PRE_SHUFFLE: `coeff` is the tensor the coefficient network
  * produces before its final pixel-shuffle, [N][L*s*s][h][w] (so coeff->c = L*scale*scale and
- * coeff->h, coeff->w are the LR sizes); the call gives exactly the result of shuffling it to
+ * coeff->h, coeff->w are the LR sizes); the call gives the result of shuffling it to
  * [N][L][s*h][s*w] first, without that 2 x (L * H * W) byte pass over memory.  Every kernel
  * takes it; the matrix-core kernel for k = 5, C = 3, f16 coefficients with up to 8 or 65 to 72
  * folded atoms, or bf16 coefficients with 65 to 72 and an LR width that is a multiple of 4 (byte
- * offsets), the generic kernel otherwise.
+ * offsets), the second matrix-core kernel or the generic one otherwise (see above).
  *
  * opts->coeff_layout = SR_COEFF_PIXEL_MAJOR: `coeff` is stored [N][s*h][s*w][L] (described with
  * c = L, h = s*h, w = s*w as for the planar order).  A wavefront's row of 128 pixels is then one
@@ -222,7 +230,7 @@ int sr_dict_assemble_selective(const sr_tensor* lr, const sr_tensor* coeff, cons
  * (the normalisation needs every atom), and so are f8 logits.  Logits of -infinity give a zero coefficient;
  * NaN or +infinity logits give unspecified results.  The matrix-core kernel takes k = 5, C = 3, 49 to 72
  * f16 or bf16 atoms in the planar order or (LR width a multiple of 4) in the order before the pixel-shuffle, under 4 GB
- * per image; the generic kernel everything else.
+ * per image; the second matrix-core kernel or the generic one everything else (see above).
  *
  * opts->tile (the launch-shape search of section III-B, Eq. 11-12, as a small set of compiled
  * tile shapes): index 0 is the library's default for the frame and is always accepted.  (By
@@ -315,7 +323,7 @@ int sr_dict_assemble_launch_shape(const sr_tensor* lr, const sr_tensor* coeff, c
 /* How the matrix-core kernel would walk the images of this call on the current device (256 CUs where there is none):
  * walk[0] = 1: tiles of walk[1] x walk[2] HR pixels, each of a workgroup's wavefronts together; walk[0] = 2: strips of
  * walk[1] columns in segments of walk[2] rows, each of one wavefront alone; walk[3] = tiles or segments of the call, walk[4]
- * = workgroups launched, walk[5] = wavefronts of each.  All zero with the generic kernel and for an empty call.  Returns as
+ * = workgroups launched, walk[5] = wavefronts of each.  All zero where sr_dict_assemble_plan says SR_KERNEL_GENERIC and for an empty call.  Returns as
  * sr_dict_assemble_plan.  Host only. */
 int sr_dict_assemble_walk(const sr_tensor* lr, const sr_tensor* coeff, const sr_tensor* dict,
                           int L, int k, int scale, int channels,

@@ -293,8 +293,8 @@ __global__ __launch_bounds__(NT, 1) void k_atom_gram(const GramArgs a) {
 // responses of atom 16 nb + c16 at samples 4 kq .. 4 kq + 3, and as an operand of step e it has to supply row (column) c16 at
 // sample kq of the four of that step, i.e. sample 4 kq + e: its e-th response as it stands, for both operands (the order of
 // the samples does not matter to the sum).  So nothing passes through LDS between the two contractions and no wavefront waits for
-// another before the end; two of them per SIMD take turns on the matrix pipe.  A block's sum over the 16 samples of
-// an item is fp32 and is added to a double at once.
+// another before the end; two of them per SIMD take turns on the matrix pipe.  A block's sum over four
+// items (64 samples and channels) is fp32, then it is added to a double.
 // Loads: the patch operands (one image element per lane and step) and the targets go out one item ahead, the coefficients,
 // which the channels of 16 samples share, as soon as the last channel has used the ones before; all of them
 // straight from global memory, whose lines neighbouring items share.
@@ -304,7 +304,8 @@ __global__ __launch_bounds__(NT, 1) void k_atom_gram(const GramArgs a) {
 // instruction adds its 4 cycles, a double-precision one 8 to 13), so every vector instruction counts: patch and sample offsets move
 // by a constant from segment to segment, four adjacent coefficients are one load, doubles are added every fourth item only.  The
 // fp32 sums (60 registers for 72 atoms) and the doubles (120) leave no room for the rest at two wavefronts per SIMD, so half of the
-// doubles live in LDS; one wavefront per SIMD holds all in registers but waits for memory (865 us against 660 below).
+// doubles live in LDS; one wavefront per SIMD holds all in registers but waits for memory (1920 x 1080 x3: 865 us against 660, both without
+// the one-load coefficients and the constant offset steps, which brought the latter to 645).
 // Before, eight wavefronts per workgroup in two roles passed 64-sample tiles through LDS, a barrier per channel.  Up-sampling and
 // normal equations, 72 atoms of 5x5, before / now, us: 1920 x 1080 x3 fp16 766 / 645 (the 35 + 60 matrix instructions of
 // every item are 480 of it), 1304 x 1134 x3 fp8 636 / 485, 160 x 112 x3 every second pixel 32.5 / 22; 60 atoms 1302 x 1227 x1 328 /

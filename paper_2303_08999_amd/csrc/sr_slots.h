@@ -17,7 +17,7 @@
 // What bounds it now: for large frames of many atoms the coefficients (logits 1638 x 1608 x1, 128 atoms: 153 us, 4.5 TB/s), for three
 // channels the filtering, whose slots share no patch values, and the up-sampling (together half of a 1020 x 1060 x3 frame), for small
 // ones the latency of one tile.  Generic kernel / this one, us: before the pixel-shuffle, 216 x 230 x3 fp16 72 atoms 28 / 12, 1020 x
-// 1060 x3 bfloat16 72 atoms 120 / 51, fp8 110 / 59, fp32 133 / 75; logits, 180 x 234 x1 fp16 72 atoms 46 / 13, 1104 x 687 x3 bfloat16 104
+// 1060 x3 bfloat16 72 atoms 120 / 48, fp8 110 / 59, fp32 133 / 75; logits, 180 x 234 x1 fp16 72 atoms 46 / 13, 1104 x 687 x3 bfloat16 104
 // atoms of 3x3 118 / 49, 1152 x 945 x3 fp16 128 atoms of 7x7 342 / 96.
 //
 // Precision: fp32 coefficients go through v_mfma_f32_32x32x2_f32 (products and sums fp32).  16- and 8-bit ones and the
