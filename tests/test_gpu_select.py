@@ -236,3 +236,94 @@ def test_selection_finds_the_dominant_atoms_of_the_selective_workload():
     err_plain = float(((plain - dense) ** 2).mean())
     err_scaled = float(((scaled - dense) ** 2).mean())
     assert err_scaled < 0.25 * err_plain
+
+
+def _reference(up, coeff, d, target, stride):
+    """[L + 1][L + 1]: the products of the responses and the target, in 64 bits; and by atom the 2-norm, over the samples, of what bounds a
+    response: coefficient x largest of the sample's taps x sum of the atom's magnitudes (for the target: its own)."""
+    n, c, h, w = up.shape
+    L, k = coeff.shape[1], d.shape[-1]
+    r = (k - 1) // 2
+    taps = torch.nn.functional.pad(up.double(), (r, r, r, r), mode="replicate")
+    out = torch.zeros((L + 1, L + 1), device=DEV, dtype=torch.float64)
+    most = torch.zeros(L, device=DEV, dtype=torch.float64)
+    for b in range(n):
+        phi = coeff[b].double()[:, ::stride, ::stride].reshape(L, -1)
+        for ch in range(c):
+            patch = torch.stack([taps[b, ch, i // k:i // k + h, i % k:i % k + w][::stride, ::stride].reshape(-1) for i in range(k * k)])
+            resp = torch.cat([(d.reshape(L, -1).double() @ patch) * phi, target[b, ch].double()[::stride, ::stride].reshape(1, -1)])
+            out += resp @ resp.T.contiguous()
+            most += ((phi * patch.abs().amax(dim=0)) ** 2).sum(dim=1)
+    most = torch.sqrt(most) * d.reshape(L, -1).double().abs().sum(dim=1)
+    return out.cpu().numpy(), np.append(most.cpu().numpy(), np.sqrt(out[L, L].item()))
+
+
+def _split(got, L):
+    full = np.empty((L + 1, L + 1))
+    full[:L, :L], full[L, :L], full[:L, L], full[L, L] = got[:L * L].reshape(L, L), got[L * L:L * L + L], got[L * L:L * L + L], got[L * L + L]
+    return full
+
+
+# Calls of 6144 (8192, one channel 16384) items of 16 samples and one channel and more, fewer items for some wavefronts than for others: rows whose last item
+# has 1, 4, 13 and 16 samples, every pixel and a lattice, several images, both block counts at an edge (the last block may hold the target only)
+SPLIT = [(1, 3, 250, 417, 72, 5, "f16", 1), (2, 2, 213, 260, 79, 5, "f32", 1), (1, 1, 1100, 1197, 64, 5, "bf16", 1), (1, 3, 241, 353, 72, 5, "f8", 1),
+         (1, 3, 500, 833, 72, 5, "f16", 2), (3, 1, 790, 1029, 63, 5, "f8", 3), (1, 4, 181, 417, 48, 5, "f32", 1), (1, 3, 250, 420, 47, 5, "f16", 1),
+         (1, 3, 261, 433, 72, 3, "bf16", 1), (1, 3, 520, 865, 66, 3, "f32", 2), (1, 3, 270, 433, 60, 7, "f16", 1), (1, 2, 520, 1000, 31, 7, "f8", 2)]
+
+
+@pytest.mark.parametrize("n,c,h,w,L,k,cd,stride", SPLIT)
+@pytest.mark.parametrize("values", ["plain", "dark first", "peaks"])
+def test_many_samples(n, c, h, w, L, k, cd, stride, values):
+    """plain: coefficients as a softmax gives them.  dark first: no light in the upper rows, then 1e-6 of it, then all (the operands' scales
+    have to be found late and lowered).  peaks: single pixels of the image and coefficients far above the others (scales lowered within a wavefront)."""
+    g = torch.Generator(device=DEV).manual_seed(L * 1000 + w)
+    up, target = (torch.rand((n, c, h, w), generator=g, device=DEV) for _ in range(2))
+    z = torch.randn((n, L, h, w), generator=g, device=DEV)
+    d = torch.randn((L, k, k), generator=g, device=DEV) / k
+    if values == "dark first":
+        up[:, :, :h // 3] = 0
+        target[:, :, :h // 4] = 0
+        up[:, :, h // 3:h // 2] *= 1e-6
+    if values == "peaks":
+        for t in (up, z, target):
+            t.view(-1)[torch.randint(0, t.numel(), (40,), generator=g, device=DEV)] *= 300 if t is not z else 4
+    phi = torch.softmax(z, dim=1)
+    coeff = phi.to({"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16, "f8": torch.float8_e4m3fn}[cd])
+    got = sr.sr_atom_gram(up, coeff, d, target, L, k, c, stride).cpu().numpy()
+    again = sr.sr_atom_gram(up, coeff, d, target, L, k, c, stride).cpu().numpy()
+    stored = coeff.float()
+    ref, most = _reference(up, stored, d, target, stride)
+    assert np.array_equal(got, again) and got[-1] == n * c * len(range(0, h, stride)) * len(range(0, w, stride))
+    # a response is off by at most 2^-24 of `most` and 2^-24 of itself (the operand's two parts), its dot product's rounding included: Cauchy-Schwarz over the
+    # samples; sums round to 2^-24 of themselves
+    size = np.sqrt(np.diag(ref))
+    bound = 2.0 ** -24 * (np.outer(most + size, size) + np.outer(size, most + size) + np.outer(size, size))
+    assert (np.abs(_split(got, L) - ref) <= bound).all()
+    if values == "plain":
+        # roundings of either sign: over 10^5 samples they average out (a cut towards zero, 2^-25 of a product, would be seen: 3e-8)
+        assert np.abs(_split(got, L) - ref).sum() <= 1e-7 * np.abs(ref).sum()
+        assert abs(((_split(got, L) - ref) / np.outer(size, size)).mean()) <= 4e-9
+
+
+@pytest.mark.parametrize("where", ["coefficient inf", "coefficient nan", "image inf", "image nan", "dictionary inf", "target nan"])
+def test_many_samples_with_infinities_and_nan(where):
+    """They reach the sums they take part in, as fp32 products would, and no other; those stay as near as before."""
+    n, c, h, w, L, k = 1, 3, 250, 420, 72, 5
+    g = torch.Generator(device=DEV).manual_seed(11)
+    up, target = (torch.rand((n, c, h, w), generator=g, device=DEV) for _ in range(2))
+    coeff = torch.softmax(torch.randn((n, L, h, w), generator=g, device=DEV), dim=1)
+    d = torch.rand((L, k, k), generator=g, device=DEV) + 0.1                   # (all positive: an infinity stays one)
+    what, value = where.split()
+    {"coefficient": coeff[0, 70], "image": up[0, 1], "dictionary": d[70], "target": target[0, 2]}[what].view(-1)[
+        {"coefficient": 210 * w + 5, "image": 200 * w + 7, "dictionary": 3, "target": 99 * w + 33}[what]] = float(value)
+    got = _split(sr.sr_atom_gram(up, coeff, d, target, L, k, c, 1).cpu().numpy(), L)
+    hit = np.zeros(L + 1, bool)
+    hit[{"coefficient": [70], "image": range(L), "dictionary": [70], "target": [L]}[what]] = True
+    mine = hit[:, None] | hit[None, :]
+    assert not np.isfinite(got[mine]).any() and (value != "inf" or np.isposinf(got[mine]).all())
+    for t in (coeff, up, d, target):
+        t.nan_to_num_(0.0, 0.0, 0.0)
+    ref, _ = _reference(up, coeff, d, target, 1)
+    size = np.sqrt(np.diag(ref))
+    if what != "image":                              # (positive values: a response is as large as what bounds it, within a few times)
+        assert (np.abs(got - ref) <= 1e-6 * np.outer(size, size))[~mine].all()
