@@ -57,7 +57,23 @@ bool generic_faster(const AssembleArgs& a, int k) {
     return a.coeff_dtype == SR_F32 && px > 120000 && n > 32 && n <= (k == 3 || a.C != 1 ? 42 : 36);
 }
 
-// Planar coefficients that the streaming kernel has an instantiation for and this one is faster with (and gives the same bits).  Both launches are
+// Before the pixel-shuffle the streaming kernel's forms have tiles of 128 x 16 (scale 2), 384 x 8 (3) and 256 x 8 (4) only, so small frames leave most
+// CUs idle, and where the LR width is no multiple of 4 (but the HR width is) it loads element by element.  `ratio` as in slots_faster, of whole tiles; limits from 160 drawn
+// calls of 16 thousand to 2.2 million pixels (fp16 and bfloat16, 65 to 72 atoms, rotating inputs; same bits in all).  Streaming / this, us:
+//   element by element, always: x2 102 thousand pixels 30.1 / 14.7, 659 thousand 90 / 38, x4 17 thousand 29.4 / 11.5, 751 thousand 104 / 45.
+//   from a ratio of 1.6 on: x2 16 thousand 23.6 / 10.4, 161 thousand 25.2 / 18.1, 626 thousand 43.9 / 34.0; x3 20 thousand 19.4 / 10.5, 178 thousand 24.8 / 19.2,
+//   344 thousand 24.3 / 24.1; x4 18 thousand 22.0 / 10.9, 126 thousand 24.0 / 15.2.  Below: x2 0.90 to 1.22 of each other, x3 0.78 to 1.03, x4 0.83 to 1.06,
+//   but scales 2 and 4 in one tile for a CU at most from 1.33 on 1.08 to 1.27 (x4 337 thousand 22.7 / 21.0, x2 278 thousand 25.7 / 20.3).
+static bool pre_shuffle_faster(const AssembleArgs& a, int k) {
+    if (a.w % 4 != 0) return true;
+    Walk s, t;
+    if (launch_mfma(a, k, a.io_f16, 0, LaunchTo(&s)) != hipSuccess || launch_slots(a, k, true, LaunchTo(&t)) != hipSuccess) return false;
+    const long long cus = units_of(a);
+    const long long there = (s.pieces + cus - 1) / cus * s.width * s.rows, here = (t.pieces + cus - 1) / cus * t.width * t.rows;
+    return 10 * there >= 16 * here || (a.s != 3 && s.pieces <= cus && 100 * there >= 133 * here);
+}
+
+// Coefficients that the streaming kernel has an instantiation for and this one is faster with (and gives the same bits).  Planar ones: both launches are
 // known before either is made, and what decides is the work of the fullest CU.  Counted in pixels: those of its tiles or of its
 // wavefronts' strip segments, plus 9 for each of the k - 1 rows that a tile, or each wavefront's segment, up-samples beyond its own
 // (per 128 columns), plus 24 for what a tile costs whatever its size.  `ratio` is the streaming kernel's count over this one's.  The limits were
@@ -76,7 +92,8 @@ bool generic_faster(const AssembleArgs& a, int k) {
 // Left out: capacities that this kernel has not (5x5: 8, 16 and 48; 3x3: 8); 5x5 atoms of three channels up to 72 in 16 bits, whose default tile is one of
 // the shapes that a caller can ask for.
 bool slots_faster(const AssembleArgs& a, int k) {
-    if (a.pre_shuffle || a.pixel_major || a.blocked || a.logits || a.C == 2 || !slots_supported(a, k)) return false;
+    if (a.pixel_major || a.blocked || a.logits || a.C == 2 || !slots_supported(a, k)) return false;
+    if (a.pre_shuffle) return pre_shuffle_faster(a, k);
     const int n = a.n_fold, built = n <= 32 ? 4 : n <= 72 ? 9 : 16, streaming = mfma_capacity(a, k);
     if (a.coeff_dtype == SR_F8E4M3) return k == 7 || n > 72;               // (of more than 72 atoms of 3x3 and 5x5 none is built there)
     const bool f32 = a.coeff_dtype == SR_F32;

@@ -172,3 +172,27 @@ def test_pre_shuffle_call_replays_inside_a_captured_graph(scale):
         torch.cuda.synchronize()
         eager = run(fresh, wl, fp, MFMA, sr.SR_COEFF_PRE_SHUFFLE)
         assert torch.equal(out, eager), f"replay {rep}"
+
+
+# Either side of the line between the two matrix-core kernels: ragged last tiles of both, one tile for a CU and more, LR widths that are no multiple of 4 but make HR
+# widths that are (not the streaming kernel's element-wise form there)
+@pytest.mark.parametrize("n,h,w,s,L,coeff,image,runs", [
+    (1, 24, 24, 2, 72, "f16", "f32", sr.SR_RUNS_SLOTS), (1, 150, 452, 2, 65, "bf16", "f16", sr.SR_RUNS_SLOTS), (2, 141, 500, 2, 72, "f16", "f32", sr.SR_RUNS_SLOTS),
+    (1, 333, 460, 2, 72, "f16", "f32", sr.SR_RUNS_STREAMING), (1, 61, 100, 3, 72, "f16", "f16", sr.SR_RUNS_SLOTS), (1, 130, 388, 3, 72, "bf16", "f32", sr.SR_RUNS_STREAMING),
+    (1, 199, 300, 3, 70, "f16", "f32", sr.SR_RUNS_STREAMING), (1, 227, 260, 3, 72, "f16", "f32", sr.SR_RUNS_SLOTS), (1, 33, 68, 4, 72, "f16", "f32", sr.SR_RUNS_SLOTS),
+    (1, 131, 172, 4, 72, "bf16", "f16", sr.SR_RUNS_STREAMING), (1, 205, 260, 4, 65, "f16", "f32", sr.SR_RUNS_STREAMING), (3, 101, 132, 4, 72, "f16", "f16", sr.SR_RUNS_STREAMING),
+    (1, 150, 450, 2, 72, "f16", "f32", sr.SR_RUNS_SLOTS), (1, 600, 902, 2, 72, "f16", "f16", sr.SR_RUNS_SLOTS), (2, 60, 151, 4, 66, "f16", "f16", sr.SR_RUNS_SLOTS),
+    (1, 300, 419, 4, 72, "f16", "f32", sr.SR_RUNS_SLOTS)])
+def test_either_matrix_core_kernel_gives_the_planar_calls_bits(n, h, w, s, L, coeff, image, runs):
+    wl = sr_synth.Workload("ps_line", 400, n, 3, h, w, s, L, 5, coeff, image, 0.0, 1.5)
+    inp = sr_synth.make_inputs(wl, DEV)
+    pre = sr_synth.to_pre_shuffle(inp["coeff"], s)
+    out = torch.empty((n, 3, wl.H, wl.W), device=DEV, dtype=inp["lr"].dtype)
+    for kernel in (sr.SR_KERNEL_AUTO, MFMA):
+        opts = sr.make_options(kernel, 0, sr.SR_COEFF_PRE_SHUFFLE)
+        assert sr.sr_dict_assemble_runs(inp["lr"], pre, inp["dict"], L, 5, s, 3, out, opts=opts)[0] == runs
+        out.fill_(float("nan"))
+        sr.sr_dict_assemble_ex(inp["lr"], pre, inp["dict"], L, 5, s, 3, out, opts=opts)
+        planar = torch.empty_like(out)
+        sr.sr_dict_assemble(inp["lr"], inp["coeff"], inp["dict"], L, 5, s, 3, planar)
+        assert torch.equal(out, planar)
