@@ -748,8 +748,8 @@ static hipError_t launch_slots_n(const AssembleArgs& a, const LaunchTo& st) {
         return a.pre_shuffle ? launch_slots_p<K, CM, CT, NP8, KIND, true>(a, st) : launch_slots_p<K, CM, CT, NP8, KIND, false>(a, st);
     else if constexpr (NP8 == 16 || (CT == CT_F8 ? K == 7 : CT == CT_F32 || K != 5 || CM == 1))      // (what slots_faster sends here)
         return a.pre_shuffle ? hipErrorInvalidValue : launch_slots_p<K, CM, CT, NP8, KIND, false>(a, st);
-    else if constexpr (K == 5 && CM == 3 && NP8 <= 9 && (CT == CT_F16 || (CT == CT_BF16 && NP8 == 9)))
-        return a.pre_shuffle ? launch_slots_p<K, CM, CT, NP8, KIND, true>(a, st) : hipErrorInvalidValue;
+    else if constexpr (K == 5 && CM == 3 && (CT == CT_F16 || CT == CT_BF16))
+        return a.pre_shuffle ? launch_slots_p<K, CM, CT, NP8, KIND, true>(a, st) : launch_slots_p<K, CM, CT, NP8, KIND, false>(a, st);
     else
         return hipErrorInvalidValue;
 }

@@ -89,18 +89,22 @@ static bool pre_shuffle_faster(const AssembleArgs& a, int k) {
 //   SIMD, tiles of sixteen rows): 0.925 in tiles of four and eight rows, 0.95 in lower ones (0.94 .. 3.2), 7x7 0.76 (0.95 .. 3.2).
 //   fp32 atoms of 7x7, 27 to 32 of them, in the streaming kernel's capacity of 72: 0.85 (1.4 .. 1.9).
 //   One tile for a CU at most: always (1.0 .. 3.2).  8-bit coefficients of 7x7, and of more than 72 atoms: always (0.96 .. 2.3).
-// Left out: capacities that this kernel has not (5x5: 8, 16 and 48; 3x3: 8); 5x5 atoms of three channels up to 72 in 16 bits, whose default tile is one of
-// the shapes that a caller can ask for.
+//   5x5 atoms of three channels up to 72 in 16 bits (430 drawn calls of their own, the same bits in all; sr_dict_assemble_tile keeps saying the streaming
+//   kernel's tile 0): against tiles of 128 x 4 1.1 (1.01 .. 1.27: 21 thousand pixels 10.5 / 8.2, 57 thousand 9.7 / 8.9, 175 thousand 14.2 / 12.3; 2 thousand 8.9 / 8.4,
+//   below that 8.4 to 9.2 / 8.2 to 8.6, the launch alone: not taken), and in a
+//   second round there 0.995 (1.05 .. 1.2: 298 thousand 19.4 / 16.2; in one round 512 x 512 13.2 / 15.0 from the memory-side cache, 17.9 / 16.1 from memory);
+//   against taller tiles 1.2 (1.08 .. 1.28); against strips nowhere (0.78 .. 1.1).  8-bit ones gain 3 % there or lose.
+// Left out otherwise: capacities that this kernel has not (5x5: 8, 16 and 48; 3x3: 8).
 bool slots_faster(const AssembleArgs& a, int k) {
     if (a.pixel_major || a.blocked || a.logits || a.C == 2 || !slots_supported(a, k)) return false;
     if (a.pre_shuffle) return pre_shuffle_faster(a, k);
     const int n = a.n_fold, built = n <= 32 ? 4 : n <= 72 ? 9 : 16, streaming = mfma_capacity(a, k);
     if (a.coeff_dtype == SR_F8E4M3) return k == 7 || n > 72;               // (of more than 72 atoms of 3x3 and 5x5 none is built there)
     const bool f32 = a.coeff_dtype == SR_F32;
-    if (k == 5 && a.C == 3 && n <= 72 && !f32) return false;
+    const bool common = k == 5 && a.C == 3 && n <= 72 && !f32;
     const long long cus = units_of(a);
-    if ((a.W + 127ll) / 128 * a.H * a.N <= cus) return true;               // (single rows)
-    if (built > streaming) return false;
+    if (!common && (a.W + 127ll) / 128 * a.H * a.N <= cus) return true;    // (single rows)
+    if (!common && built > streaming) return false;
     Walk s, t;
     if (launch_mfma(a, k, a.io_f16, 0, LaunchTo(&s)) != hipSuccess || launch_slots(a, k, true, LaunchTo(&t)) != hipSuccess) return false;
     // in half pixels
@@ -109,6 +113,7 @@ bool slots_faster(const AssembleArgs& a, int k) {
                                         : ((s.pieces + s.waves - 1) / s.waves + cus - 1) / cus * s.waves * wide;
     const int width = f32 && t.rows >= 4 && a.W < 128 ? (a.W + 31) / 32 * 32 : 128;      // (a narrow image: its units only)
     const long long here = (t.pieces + cus - 1) / cus * (2ll * width * t.rows + halo * width / 128 + fixed);
+    if (common) return s.form == 1 && (long long)a.N * a.H * a.W >= 2048 && 1000 * there >= (s.rows > 4 ? 1200 : t.rows == 4 && s.pieces > 2 * cus ? 995 : 1100) * here;
     const bool shared_lines = !f32 && a.W % 16 != 0, many = n > 72;
     const int limit = built < streaming                       ? 850         // thousandths
                       : many && f32                           ? (k == 7 ? 760 : t.rows >= 4 ? 925 : 950)

@@ -263,3 +263,28 @@ def test_infinities_and_nan_as_in_the_generic_kernel(c, L, k, cd, pre, logits, i
         assert torch.equal(torch.nan_to_num(got[odd], 7.0), torch.nan_to_num(gen[odd], 7.0)), what
         tol = (2.5e-4 if logits else 5e-5) + (2.0 ** -10 if io == "f16" else 0.0)
         assert not (~odd).any() or float((got - gen)[~odd].abs().max()) <= tol * max(1.0, float(gen[~odd].abs().max())), what
+
+
+# 5x5 atoms of three channels in 16 bits, the commonest calls: a small frame alone runs here, in a batch on the streaming kernel (in tiles or strips); capacities
+# 32 and 72 at their edges, ragged rows, narrow images, one row of tiles
+@pytest.mark.parametrize("h, w, s, L, kept, cd, io", [
+    (40, 56, 2, 72, None, "f16", "f32"), (45, 47, 3, 72, None, "bf16", "f16"), (56, 85, 3, 72, None, "f16", "f32"), (12, 60, 4, 72, None, "f16", "f16"),
+    (130, 253, 3, 33, None, "bf16", "f32"), (29, 44, 3, 65, None, "f16", "f32"), (61, 68, 2, 72, 50, "f16", "f32"), (250, 300, 2, 32, None, "bf16", "f32"),
+    (141, 237, 3, 72, 17, "f16", "f16"), (122, 163, 4, 72, None, "f16", "f32"), (216, 306, 2, 48, None, "bf16", "f32")])
+def test_a_small_frame_has_the_bits_it_has_in_a_batch(h, w, s, L, kept, cd, io):
+    wl = sr_synth.Workload("slotsb", 73, 2, 3, h, w, s, L, 5, cd, io, 0.0, 1.5)
+    inp = sr_synth.make_inputs(wl, DEV)
+    atoms = None if kept is None else np.sort(np.random.default_rng(L).choice(L, size=kept, replace=False)).astype(np.int32)
+    gamma = None if kept is None else np.linspace(0.5, 1.5, kept).astype(np.float32)
+    n = 2 + 2_000_000 // (wl.H * wl.W)
+    many = sr_synth.Workload("slotsb", 73, n, 3, h, w, s, L, 5, cd, io, 0.0, 1.5)
+    batch = {"lr": inp["lr"][torch.arange(n, device=DEV) % 2].contiguous(), "dict": inp["dict"]}
+    coeff = inp["coeff"][torch.arange(n, device=DEV) % 2].contiguous()
+    assert runs(batch, many, coeff, False, False, atoms)[0] == sr.SR_RUNS_STREAMING
+    together = run(batch, many, coeff, AUTO, False, False, atoms, gamma)
+    for b in range(2):
+        one = sr_synth.Workload("slotsb", 73, 1, 3, h, w, s, L, 5, cd, io, 0.0, 1.5)
+        alone = {"lr": inp["lr"][b:b + 1].contiguous(), "dict": inp["dict"]}
+        assert runs(alone, one, inp["coeff"][b:b + 1], False, False, atoms)[0] == sr.SR_RUNS_SLOTS
+        assert torch.equal(run(alone, one, inp["coeff"][b:b + 1].contiguous(), AUTO, False, False, atoms, gamma)[0], together[b])
+        assert torch.equal(together[b + n // 2 * 2 - 2], together[b])
