@@ -392,7 +392,8 @@ __device__ __forceinline__ void divmod_scale(int v, int s, int& q, int& r) {
 // of contiguous memory per load) and holds the B operand of that 16-atom step and slot as it stands: no re-packing, no
 // staging, and the slots are the planar form's four adjacent pixels, so stage 4 and the store are the planar form's too.
 // (8-bit coefficients in the same order: 8 bytes per lane and piece, widened to the operand with four conversions.)
-template <int K, int C, int NP8, int PX, int WR, int NW, int NU, int WPE, int CT, int SMIN, bool BIG, int PSM = 0, int STRIP = 0>
+// KEEP: coefficient loads leave their lines in the caches (see keep_lines).
+template <int K, int C, int NP8, int PX, int WR, int NW, int NU, int WPE, int CT, int SMIN, bool BIG, int PSM = 0, int STRIP = 0, bool KEEP = false>
 __global__ __launch_bounds__(64 * NW, WPE)
 void k_assemble_mfma(const AssembleArgs a) {
     constexpr int NSUB = PSM == 4 ? 2 : (PSM == 3 ? 3 : 1);   // units per tile row
@@ -733,7 +734,9 @@ void k_assemble_mfma(const AssembleArgs a) {
             }
             return r;
         } else {
-            return __builtin_nontemporal_load((const Raw*)caddr(cimg, pix_off[0] + plane_off));
+            const Raw* const at = (const Raw*)caddr(cimg, pix_off[0] + plane_off);
+            if constexpr (KEEP) return *at;
+            else return __builtin_nontemporal_load(at);
         }
     };
 
@@ -1804,6 +1807,33 @@ inline void walk_of(AssembleArgs& a, int ntiles, int blocks, int per_block) {
     a.inv_tx = (unsigned)((1ull << 32) / (unsigned)a.tiles_x - (a.tiles_x == 1 ? 1 : 0));
 }
 
+// Whether a call's coefficients are loaded with ordinary instead of streaming loads: rows that are no whole number of 128-byte lines, so that neighbouring tiles or
+// strips share lines, which come from memory twice where the first reader lets them go (and streaming is 3 to 17 % faster where
+// nothing is shared: 4K x4 fp16 244 / 278 us).  From frames of 400 thousand pixels on; smaller ones lie in the memory-side cache (0.95 to 1.04 of each other).
+// 400 drawn calls, three states in turn, the same bits in all; streaming / ordinary us, and the ratios over the calls from the line on:
+//   7x7: 2574 thousand pixels x3 121 atoms 200 / 158, 3308 thousand 72 atoms 1.23; all 1.00 .. 1.26, but one channel in rows off 128 bytes by 64 0.96 .. 1.07 (left)
+//   5x5, 8-bit: 3175 thousand x3 78.5 / 66, 5391 thousand x1 119 / 99; 0.97 .. 1.25, mean 1.11, but by 64 0.96 .. 1.06 (left)
+//   5x5, 16-bit, three channels: rows off 32 bytes 8035 thousand 46 atoms 245 / 191, 8306 thousand 316 / 290, 0.98 .. 1.28; rows off 128 only, which share
+//   fewer lines: up to 40 atoms (less stream beside it) 1.02 .. 1.13, up to 72 0.94 .. 1.03 (left streaming), more from 2 million pixels 1.03 .. 1.12
+//   (0.98 .. 1.00 below)
+//   ... one channel: up to 50 atoms in rows off 32 bytes 1.00 .. 1.14; more 0.91 .. 1.04 (left streaming)
+//   logits: rows off 64 bytes, and those off 32 with them, 1.00 .. 1.10; 64 of 128 bytes 0.96 (left)
+//   3x3, three channels, 16- and 8-bit, from 1 million pixels: 1.10 .. 1.22
+// fp32: no gain was measured, not built.
+inline bool keep_lines(const AssembleArgs& a, int k, bool logits) {
+    const long long px = (long long)a.N * a.H * a.W;
+    const bool f8 = a.coeff_dtype == SR_F8E4M3;
+    const long long off = (long long)a.W * (f8 ? 1 : 2) % 128;
+    if (off == 0 || px < 400000) return false;
+    if (logits) return off != 64;
+    if (k == 7) return a.C == 3 || off != 64;
+    if (k == 5 && f8) return off != 64;
+    if (k == 3) return a.C == 3 && px >= 1000000;
+    if (a.C == 1) return a.n_fold <= 50 && off % 32 != 0;
+    if (a.C != 3) return false;
+    return a.n_fold <= 40 || (a.n_fold <= 72 ? off % 32 != 0 : px >= 2000000);
+}
+
 template <int K, int C, int NP8, int PX, int WR, int NW, int NU, int WPE, int CT = CT_F16, int SMIN = 2, bool BIG = false,
           int PSM = 0, int STRIP = 0>
 hipError_t launch_one(const AssembleArgs& a0, const LaunchTo& st) {
@@ -1862,6 +1892,12 @@ hipError_t launch_one(const AssembleArgs& a0, const LaunchTo& st) {
     a.xlast = xlast;
     a.seg_rows = seg_rows;
     walk_of(a, (int)nt, blocks, STRIP ? NW : 1);
+    constexpr bool LG = CT == CT_LOGIT || CT == CT_LOGIT_BF16;
+    if constexpr (PSM == 0 && !BIG && NP8 >= 4 && (C == 3 || (C == 1 && K != 3)) && (LG || CT == CT_F16 || CT == CT_BF16 || CT == CT_F8))
+        if (keep_lines(a0, K, LG)) {
+            hipLaunchKernelGGL((k_assemble_mfma<K, C, NP8, PX, WR, NW, NU, WPE, CT, SMIN, BIG, PSM, STRIP, true>), dim3(blocks), dim3(F::NT), 0, st.stream, a);
+            return hipGetLastError();
+        }
     hipLaunchKernelGGL((k_assemble_mfma<K, C, NP8, PX, WR, NW, NU, WPE, CT, SMIN, BIG, PSM, STRIP>), dim3(blocks), dim3(F::NT), 0, st.stream, a);
     return hipGetLastError();
 }
@@ -1879,7 +1915,8 @@ hipError_t launch_one(const AssembleArgs& a0, const LaunchTo& st) {
 //   channel, which has half the other work to hide a miss behind: half of it), and work for 94 % of the resident lanes (128 atoms: 85 %).
 //   Neighbouring pieces of a row then share lines.  Tiles side by side ask for them at about the same time; wavefronts that
 //   walk strips drift apart, the loads are streaming ones, and the line comes from memory twice (with loads that stay in the
-//   L2, 128 atoms 1536 x 2040 x3 263 -> 215 us, but whole lines 4K 239 -> 278).  Strips have to save 8 % of the rows.
+//   L2, 128 atoms 1536 x 2040 x3 263 -> 215 us, but whole lines 4K 239 -> 278: keep_lines, since when both forms take the same time there,
+//   110 drawn calls within 2 %).  Strips have to save 8 % of the rows.
 //   Scale 3, tiles of at most two rows per SIMD: a segment of one row up-samples K + 1 rows for it, one after the other; and
 //   the same with up to three rows where a row is cheap to fold (one channel, few atoms, two pixels per lane) and strips save
 //   at most a quarter of them.

@@ -225,3 +225,33 @@ def test_images_of_just_below_4_gb(h, w, scale, L):
     assert torch.isnan(guard[n:]).all()
     worst = max(float((a - b).abs().max()) for a, b in zip(got[0, 0].split(2048), want[0, 0].split(2048)))
     assert worst <= 5e-5 * max(1.0, float(want.abs().max()))
+
+
+# Rows that share 128-byte lines are read with ordinary loads from 400 thousand pixels on: a frame alone is below that, in a batch it is not.  Every
+# family of the rule, either form, rows off by 2 to 96 bytes, the last strip or tile moved left and not
+@pytest.mark.parametrize("c, h, w, s, L, k, cd, kind", [
+    (3, 100, 153, 4, 72, 5, "f16", "values"), (3, 130, 250, 2, 57, 5, "bf16", "values"), (3, 96, 168, 3, 72, 5, "f8", "values"), (1, 90, 202, 4, 72, 5, "f8", "values"),
+    (3, 61, 151, 4, 72, 7, "f16", "values"), (1, 70, 141, 4, 128, 7, "bf16", "values"), (3, 101, 170, 3, 72, 5, "f16", "logits"), (3, 80, 130, 4, 66, 5, "bf16", "logits"),
+    (3, 100, 150, 4, 128, 3, "f16", "values"), (3, 120, 209, 3, 128, 5, "f16", "values"), (1, 110, 201, 4, 50, 5, "f16", "values"), (3, 90, 141, 4, 30, 5, "f16", "values")])
+def test_rows_that_share_lines_have_the_same_bits(c, h, w, s, L, k, cd, kind):
+    wl = sr_synth.Workload("lines", 74, 2, c, h, w, s, L, k, cd, "f32", 0.0, 1.5)
+    inp = sr_synth.make_inputs(wl, DEV)
+    coeff = sr_synth.make_logits(wl, DEV) if kind == "logits" else inp["coeff"]
+    assert wl.H * wl.W < 400_000 and wl.W * (1 if cd == "f8" else 2) % 128 != 0
+    opts = sr.make_options(coeff_kind=sr.SR_COEFF_LOGITS if kind == "logits" else sr.SR_COEFF_VALUES)
+
+    def run(n):
+        pick = torch.arange(n, device=DEV) % 2
+        out = torch.full((n, c, wl.H, wl.W), float("nan"), device=DEV)
+        raw = coeff.view(torch.uint8) if cd == "f8" else coeff
+        sr.sr_dict_assemble_ex(inp["lr"][pick].contiguous(), raw[pick].contiguous().view(coeff.dtype), inp["dict"], L, k, s, c, out, opts=opts)
+        torch.cuda.synchronize()
+        return out
+
+    many = run(2 * (1 + 1_100_000 // (wl.H * wl.W)))
+    one = run(1)
+    assert torch.isfinite(many).all() and torch.equal(many[0], one[0]) and torch.equal(many[-2], one[0]) and torch.equal(many[-1], many[1])
+    if kind == "values":                             # (and the vector-ALU kernel agrees)
+        gen = torch.empty_like(one)
+        sr.sr_dict_assemble_ex(inp["lr"][:1], coeff[:1], inp["dict"], L, k, s, c, gen, opts=sr.make_options(sr.SR_KERNEL_GENERIC))
+        assert float((gen - one).abs().max()) <= (1e-4 if cd == "bf16" else 5e-5) * max(1.0, float(gen.abs().max()))
