@@ -1819,13 +1819,15 @@ inline void walk_of(AssembleArgs& a, int ntiles, int blocks, int per_block) {
 //   ... one channel: up to 50 atoms in rows off 32 bytes 1.00 .. 1.14; more 0.91 .. 1.04 (left streaming)
 //   logits: rows off 64 bytes, and those off 32 with them, 1.00 .. 1.10; 64 of 128 bytes 0.96 (left)
 //   3x3, three channels, 16- and 8-bit, from 1 million pixels: 1.10 .. 1.22
+//   before the pixel-shuffle (rows of the LR image), values and logits (25 of 130 more calls): 5559 thousand x2 258 / 219, 5362 thousand x4 logits 232 / 198; 0.98 ..
+//   1.18, by 64 bytes 0.94 .. 1.01 (left), whole lines 0.90 .. 1.02
 // fp32: no gain was measured, not built.
 inline bool keep_lines(const AssembleArgs& a, int k, bool logits) {
     const long long px = (long long)a.N * a.H * a.W;
     const bool f8 = a.coeff_dtype == SR_F8E4M3;
-    const long long off = (long long)a.W * (f8 ? 1 : 2) % 128;
+    const long long off = (long long)(a.pre_shuffle ? a.w : a.W) * (f8 ? 1 : 2) % 128;
     if (off == 0 || px < 400000) return false;
-    if (logits) return off != 64;
+    if (logits || a.pre_shuffle) return off != 64;
     if (k == 7) return a.C == 3 || off != 64;
     if (k == 5 && f8) return off != 64;
     if (k == 3) return a.C == 3 && px >= 1000000;
@@ -1893,7 +1895,7 @@ hipError_t launch_one(const AssembleArgs& a0, const LaunchTo& st) {
     a.seg_rows = seg_rows;
     walk_of(a, (int)nt, blocks, STRIP ? NW : 1);
     constexpr bool LG = CT == CT_LOGIT || CT == CT_LOGIT_BF16;
-    if constexpr (PSM == 0 && !BIG && NP8 >= 4 && (C == 3 || (C == 1 && K != 3)) && (LG || CT == CT_F16 || CT == CT_BF16 || CT == CT_F8))
+    if constexpr ((PSM == 0 || PSM == 2 || PSM == 3 || PSM == 4) && !BIG && NP8 >= 4 && (C == 3 || (C == 1 && K != 3)) && (LG || CT == CT_F16 || CT == CT_BF16 || CT == CT_F8))
         if (keep_lines(a0, K, LG)) {
             hipLaunchKernelGGL((k_assemble_mfma<K, C, NP8, PX, WR, NW, NU, WPE, CT, SMIN, BIG, PSM, STRIP, true>), dim3(blocks), dim3(F::NT), 0, st.stream, a);
             return hipGetLastError();

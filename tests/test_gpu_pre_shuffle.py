@@ -182,7 +182,8 @@ def test_pre_shuffle_call_replays_inside_a_captured_graph(scale):
     (1, 199, 300, 3, 70, "f16", "f32", sr.SR_RUNS_STREAMING), (1, 227, 260, 3, 72, "f16", "f32", sr.SR_RUNS_SLOTS), (1, 33, 68, 4, 72, "f16", "f32", sr.SR_RUNS_SLOTS),
     (1, 131, 172, 4, 72, "bf16", "f16", sr.SR_RUNS_STREAMING), (1, 205, 260, 4, 65, "f16", "f32", sr.SR_RUNS_STREAMING), (3, 101, 132, 4, 72, "f16", "f16", sr.SR_RUNS_STREAMING),
     (1, 150, 450, 2, 72, "f16", "f32", sr.SR_RUNS_SLOTS), (1, 600, 902, 2, 72, "f16", "f16", sr.SR_RUNS_SLOTS), (2, 60, 151, 4, 66, "f16", "f16", sr.SR_RUNS_SLOTS),
-    (1, 300, 419, 4, 72, "f16", "f32", sr.SR_RUNS_SLOTS)])
+    (1, 300, 419, 4, 72, "f16", "f32", sr.SR_RUNS_SLOTS),
+    (1, 401, 516, 2, 72, "f16", "f32", sr.SR_RUNS_STREAMING), (1, 331, 388, 3, 66, "bf16", "f16", sr.SR_RUNS_STREAMING), (2, 131, 260, 4, 72, "f16", "f32", sr.SR_RUNS_STREAMING)])
 def test_either_matrix_core_kernel_gives_the_planar_calls_bits(n, h, w, s, L, coeff, image, runs):
     wl = sr_synth.Workload("ps_line", 400, n, 3, h, w, s, L, 5, coeff, image, 0.0, 1.5)
     inp = sr_synth.make_inputs(wl, DEV)
