@@ -14,7 +14,9 @@ bool mfma_list_supported(const AssembleArgs& a, int k, bool value_f16) {
 }
 
 // Up to 72 atoms: the dense form's operand steps (four of 16 atoms and one of 8); scale 4 in strips, scale 3 in strips or 128 x 8
-// tiles, scale 2 in 128 x 8 tiles.  Up to 128: eight steps, 128 x 8 tiles at every scale (35 KB of scatter scratch).  Lists of up to 8
+// tiles, scale 2 in 128 x 8 tiles, but frames of at most one row for every SIMD in strips: rows of four wavefronts each instead of a few tiles of
+// eight (tiles / strips, us, lists of 1 to 16: 16 thousand pixels 11.2 / 9.4, 101 thousand 11.5 / 9.7, 60 drawn calls 1.18 to 1.26 there).  Larger ones would need two of
+// these workgroups on a CU, whose LDS (86 KB each) does not fit: 128 thousand pixels 11.5 / 17.2, 1905 thousand 49 / 55.  Up to 128: eight steps, 128 x 8 tiles at every scale (35 KB of scatter scratch).  Lists of up to 8
 // entries keep half the registers.
 // Scale 4 in one run of three forms, lists of 8 (us, 128 x 16 tiles with the scale-4 footprint / 128 x 8 / strips):
 // 240 x 320 15.4 / - / 9.3, 480 x 640 16.3 / 14.4 / 13.7, 720 x 1280 22.0 / 25.4 / 21.1, 800 x 1200 22.7 / 25.5 /
@@ -25,6 +27,7 @@ static hipError_t launch_ct(const AssembleArgs& a, const LaunchTo& st) {
     if (a.L <= 72) {
         if (a.s == 4) return launch_one<5, 3, 9, 4, 1, 4, 1, 2, CT, 4, false, 0, 4>(a, st);
         if (a.s == 3 && strip_form(a, 0, 128, 128, 8)) return launch_one<5, 3, 9, 4, 1, 4, 1, 2, CT, 3, false, 0, 3>(a, st);
+        if (a.s == 2 && (a.W + 127ll) / 128 * a.H * a.N <= 4ll * units_of(a)) return launch_one<5, 3, 9, 4, 1, 4, 1, 1, CT, 2, false, 0, 2>(a, st);
         return launch_one<5, 3, 9, 4, 1, 4, 2, 2, CT, 2>(a, st);
     }
     return launch_one<5, 3, 16, 4, 1, 4, 2, 2, CT, 2>(a, st);

@@ -193,3 +193,23 @@ def test_list_call_replays_inside_a_captured_graph(kernel):
         torch.cuda.synchronize()
         eager = run(fresh, wl, fi, fv, kernel)
         assert torch.equal(out, eager), f"replay {rep}"
+
+
+@pytest.mark.parametrize("h,w,L,T,io", [(40, 66, 72, 8, "f32"), (3, 2, 9, 1, "f32"), (1, 130, 72, 16, "f16"), (128, 256, 72, 8, "f32"), (60, 64, 40, 5, "f16"),
+                                        (64, 258, 65, 9, "f32"), (85, 382, 72, 16, "f32")])
+def test_small_frames_at_scale_2_take_strips_with_the_tiles_bits(h, w, L, T, io):
+    """At most one row for every SIMD: strips; the same frames in a batch beyond that: tiles."""
+    wl = sr_synth.Workload("list2", 480, 1, 3, h, w, 2, L, 5, "f16", io, 0.0, 1.5)
+    inp = sr_synth.make_inputs(wl, DEV)
+    idx, val = sr_synth.to_list(inp["coeff"], T)
+    rows = (wl.W + 127) // 128 * wl.H
+    n = 4 * torch.cuda.get_device_properties(0).multi_processor_count // rows + 1
+    out = torch.full((1, 3, wl.H, wl.W), float("nan"), device=DEV, dtype=inp["lr"].dtype)
+    many = torch.full((n, 3, wl.H, wl.W), float("nan"), device=DEV, dtype=inp["lr"].dtype)
+    batch = [t.expand(n, -1, -1, -1).contiguous() for t in (inp["lr"], idx, val)]
+    assert sr.sr_dict_assemble_list_walk(inp["lr"], idx, val, inp["dict"], L, 5, 2, 3, T, out)[1][0] == 2
+    assert sr.sr_dict_assemble_list_walk(*batch, inp["dict"], L, 5, 2, 3, T, many)[1][0] == 1
+    sr.sr_dict_assemble_list(inp["lr"], idx, val, inp["dict"], L, 5, 2, 3, T, out)
+    sr.sr_dict_assemble_list(*batch, inp["dict"], L, 5, 2, 3, T, many)
+    torch.cuda.synchronize()
+    assert torch.isfinite(many).all() and all(torch.equal(many[b], out[0]) for b in (0, n // 2, n - 1))
