@@ -307,7 +307,7 @@ __global__ __launch_bounds__(NTT, 2) void k_atom_gram_split(const GramArgs a, un
 
     // The dictionary in three fp16 parts, times a power of two that brings its largest entry to 2^14; the large parts on one grid for an atom.
     // Lane (c16, kq), step nk, block nb: the taps of slots 8 nk .. 8 nk + 7, of atom 16 nb + c16.
-    constexpr int DIT = (N16 * 64 + 255) / 256;                       // (a workgroup has 256 threads or 512)
+    constexpr int DIT = (N16 * 64 + 255) / 256;                       // (for workgroups of 256 threads and more)
     float dv[DIT][8 * NK];
     unsigned dmax = 0;
 #pragma unroll
