@@ -61,10 +61,9 @@ size_t sr_atom_gram_workspace_bytes(int L);
  *             M       = number of samples p
  *
  * k in {3,5,7}, 1 <= L <= SR_SELECT_MAX_ATOMS, 1 <= C <= SR_MAX_CHANNELS.
- * Responses are formed and summed over runs of 64 samples in fp32, or, for many
- * samples of up to 79 atoms, from fp16 parts of 24 bits with fp32 sums (as near to
- * the exact result), and in double from there on, in a fixed order: the result is
- * the same from run to run.  Enqueued on `stream`, no synchronisation; nothing is allocated.
+ * Responses are formed in fp32, summed in fp32 over runs of 64 samples and in
+ * double from there on, in a fixed order: the result is the same from run to
+ * run.  Enqueued on `stream`, no synchronisation; nothing is allocated.
  * N = 0 or an empty image writes all zeros.
  */
 int sr_atom_gram(const sr_tensor* up, const sr_tensor* coeff, const sr_tensor* dict,

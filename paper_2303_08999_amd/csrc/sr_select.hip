@@ -13,8 +13,8 @@
 // each workgroup leaves its partial sums in the caller's scratch and a second kernel
 // adds them in a fixed order.
 //
-// Four forms of the first kernel.  k_atom_gram_split (sr_gram.h; many samples of up to 79 atoms) and k_atom_gram_tri (up to 79 atoms): every wavefront
-// forms responses and contracts them in its own registers, on the fp16 or the fp32 matrix instructions.  k_atom_gram_rows (more atoms, lattice strides up to 4): runs
+// Three forms of the first kernel.  k_atom_gram_tri (up to 79 atoms): every wavefront forms responses and contracts them
+// in its own registers.  k_atom_gram_rows (more atoms, lattice strides up to 4): runs
 // are segments of one lattice row, eight wavefronts per workgroup split into four
 // that form responses (their dot products on the matrix cores too) and four that
 // contract, all global loads coalesced and parked in LDS.  k_atom_gram (what is left):
@@ -31,9 +31,7 @@
 #include <type_traits>
 #include <vector>
 
-#include "sr_gram.h"
-
-using namespace gram;
+#include "../../include/sr_select.h"
 
 namespace {
 
@@ -41,6 +39,52 @@ constexpr int NT = 256;          // threads per workgroup
 constexpr int RUN = 64;          // samples per run
 constexpr int TSS = RUN + 4;     // floats per tile column: 16-byte loads of 16 columns x 4 sample groups miss each other's banks
 constexpr int GRID = 512;        // workgroups (two per CU)
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+struct GramArgs {
+    const float* up;
+    const void* coeff;
+    const float* dict;
+    const float* target;
+    double* ws;
+    int N, C, H, W, L, stride, ny, nx;
+    int n16, ntile;              // 16-column blocks covering L + 1 columns, blocks in the upper triangle
+};
+
+int column_blocks(int L) { return (L + 1 + 15) / 16; }
+int upper_blocks(int n) { return n * (n + 1) / 2; }
+
+struct e4m3 { unsigned char bits; };        // 8-bit E4M3 storage, widened exactly by the conversion instruction
+__device__ __forceinline__ float widen(float v) { return v; }
+__device__ __forceinline__ float widen(__half v) { return __half2float(v); }
+__device__ __forceinline__ float widen(e4m3 v) { return __builtin_amdgcn_cvt_f32_fp8((int)v.bits, 0); }
+struct bf16v { unsigned short bits; };      // bfloat16 storage: the upper half of a binary32
+__device__ __forceinline__ float widen(bf16v v) { return __uint_as_float((unsigned)v.bits << 16); }
+// a coefficient as stored (loaded as an integer, which a load widens by itself), and back
+template <int BYTES> struct BitsOf;
+template <> struct BitsOf<4> { typedef unsigned type; };
+template <> struct BitsOf<2> { typedef unsigned short type; };
+template <> struct BitsOf<1> { typedef unsigned char type; };
+template <typename TC>
+__device__ __forceinline__ TC from_bits(unsigned b) {
+    if constexpr (sizeof(TC) == 4) return __builtin_bit_cast(TC, b);
+    else if constexpr (sizeof(TC) == 2) return __builtin_bit_cast(TC, (unsigned short)b);
+    else return __builtin_bit_cast(TC, (unsigned char)b);
+}
+// x times the coefficient in bits 8 AT .. of a word (fp16: the half is widened by the multiplication itself)
+template <typename TC, int AT>
+__device__ __forceinline__ float times_stored(unsigned word, float x) {
+    if constexpr (std::is_same<TC, __half>::value) {
+        float r;
+        if constexpr (AT == 0) asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel_hi:[1,0,0]" : "=v"(r) : "v"(word), "v"(x));
+        else asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(word), "v"(x));
+        return r;
+    } else {
+        return widen(from_bits<TC>(word >> (8 * AT))) * x;
+    }
+}
+__device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
 // q-th block of the upper triangle of an n x n block matrix, row-major: (bi, bj) with bi <= bj
 __device__ __forceinline__ void block_of(int q, int n, int& bi, int& bj) {
@@ -267,6 +311,20 @@ __global__ __launch_bounds__(NT, 1) void k_atom_gram(const GramArgs a) {
 // every item are 480 of it), 1304 x 1134 x3 fp8 636 / 485, 160 x 112 x3 every second pixel 32.5 / 22; 60 atoms 1302 x 1227 x1 328 /
 // 149; 40 atoms 268 x 218 x3 53 / 25.
 // ---------------------------------------------------------------------------
+constexpr int NTT = 512;         // at most eight wavefronts
+constexpr int GRIDT = 256;       // at most one workgroup per CU
+
+// block b of the upper triangle of an N x N block matrix, row-major
+template <int N>
+struct UpperBlocks {
+    int row[N * (N + 1) / 2], col[N * (N + 1) / 2];
+    constexpr UpperBlocks() : row(), col() {
+        int b = 0;
+        for (int i = 0; i < N; ++i)
+            for (int j = i; j < N; ++j) { row[b] = i; col[b] = j; ++b; }
+    }
+};
+
 // WIDE: planes so large that 16 of them, or one's patch operands, pass 4 GB: offsets within a row, and 64 bits for the lane's plane.
 template <int K, typename TC, int N16, bool WIDE>
 __global__ __launch_bounds__(NTT, 2) void k_atom_gram_tri(const GramArgs a, unsigned long long items) {
@@ -1231,11 +1289,7 @@ int atom_gram(const sr_tensor* up, const sr_tensor* coeff, const sr_tensor* dict
         else SR_GRAM_LAUNCH_T(KS, e4m3);                                                                    \
     } while (0)
     if (empty) grid = 0;                                   // no sums: zeros (the pointers may be null, and nothing divides by an empty row)
-    else if (tri && split_faster(k, a.n16, channels, coeff->dtype, items)) {
-        grid = GRIDT;                                      // (eight items and more for a wavefront)
-        const auto launch = k == 3 ? launch_split_k3 : k == 5 ? launch_split_k5 : launch_split_k7;
-        if (launch(a, coeff->dtype, items, grid, st) != hipSuccess) return SR_ERR_LAUNCH;
-    } else switch (k) {
+    else switch (k) {
     case 3:  SR_GRAM_LAUNCH(3); break;
     case 5:  SR_GRAM_LAUNCH(5); break;
     default: SR_GRAM_LAUNCH(7); break;

@@ -258,24 +258,24 @@ def _reference(up, coeff, d, target, stride):
     return out.cpu().numpy(), np.append(most.cpu().numpy(), np.sqrt(out[L, L].item()))
 
 
-def _split(got, L):
+def _matrix(got, L):
     full = np.empty((L + 1, L + 1))
     full[:L, :L], full[L, :L], full[:L, L], full[L, L] = got[:L * L].reshape(L, L), got[L * L:L * L + L], got[L * L:L * L + L], got[L * L + L]
     return full
 
 
-# Calls of 6144 (8192, one channel 16384) items of 16 samples and one channel and more, fewer items for some wavefronts than for others: rows whose last item
+# Calls of 6144 items of 16 samples and one channel and more (several for a wavefront), fewer items for some wavefronts than for others: rows whose last item
 # has 1, 4, 13 and 16 samples, every pixel and a lattice, several images, both block counts at an edge (the last block may hold the target only)
-SPLIT = [(1, 3, 250, 417, 72, 5, "f16", 1), (2, 2, 213, 260, 79, 5, "f32", 1), (1, 1, 1100, 1197, 64, 5, "bf16", 1), (1, 3, 241, 353, 72, 5, "f8", 1),
+MANY = [(1, 3, 250, 417, 72, 5, "f16", 1), (2, 2, 213, 260, 79, 5, "f32", 1), (1, 1, 1100, 1197, 64, 5, "bf16", 1), (1, 3, 241, 353, 72, 5, "f8", 1),
          (1, 3, 500, 833, 72, 5, "f16", 2), (3, 1, 790, 1029, 63, 5, "f8", 3), (1, 4, 181, 417, 48, 5, "f32", 1), (1, 3, 250, 420, 47, 5, "f16", 1),
          (1, 3, 261, 433, 72, 3, "bf16", 1), (1, 3, 520, 865, 66, 3, "f32", 2), (1, 3, 270, 433, 60, 7, "f16", 1), (1, 2, 520, 1000, 31, 7, "f8", 2)]
 
 
-@pytest.mark.parametrize("n,c,h,w,L,k,cd,stride", SPLIT)
+@pytest.mark.parametrize("n,c,h,w,L,k,cd,stride", MANY)
 @pytest.mark.parametrize("values", ["plain", "dark first", "peaks"])
 def test_many_samples(n, c, h, w, L, k, cd, stride, values):
-    """plain: coefficients as a softmax gives them.  dark first: no light in the upper rows, then 1e-6 of it, then all (the operands' scales
-    have to be found late and lowered).  peaks: single pixels of the image and coefficients far above the others (scales lowered within a wavefront)."""
+    """plain: coefficients as a softmax gives them.  dark first: no light in the upper rows, then 1e-6 of it, then all.
+    peaks: single pixels of the image and coefficients far above the others."""
     g = torch.Generator(device=DEV).manual_seed(L * 1000 + w)
     up, target = (torch.rand((n, c, h, w), generator=g, device=DEV) for _ in range(2))
     z = torch.randn((n, L, h, w), generator=g, device=DEV)
@@ -294,15 +294,15 @@ def test_many_samples(n, c, h, w, L, k, cd, stride, values):
     stored = coeff.float()
     ref, most = _reference(up, stored, d, target, stride)
     assert np.array_equal(got, again) and got[-1] == n * c * len(range(0, h, stride)) * len(range(0, w, stride))
-    # a response is off by at most 2^-24 of `most` and 2^-24 of itself (the operand's two parts), its dot product's rounding included: Cauchy-Schwarz over the
-    # samples; sums round to 2^-24 of themselves
+    # the dot product of a response rounds to 2^-24 of its partial sums, each well below `most`, and the response to 2^-24 of itself: Cauchy-Schwarz over the
+    # samples; sums round to 2^-24 of themselves, and over so many samples roundings average out
     size = np.sqrt(np.diag(ref))
     bound = 2.0 ** -24 * (np.outer(most + size, size) + np.outer(size, most + size) + np.outer(size, size))
-    assert (np.abs(_split(got, L) - ref) <= bound).all()
+    assert (np.abs(_matrix(got, L) - ref) <= bound).all()
     if values == "plain":
         # roundings of either sign: over 10^5 samples they average out (a cut towards zero, 2^-25 of a product, would be seen: 3e-8)
-        assert np.abs(_split(got, L) - ref).sum() <= 1e-7 * np.abs(ref).sum()
-        assert abs(((_split(got, L) - ref) / np.outer(size, size)).mean()) <= 4e-9
+        assert np.abs(_matrix(got, L) - ref).sum() <= 1e-7 * np.abs(ref).sum()
+        assert abs(((_matrix(got, L) - ref) / np.outer(size, size)).mean()) <= 4e-9
 
 
 @pytest.mark.parametrize("where", ["coefficient inf", "coefficient nan", "image inf", "image nan", "dictionary inf", "target nan"])
@@ -316,7 +316,7 @@ def test_many_samples_with_infinities_and_nan(where):
     what, value = where.split()
     {"coefficient": coeff[0, 70], "image": up[0, 1], "dictionary": d[70], "target": target[0, 2]}[what].view(-1)[
         {"coefficient": 210 * w + 5, "image": 200 * w + 7, "dictionary": 3, "target": 99 * w + 33}[what]] = float(value)
-    got = _split(sr.sr_atom_gram(up, coeff, d, target, L, k, c, 1).cpu().numpy(), L)
+    got = _matrix(sr.sr_atom_gram(up, coeff, d, target, L, k, c, 1).cpu().numpy(), L)
     hit = np.zeros(L + 1, bool)
     hit[{"coefficient": [70], "image": range(L), "dictionary": [70], "target": [L]}[what]] = True
     mine = hit[:, None] | hit[None, :]
@@ -327,3 +327,79 @@ def test_many_samples_with_infinities_and_nan(where):
     size = np.sqrt(np.diag(ref))
     if what != "image":                              # (positive values: a response is as large as what bounds it, within a few times)
         assert (np.abs(got - ref) <= 1e-6 * np.outer(size, size))[~mine].all()
+
+
+def _fp32_bound(up, coeff, d, target, stride):
+    """Of each entry, for responses and sums formed in fp32: k^2 roundings of the dot product and one of the response, for both factors, and
+    64 of the sum, each of 2^-24 of what the magnitudes add up to."""
+    size, _ = _reference(up.abs(), coeff.abs(), d.abs(), target.abs(), stride)
+    return (2 * (d.shape[-1] ** 2 + 1) + 64) * 2.0 ** -24 * size
+
+
+@pytest.mark.parametrize("n,c,h,w,L,k,cd,stride", MANY)
+@pytest.mark.parametrize("values", ["atoms", "coefficients", "outlier"])
+def test_many_samples_of_atoms_of_any_magnitude(n, c, h, w, L, k, cd, stride, values):
+    """Each entry as near as fp32 has it, however small its atoms' responses are beside the others': atoms (or their coefficients) of 2^-20 to
+    2^-40 of the largest, or one response far above all others."""
+    g = torch.Generator(device=DEV).manual_seed(L * 1000 + w)
+    up, target = (torch.rand((n, c, h, w), generator=g, device=DEV) for _ in range(2))
+    phi = torch.softmax(torch.randn((n, L, h, w), generator=g, device=DEV), dim=1)
+    d = torch.randn((L, k, k), generator=g, device=DEV) / k
+    small = torch.ones(L, device=DEV)
+    if values == "outlier":
+        phi[0, L // 2, 0, 0] = 400.0
+        d[L // 2] *= 2.0 ** 30
+    else:
+        small[1::2] = 2.0 ** -torch.linspace(20, 40, L, device=DEV)[1::2].round()
+    if values == "coefficients" and cd in ("f32", "bf16"):
+        phi *= small[None, :, None, None]
+    else:                                            # (fp16 and 8 bits do not hold such coefficients)
+        d *= small[:, None, None]
+    coeff = phi.to({"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16, "f8": torch.float8_e4m3fn}[cd])
+    got = _matrix(sr.sr_atom_gram(up, coeff, d, target, L, k, c, stride).cpu().numpy(), L)
+    ref, _ = _reference(up, coeff.float(), d, target, stride)
+    assert (np.abs(got - ref) <= _fp32_bound(up, coeff.float(), d, target, stride)).all()
+
+
+@pytest.mark.parametrize("sharp", [1, 10, 30])
+@pytest.mark.parametrize("c,L,k,cd,stride", [(3, 72, 5, "f32", 1), (3, 72, 5, "f16", 1), (1, 72, 3, "bf16", 1), (3, 60, 7, "f32", 1), (3, 72, 5, "f32", 2)])
+def test_many_samples_of_sharp_coefficients(c, L, k, cd, stride, sharp):
+    """Softmax of Gaussian logits times `sharp`: few samples make up an entry then, and within the samples that an atom dominates the others' coefficients are tiny."""
+    g = torch.Generator(device=DEV).manual_seed(sharp * 100 + L)
+    h, w = (500, 833) if stride == 2 else (330, 833)
+    up, target = (torch.rand((1, c, h, w), generator=g, device=DEV) for _ in range(2))
+    phi = torch.softmax(sharp * torch.randn((1, L, h, w), generator=g, device=DEV), dim=1)
+    d = torch.rand((L, k, k), generator=g, device=DEV) / k
+    coeff = phi.to({"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[cd])
+    got = _matrix(sr.sr_atom_gram(up, coeff, d, target, L, k, c, stride).cpu().numpy(), L)
+    ref, _ = _reference(up, coeff.float(), d, target, stride)
+    off = np.abs(got - ref) / ref                    # (all values are positive)
+    # an entry of one sample is off by the roundings of two dot products, k^2 of either sign and up to 2^-25 of a partial sum each: their rms is k / 4 x 2^-24, and
+    # less where several samples make up the entry (fp32 sums: largest 3.0e-8 to 7.4e-8, median up to 1.4e-8)
+    assert off.max() <= 2.0 ** -23 and np.median(off) <= 2.0 ** -25
+
+
+@pytest.mark.parametrize("n,c,h,w,L,k,cd,stride", MANY)
+@pytest.mark.parametrize("what", ["image", "target", "coefficient"])
+def test_many_samples_that_start_tiny(n, c, h, w, L, k, cd, stride, what):
+    """Finite values of any magnitude give finite sums: a dictionary of 1e-5 and rows of 1e-30 before ordinary ones; a target, or coefficients, that go from
+    1e-30 to 1e9."""
+    if what == "coefficient" and cd not in ("f32", "bf16"):
+        pytest.skip("the type holds no such coefficients")
+    g = torch.Generator(device=DEV).manual_seed(L * 1000 + w)
+    up, target = (torch.rand((n, c, h, w), generator=g, device=DEV) for _ in range(2))
+    phi = torch.softmax(torch.randn((n, L, h, w), generator=g, device=DEV), dim=1)
+    d = torch.randn((L, k, k), generator=g, device=DEV) / k
+    row = torch.arange(h, device=DEV) % 8            # (wavefronts own runs of rows: each meets the change)
+    ramp = torch.where(row < 4, 1e-30, 1e9 if what != "image" else 1.0).reshape(-1, 1) * torch.ones(w, device=DEV)
+    if what == "image":
+        up *= ramp
+        d *= 1e-5
+    elif what == "target":
+        target *= ramp
+    else:
+        phi *= ramp
+    coeff = phi.to({"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16, "f8": torch.float8_e4m3fn}[cd])
+    got = _matrix(sr.sr_atom_gram(up, coeff, d, target, L, k, c, stride).cpu().numpy(), L)
+    ref, _ = _reference(up, coeff.float(), d, target, stride)
+    assert np.isfinite(got).all() and (np.abs(got - ref) <= _fp32_bound(up, coeff.float(), d, target, stride)).all()
