@@ -131,6 +131,8 @@ bool mfma_supported(const AssembleArgs& a, int k, int coeff_dtype, int tile) {
     if (a.pre_shuffle && !(k == 5 && a.C == 3 && (np8 == 1 || np8 == 9) && !beyond_4gb(a, coeff_dtype) && a.W % px == 0 &&
                            tile == 0 && (coeff_dtype == SR_F16 || (coeff_dtype == SR_BF16 && np8 == 9 && a.w % 4 == 0))))
         return false;
+    // (LR widths off multiples of 4 at scale 2 have no instantiation here but for short lists: k_assemble_slots runs all that fit a device)
+    if (a.pre_shuffle && np8 == 9 && a.s == 2 && a.w % 4 != 0 && !slots_supported(a, k)) return false;
     if (beyond_4gb(a, coeff_dtype) && np8_big(np8) == 0) return false;                     // element offsets: up to 72 atoms
     // Alternative tile shapes exist for one family only (5x5 atoms, three channels, 65 to 72 fp16
     // atoms, byte offsets); everywhere else only the default (index 0) is accepted, so that a

@@ -27,12 +27,12 @@ hipError_t launch_mfma_k5_ps(const AssembleArgs& a, int np8, const LaunchTo& st)
         if (perm && a.s == 4) return launch_one<5, 3, 9, 4, 1, 4, 4, 2, CT_F16, 4, false, 4>(a, st);   // 256 x 8
         if (perm && a.s == 3) return launch_one<5, 3, 9, 4, 1, 8, 3, 2, CT_F16, 3, false, 3>(a, st);   // 384 x 8
         if (perm) return launch_one<5, 3, 9, 4, 1, 4, 4, 2, CT_F16, 2, false, 2>(a, st);               // 128 x 16
-        // LR widths that are not a multiple of 4 (what k_assemble_slots does not take: frames beyond its tile count): one 16-bit load per pixel and plane.  Every load occupies a
-        // register until its pair is packed, twice the registers of the planar form for a unit in flight: one
-        // wavefront per SIMD, as two workgroups of two wavefronts per CU, so that one streams while the other
-        // up-samples.
+        // Other LR widths run on k_assemble_slots (slots_faster).  What it does not take: at scale 4 a width of 1, whose rows have no whole word of
+        // coefficients.  One 16-bit load per pixel and plane; every load occupies a register until its pair is packed, twice the registers
+        // of the planar form for a unit in flight: one wavefront per SIMD, as two workgroups of two wavefronts per CU, so that
+        // one streams while the other up-samples.
         if (a.s == 4) return launch_one<5, 3, 9, 4, 1, 2, 6, 1, CT_F16, 4, false, 1>(a, st);           // 128 x 12
-        return launch_one<5, 3, 9, 4, 1, 2, 4, 1, CT_F16, 2, false, 1>(a, st);                         // 128 x 8
+        return hipErrorInvalidValue;                                                                   // (mfma_supported)
     default: return hipErrorInvalidValue;
     }
 }

@@ -47,6 +47,8 @@ CASES = [
     (1, 3, 20, 30, 4, 72, 5, "bf16", "f32", None),      # bfloat16, LR width not a multiple of 4: the generic kernel
     (1, 3, 15, 17, 3, 72, 5, "f16", "f32", None),       # HR width 51: not whole pixel groups
     (1, 3, 23, 18, 3, 72, 5, "f16", "f32", None),       # scale 3, LR width not a multiple of 4: one 16-bit load per pixel and plane
+    (1, 3, 29, 1, 4, 72, 5, "f16", "f32", None),        # a single LR column: one 16-bit load per pixel and plane, three tiles
+    (2, 3, 13, 1, 4, 72, 5, "f16", "f16", 67),
 ]
 
 

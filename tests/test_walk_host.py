@@ -204,3 +204,15 @@ def test_more_tiles_than_32_bits_count():
     for call in (dict(pre=True, cd="f8"), dict(logits=True, C=1), dict(C=2, cd="f32")):
         assert runs(n=65535, H=262140, W=8, s=2, L=72, **call) == (sr.SR_RUNS_GENERIC, (0,) * 6)
         assert runs(n=600, H=262140, W=8, s=2, L=72, **call)[0] == sr.SR_RUNS_SLOTS
+
+
+def test_lr_widths_off_multiples_of_4_before_the_pixel_shuffle():
+    """fp16, 65 to 72 atoms, HR widths of whole groups: the second matrix-core kernel; a single LR column, whose rows hold no word of coefficients, stays on the streaming
+    one's element-wise form, and frames beyond the tile count at scale 2 (more coefficients than a device holds) are the generic kernel's."""
+    for s, W in ((4, 8), (4, 20), (4, 132), (2, 4), (2, 12), (2, 1004)):
+        for kernel in (sr.SR_KERNEL_AUTO, sr.SR_KERNEL_MFMA):
+            assert runs(H=24, W=W, s=s, cd="f16", pre=True, kernel=kernel)[0] == sr.SR_RUNS_SLOTS
+    for kernel in (sr.SR_KERNEL_AUTO, sr.SR_KERNEL_MFMA):
+        assert runs(H=24, W=4, s=4, cd="f16", pre=True, kernel=kernel) == (sr.SR_RUNS_STREAMING, (TILES, 128, 12, 2, 2, 2))
+    beyond = dict(n=65535, H=32800, W=4, s=2, cd="f16", pre=True)
+    assert runs(**beyond) == (sr.SR_RUNS_GENERIC, (0,) * 6) and runs(**beyond, kernel=sr.SR_KERNEL_MFMA)[0] == -3
