@@ -554,6 +554,9 @@ def main():
             walk = sr.sr_dict_assemble_walk(inp["lr"], coeffs[0], inp["dict"], wl.L, wl.k, wl.scale, wl.c, outs[0],
                                             kept=kept, opts=sr.make_options(sr.SR_KERNEL_MFMA, t))[1]
             name = f"strips of {walk[1]} in segments of {walk[2]} rows" if walk[0] == 2 else f"{shape[0]}x{shape[1]}"
+            if sr.sr_dict_assemble_runs(inp["lr"], coeffs[0], inp["dict"], wl.L, wl.k, wl.scale, wl.c, outs[0], kept=kept,
+                                        opts=sr.make_options(sr.SR_KERNEL_MFMA, t))[0] == sr.SR_RUNS_SLOTS:
+                name, shape = f"second matrix-core kernel, {walk[1]}x{walk[2]}", (walk[1], walk[2], walk[5], 0)
             rows.append({"index": t, "tile": name, "wavefronts_per_workgroup": shape[2],
                          "workgroups_per_cu": shape[3], "median_us_single_launch": round(ms * 1e3, 1)})
         result["tile_sweep"] = rows

@@ -151,12 +151,11 @@ typedef struct {
  *
  * Supported: k in {3,5,7}; scale in {2,3,4}; 1 <= L <= SR_MAX_ATOMS;
  * 1 <= C <= SR_MAX_CHANNELS; N >= 0 (N = 0 or an empty image is a no-op
- * returning SR_OK).  Where the streaming matrix-core kernel runs (see
- * sr_dict_assemble_runs) and the coefficients are f16, f8 or logits, the dictionary
- * entries, times gamma where there is one, must be finite in fp16 (below 65504),
- * and infinite coefficients may give NaN; the other kernels take any finite value
- * and give infinities and NaN as plain fp32 sums do.  f8 NaN codes give
- * unspecified results.
+ * returning SR_OK).  Where sr_dict_assemble_plan says SR_KERNEL_MFMA and the
+ * coefficients are f16, f8 or logits, the dictionary entries, times gamma where
+ * there is one, must be finite in fp16 (below 65504), and infinite coefficients
+ * may give NaN; all other calls take any finite value and give infinities and NaN
+ * as plain fp32 sums do.  f8 NaN codes give unspecified results.
  */
 int sr_dict_assemble(const sr_tensor* lr, const sr_tensor* coeff, const sr_tensor* dict,
                      int L, int k, int scale, int channels,
@@ -194,8 +193,9 @@ int sr_dict_assemble_selective(const sr_tensor* lr, const sr_tensor* coeff, cons
  *   f8  coefficients: as f32, and lr->data 4-byte aligned with an even number of
  *                     elements if the image is f16;
  *   images beyond 4 GB of coefficients (element offsets): at most 72 folded atoms.
- * Of these planar calls a second matrix-core kernel serves those that it is faster with, with the same bits (f8
- * coefficients of more than 72 atoms with k = 3 or 5, which the first has no instantiation for, and of k = 7: all of them).
+ * Of these calls a second matrix-core kernel serves those that it is faster with, small frames above all, with the same bits (f8
+ * coefficients of more than 72 atoms with k = 3 or 5, which the first has no instantiation for, and of k = 7: all of them), where no tile
+ * index is given.
  * With SR_KERNEL_AUTO it also serves most other cases of the planar order and the one before the pixel-shuffle: C up to 3, at
  * most 128 folded atoms, but few atoms.  The generic kernel runs what is left, and whatever SR_KERNEL_GENERIC asks for.
  * sr_dict_assemble_runs says which one a call gets.
@@ -206,7 +206,8 @@ int sr_dict_assemble_selective(const sr_tensor* lr, const sr_tensor* coeff, cons
  * [N][L][s*h][s*w] first, without that 2 x (L * H * W) byte pass over memory.  Every kernel
  * takes it; the matrix-core kernel for k = 5, C = 3, f16 coefficients with up to 8 or 65 to 72
  * folded atoms, or bf16 coefficients with 65 to 72 and an LR width that is a multiple of 4 (byte
- * offsets), the second matrix-core kernel or the generic one otherwise (see above).
+ * offsets; of 65 to 72 atoms the second matrix-core kernel serves small frames and LR widths that are no multiple of 4, with the
+ * same bits), the second matrix-core kernel or the generic one otherwise (see above).
  *
  * opts->coeff_layout = SR_COEFF_PIXEL_MAJOR: `coeff` is stored [N][s*h][s*w][L] (described with
  * c = L, h = s*h, w = s*w as for the planar order).  A wavefront's row of 128 pixels is then one
@@ -234,8 +235,9 @@ int sr_dict_assemble_selective(const sr_tensor* lr, const sr_tensor* coeff, cons
  *
  * opts->tile (the launch-shape search of section III-B, Eq. 11-12, as a small set of compiled
  * tile shapes): index 0 is the library's default for the frame and is always accepted.  (By
- * default a frame may be walked in strips of 128 columns instead of tiles, see sr_dict_assemble_walk; sr_dict_assemble_tile
- * and sr_dict_assemble_launch_shape then report for index 0 the tile shape it would take otherwise.)  Other
+ * default a frame may be walked in strips of 128 columns instead of tiles, or run on the second matrix-core kernel, see
+ * sr_dict_assemble_walk and sr_dict_assemble_runs; sr_dict_assemble_tile and sr_dict_assemble_launch_shape then report for index 0
+ * the tile shape that the streaming kernel would take otherwise.)  Other
  * indices exist only where alternative shapes are built - k = 5, C = 3, 65 to 72 folded f16
  * atoms, byte offsets: 1 = 64x8, 2 = 128x4, 3 = 64x16, 4 = 128x8, 5 = 64x32, 6 = 128x16,
  * 7 = 128x24 (scale 4 only) HR pixels per workgroup, i.e. 1, 1, 2, 2, 4, 4, 6 row groups per
@@ -301,9 +303,10 @@ int sr_dict_assemble_plan(const sr_tensor* lr, const sr_tensor* coeff, const sr_
                           const sr_tensor* out,
                           const int* kept, int n_kept, const sr_options* opts);
 
-/* As sr_dict_assemble_plan, and also reports the tile (HR pixels per workgroup) of the
- * matrix-core instantiation that would run: *tile_w x *tile_h, or 0 x 0 where the library
- * does not report it (generic kernel; families with a single built shape).  Host only. */
+/* As sr_dict_assemble_plan, and also reports the tile (HR pixels per workgroup) that the index
+ * stands for in the streaming matrix-core kernel: *tile_w x *tile_h, or 0 x 0 where the library
+ * does not report it (generic kernel; families with a single built shape).  Index 0 need not run in it:
+ * see opts->tile above; sr_dict_assemble_runs says what is launched.  Host only. */
 int sr_dict_assemble_tile(const sr_tensor* lr, const sr_tensor* coeff, const sr_tensor* dict,
                           int L, int k, int scale, int channels,
                           const sr_tensor* out,
@@ -320,7 +323,7 @@ int sr_dict_assemble_launch_shape(const sr_tensor* lr, const sr_tensor* coeff, c
                                   const int* kept, int n_kept, const sr_options* opts,
                                   int shape[4]);
 
-/* How the matrix-core kernel would walk the images of this call on the current device (256 CUs where there is none):
+/* How the matrix-core kernel that serves this call would walk its images on the current device (256 CUs where there is none):
  * walk[0] = 1: tiles of walk[1] x walk[2] HR pixels, each of a workgroup's wavefronts together; walk[0] = 2: strips of
  * walk[1] columns in segments of walk[2] rows, each of one wavefront alone; walk[3] = tiles or segments of the call, walk[4]
  * = workgroups launched, walk[5] = wavefronts of each.  All zero where sr_dict_assemble_plan says SR_KERNEL_GENERIC and for an empty call.  Returns as
@@ -338,7 +341,7 @@ typedef enum {
     SR_RUNS_STREAMING = 2,     /* the streaming matrix-core kernel                 */
     SR_RUNS_SLOTS     = 3      /* the second matrix-core kernel, which serves most
                                   of what sr_dict_assemble_plan calls generic and
-                                  some planar calls of the streaming kernel        */
+                                  some calls of the streaming kernel               */
 } sr_runs;
 int sr_dict_assemble_runs(const sr_tensor* lr, const sr_tensor* coeff, const sr_tensor* dict,
                           int L, int k, int scale, int channels,

@@ -239,7 +239,7 @@ def sr_dict_assemble_list_ex(lr, index, value, dict, L, k, scale, channels, entr
 
 
 def sr_dict_assemble_tile(lr, coeff, dict, L, k, scale, channels, out, kept=None, n_kept=None, opts=None):
-    """(kernel or negative status, tile width, tile height) the call would run with."""
+    """(kernel or negative status, tile width, tile height) of the tile index in the streaming matrix-core kernel; see the header."""
     a, b, c, o = describe(lr), describe_coeff(coeff, opts), describe(_dict4(dict)), describe(out)
     ka, n, _ga, _keep = _host_lists(kept, None)
     n = n if n_kept is None else int(n_kept)

@@ -14,10 +14,12 @@ from . import binding as _b
 
 def sweep_tiles(lr, coeff, dict, L, k, scale, channels, out, kept=None, gamma=None,
                 reps: int = 5, max_tiles: int = 10):
-    """Time every launch shape (tile, workgroup size, residency) of the matrix-core kernel for these arguments.
+    """Time the library's default (index 0: a tile shape, strips, or the second matrix-core kernel, see
+    `sr_dict_assemble_runs`) and every launch shape (tile, workgroup size, residency) of the streaming matrix-core
+    kernel for these arguments.
 
     Returns a list of (tile index, median milliseconds); empty if the
-    matrix-core kernel does not take the case.  `out` is overwritten."""
+    matrix-core kernels do not take the case.  `out` is overwritten."""
     import torch
 
     results = []
@@ -46,6 +48,6 @@ def sweep_tiles(lr, coeff, dict, L, k, scale, channels, out, kept=None, gamma=No
 
 
 def best_tile(*args, **kwargs) -> int:
-    """Index of the fastest tile shape (0, the library default, if none applies)."""
+    """Index of the fastest: a tile shape, or 0, the library default (also if none applies)."""
     res = sweep_tiles(*args, **kwargs)
     return min(res, key=lambda r: r[1])[0] if res else 0
