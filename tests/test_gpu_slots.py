@@ -7,7 +7,7 @@ import torch
 
 import paper_2303_08999_amd as sr
 import sr_synth
-from test_gpu_parity import DEV, GENERIC, host, tolerance_ok
+from test_gpu_parity import DEV, GENERIC, assert_parity, host, tolerance_ok
 from test_gpu_logits import assert_logits_parity
 
 pytestmark = pytest.mark.gpu
@@ -271,7 +271,7 @@ def test_infinities_and_nan_as_in_the_generic_kernel(c, L, k, cd, pre, logits, i
     (40, 56, 2, 72, None, "f16", "f32"), (45, 47, 3, 72, None, "bf16", "f16"), (56, 85, 3, 72, None, "f16", "f32"), (12, 60, 4, 72, None, "f16", "f16"),
     (130, 253, 3, 33, None, "bf16", "f32"), (29, 44, 3, 65, None, "f16", "f32"), (61, 68, 2, 72, 50, "f16", "f32"), (250, 300, 2, 32, None, "bf16", "f32"),
     (141, 237, 3, 72, 17, "f16", "f16"), (122, 163, 4, 72, None, "f16", "f32"), (216, 306, 2, 48, None, "bf16", "f32")])
-def test_a_small_frame_has_the_bits_it_has_in_a_batch(h, w, s, L, kept, cd, io):
+def test_a_small_frame_has_the_bits_it_has_in_a_batch(oracle, h, w, s, L, kept, cd, io):
     wl = sr_synth.Workload("slotsb", 73, 2, 3, h, w, s, L, 5, cd, io, 0.0, 1.5)
     inp = sr_synth.make_inputs(wl, DEV)
     atoms = None if kept is None else np.sort(np.random.default_rng(L).choice(L, size=kept, replace=False)).astype(np.int32)
@@ -288,3 +288,39 @@ def test_a_small_frame_has_the_bits_it_has_in_a_batch(h, w, s, L, kept, cd, io):
         assert runs(alone, one, inp["coeff"][b:b + 1], False, False, atoms)[0] == sr.SR_RUNS_SLOTS
         assert torch.equal(run(alone, one, inp["coeff"][b:b + 1].contiguous(), AUTO, False, False, atoms, gamma)[0], together[b])
         assert torch.equal(together[b + n // 2 * 2 - 2], together[b])
+        # (and both are what the oracle gives: the streaming kernel's small, ragged frames too)
+        ref = oracle.dict_assemble(alone["lr"].cpu().numpy(), sr_synth.stored_numpy(inp["coeff"][b:b + 1].contiguous()), inp["dict"].cpu().numpy(), s, kept=atoms, gamma=gamma)
+        assert_parity(together[b:b + 1].float().cpu().numpy(), ref, cd, io == "f16", "in a batch")
+
+
+@pytest.mark.parametrize("h, w, s, L, cd, io, pre", [
+    (40, 56, 2, 72, "f16", "f32", False), (45, 47, 3, 72, "bf16", "f16", False), (30, 60, 4, 66, "f16", "f16", True), (41, 66, 2, 72, "f16", "f32", True),
+    (20, 33, 4, 72, "f16", "f32", True), (29, 44, 3, 72, "bf16", "f32", True)])
+def test_small_frames_of_element_aligned_tensors_and_values_beyond_fp16(h, w, s, L, cd, io, pre):
+    """Tensors that start one element into their allocation, and a dictionary or a coefficient outside fp16 or not finite: what the same frame has in aligned tensors, and
+    in a batch (which the streaming kernel serves where the LR width is a multiple of 4 or the order is planar)."""
+    wl = sr_synth.Workload("slotsa", 75, 1, 3, h, w, s, L, 5, cd, io, 0.0, 1.5)
+    inp = sr_synth.make_inputs(wl, DEV)
+    coeff = sr_synth.to_pre_shuffle(inp["coeff"], s) if pre else inp["coeff"]
+    assert runs(inp, wl, coeff, pre, False)[0] == sr.SR_RUNS_SLOTS
+
+    def shifted(t):
+        return torch.zeros(t.numel() + 1, device=DEV, dtype=t.dtype)[1:].view(t.shape).copy_(t)
+
+    moved = {"lr": shifted(inp["lr"]), "dict": shifted(inp["dict"])}
+    assert torch.equal(run(moved, wl, shifted(coeff), AUTO, pre, False), run(inp, wl, coeff, AUTO, pre, False))
+    n = 1 + 3_500_000 // (wl.H * wl.W)
+    many = sr_synth.Workload("slotsa", 75, n, 3, h, w, s, L, 5, cd, io, 0.0, 1.5)
+    for what in ("dictionary", "inf", "nan"):
+        one, c = dict(inp), coeff.clone()
+        if what == "dictionary":
+            one["dict"] = inp["dict"].clone()
+            one["dict"].view(L, 25)[3] = 1e5
+        else:
+            c.view(-1)[c.numel() // 2 + 7] = float(what)
+        batch = {"lr": inp["lr"].expand(n, -1, -1, -1).contiguous(), "dict": one["dict"]}
+        cs = c.expand(n, -1, -1, -1).contiguous()
+        if not pre or (s != 3 and w % 4 == 0):
+            assert runs(batch, many, cs, pre, False)[0] == sr.SR_RUNS_STREAMING
+        alone, together = run(one, wl, c, AUTO, pre, False), run(batch, many, cs, AUTO, pre, False)
+        assert torch.equal(torch.nan_to_num(alone[0], 7.0, 8.0, 9.0), torch.nan_to_num(together[n // 2], 7.0, 8.0, 9.0)), what
