@@ -227,12 +227,14 @@ def test_images_of_just_below_4_gb(h, w, scale, L):
     assert worst <= 5e-5 * max(1.0, float(want.abs().max()))
 
 
-# Rows that share 128-byte lines are read with ordinary loads from 400 thousand pixels on: a frame alone is below that, in a batch it is not.  Every
+# Rows that share 128-byte lines are read with ordinary loads from 400 thousand pixels on: a frame alone is below that (some run on the second matrix-core kernel then), in a batch it is not.  Every
 # family of the rule, either form, rows off by 2 to 96 bytes, the last strip or tile moved left and not
 @pytest.mark.parametrize("c, h, w, s, L, k, cd, kind", [
     (3, 100, 153, 4, 72, 5, "f16", "values"), (3, 130, 250, 2, 57, 5, "bf16", "values"), (3, 96, 168, 3, 72, 5, "f8", "values"), (1, 90, 202, 4, 72, 5, "f8", "values"),
     (3, 61, 151, 4, 72, 7, "f16", "values"), (1, 70, 141, 4, 128, 7, "bf16", "values"), (3, 101, 170, 3, 72, 5, "f16", "logits"), (3, 80, 130, 4, 66, 5, "bf16", "logits"),
-    (3, 100, 150, 4, 128, 3, "f16", "values"), (3, 120, 209, 3, 128, 5, "f16", "values"), (1, 110, 201, 4, 50, 5, "f16", "values"), (3, 90, 141, 4, 30, 5, "f16", "values")])
+    (3, 100, 150, 4, 128, 3, "f16", "values"), (3, 120, 209, 3, 128, 5, "f16", "values"),      # (on the second matrix-core kernel, in a batch too: the line between both)
+    (3, 100, 150, 3, 72, 3, "f16", "values"), (3, 77, 104, 3, 128, 3, "bf16", "values"), (3, 120, 209, 2, 66, 3, "f8", "values"),
+    (3, 77, 104, 2, 128, 5, "f16", "values"), (3, 90, 168, 4, 100, 5, "bf16", "values"), (1, 110, 201, 4, 50, 5, "f16", "values"), (3, 90, 141, 4, 30, 5, "f16", "values")])
 def test_rows_that_share_lines_have_the_same_bits(c, h, w, s, L, k, cd, kind):
     wl = sr_synth.Workload("lines", 74, 2, c, h, w, s, L, k, cd, "f32", 0.0, 1.5)
     inp = sr_synth.make_inputs(wl, DEV)
@@ -248,7 +250,12 @@ def test_rows_that_share_lines_have_the_same_bits(c, h, w, s, L, k, cd, kind):
         torch.cuda.synchronize()
         return out
 
-    many = run(2 * (1 + 1_100_000 // (wl.H * wl.W)))
+    n = 2 * (1 + 1_100_000 // (wl.H * wl.W))         # two million pixels and more
+    batch = [torch.empty((n, *t.shape[1:]), device=DEV, dtype=t.dtype) for t in (inp["lr"], coeff, torch.empty((1, c, wl.H, wl.W), device=DEV))]
+    launched = sr.sr_dict_assemble_runs(batch[0], batch[1], inp["dict"], L, k, s, c, batch[2], opts=opts)[0]
+    del batch
+    assert launched == (sr.SR_RUNS_SLOTS if (w, L) in ((150, 128), (209, 128)) else sr.SR_RUNS_STREAMING)
+    many = run(n)
     one = run(1)
     assert torch.isfinite(many).all() and torch.equal(many[0], one[0]) and torch.equal(many[-2], one[0]) and torch.equal(many[-1], many[1])
     if kind == "values":                             # (and the vector-ALU kernel agrees)
