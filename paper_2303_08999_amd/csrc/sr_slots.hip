@@ -82,9 +82,11 @@ static bool pre_shuffle_faster(const AssembleArgs& a, int k) {
 //   tiles of one or two rows, in one round: 1.03 (0.91 .. 1.6), 3x3 0.97 (0.94 .. 1.4).  For more than 72 atoms, which take two pixels per lane there, 0.86
 //   (0.96 .. 2.1); 7x7 in one channel 0.88 (1.0 .. 1.6), in three 1.06, 1.03 for more than 72 (0.96 .. 1.3).
 //   tiles of four and eight rows: 1.13 (1.02 .. 1.4); from 0.9 to there 0.7 .. 1.15: strips win the large frames.
-//   16-bit rows that start on no multiple of 32 bytes, whose streaming loads take the shared lines twice: 3x3, launches of one round, 1.04 (0.97 ..
+//   16-bit rows that start on no multiple of 32 bytes, whose shared lines the streaming kernel takes twice unless keep_lines holds: 3x3, launches of one round, 1.04 (0.97 ..
 //   1.4), three channels at scales 2 and 3 0.97 (0.93 .. 1.4); more than 72 atoms of 5x5 0.855 (0.92 .. 1.5), but frames of few
 //   tiles at scale 4, where the streaming tiles are larger: 1.05 (1.02 .. 1.3), against those of 24 rows and three channels 0.72 (0.97 .. 1.26).
+//   Where keep_lines holds (three channels, 2 million pixels and more), up to 104 atoms against strips 1.0 (98 drawn calls from 0.86 to there: 0.80 .. 1.03, mean 0.95: 2080
+//   thousand 77 atoms 83 / 103); more atoms 0.89 .. 1.06, mean 0.985, against tiles 0.99 .. 1.10, more than 72 of 3x3 1.01 .. 1.10: as without.
 //   More than 72 atoms of 3x3 (no strips there), in tiles of four rows or such rows: 0.95 (0.97 .. 1.7); more than 72 of fp32 (one wavefront per
 //   SIMD, tiles of sixteen rows): 0.925 in tiles of four and eight rows, 0.95 in lower ones (0.94 .. 3.2), 7x7 0.76 (0.95 .. 3.2).
 //   fp32 atoms of 7x7, 27 to 32 of them, in the streaming kernel's capacity of 72: 0.85 (1.4 .. 1.9).
@@ -119,7 +121,7 @@ bool slots_faster(const AssembleArgs& a, int k) {
                       : many && f32                           ? (k == 7 ? 760 : t.rows >= 4 ? 925 : 950)
                       : t.rows <= 2 && (many || k == 7 || t.pieces <= 3 * cus) ? (k == 7 && a.C == 3 ? (many ? 1030 : 1060) : many ? 860 : k == 7 ? 880 : k == 3 ? 970 : 1030)
                       : many && k == 3 && (shared_lines || t.rows == 4) ? 950
-                      : shared_lines && many && k == 5        ? (a.s == 4 && t.pieces <= 2 * cus ? (s.rows == 24 && a.C == 3 ? 720 : 1050) : 855)
+                      : shared_lines && many && k == 5        ? (n <= 104 && s.form == 2 && keep_lines(a, k, false) ? 1000 : a.s == 4 && t.pieces <= 2 * cus ? (s.rows == 24 && a.C == 3 ? 720 : 1050) : 855)
                       : shared_lines && k == 3 && t.pieces <= 3 * cus ? (a.C == 3 && a.s != 4 && t.pieces <= 2 * cus ? 970 : 1040)
                                                               : 1130;
     return 1000 * there >= limit * here;
