@@ -1,6 +1,6 @@
 // Matrix-core kernel for calls that the streaming kernel (sr_mfma_kernel.h) has no instantiation for: coefficients before the
 // network's pixel-shuffle and logits, for every coefficient type, atom size and scale, one to three channels, up to 128 folded
-// atoms, any width; planar coefficients in two channels, narrow ragged frames and the like; and planar calls of the streaming kernel that are
+// atoms, any width; planar coefficients in two channels, narrow ragged frames and the like; and calls of the streaming kernel, of either order, that are
 // faster here (slots_faster).  All but the last ran on the generic kernel, which folds on the
 // vector ALUs and reads a pixel's coefficients eight at a time, one memory latency after the other: that is what bounded all but the
 // largest of them.  Here a wavefront takes a UNIT, 32 lanes times the pixels of a 32-bit word of coefficients, requests all of its
